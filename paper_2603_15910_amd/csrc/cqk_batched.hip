@@ -73,10 +73,74 @@ struct BatArgs {
   int32_t* bhist;       // planning: rows per length bucket of each block of kPBlock rows
 };
 
-// The call's counters: rows of each class, work items, the work queue, the
-// flags, the survivors total and the rows whose lists overflowed.
-constexpr int CTR_NLONG = 0, CTR_NSHORT = 1, CTR_NITEMS = 2, CTR_QUEUE = 3, CTR_FLAGS = 4,
-              CTR_SURV = 6, CTR_OVER = 7, CTR_TOTAL = 8;
+// The call's counters, in lines of 32 ints (128 bytes): line 0 holds the rows
+// of each class and the work items, the next kQueues lines one work queue
+// each, the last kQueues lines the call's outcome as summed by the blocks of
+// one queue (flags, survivors, rows whose lists overflowed).  Atomics on one
+// address take turns at about 13 ns each on this part, so one shared queue
+// and one shared survivor total, updated per row, bounded every call of many
+// rows (65 536 rows of 64-512 values: 1.70 ms for 147 456 atomics): blocks
+// now share a queue in groups of grid / kQueues and add their outcome once.
+constexpr int CTR_NLONG = 0, CTR_NSHORT = 1, CTR_NITEMS = 2;
+constexpr int CTR_FLAGS = 0, CTR_SURV = 1, CTR_OVER = 2;
+constexpr int kQueues = 32, kCtrLine = 32;
+constexpr int CTR_QUEUE0 = kCtrLine, CTR_STAT0 = (1 + kQueues) * kCtrLine,
+              CTR_TOTAL = (1 + 2 * kQueues) * kCtrLine;
+
+// A block's outcome, in LDS until the block ends.
+struct BatStat {
+  int32_t flags, surv, over;
+};
+
+__device__ __forceinline__ void stat_init(BatStat& t) {
+  if (threadIdx.x == 0) t.flags = t.surv = t.over = 0;
+}
+
+// Adds the block's outcome to its group's line.  MAXOVER: `over` is a maximum
+// (the general form's iteration count), not a sum.
+template <bool MAXOVER>
+__device__ __forceinline__ void stat_flush(const BatStat& t, int32_t* counters) {
+  if (threadIdx.x == 0) {
+    int32_t* line = counters + CTR_STAT0 + (blockIdx.x % kQueues) * kCtrLine;
+    if (t.flags) atomicOr(&line[CTR_FLAGS], t.flags);
+    if (t.surv) atomicAdd(&line[CTR_SURV], t.surv);
+    if (t.over) {
+      if (MAXOVER) atomicMax(&line[CTR_OVER], t.over);
+      else atomicAdd(&line[CTR_OVER], t.over);
+    }
+  }
+}
+
+// The work items of one block: those of its group's queue (queue q holds
+// items q, q + kQueues, ...), then those of the queues that still hold some.
+// No item is a block's by its number: a grid larger than the GPU can hold
+// starts its last blocks late, and their items (long rows, at the list's
+// start) would wait for them.  Called by the whole first wave of the block;
+// returns nitems or more once every queue is empty.
+struct ItemSource {
+  int own = (int)(blockIdx.x % kQueues);
+  __device__ __forceinline__ int next(int32_t* counters, int nitems) {
+    const int lane = threadIdx.x & (kWave - 1);
+    for (;;) {
+      int k = 0;
+      if (lane == 0) k = atomicAdd(&counters[CTR_QUEUE0 + own * kCtrLine], 1);
+      k = __builtin_amdgcn_readfirstlane(k);
+      const int64_t item = own + (int64_t)k * kQueues;
+      if (item < nitems) return (int)item;
+      // the queues that still hold items, in one round trip; the next one
+      // after this block's
+      int64_t at = nitems;
+      if (lane < kQueues)
+        at = lane + (int64_t)__hip_atomic_load(&counters[CTR_QUEUE0 + lane * kCtrLine],
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) *
+                        kQueues;
+      const uint64_t m = __ballot(at < nitems);
+      if (m == 0) return nitems;
+      const uint64_t up = m >> own << own;
+      own = __builtin_ctzll(up ? up : m);
+    }
+  }
+};
 
 // Length bucket of a row of L values: its bit length, in the wave-row range
 // if L <= wave_max, else in the workgroup-row range.  (Finer buckets, with
@@ -132,12 +196,8 @@ __global__ __launch_bounds__(kPBlock) void bat_count_kernel(Args A) {
     for (int q = 0; q < kPW; ++q) c += wh[q][threadIdx.x];
     A.bhist[(size_t)blockIdx.x * kNB + threadIdx.x] = c;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    A.counters[CTR_QUEUE] = 0;
-    A.counters[CTR_FLAGS] = 0;
-    A.counters[CTR_SURV] = 0;
-    A.counters[CTR_OVER] = 0;
-  }
+  if (blockIdx.x == 0)
+    for (int i = CTR_QUEUE0 + (int)threadIdx.x; i < CTR_TOTAL; i += kPBlock) A.counters[i] = 0;
 }
 
 template <typename Args>
@@ -283,6 +343,7 @@ struct BatLds {
   int32_t si[kWaves][kSurvW];
   double ws[kWaves][8];
   double red[3 * kWaves];
+  BatStat stat;
   int item;
 };
 
@@ -561,7 +622,7 @@ __device__ void solve_long_row(const BatArgs& A, int s, int64_t base, int64_t n,
   if (!(rd >= 0.0) || !(rd < inf_d())) {
     for (int64_t i = threadIdx.x; i < n; i += kBlock) x[i] = 0.f;
     if (threadIdx.x == 0) {
-      atomicOr(&A.counters[CTR_FLAGS], kBadRadius);
+      atomicOr(&L.stat.flags, kBadRadius);
       if (A.lam_out) A.lam_out[s] = __builtin_nan("");
       if (A.nfree_out) A.nfree_out[s] = 0;
     }
@@ -604,8 +665,8 @@ __device__ void solve_long_row(const BatArgs& A, int s, int64_t base, int64_t n,
   if (bad > 0.0 || n == 0 || rd == 0.0) {
     // x is already zero
     if (threadIdx.x == 0) {
-      if (bad > 0.0) atomicOr(&A.counters[CTR_FLAGS], kBadValue);
-      if (n == 0 && rd > 0.0) atomicOr(&A.counters[CTR_FLAGS], kInfeasible);
+      if (bad > 0.0) atomicOr(&L.stat.flags, kBadValue);
+      if (n == 0 && rd > 0.0) atomicOr(&L.stat.flags, kInfeasible);
       if (A.lam_out) A.lam_out[s] = (bad > 0.0 || n == 0) ? __builtin_nan("") : 0.0;
       if (A.nfree_out) A.nfree_out[s] = 0;
     }
@@ -647,8 +708,8 @@ __device__ void solve_long_row(const BatArgs& A, int s, int64_t base, int64_t n,
     if (threadIdx.x == 0) {
       if (A.lam_out) A.lam_out[s] = lam;
       if (A.nfree_out) A.nfree_out[s] = (int32_t)tn[0];
-      atomicAdd(&A.counters[CTR_SURV], ntot);
-      atomicAdd(&A.counters[CTR_OVER], 1);
+      atomicAdd(&L.stat.surv, ntot);
+      atomicAdd(&L.stat.over, 1);
     }
     return;
   }
@@ -672,7 +733,7 @@ __device__ void solve_long_row(const BatArgs& A, int s, int64_t base, int64_t n,
     for (int w = 0; w < kWaves; ++w) nft += L.ws[w][W_NF];
     if (A.lam_out) A.lam_out[s] = lam;
     if (A.nfree_out) A.nfree_out[s] = (int32_t)nft;
-    atomicAdd(&A.counters[CTR_SURV], ntot);
+    atomicAdd(&L.stat.surv, ntot);
   }
 }
 
@@ -720,7 +781,7 @@ __device__ void solve_medium_row(const BatArgs& A, int s, int64_t base, int64_t 
   if (!(rd >= 0.0) || !(rd < inf_d())) {
     for (int64_t i = lane; i < n; i += kWave) x[i] = 0.f;
     if (lane == 0) {
-      atomicOr(&A.counters[CTR_FLAGS], kBadRadius);
+      atomicOr(&L.stat.flags, kBadRadius);
       if (A.lam_out) A.lam_out[s] = __builtin_nan("");
       if (A.nfree_out) A.nfree_out[s] = 0;
     }
@@ -734,7 +795,7 @@ __device__ void solve_medium_row(const BatArgs& A, int s, int64_t base, int64_t 
   if (bad || rd == 0.0) {
     // x is already zero
     if (lane == 0) {
-      if (bad) atomicOr(&A.counters[CTR_FLAGS], kBadValue);
+      if (bad) atomicOr(&L.stat.flags, kBadValue);
       if (A.lam_out) A.lam_out[s] = bad ? __builtin_nan("") : 0.0;
       if (A.nfree_out) A.nfree_out[s] = 0;
     }
@@ -786,8 +847,8 @@ __device__ void solve_medium_row(const BatArgs& A, int s, int64_t base, int64_t 
   if (lane == 0) {
     if (A.lam_out) A.lam_out[s] = lam;
     if (A.nfree_out) A.nfree_out[s] = (int32_t)nf;
-    atomicAdd(&A.counters[CTR_SURV], R.nw);
-    if (over) atomicAdd(&A.counters[CTR_OVER], 1);
+    atomicAdd(&L.stat.surv, R.nw);
+    if (over) atomicAdd(&L.stat.over, 1);
   }
 }
 
@@ -795,7 +856,7 @@ __device__ void solve_medium_row(const BatArgs& A, int s, int64_t base, int64_t 
 // One wave row (L <= 64 * SP), values in registers.
 // ---------------------------------------------------------------------------
 template <int SP>
-__device__ void solve_short_row(const BatArgs& A, int s, int64_t base, int64_t L) {
+__device__ void solve_short_row(const BatArgs& A, int s, int64_t base, int64_t L, BatStat& stat) {
   const int lane = threadIdx.x & (kWave - 1);
   const double rd = row_radius(A, s);
   const float* y = A.y + base;
@@ -836,7 +897,7 @@ __device__ void solve_short_row(const BatArgs& A, int s, int64_t base, int64_t L
       if (bad_r) f |= kBadRadius;
       if (bad > 0.0) f |= kBadValue;
       if (L == 0 && rd > 0.0) f |= kInfeasible;
-      if (f) atomicOr(&A.counters[CTR_FLAGS], f);
+      if (f) atomicOr(&stat.flags, f);
       if (A.lam_out) A.lam_out[s] = (f) ? __builtin_nan("") : 0.0;
       if (A.nfree_out) A.nfree_out[s] = 0;
     }
@@ -946,8 +1007,13 @@ __global__ __launch_bounds__(kBlock, 3) void bat_solve_kernel(BatArgs A) {
   const int nshort = A.counters[CTR_NSHORT];
   const int nitems = A.counters[CTR_NITEMS];
   const int nsg = nitems - nlong;
+  ItemSource src;
+  stat_init(L.stat);
   for (;;) {
-    if (threadIdx.x == 0) L.item = atomicAdd(&A.counters[CTR_QUEUE], 1);
+    if (threadIdx.x < kWave) {
+      const int next = src.next(A.counters, nitems);
+      if (threadIdx.x == 0) L.item = next;
+    }
     __syncthreads();
     const int item = L.item;
     __syncthreads();
@@ -960,12 +1026,13 @@ __global__ __launch_bounds__(kBlock, 3) void bat_solve_kernel(BatArgs A) {
       if (k < nshort) {
         const size_t e = (size_t)nlong + k;
         const int64_t Lr = A.lrow[2 * e + 1];
-        if (Lr <= A.small_max) solve_short_row<SP>(A, A.list[e], A.lrow[2 * e], Lr);
+        if (Lr <= A.small_max) solve_short_row<SP>(A, A.list[e], A.lrow[2 * e], Lr, L.stat);
         else solve_medium_row(A, A.list[e], A.lrow[2 * e], Lr, L);
       }
     }
     __syncthreads();
   }
+  stat_flush<false>(L.stat, A.counters);
 }
 
 // ---------------------------------------------------------------------------
@@ -1124,8 +1191,12 @@ __global__ __launch_bounds__(kBlock) void bat_vjp_kernel(BatArgs A) {
   const int nshort = A.counters[CTR_NSHORT];
   const int nitems = A.counters[CTR_NITEMS];
   const int nsg = nitems - nlong;
+  ItemSource src;
   for (;;) {
-    if (threadIdx.x == 0) L.item = atomicAdd(&A.counters[CTR_QUEUE], 1);
+    if (threadIdx.x < kWave) {
+      const int next = src.next(A.counters, nitems);
+      if (threadIdx.x == 0) L.item = next;
+    }
     __syncthreads();
     const int item = L.item;
     __syncthreads();
@@ -1168,7 +1239,6 @@ __global__ __launch_bounds__(kBlock) void bat_vjp_kernel(BatArgs A) {
 //   grad_a = [F](g - b mu)/d,   grad_r = mu   (both 0 when F is empty).
 // ===========================================================================
 constexpr int kCqkU = 4;    // values per thread in flight in a workgroup pass
-constexpr int CTR_ITSUM = CTR_SURV, CTR_ITMAX = CTR_OVER;
 
 struct BatCqkArgs {
   int32_t nseg;
@@ -1213,16 +1283,16 @@ __device__ __forceinline__ GenState cqk_row_state(const BatCqkArgs& A, double r)
 
 // Per-row outputs and the call's flags, by one thread of the row's owner.
 __device__ __forceinline__ void cqk_row_report(const BatCqkArgs& A, int s, const GenState& st,
-                                               double lam) {
+                                               double lam, BatStat& stat) {
   if (A.lam_out) A.lam_out[s] = lam;
   if (A.status_out) A.status_out[s] = st.status;
   int f = 0;
   if (st.status == CQK_INVALID_ARG) f = kBadValue;
   else if (st.status == CQK_INFEASIBLE) f = kInfeasible;
   else if (st.status == CQK_NOT_CONVERGED) f = kNotConverged;
-  if (f) atomicOr(&A.counters[CTR_FLAGS], f);
-  atomicAdd(&A.counters[CTR_ITSUM], st.iter);
-  atomicMax(&A.counters[CTR_ITMAX], st.iter);
+  if (f) atomicOr(&stat.flags, f);
+  atomicAdd(&stat.surv, st.iter);
+  atomicMax(&stat.over, st.iter);
 }
 
 // The arrays of a call in their element type (FP64 values are used as
@@ -1251,7 +1321,8 @@ __device__ __forceinline__ bool cqk_has_lambda(const GenState& st) {
 // One wave row (L <= 64 * SP), per-index form in registers.
 // ---------------------------------------------------------------------------
 template <int SP, typename TIn>
-__device__ void cqk_short_row(const BatCqkArgs& A, int s, int64_t base, int64_t L) {
+__device__ void cqk_short_row(const BatCqkArgs& A, int s, int64_t base, int64_t L,
+                              BatStat& stat) {
   const CqkArrays<TIn> V(A);
   const int lane = threadIdx.x & (kWave - 1);
   double c[SP], sv[SP], bl[SP], bu[SP];
@@ -1326,7 +1397,7 @@ __device__ void cqk_short_row(const BatCqkArgs& A, int s, int64_t base, int64_t 
     const int64_t i = lane + (int64_t)k * kWave;
     if (i < L) V.x[base + i] = (TIn)(ok ? cqk_x_at(V, base + i, lam) : __builtin_nan(""));
   }
-  if (lane == 0) cqk_row_report(A, s, st, lam);
+  if (lane == 0) cqk_row_report(A, s, st, lam, stat);
 }
 
 // ---------------------------------------------------------------------------
@@ -1336,6 +1407,7 @@ struct CqkLds {
   double red[8 * kWaves];
   double tot[8];
   KeySum ks[2];
+  BatStat stat;
   int item;
 };
 
@@ -1441,7 +1513,7 @@ __device__ void cqk_long_row(const BatCqkArgs& A, int s, int64_t base, int64_t L
     const double t = fma(vb, lam, va) / vd;
     x[i] = (TIn)(ok ? fmin(fmax(t, vl), vu) : __builtin_nan(""));
   });
-  if (threadIdx.x == 0) cqk_row_report(A, s, st, lam);
+  if (threadIdx.x == 0) cqk_row_report(A, s, st, lam, S.stat);
 }
 
 template <int SP, typename TIn>
@@ -1451,8 +1523,13 @@ __global__ __launch_bounds__(kBlock) void bat_cqk_solve_kernel(BatCqkArgs A) {
   const int nshort = A.counters[CTR_NSHORT];
   const int nitems = A.counters[CTR_NITEMS];
   const int nsg = nitems - nlong;
+  ItemSource src;
+  stat_init(S.stat);
   for (;;) {
-    if (threadIdx.x == 0) S.item = atomicAdd(&A.counters[CTR_QUEUE], 1);
+    if (threadIdx.x < kWave) {
+      const int next = src.next(A.counters, nitems);
+      if (threadIdx.x == 0) S.item = next;
+    }
     __syncthreads();
     const int item = S.item;
     __syncthreads();
@@ -1472,11 +1549,12 @@ __global__ __launch_bounds__(kBlock) void bat_cqk_solve_kernel(BatCqkArgs A) {
       const int k = idx * kWaves + (int)(threadIdx.x / kWave);
       if (k < nshort) {
         const size_t e = (size_t)nlong + k;
-        cqk_short_row<SP, TIn>(A, A.list[e], A.lrow[2 * e], A.lrow[2 * e + 1]);
+        cqk_short_row<SP, TIn>(A, A.list[e], A.lrow[2 * e], A.lrow[2 * e + 1], S.stat);
       }
     }
     __syncthreads();
   }
+  stat_flush<true>(S.stat, A.counters);
 }
 
 // Backward of one wave row.
@@ -1601,8 +1679,12 @@ __global__ __launch_bounds__(kBlock) void bat_cqk_vjp_kernel(BatCqkArgs A) {
   const int nshort = A.counters[CTR_NSHORT];
   const int nitems = A.counters[CTR_NITEMS];
   const int nsg = nitems - nlong;
+  ItemSource src;
   for (;;) {
-    if (threadIdx.x == 0) S.item = atomicAdd(&A.counters[CTR_QUEUE], 1);
+    if (threadIdx.x < kWave) {
+      const int next = src.next(A.counters, nitems);
+      if (threadIdx.x == 0) S.item = next;
+    }
     __syncthreads();
     const int item = S.item;
     __syncthreads();
@@ -1628,6 +1710,19 @@ __global__ __launch_bounds__(kBlock) void bat_cqk_vjp_kernel(BatCqkArgs A) {
     }
     __syncthreads();
   }
+}
+
+// The outcome of a forward call from the host copy of its counters: the
+// groups' lines combined.
+BatStat host_stat(const int32_t* hc, bool max_over) {
+  BatStat t{0, 0, 0};
+  for (int q = 0; q < kQueues; ++q) {
+    const int32_t* line = hc + CTR_STAT0 + q * kCtrLine;
+    t.flags |= line[CTR_FLAGS];
+    t.surv += line[CTR_SURV];
+    t.over = max_over ? std::max(t.over, line[CTR_OVER]) : t.over + line[CTR_OVER];
+  }
+  return t;
 }
 
 struct BatWs {
@@ -1889,15 +1984,16 @@ cqk_status run_batched_cqk(cqk_ctx* ctx, int32_t nseg, const int64_t* offsets, c
   int32_t* hc = (int32_t*)ctx->host_pinned;
   const bool timing = o.timing != 0;
   auto fill = [ctx, hc, timing](cqk_info* inf) {
-    const int flags = hc[CTR_FLAGS];
+    const BatStat t = host_stat(hc, true);
+    const int flags = t.flags;
     int status = CQK_OK;
     if (flags & kBadValue) status = CQK_INVALID_ARG;
     else if (flags & kInfeasible) status = CQK_INFEASIBLE;
     else if (flags & kNotConverged) status = CQK_NOT_CONVERGED;
     std::memset(inf, 0, sizeof(*inf));
     inf->status = status;
-    inf->iterations = hc[CTR_ITMAX];
-    inf->passes = hc[CTR_ITSUM];
+    inf->iterations = t.over;
+    inf->passes = t.surv;
     if (timing) {
       float ms = 0.f;
       hipEventElapsedTime(&ms, ctx->events[0], ctx->events[1]);
@@ -2042,16 +2138,17 @@ bool valid_schedule(const cqk_batch_schedule& sc) {
 // counters.
 void bat_fill_info(cqk_ctx* ctx, cqk_info* inf) {
   const int32_t* hc = (const int32_t*)ctx->host_pinned;
-  const int flags = hc[CTR_FLAGS];
+  const BatStat t = host_stat(hc, false);
+  const int flags = t.flags;
   int status = CQK_OK;
   if (flags & (kBadRadius | kBadValue)) status = CQK_INVALID_ARG;
   else if (flags & kInfeasible) status = CQK_INFEASIBLE;
   std::memset(inf, 0, sizeof(*inf));
   inf->status = status;
-  inf->n_after_init = hc[CTR_SURV];
+  inf->n_after_init = t.surv;
   inf->iterations = 0;
   inf->passes = 1;
-  inf->rows_spilled = hc[CTR_OVER];
+  inf->rows_spilled = t.over;
   if (ctx->bat_timing) {
     float ms = 0.f;
     hipEventElapsedTime(&ms, ctx->events[0], ctx->events[1]);
