@@ -66,6 +66,10 @@ def cqk_reserve(ctx: int, max_n: int, max_seg: int) -> int:
     return lib().cqk_reserve(C.c_void_p(ctx), max_n, max_seg)
 
 
+def cqk_set_team_wait(ctx: int, ticks: int) -> int:
+    return lib().cqk_set_team_wait(C.c_void_p(ctx), ticks)
+
+
 def cqk_status_string(status: int) -> str:
     return lib().cqk_status_string(status).decode()
 

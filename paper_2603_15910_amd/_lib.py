@@ -147,6 +147,7 @@ SIGNATURES = {
     "cqk_destroy": (None, [_P]),
     "cqk_set_stream": (C.c_int, [_P, _P]),
     "cqk_reserve": (C.c_int, [_P, _I64, _I32]),
+    "cqk_set_team_wait": (C.c_int, [_P, _I64]),
     "cqk_status_string": (C.c_char_p, [_I32]),
     "cqk_default_opts": (None, [_OPTS]),
     "cqk_last_trace": (C.c_int, [_P, C.POINTER(cqk_trace_rec), _I32, C.POINTER(_I32)]),

@@ -12,6 +12,7 @@
 
 #include "../../include/cqk.h"
 #include "cqk_internal.h"
+#include "cqk_team.h"
 
 namespace cqk {
 
@@ -57,6 +58,24 @@ cqk_status ensure_buffer(cqk_ctx* ctx, DeviceBuf& b, size_t bytes) {
   b.ptr = p;
   b.bytes = want;
   return CQK_OK;
+}
+
+bool team_ready(cqk_ctx* ctx, uint32_t need) {
+  if (ctx->team_wait == 0) return false;
+  const bool fresh = ctx->team.ptr == nullptr;
+  if (fresh && ensure_buffer(ctx, ctx->team, kTeamSlotBytes + kTeamCtlBytes) != CQK_OK)
+    return false;
+  if (!fresh && ctx->team_tag < 0x80000000u - need) return true;
+  if (stream_capturing(ctx->stream)) return true;  // its tags come from device memory
+  // waited for: the next call may come on another stream
+  if (hipMemsetAsync(ctx->team.ptr, 0, kTeamSlotBytes + (fresh ? kTeamCtlBytes : 0),
+                     ctx->stream) != hipSuccess ||
+      hipStreamSynchronize(ctx->stream) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  ctx->team_tag = 0;
+  return true;
 }
 
 cqk_status ensure_events(cqk_ctx* ctx, size_t count) {
@@ -297,6 +316,7 @@ void cqk_destroy(cqk_ctx* ctx) {
   if (ctx->state.ptr) hipFree(ctx->state.ptr);
   if (ctx->bitmap.ptr) hipFree(ctx->bitmap.ptr);
   if (ctx->spg.ptr) hipFree(ctx->spg.ptr);
+  if (ctx->team.ptr) hipFree(ctx->team.ptr);
   if (ctx->host_pinned) hipHostFree(ctx->host_pinned);
   for (hipEvent_t e : ctx->events) hipEventDestroy(e);
   delete ctx;
@@ -319,7 +339,17 @@ cqk_status cqk_reserve(cqk_ctx* ctx, int64_t max_n, int32_t max_seg) {
   const size_t want = std::max(gen, (size_t)max_n * 64) + (size_t)max_seg * 64 + (4u << 20);
   cqk_status st = ensure_buffer(ctx, ctx->ws, want);
   if (st != CQK_OK) return st;
-  return ensure_buffer(ctx, ctx->state, 1024 + sizeof(cqk_trace_rec) * kMaxTrace);
+  st = ensure_buffer(ctx, ctx->state, 1024 + sizeof(cqk_trace_rec) * kMaxTrace);
+  if (st != CQK_OK) return st;
+  // without these a captured call takes its multi-launch route
+  (void)team_ready(ctx, 0);
+  return CQK_OK;
+}
+
+cqk_status cqk_set_team_wait(cqk_ctx* ctx, int64_t ticks) {
+  if (!ctx || ticks < 0) return CQK_INVALID_ARG;
+  ctx->team_wait = (uint64_t)ticks;
+  return CQK_OK;
 }
 
 const char* cqk_status_string(int32_t s) {

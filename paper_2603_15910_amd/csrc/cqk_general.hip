@@ -64,6 +64,7 @@
 #include "cqk_alg1.h"
 #include "cqk_device.h"
 #include "cqk_internal.h"
+#include "cqk_team.h"
 
 namespace cqk {
 namespace {
@@ -1470,7 +1471,7 @@ template <typename TIn>
 __global__ __launch_bounds__(kBlock) void gen_finalize_kernel(GenArgs A) {
   GenState* st = A.st;
   const int status = st->status;
-  if (status != CQK_OK && status != CQK_NOT_CONVERGED) return;
+  if ((status != CQK_OK && status != CQK_NOT_CONVERGED) || st->team_done) return;
   constexpr int V = VecWidth<TIn>::value;
   const double lam = st->lam_final;
   const int64_t count = A.n;
@@ -1563,7 +1564,7 @@ __global__ __launch_bounds__(kBlock) void gen_finalize_kernel(GenArgs A) {
 __global__ __launch_bounds__(kRBlock) void gen_finalize_reduce_kernel(GenArgs A, int G) {
   GenState* st = A.st;
   const int status = st->status;
-  if (status != CQK_OK && status != CQK_NOT_CONVERGED) return;
+  if ((status != CQK_OK && status != CQK_NOT_CONVERGED) || st->team_done) return;
   __shared__ double lds[3 * (kRBlock / kWave)];
   __shared__ double tot[3];
   reduce_partials<3, 0, 0, kRBlock>(A.partials, G, lds, tot);
@@ -1575,6 +1576,319 @@ __global__ __launch_bounds__(kRBlock) void gen_finalize_reduce_kernel(GenArgs A,
 }
 
 __global__ void gen_init_kernel(GenState* st, GenState init) { *st = init; }
+
+// ---------------------------------------------------------------------------
+// The whole solve in one launch, for inputs whose per-index form fits the
+// compute units' registers (kTeamBlock threads of E values, one block per
+// compute unit: 2 097 152 indices on 256).  The arrays are read once, every
+// evaluation runs on registers, the blocks exchange their sums through
+// memory (cqk_team.h) and each runs the scalar update itself on the same
+// totals, so all hold the same state; the arrays are read a second time
+// (from cache at these sizes) when x is written with eq. (xopt) as the
+// x-writing pass does.  Algorithm 1's iterates are those of the multi-launch
+// route to the rounding of sums added in another order.
+// What bounds it is latency: launch, load, about 3 us per evaluation, store.
+// Whole calls, FP64, multi-launch route against this one: n = 1e3 92 / 35 us,
+// 1e5 93 / 41, 5e5 98 / 44, 1e6 117 / 57, 2e6 167 / 86.
+// ---------------------------------------------------------------------------
+struct TeamResult {   // in the context's pinned host memory
+  double lam_final, lam0, bytes;
+  int32_t status, iter, passes, stop_reason;
+  int32_t gave_up;    // 1: some block's wait ran out; nothing here counts
+  uint32_t tag;       // the last exchange's tag
+  int32_t ntrace, pad_;
+  double part[3 * kTeamMax];  // per block: b^T x, sum |b x|, free indices
+};
+
+// Device memory behind the record slots: the control words of queued and
+// captured launches, whose tags come from device memory (a replay must not
+// repeat its tags; they have the top bit set, those of waiting calls clear),
+// and what such a launch leaves for the kernels queued behind it.
+struct TeamCtl {
+  uint32_t base, next;   // tags of the current launch; first tag never used
+  GenState state;
+  TeamResult res;
+};
+static_assert(sizeof(TeamCtl) <= kTeamCtlBytes, "the control block fits its reserve");
+constexpr uint32_t kTeamDeviceTags = 0x80000000u;
+
+struct TeamArgs {
+  const void *d, *a, *b, *l, *u, *xw;
+  void* x;
+  int64_t n;
+  int32_t formula;    // lam_0 from eq. (CQKlambda0)
+  int32_t max_pass;
+  GenState init;
+  Team team;
+  TeamResult* res;
+  TeamCtl* ctl;       // queued or captured call: tags from here, state left here
+};
+
+// Before a queued or captured one-launch solve: the run state of the kernels
+// queued behind it, a fresh range of tags (the slots are cleared when the
+// range starts over) and a clear result.
+__global__ __launch_bounds__(256) void gen_team_init_kernel(GenState* st, GenState init,
+                                                            TeamCtl* ctl, uint64_t* slots,
+                                                            uint32_t need) {
+  const uint32_t next = ctl->next;
+  const bool wrap = next == 0 || next > 0xffffffffu - need;
+  __syncthreads();
+  if (wrap)
+    for (size_t i = threadIdx.x; i < kTeamSlotBytes / sizeof(uint64_t); i += 256) slots[i] = 0;
+  if (threadIdx.x == 0) {
+    *st = init;
+    const uint32_t base = wrap ? kTeamDeviceTags : next;
+    ctl->base = base;
+    ctl->next = base + need;
+    ctl->res.gave_up = 0;
+  }
+}
+
+// After it: its state becomes the run state, so the passes queued behind
+// return at once, unless a block gave up; then those passes do the solve.
+__global__ void gen_team_commit_kernel(GenState* st, TeamCtl* ctl) {
+  if (ctl->res.gave_up) return;
+  *st = ctl->state;
+  st->team_done = (st->status != kRunning) ? 1 : 0;
+}
+
+template <typename TIn, int E>
+__global__ __launch_bounds__(kTeamBlock) void gen_team_kernel(TeamArgs A) {
+  constexpr int V = VecWidth<TIn>::value;
+  constexpr int NW = kTeamBlock / kWave;
+  // vectors of a load group (with E = 16 the form leaves registers for four
+  // values of each array in flight)
+  constexpr int Q = (E == 8 ? 8 : 4) / V;
+  __shared__ GenState st;
+  __shared__ double lds[8 * NW], mine[8], tot[8], all[8 * kTeamMax];
+  __shared__ KeySum ktot[2];
+  __shared__ int gave_up;
+  const int tid = threadIdx.x;
+  const int64_t n = A.n;
+  const int64_t base = (int64_t)blockIdx.x * (kTeamBlock * E);
+  const bool whole = base + kTeamBlock * E <= n;
+  const TIn* pd = (const TIn*)A.d;
+  const TIn* pa = (const TIn*)A.a;
+  const TIn* pb = (const TIn*)A.b;
+  const TIn* pl = (const TIn*)A.l;
+  const TIn* pu = (const TIn*)A.u;
+  const TIn* pw = (const TIn*)A.xw;
+  typedef typename Raw16<TIn>::type Raw;
+  // value e = q V + k of this thread: index base + (q kTeamBlock + tid) V + k
+  auto index = [&](int q) { return base + ((int64_t)q * kTeamBlock + tid) * V; };
+  // vectors q0 .. q0 + Q - 1 of one array, every load issued before the
+  // first use; `fill` past the end
+  auto load = [&](const TIn* p, int q0, TIn fill, Raw* o) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int64_t i = index(q0 + q);
+      if (whole) {
+        o[q] = *reinterpret_cast<const Raw*>(p + i);
+      } else {
+#pragma unroll
+        for (int k = 0; k < V; ++k) o[q][k] = (i + k < n) ? p[i + k] : fill;
+      }
+    }
+  };
+  const bool start = pw != nullptr || A.formula != 0;
+  double c[E], s[E], bl[E], bu[E];
+  double bad = 0.0;
+  double w[WM_NSUM] = {0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+  for (int q0 = 0; q0 < E / V; q0 += Q) {
+    __builtin_amdgcn_sched_barrier(0);  // one group's loads at a time
+    Raw rd[Q], ra[Q], rb[Q], rl[Q], ru[Q], rw[Q];
+    load(pd, q0, (TIn)1, rd);
+    load(pa, q0, (TIn)0, ra);
+    load(pb, q0, (TIn)1, rb);
+    load(pl, q0, (TIn)0, rl);
+    load(pu, q0, (TIn)0, ru);
+    if (pw != nullptr) load(pw, q0, (TIn)0, rw);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+#pragma unroll
+      for (int k = 0; k < V; ++k) {
+        const int e = (q0 + q) * V + k;
+        const bool in = whole || index(q0 + q) + k < n;
+        const double vl = (double)rl[q][k], vu = (double)ru[q][k];
+        double b1 = 0.0;
+        to_form((double)rd[q][k], (double)ra[q][k], (double)rb[q][k], vl, vu, c[e], s[e], bl[e],
+                bu[e], b1);
+        bad += in ? b1 : 0.0;
+        // an index past the end adds nothing: no slope, both bounds zero
+        c[e] = in ? c[e] : 0.0;
+        s[e] = in ? s[e] : 0.0;
+        if (start && in) {
+          w[WM_SALL] += c[e];
+          w[WM_QALL] += s[e];
+          if (pw != nullptr) {
+            const double vx = (double)rw[q][k];
+            const bool fr = (vx > vl) && (vx < vu);
+            const bool at_l = !fr && (vx <= vl);
+            const bool at_u = !fr && (vx >= vu);
+            w[WM_SJ] += fr ? c[e] : 0.0;
+            w[WM_QJ] += fr ? s[e] : 0.0;
+            w[WM_NJ] += fr ? 1.0 : 0.0;
+            w[WM_FIX] += at_l ? bl[e] : (at_u ? bu[e] : 0.0);
+          }
+        }
+      }
+    }
+  }
+  if (tid == 0) st = A.init;
+  if (A.ctl != nullptr) A.team.tag = A.ctl->base;
+  bool ok = true;
+  if (start) {
+    // lam_0 of the estimate, or of eq. (CQKlambda0) (gen_warm_update_kernel,
+    // gen_lambda0_update_kernel)
+    w[WM_BAD] = bad;
+    block_reduce<WM_NSUM, 0, 0, kTeamBlock>(w, nullptr, nullptr, lds, mine);
+    ok = team_exchange<WM_NSUM>(A.team, mine, all, &gave_up);
+    team_sum<WM_NSUM>(all, tot);
+    if (tid == 0) {
+      st.passes += 1;
+      st.bytes += (pw != nullptr ? st.in_bytes * 6.0 / 5.0 : st.in_bytes) * (double)n;
+      if (tot[WM_BAD] > 0.0) {
+        st.status = CQK_INVALID_ARG;
+      } else {
+        double lam0;
+        if (pw != nullptr)
+          lam0 = (tot[WM_NJ] > 0.0) ? (st.r - tot[WM_FIX] - tot[WM_SJ]) / tot[WM_QJ]
+                                    : (st.r - tot[WM_SALL]) / tot[WM_QALL];
+        else
+          lam0 = (tot[WM_QALL] > 0.0) ? (st.r - tot[WM_SALL]) / tot[WM_QALL] : 0.0;
+        st.lam = st.lam0 = lam0;
+      }
+      st.ntrace += 1;
+    }
+  }
+  __syncthreads();
+  // every block takes the same branches: the state is the same in all
+  for (int pass = 0; ok && pass < A.max_pass && st.status == kRunning; ++pass) {
+    const double lam = st.lam;
+    if (st.mode == kModeEval) {
+      Acc acc;
+      acc_init(acc);
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        eval_index<false>(acc, c[e], s[e], bl[e], bu[e], lam, 0.0, 0.0);
+      const double v[5] = {acc.s[P_P], acc.s[P_A], acc.s[P_QP], acc.s[P_QM], bad};
+      block_reduce<5, 0, 0, kTeamBlock>(v, nullptr, nullptr, lds, mine);
+      ok = team_exchange<5>(A.team, mine, all, &gave_up);
+      team_sum<5>(all, tot);
+      if (tid == 0) {
+        double t[NSUM];
+#pragma unroll
+        for (int i = 0; i < NSUM; ++i) t[i] = 0.0;
+        t[P_P] = tot[0];
+        t[P_A] = tot[1];
+        t[P_QP] = tot[2];
+        t[P_QM] = tot[3];
+        t[P_BAD] = tot[4];
+        t[P_NIN] = (double)n;
+        // on the record in LDS: a copy in registers would cost every thread
+        // its size (256 VGPRs and spills)
+        update_after_eval(&st, t, nullptr);
+      }
+    } else {
+      KeySum ks[2] = {KeySum{inf_d(), 0.0}, KeySum{inf_d(), 0.0}};
+#pragma unroll
+      for (int e = 0; e < E; ++e) bkpt_index(ks, c[e], s[e], bl[e], bu[e], lam);
+      block_ks_min<2, kTeamBlock>(ks, lds, ktot);
+      if (tid < 4) mine[tid] = (tid & 1) ? ktot[tid >> 1].w : ktot[tid >> 1].k;
+      __syncthreads();
+      ok = team_exchange<4>(A.team, mine, all, &gave_up);
+      if (tid < kWave) {
+        const int T = gridDim.x;
+        KeySum k2[2] = {KeySum{inf_d(), 0.0}, KeySum{inf_d(), 0.0}};
+        for (int g = tid; g < T; g += kWave) {
+          k2[0] = ks_min(k2[0], KeySum{all[g], all[T + g]});
+          k2[1] = ks_min(k2[1], KeySum{all[2 * T + g], all[3 * T + g]});
+        }
+        k2[0] = wave_ks_min(k2[0]);
+        k2[1] = wave_ks_min(k2[1]);
+        if (tid == 0) update_after_bkpt(&st, k2, nullptr);
+      }
+    }
+    __syncthreads();
+  }
+  if (!ok) {
+    if (tid == 0) A.res->gave_up = 1;
+    return;
+  }
+  const int status = st.status;
+  double sums[3] = {0.0, 0.0, 0.0};
+  if (status == CQK_OK || status == CQK_NOT_CONVERGED) {
+    const double lam = st.lam_final;
+    TIn* px = (TIn*)A.x;
+#pragma unroll
+    for (int q0 = 0; q0 < E / V; q0 += Q) {
+      __builtin_amdgcn_sched_barrier(0);
+      Raw rd[Q], ra[Q], rb[Q], rl[Q], ru[Q];
+      load(pd, q0, (TIn)1, rd);
+      load(pa, q0, (TIn)0, ra);
+      load(pb, q0, (TIn)0, rb);
+      load(pl, q0, (TIn)0, rl);
+      load(pu, q0, (TIn)0, ru);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const int64_t i = index(q0 + q);
+        Raw o;
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+          const double vb = (double)rb[q][k], vl = (double)rl[q][k], vu = (double)ru[q][k];
+          const double t = fma(vb, lam, (double)ra[q][k]) / (double)rd[q][k];
+          o[k] = (TIn)fmin(fmax(t, vl), vu);
+          const double xr = (double)o[k];
+          if (whole || i + k < n) {
+            sums[0] += vb * xr;
+            sums[1] += fabs(vb * xr);
+            sums[2] += (xr > vl && xr < vu) ? 1.0 : 0.0;
+          }
+        }
+        if (whole) {
+          st16(px + i, o);
+        } else {
+#pragma unroll
+          for (int k = 0; k < V; ++k)
+            if (i + k < n) px[i + k] = o[k];
+        }
+      }
+    }
+  }
+  block_reduce<3, 0, 0, kTeamBlock>(sums, nullptr, nullptr, lds, tot);
+  if (tid < 3) A.res->part[3 * blockIdx.x + tid] = tot[tid];
+  if (blockIdx.x == 0 && tid == 0) {
+    TeamResult& R = *A.res;
+    R.lam_final = st.lam_final;
+    R.lam0 = st.lam0;
+    R.bytes = st.bytes;
+    R.status = status;
+    R.iter = st.iter;
+    R.passes = st.passes;
+    R.stop_reason = st.stop_reason;
+    R.tag = A.team.tag;
+    R.ntrace = st.ntrace;
+    if (A.ctl != nullptr) A.ctl->state = st;
+  }
+}
+
+// Values per thread and blocks of a one-launch solve of n indices, E = 0 when
+// it does not apply: the fewest values per thread that one block per compute
+// unit allows, so that the loads and evaluations are short and all compute
+// units share them.  (One block of 16 values per thread instead of four of 4
+// saves the exchanges but loads slower: n = 8192 48 against 40 us.)
+struct TeamShape {
+  int E, T;
+};
+TeamShape team_shape(int64_t n, int num_cus) {
+  const int64_t cap = std::min(num_cus, kTeamMax);
+  for (int E : {4, 8, 16}) {
+    const int64_t T = (n + (int64_t)kTeamBlock * E - 1) / ((int64_t)kTeamBlock * E);
+    if (T <= cap) return {E, (int)T};
+  }
+  return {0, 0};
+}
 
 int choose_grid(int64_t n, int num_cus) {
   const int64_t want = (n + 1023) / 1024;
@@ -1723,7 +2037,92 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     stt = ensure_events(ctx, nev);
     if (stt != CQK_OK) return stt;
   }
-  hipLaunchKernelGGL(gen_init_kernel, dim3(1), dim3(1), 0, s, A.st, init);
+  // One launch where the problem fits the registers.  Traced and timed calls
+  // report single passes and keep the multi-launch route.
+  const TeamShape shape = team_shape(n, ctx->num_cus);
+  const uint32_t need = 2 * (uint32_t)std::min(o.max_iter, 1 << 20) + 8;
+  const bool team = shape.E != 0 && !o.trace && !o.timing && o.max_iter <= (1 << 20) &&
+                    team_ready(ctx, need);
+  TeamCtl* const ctl = team ? (TeamCtl*)((char*)ctx->team.ptr + kTeamSlotBytes) : nullptr;
+  auto launch_team = [&](TeamResult* res, TeamCtl* tc) {
+    TeamArgs T{};
+    T.d = d;
+    T.a = a;
+    T.b = b;
+    T.l = l;
+    T.u = u;
+    T.xw = xw;
+    T.x = x;
+    T.n = n;
+    T.formula = formula ? 1 : 0;
+    T.max_pass = 2 * o.max_iter + 4;
+    T.init = init;
+    T.init.compaction = CQK_COMPACT_OFF;
+    T.init.trace_cap = 0;
+    T.team = Team{(uint64_t*)ctx->team.ptr, ctx->team_tag, 0, ctx->team_wait};
+    T.res = res;
+    T.ctl = tc;
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(shape.T), dim3(kTeamBlock), 0, s, T);
+    };
+    if (shape.E == 4) go(gen_team_kernel<TIn, 4>);
+    else if (shape.E == 8) go(gen_team_kernel<TIn, 8>);
+    else go(gen_team_kernel<TIn, 16>);
+  };
+  // what the x-writing pass sums up, from the blocks' shares
+  auto team_sums = [r](const TeamResult& R, int T, cqk_info* inf) {
+    double p = 0.0, q = 0.0, nf = 0.0;
+    for (int g = 0; g < T; ++g) {
+      p += R.part[3 * g];
+      q += R.part[3 * g + 1];
+      nf += R.part[3 * g + 2];
+    }
+    inf->residual = std::fabs(p - r);
+    inf->abs_bx = q;
+    inf->n_free = (int64_t)nf;
+  };
+  if (team && !deferred) {
+    TeamResult* res = (TeamResult*)ctx->host_pinned;
+    res->gave_up = 0;
+    launch_team(res, nullptr);
+    if (hip_ok(hipGetLastError()) != CQK_OK) return CQK_DEVICE_ERROR;
+    ctx->team_tag += need;
+    if (hip_ok(hipStreamSynchronize(s)) != CQK_OK) return CQK_DEVICE_ERROR;
+    const TeamResult& R = *res;
+    if (!R.gave_up) {
+      ctx->team_tag = R.tag;
+      ctx->last_trace.clear();
+      ctx->last_trace_count = R.ntrace;
+      ctx->last_pass_ms.clear();
+      cqk_info out;
+      std::memset(&out, 0, sizeof(out));
+      out.status = (R.status == kRunning) ? CQK_NOT_CONVERGED : R.status;
+      out.iterations = R.iter;
+      out.passes = R.passes;
+      out.stop_reason = R.stop_reason;
+      out.lambda = R.lam_final;
+      out.lambda0 = R.lam0;
+      team_sums(R, shape.T, &out);
+      out.pass_bytes = R.bytes;
+      out.finalize_bytes = (double)n * (6.0 * sizeof(TIn));
+      out.pass_launches = 1;
+      ctx->trivial = out;
+      ctx->last = [ctx](cqk_info* inf) -> cqk_status {
+        *inf = ctx->trivial;
+        return CQK_OK;
+      };
+      if (info) *info = out;
+      return CQK_OK;
+    }
+  }
+  if (team && deferred) {
+    hipLaunchKernelGGL(gen_team_init_kernel, dim3(1), dim3(256), 0, s, A.st, init, ctl,
+                       (uint64_t*)ctx->team.ptr, need);
+    launch_team(&ctl->res, ctl);
+    hipLaunchKernelGGL(gen_team_commit_kernel, dim3(1), dim3(1), 0, s, A.st, ctl);
+  } else {
+    hipLaunchKernelGGL(gen_init_kernel, dim3(1), dim3(1), 0, s, A.st, init);
+  }
   if (hip_ok(hipGetLastError()) != CQK_OK) return CQK_DEVICE_ERROR;
   int ev = 2;
   int npass = 0;  // grid passes queued
@@ -1842,10 +2241,18 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     inf->pass_bytes = hs->bytes;
     return CQK_OK;
   };
-  ctx->last = [hs, A, report](cqk_info* inf) -> cqk_status {
+  const int team_blocks = shape.T;
+  ctx->last = [hs, A, report, ctl, team_sums, team_blocks](cqk_info* inf) -> cqk_status {
     if (hip_ok(hipMemcpy(hs, A.st, sizeof(GenState), hipMemcpyDeviceToHost)) != CQK_OK)
       return CQK_DEVICE_ERROR;
-    return report(inf);
+    const bool done = hs->team_done != 0;
+    const cqk_status st = report(inf);
+    if (st != CQK_OK || !done) return st;
+    TeamResult* R = (TeamResult*)hs;  // the state copy has been read
+    if (hip_ok(hipMemcpy(R, &ctl->res, sizeof(TeamResult), hipMemcpyDeviceToHost)) != CQK_OK)
+      return CQK_DEVICE_ERROR;
+    team_sums(*R, team_blocks, inf);
+    return CQK_OK;
   };
   if (deferred) {
     if (info) {

@@ -71,6 +71,7 @@ struct GenState {
   int32_t skip;                   // sides the next evaluation does not write (bit k: side k)
   int32_t warm;                   // 1: lam_0 comes from a primal estimate
   int32_t lam0_later;             // 1: lam_0 is computed after the sample (warm or formula start)
+  int32_t team_done;              // 1: a one-launch solve wrote x and this state
 };
 
 // Run state of the simplex / l1 solver (Algorithm 4 on a compacted set).
@@ -142,6 +143,12 @@ struct cqk_ctx {
   cqk_info trivial{};               // the last call answered on the host
   int32_t* bat_counters = nullptr;  // device counters of the last batched forward call
   bool bat_timing = false;          // that call recorded events[0..1]
+  // One-launch solves (cqk_team.h): the blocks' record slots (zeroed when
+  // allocated), the last tag used in them, the longest wait of an exchange in
+  // ticks of the 100 MHz clock (0: such solves are not used).
+  cqk::DeviceBuf team;
+  uint32_t team_tag = 0;
+  uint64_t team_wait = 2000000;
   void* scratch = nullptr;  // this device's no-allocation planning buffers (noalloc_scratch)
 };
 
@@ -150,6 +157,12 @@ namespace cqk {
 // Grows b to at least `bytes`.  While ctx's stream is capturing a graph it
 // allocates nothing: a buffer too small then gives CQK_NO_MEMORY.
 cqk_status ensure_buffer(cqk_ctx* ctx, DeviceBuf& b, size_t bytes);
+// Makes the record slots and control block of a one-launch solve ready for
+// `need` exchanges of a waiting call (tags team_tag + 1 ..., below 2^31):
+// allocates and zeroes them on first use, clears the slots when the tags run
+// out.  false: the caller takes its multi-launch route (a capturing stream
+// whose context has no slots yet among them).
+bool team_ready(cqk_ctx* ctx, uint32_t need);
 // true while stream s is capturing a graph
 bool stream_capturing(hipStream_t s);
 cqk_status hip_ok(hipError_t e);
