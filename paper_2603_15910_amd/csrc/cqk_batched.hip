@@ -75,8 +75,9 @@ struct BatArgs {
 
 // The call's counters, in lines of 32 ints (128 bytes): line 0 holds the rows
 // of each class and the work items, the next kQueues lines one work queue
-// each, the last kQueues lines the call's outcome as summed by the blocks of
-// one queue (flags, survivors, rows whose lists overflowed).  Atomics on one
+// each, the next kQueues the queues of a second kernel (the general form's
+// wave rows), the last kQueues lines the call's outcome as summed by the
+// blocks of one queue (flags, survivors, rows whose lists overflowed).  Atomics on one
 // address take turns at about 13 ns each on this part, so one shared queue
 // and one shared survivor total, updated per row, bounded every call of many
 // rows (65 536 rows of 64-512 values: 1.70 ms for 147 456 atomics): blocks
@@ -84,8 +85,9 @@ struct BatArgs {
 constexpr int CTR_NLONG = 0, CTR_NSHORT = 1, CTR_NITEMS = 2;
 constexpr int CTR_FLAGS = 0, CTR_SURV = 1, CTR_OVER = 2;
 constexpr int kQueues = 32, kCtrLine = 32;
-constexpr int CTR_QUEUE0 = kCtrLine, CTR_STAT0 = (1 + kQueues) * kCtrLine,
-              CTR_TOTAL = (1 + 2 * kQueues) * kCtrLine;
+constexpr int CTR_QUEUE0 = kCtrLine, CTR_QUEUE1 = (1 + kQueues) * kCtrLine,
+              CTR_STAT0 = (1 + 2 * kQueues) * kCtrLine,
+              CTR_TOTAL = (1 + 3 * kQueues) * kCtrLine;
 
 // A block's outcome, in LDS until the block ends.
 struct BatStat {
@@ -119,11 +121,11 @@ __device__ __forceinline__ void stat_flush(const BatStat& t, int32_t* counters) 
 // returns nitems or more once every queue is empty.
 struct ItemSource {
   int own = (int)(blockIdx.x % kQueues);
-  __device__ __forceinline__ int next(int32_t* counters, int nitems) {
+  __device__ __forceinline__ int next(int32_t* queues, int nitems) {
     const int lane = threadIdx.x & (kWave - 1);
     for (;;) {
       int k = 0;
-      if (lane == 0) k = atomicAdd(&counters[CTR_QUEUE0 + own * kCtrLine], 1);
+      if (lane == 0) k = atomicAdd(&queues[own * kCtrLine], 1);
       k = __builtin_amdgcn_readfirstlane(k);
       const int64_t item = own + (int64_t)k * kQueues;
       if (item < nitems) return (int)item;
@@ -131,7 +133,7 @@ struct ItemSource {
       // after this block's
       int64_t at = nitems;
       if (lane < kQueues)
-        at = lane + (int64_t)__hip_atomic_load(&counters[CTR_QUEUE0 + lane * kCtrLine],
+        at = lane + (int64_t)__hip_atomic_load(&queues[lane * kCtrLine],
                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) *
                         kQueues;
       const uint64_t m = __ballot(at < nitems);
@@ -1011,7 +1013,7 @@ __global__ __launch_bounds__(kBlock, 3) void bat_solve_kernel(BatArgs A) {
   stat_init(L.stat);
   for (;;) {
     if (threadIdx.x < kWave) {
-      const int next = src.next(A.counters, nitems);
+      const int next = src.next(A.counters + CTR_QUEUE0, nitems);
       if (threadIdx.x == 0) L.item = next;
     }
     __syncthreads();
@@ -1194,7 +1196,7 @@ __global__ __launch_bounds__(kBlock) void bat_vjp_kernel(BatArgs A) {
   ItemSource src;
   for (;;) {
     if (threadIdx.x < kWave) {
-      const int next = src.next(A.counters, nitems);
+      const int next = src.next(A.counters + CTR_QUEUE0, nitems);
       if (threadIdx.x == 0) L.item = next;
     }
     __syncthreads();
@@ -1322,7 +1324,7 @@ __device__ __forceinline__ bool cqk_has_lambda(const GenState& st) {
 // ---------------------------------------------------------------------------
 template <int SP, typename TIn>
 __device__ void cqk_short_row(const BatCqkArgs& A, int s, int64_t base, int64_t L,
-                              BatStat& stat) {
+                              double r, BatStat& stat) {
   const CqkArrays<TIn> V(A);
   const int lane = threadIdx.x & (kWave - 1);
   double c[SP], sv[SP], bl[SP], bu[SP];
@@ -1353,7 +1355,9 @@ __device__ void cqk_short_row(const BatCqkArgs& A, int s, int64_t base, int64_t 
       }
     }
   }
-  const double r = A.r[s];
+  // slots in use, the same for the whole wave: a short row skips the others
+  // (the lanes past its end hold zeros, which add nothing to any sum)
+  const int nk = __builtin_amdgcn_readfirstlane((int)((L + kWave - 1) / kWave));
   GenState st = cqk_row_state(A, r);
   if (wave_sum(bad) > 0.0 || !(fabs(r) < inf_d())) {
     st.status = CQK_INVALID_ARG;
@@ -1370,21 +1374,19 @@ __device__ void cqk_short_row(const BatCqkArgs& A, int s, int64_t base, int64_t 
       acc_init(acc);
 #pragma unroll
       for (int k = 0; k < SP; ++k)
-        if (lane + (int64_t)k * kWave < L) eval_index<false>(acc, c[k], sv[k], bl[k], bu[k], st.lam, st.lo, st.hi);
+        if (k < nk) eval_index<false>(acc, c[k], sv[k], bl[k], bu[k], st.lam, 0.0, 0.0);
       double t[NSUM];
 #pragma unroll
       for (int i = 0; i < NSUM; ++i) t[i] = 0.0;
-      t[P_P] = wave_sum(acc.s[P_P]);
-      t[P_A] = wave_sum(acc.s[P_A]);
-      t[P_QP] = wave_sum(acc.s[P_QP]);
-      t[P_QM] = wave_sum(acc.s[P_QM]);
+      static_assert(P_P == 0 && P_A == 1 && P_QP == 2 && P_QM == 3, "the four sums");
+      wave_sum4(acc.s, t);
       t[P_NIN] = (double)L;
       update_after_eval(&st, t, nullptr);
     } else {
       KeySum ks[2] = {KeySum{inf_d(), 0.0}, KeySum{inf_d(), 0.0}};
 #pragma unroll
       for (int k = 0; k < SP; ++k)
-        if (lane + (int64_t)k * kWave < L) bkpt_index(ks, c[k], sv[k], bl[k], bu[k], st.lam);
+        if (k < nk) bkpt_index(ks, c[k], sv[k], bl[k], bu[k], st.lam);
       ks[0] = wave_ks_min(ks[0]);
       ks[1] = wave_ks_min(ks[1]);
       update_after_bkpt(&st, ks, nullptr);
@@ -1392,10 +1394,34 @@ __device__ void cqk_short_row(const BatCqkArgs& A, int s, int64_t base, int64_t 
   }
   const bool ok = cqk_has_lambda(st);
   const double lam = ok ? st.lam_final : __builtin_nan("");
+  if (L > 0) {
+    // the row again (from cache): a slot's loads unguarded, issued together
+    constexpr int H = 4;
 #pragma unroll
-  for (int k = 0; k < SP; ++k) {
-    const int64_t i = lane + (int64_t)k * kWave;
-    if (i < L) V.x[base + i] = (TIn)(ok ? cqk_x_at(V, base + i, lam) : __builtin_nan(""));
+    for (int k0 = 0; k0 < SP; k0 += H) {
+      if (k0 < nk) {
+        TIn rd[H], ra[H], rb[H], rl[H], ru[H];
+#pragma unroll
+        for (int k = 0; k < H; ++k) {
+          const int64_t i = lane + (int64_t)(k0 + k) * kWave;
+          const int64_t e = base + (i < L ? i : L - 1);
+          rd[k] = V.d[e];
+          ra[k] = V.a[e];
+          rb[k] = V.b[e];
+          rl[k] = V.l[e];
+          ru[k] = V.u[e];
+        }
+#pragma unroll
+        for (int k = 0; k < H; ++k) {
+          const int64_t i = lane + (int64_t)(k0 + k) * kWave;
+          if (k0 + k < nk) {
+            const double xv = fmin(fmax(fma((double)rb[k], lam, (double)ra[k]) / (double)rd[k],
+                                        (double)rl[k]), (double)ru[k]);
+            if (i < L) V.x[base + i] = (TIn)(ok ? xv : __builtin_nan(""));
+          }
+        }
+      }
+    }
   }
   if (lane == 0) cqk_row_report(A, s, st, lam, stat);
 }
@@ -1516,42 +1542,81 @@ __device__ void cqk_long_row(const BatCqkArgs& A, int s, int64_t base, int64_t L
   if (threadIdx.x == 0) cqk_row_report(A, s, st, lam, S.stat);
 }
 
+// The wave rows, four to a block at a time; each wave takes kRowsPerWave rows
+// of an item one after the other when there are enough items to go round, so
+// the block meets less often.  A kernel of its own: the registers of a
+// workgroup row's loads would cost its waves' occupancy.
+constexpr int kRowsPerWave = 4;
+
+// Lane j's value in every lane, as a scalar.
+template <typename T>
+__device__ __forceinline__ T lane_value(T v, int j) {
+  static_assert(sizeof(T) == 8, "two 32-bit halves");
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, j);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), j);
+  return __builtin_bit_cast(T, ((uint64_t)hi << 32) | lo);
+}
+
 template <int SP, typename TIn>
+__global__ __launch_bounds__(kBlock, 3) void bat_cqk_wave_kernel(BatCqkArgs A) {
+  __shared__ BatStat stat;
+  __shared__ int item_s;
+  const int nlong = A.counters[CTR_NLONG];
+  const int nshort = A.counters[CTR_NSHORT];
+  const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int per = min(kRowsPerWave, max(1, nshort / ((int)gridDim.x * kWaves * kRowsPerWave)));
+  const int nitems = (nshort + kWaves * per - 1) / (kWaves * per);
+  ItemSource src;
+  stat_init(stat);
+  for (;;) {
+    if (threadIdx.x < kWave) {
+      const int next = src.next(A.counters + CTR_QUEUE1, nitems);
+      if (threadIdx.x == 0) item_s = next;
+    }
+    __syncthreads();
+    const int item = item_s;
+    __syncthreads();
+    if (item >= nitems) break;
+    // the wave's rows of this item: ids, extents and right-hand sides in two
+    // round trips for all of them, one lane each
+    const int lane = threadIdx.x & (kWave - 1);
+    const int k0 = item * per * kWaves + wid;
+    int id = 0;
+    int64_t first = 0, len = 0;
+    double rhs = 0.0;
+    if (lane < per && k0 + lane * kWaves < nshort) {
+      const size_t e = (size_t)nlong + k0 + lane * kWaves;
+      id = A.list[e];
+      first = A.lrow[2 * e];
+      len = A.lrow[2 * e + 1];
+      rhs = A.r[id];
+    }
+    for (int j = 0; j < per && k0 + j * kWaves < nshort; ++j)
+      cqk_short_row<SP, TIn>(A, __builtin_amdgcn_readlane(id, j), lane_value(first, j),
+                             lane_value(len, j), lane_value(rhs, j), stat);
+  }
+  __syncthreads();
+  stat_flush<true>(stat, A.counters);
+}
+
+// The workgroup rows.
+template <typename TIn>
 __global__ __launch_bounds__(kBlock) void bat_cqk_solve_kernel(BatCqkArgs A) {
   __shared__ CqkLds S;
   const int nlong = A.counters[CTR_NLONG];
-  const int nshort = A.counters[CTR_NSHORT];
-  const int nitems = A.counters[CTR_NITEMS];
-  const int nsg = nitems - nlong;
   ItemSource src;
   stat_init(S.stat);
   for (;;) {
     if (threadIdx.x < kWave) {
-      const int next = src.next(A.counters, nitems);
+      const int next = src.next(A.counters + CTR_QUEUE0, nlong);
       if (threadIdx.x == 0) S.item = next;
     }
     __syncthreads();
-    const int item = S.item;
+    const int idx = S.item;
     __syncthreads();
-    if (item >= nitems) break;
-    int idx;
-    bool is_long;
-    if (A.short_first) {
-      is_long = item >= nsg;
-      idx = is_long ? item - nsg : item;
-    } else {
-      is_long = item < nlong;
-      idx = is_long ? item : item - nlong;
-    }
-    if (is_long) {
-      cqk_long_row<TIn>(A, A.list[idx], A.lrow[2 * (size_t)idx], A.lrow[2 * (size_t)idx + 1], S);
-    } else {
-      const int k = idx * kWaves + (int)(threadIdx.x / kWave);
-      if (k < nshort) {
-        const size_t e = (size_t)nlong + k;
-        cqk_short_row<SP, TIn>(A, A.list[e], A.lrow[2 * e], A.lrow[2 * e + 1], S.stat);
-      }
-    }
+    if (idx >= nlong) break;
+    cqk_long_row<TIn>(A, A.list[idx], A.lrow[2 * (size_t)idx], A.lrow[2 * (size_t)idx + 1], S);
     __syncthreads();
   }
   stat_flush<true>(S.stat, A.counters);
@@ -1682,7 +1747,7 @@ __global__ __launch_bounds__(kBlock) void bat_cqk_vjp_kernel(BatCqkArgs A) {
   ItemSource src;
   for (;;) {
     if (threadIdx.x < kWave) {
-      const int next = src.next(A.counters, nitems);
+      const int next = src.next(A.counters + CTR_QUEUE0, nitems);
       if (threadIdx.x == 0) S.item = next;
     }
     __syncthreads();
@@ -1934,10 +1999,19 @@ void launch_cqk_forward(cqk_ctx* ctx, const cqk_batch_schedule& sc, BatCqkArgs A
   dim3 grid;
   cqk_apply_schedule(ctx, sc, &A, &grid);
   plan(ctx, A);
-  if (sc.small_per == 4)
-    hipLaunchKernelGGL((bat_cqk_solve_kernel<4, TIn>), grid, dim3(kBlock), 0, ctx->stream, A);
-  else
-    hipLaunchKernelGGL((bat_cqk_solve_kernel<8, TIn>), grid, dim3(kBlock), 0, ctx->stream, A);
+  auto wave_rows = [&]() {
+    if (sc.small_per == 4)
+      hipLaunchKernelGGL((bat_cqk_wave_kernel<4, TIn>), grid, dim3(kBlock), 0, ctx->stream, A);
+    else
+      hipLaunchKernelGGL((bat_cqk_wave_kernel<8, TIn>), grid, dim3(kBlock), 0, ctx->stream, A);
+  };
+  if (sc.short_first) wave_rows();
+  // at most two workgroup rows per compute unit: a row is read five times over,
+  // and with more of them in flight fewer of the re-reads are served by the
+  // 256 MB last-level cache
+  const dim3 lgrid(std::min<unsigned>(grid.x, 2u * (unsigned)ctx->num_cus));
+  hipLaunchKernelGGL((bat_cqk_solve_kernel<TIn>), lgrid, dim3(kBlock), 0, ctx->stream, A);
+  if (!sc.short_first) wave_rows();
 }
 
 template <typename TIn>

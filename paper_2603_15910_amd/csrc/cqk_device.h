@@ -130,8 +130,8 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
 // ---------------------------------------------------------------------------
 // ---------------------------------------------------------------------------
 // Many sums over a wave by halving exchanges: at each of the six lane bits
-// (5, 4 through cross-row swizzles; 3, 2, 1, 0 through DPP mirrors and quad
-// permutes, each pairing lanes with opposite bit) a lane keeps half of the
+// (5, 4 through v_permlane32_swap / v_permlane16_swap; 3, 2, 1, 0 through DPP
+// mirrors and quad permutes, each pairing lanes with opposite bit) a lane keeps half of the
 // values it still holds, adds its partner's copy of that half, and hands the
 // other half to the partner; once one value is left the remaining steps add
 // the partner's value.  N sums then cost about N exchanges instead of the 6N
@@ -140,11 +140,32 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
 // bits.  Whole wave active.
 // ---------------------------------------------------------------------------
 namespace detail {
+// Swaps the upper half (BIT 5) or the odd rows of 16 lanes (BIT 4) of a with
+// the lower half, or the even rows, of b.  a + b is then, in the lower half
+// (even rows), a summed over the bit and b in the other: one step of the
+// halving below with no select and no trip through LDS.
+template <int BIT>
+__device__ __forceinline__ void half_swap(double& a, double& b) {
+  static_assert(BIT == 5 || BIT == 4, "the lane bits the swaps cover");
+  const uint64_t ua = __builtin_bit_cast(uint64_t, a), ub = __builtin_bit_cast(uint64_t, b);
+  const uint32_t al = (uint32_t)ua, ah = (uint32_t)(ua >> 32);
+  const uint32_t bl = (uint32_t)ub, bh = (uint32_t)(ub >> 32);
+  if constexpr (BIT == 5) {
+    const auto l = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+    a = __builtin_bit_cast(double, ((uint64_t)h[0] << 32) | l[0]);
+    b = __builtin_bit_cast(double, ((uint64_t)h[1] << 32) | l[1]);
+  } else {
+    const auto l = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+    a = __builtin_bit_cast(double, ((uint64_t)h[0] << 32) | l[0]);
+    b = __builtin_bit_cast(double, ((uint64_t)h[1] << 32) | l[1]);
+  }
+}
+
 template <int BIT>
 __device__ __forceinline__ double lane_swap(double v) {
-  if constexpr (BIT == 5) return __shfl_xor(v, 32, kWave);
-  else if constexpr (BIT == 4) return __shfl_xor(v, 16, kWave);
-  else if constexpr (BIT == 3) return dpp_move<dpp::kMirror, 0xF>(v, 0.0);
+  if constexpr (BIT == 3) return dpp_move<dpp::kMirror, 0xF>(v, 0.0);
   else if constexpr (BIT == 2) return dpp_move<dpp::kHalfMirror, 0xF>(v, 0.0);
   else if constexpr (BIT == 1) return dpp_move<dpp::kXor2, 0xF>(v, 0.0);
   else return dpp_move<dpp::kXor1, 0xF>(v, 0.0);
@@ -152,7 +173,14 @@ __device__ __forceinline__ double lane_swap(double v) {
 
 template <int BIT, int M>
 __device__ __forceinline__ void halve(double* v, int lane) {
-  if constexpr (M > 1) {
+  if constexpr (BIT >= 4) {
+#pragma unroll
+    for (int k = 0; k < (M > 1 ? M / 2 : 1); ++k) {
+      double a = v[k], b = (M > 1) ? v[M / 2 + k] : v[k];
+      half_swap<BIT>(a, b);
+      v[k] = a + b;
+    }
+  } else if constexpr (M > 1) {
     const bool low = ((lane >> BIT) & 1) == 0;
 #pragma unroll
     for (int k = 0; k < M / 2; ++k) {
@@ -179,6 +207,19 @@ __device__ __forceinline__ void wave_sum_many(double* v) {
   detail::halve<2, detail::at_least_one(N / 8)>(v, lane);
   detail::halve<1, detail::at_least_one(N / 16)>(v, lane);
   detail::halve<0, detail::at_least_one(N / 32)>(v, lane);
+}
+
+// Four sums over the wave, the totals in every lane.
+__device__ __forceinline__ void wave_sum4(const double* in, double* out) {
+  double v[4] = {in[0], in[1], in[2], in[3]};
+  wave_sum_many<4>(v);
+  const uint64_t u = __builtin_bit_cast(uint64_t, v[0]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, 16 * i);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), 16 * i);
+    out[i] = __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+  }
 }
 
 template <int NS, int NM, int NX, int BLOCK>

@@ -72,3 +72,29 @@ def test_a_bad_row_is_reported(ctx, nseg):
     y[(nseg - 2) * n + 7] = float("nan")
     _, info = ctx.project_simplex_batched(y, _offsets(nseg, n), 1.0, check=False)
     assert info["status"] == 2   # CQK_INVALID_ARG, whichever block had the row
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("small_per", [4, 8])
+def test_cqk_row_lengths(ctx, dtype, small_per):
+    """Wave rows around their 64-value slots and limits, against the oracle
+    row by row (tests/parity.py bars)."""
+    from oracle import cqk_oracle as O
+    from tests.parity import check_cqk
+    lens = [1, 2, 63, 64, 65, 128, 129, 192, 255, 256, 257, 320, 449, 511, 512, 513, 0, 700] * 2
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    np_t = np.float64 if dtype == torch.float64 else np.float32
+    inst = W.cqk_uniform(int(off[-1]), 9, np_t)
+    mid = inst["b"].astype(np.float64) * (inst["l"].astype(np.float64) + inst["u"]) * 0.5
+    r = np.array([float(np.sum(mid[off[s]:off[s + 1]])) for s in range(len(lens))])
+    ctx.set_batch_schedule(small_per=small_per, general=True)
+    x, info = ctx.solve_batched(*[torch.from_numpy(inst[k]).cuda() for k in "dablu"],
+                                torch.from_numpy(off).cuda(), torch.from_numpy(r).cuda())
+    ctx.set_batch_schedule(general=True)
+    x = x.cpu().numpy()
+    for s, n in enumerate(lens):
+        if n == 0:
+            continue
+        row = {k: inst[k][off[s]:off[s + 1]] for k in "dablu"} | {"r": r[s]}
+        ref = O.solve_cqk(*[row[k] for k in "dablu"], r[s])
+        check_cqk(x[off[s]:off[s + 1]], row, ref, 1e-10 if dtype == torch.float64 else 1e-5)
