@@ -252,26 +252,30 @@ __device__ __forceinline__ void plan_sides(GenState* st) {
   st->skip = skip;
 }
 
+template <bool SETS>
 __device__ __forceinline__ void advance(GenState* st, double next) {
   st->lam_prev = st->lam;
   st->lam = next;
   st->mode = kModeEval;
-  if (st->compaction != CQK_COMPACT_OFF) plan_sides(st);
+  if (SETS && st->compaction != CQK_COMPACT_OFF) plan_sides(st);
   if (st->iter >= st->max_iter) {
     st->status = CQK_NOT_CONVERGED;
     st->lam_final = st->lam_prev;
   }
 }
 
-// The scalar part of Algorithm 1, run by one thread after an evaluation pass.
+// The scalar part of Algorithm 1 after an evaluation pass, run by one thread
+// on the record in device memory, or (SETS = false: no compacted sets, no
+// trace) by every lane on a copy in registers.
+template <bool SETS = true>
 __device__ __forceinline__ void update_after_eval(GenState* st, const double* t, cqk_trace_rec* tr) {
   const double lam = st->lam;
   const int source = st->src;
   const double lo_in = st->lo, hi_in = st->hi;
   // the first pass wrote the sampled-bracket set in side 0's slot instead of
   // the two sides
-  const bool spec = st->spec != 0;
-  st->spec = 0;
+  const bool spec = SETS && st->spec != 0;
+  if constexpr (SETS) st->spec = 0;
   st->passes += 1;
   if (t[P_BAD] > 0.0) {
     st->status = CQK_INVALID_ARG;
@@ -288,35 +292,40 @@ __device__ __forceinline__ void update_after_eval(GenState* st, const double* t,
     st->sn = (int64_t)t[P_SIDE + D_NOUT];
     st->spend = 1;
   }
-  // algorithmic bytes: the set read (caller's arrays or the 32-byte form) and
-  // the survivors written for both sides
-  const double nout = t[P_SIDE + D_NOUT] + t[P_SIDE + D_N + D_NOUT];
-  st->bytes += ((source == 0) ? st->in_bytes : 32.0) * t[P_NIN] + 32.0 * nout;
-  const double phi = (st->F + st->C0) + (lam * st->C1 + t[P_P]);
-  const double A = (st->AF + st->A0) + (lam * st->A1 + t[P_A]);
-  const double Qp = st->C1 + t[P_QP];
-  const double Qm = st->C1 + t[P_QM];
-  const double r0 = st->r;
+  double phi = t[P_P], A = t[P_A], Qp = t[P_QP], Qm = t[P_QM];
+  double nout = 0.0;
+  bool compacted = false;
+  if constexpr (SETS) {
+    // algorithmic bytes: the set read (caller's arrays or the 32-byte form) and
+    // the survivors written for both sides
+    nout = t[P_SIDE + D_NOUT] + t[P_SIDE + D_N + D_NOUT];
+    st->bytes += ((source == 0) ? st->in_bytes : 32.0) * t[P_NIN] + 32.0 * nout;
+    phi = (st->F + st->C0) + (lam * st->C1 + t[P_P]);
+    A = (st->AF + st->A0) + (lam * st->A1 + t[P_A]);
+    Qp = st->C1 + t[P_QP];
+    Qm = st->C1 + t[P_QM];
+    const double r0 = st->r;
   // the side the evaluation chose; its compacted set (if every wave kept it)
-  // becomes the source of the next pass
-  const int side = (phi - r0 < 0.0) ? 0 : 1;
-  const int o = P_SIDE + side * D_N;
-  const bool compacted =
-      !spec && (st->compaction != CQK_COMPACT_OFF) && (phi != r0) && (t[o + D_DROP] == 0.0);
-  if (compacted) {
-    st->F += t[o + D_F];
-    st->AF += t[o + D_AF];
-    st->C0 += t[o + D_C0];
-    st->C1 += t[o + D_C1];
-    st->A0 += t[o + D_A0];
-    st->A1 += t[o + D_A1];
-    st->src = side_dst(source, side);
-    st->n_src = (int64_t)t[o + D_NOUT];
-    // the side's bracket, within the one the source's sums hold on
-    st->vlo = (side == 0) ? lam : fmax(lo_in, st->vlo);
-    st->vhi = (side == 0) ? fmin(hi_in, st->vhi) : lam;
-  } else {
-    st->n_src = (int64_t)t[P_NIN];
+    // becomes the source of the next pass
+    const int side = (phi - r0 < 0.0) ? 0 : 1;
+    const int o = P_SIDE + side * D_N;
+    compacted =
+        !spec && (st->compaction != CQK_COMPACT_OFF) && (phi != r0) && (t[o + D_DROP] == 0.0);
+    if (compacted) {
+      st->F += t[o + D_F];
+      st->AF += t[o + D_AF];
+      st->C0 += t[o + D_C0];
+      st->C1 += t[o + D_C1];
+      st->A0 += t[o + D_A0];
+      st->A1 += t[o + D_A1];
+      st->src = side_dst(source, side);
+      st->n_src = (int64_t)t[o + D_NOUT];
+      // the side's bracket, within the one the source's sums hold on
+      st->vlo = (side == 0) ? lam : fmax(lo_in, st->vlo);
+      st->vhi = (side == 0) ? fmin(hi_in, st->vhi) : lam;
+    } else {
+      st->n_src = (int64_t)t[P_NIN];
+    }
   }
   const double r = st->r, tol = st->tol;
   const double res = phi - r;
@@ -329,7 +338,9 @@ __device__ __forceinline__ void update_after_eval(GenState* st, const double* t,
   st->hi = hi;
   const double slope = (res < 0.0) ? Qp : Qm;
   const int ti = st->ntrace;
-  trace_push(st, tr, 1, compacted ? 1 : 0, source, lam, phi, slope, (int64_t)t[P_NIN],
+  if constexpr (!SETS) st->ntrace += 1;
+  else
+    trace_push(st, tr, 1, compacted ? 1 : 0, source, lam, phi, slope, (int64_t)t[P_NIN],
              (int64_t)nout);
   st->iter += 1;
   // Section 5 criterion 1 (and the exact stop of Algorithm 1)
@@ -348,8 +359,10 @@ __device__ __forceinline__ void update_after_eval(GenState* st, const double* t,
     // slope zero: the closest breakpoint in the needed direction (the
     // sampled-bracket set is not used for it)
     st->mode = (res < 0.0) ? kModeBreakRight : kModeBreakLeft;
-    if (st->src != 0) st->spend = 0;
-    check_source_bkpt(st);
+    if constexpr (SETS) {
+      if (st->src != 0) st->spend = 0;
+      check_source_bkpt(st);
+    }
     return;
   }
   int kind = 3;  // the Newton step
@@ -364,13 +377,17 @@ __device__ __forceinline__ void update_after_eval(GenState* st, const double* t,
     }
   }
   if (next == lam) return finish(st, lam, 2);  // criterion 2, lam_{k-1} = lam_k
-  if (take_spec_set(st, next)) {
-    if (tr != nullptr && ti < st->trace_cap) tr[ti].compacted = 1;
+  if constexpr (SETS) {
+    if (take_spec_set(st, next)) {
+      if (tr != nullptr && ti < st->trace_cap) tr[ti].compacted = 1;
+    } else {
+      check_source_eval(st, next);
+    }
+    trace_push(st, tr, kind, 0, source, next, phi, slope, 0, 0);
   } else {
-    check_source_eval(st, next);
+    st->ntrace += 1;
   }
-  trace_push(st, tr, kind, 0, source, next, phi, slope, 0, 0);
-  advance(st, next);
+  advance<SETS>(st, next);
 }
 
 // Breakpoint step of Algorithm 1.  phi is constant between lam_k and the
@@ -378,13 +395,16 @@ __device__ __forceinline__ void update_after_eval(GenState* st, const double* t,
 // iterate lam_{k+1} = bp is evaluated without another pass: phi(bp) =
 // phi(lam_k) and the one-sided slope at bp is the summed s of the indices
 // whose breakpoint is bp.  The Newton step from bp follows as in Algorithm 1.
+template <bool SETS = true>
 __device__ __forceinline__ void update_after_bkpt(GenState* st, const KeySum* ks, cqk_trace_rec* tr) {
   st->passes += 1;
-  st->bytes += ((st->src == 0) ? st->in_bytes : 32.0) * (double)st->n_src;
+  if constexpr (SETS) st->bytes += ((st->src == 0) ? st->in_bytes : 32.0) * (double)st->n_src;
   const bool right = st->mode == kModeBreakRight;
-  const double bp = right ? ks[0].k : -ks[1].k;
-  const double sw = right ? ks[0].w : ks[1].w;
-  trace_push(st, tr, 2, 0, st->src, st->lam, bp, sw, (int64_t)st->n_src, 0);
+  const KeySum k0 = ks[0], k1 = ks[1];  // read before the choice: both stay in registers
+  const double bp = right ? k0.k : -k1.k;
+  const double sw = right ? k0.w : k1.w;
+  if constexpr (!SETS) st->ntrace += 1;
+  else trace_push(st, tr, 2, 0, st->src, st->lam, bp, sw, (int64_t)st->n_src, 0);
   if (!(fabs(bp) < inf_d())) {
     st->status = CQK_INFEASIBLE;
     return;
@@ -395,7 +415,8 @@ __device__ __forceinline__ void update_after_bkpt(GenState* st, const KeySum* ks
   const double lo = right ? bp : st->lo, hi = right ? st->hi : bp;
   st->lo = lo;
   st->hi = hi;
-  trace_push(st, tr, 5, 0, st->src, bp, phi, sw, 0, 0);
+  if constexpr (!SETS) st->ntrace += 1;
+  else trace_push(st, tr, 5, 0, st->src, bp, phi, sw, 0, 0);
   st->iter += 1;
   st->lam_prev = st->lam;
   st->lam = bp;
@@ -406,8 +427,10 @@ __device__ __forceinline__ void update_after_bkpt(GenState* st, const KeySum* ks
   }
   if (hi - lo < tol * fmax(fabs(hi), fabs(lo))) return finish(st, bp, 3);
   if (!(sw > 0.0)) {  // still flat past bp: search again from bp
-    if (st->src != 0) st->spend = 0;
-    check_source_bkpt(st);
+    if constexpr (SETS) {
+      if (st->src != 0) st->spend = 0;
+      check_source_bkpt(st);
+    }
     return;
   }
   const double step = res / sw;
@@ -423,9 +446,30 @@ __device__ __forceinline__ void update_after_bkpt(GenState* st, const KeySum* ks
     }
   }
   if (next == bp) return finish(st, bp, 2);
-  trace_push(st, tr, kind, 0, st->src, next, phi, sw, 0, 0);
-  if (!take_spec_set(st, next)) check_source_eval(st, next);
-  advance(st, next);
+  if constexpr (SETS) {
+    trace_push(st, tr, kind, 0, st->src, next, phi, sw, 0, 0);
+    if (!take_spec_set(st, next)) check_source_eval(st, next);
+  } else {
+    st->ntrace += 1;
+  }
+  advance<SETS>(st, next);
+}
+
+// The state a register copy needs between updates, the same in every lane of
+// a wave, moved to scalar registers (SETS = false users).
+__device__ __forceinline__ void state_to_scalars(GenState& st) {
+  st.lam = scalar(st.lam);
+  st.lo = scalar(st.lo);
+  st.hi = scalar(st.hi);
+  st.phi_lo = scalar(st.phi_lo);
+  st.phi_hi = scalar(st.phi_hi);
+  st.lam_final = scalar(st.lam_final);
+  st.status = scalar(st.status);
+  st.iter = scalar(st.iter);
+  st.passes = scalar(st.passes);
+  st.mode = scalar(st.mode);
+  st.stop_reason = scalar(st.stop_reason);
+  st.ntrace = scalar(st.ntrace);
 }
 
 }  // namespace

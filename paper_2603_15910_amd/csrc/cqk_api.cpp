@@ -63,12 +63,12 @@ cqk_status ensure_buffer(cqk_ctx* ctx, DeviceBuf& b, size_t bytes) {
 bool team_ready(cqk_ctx* ctx, uint32_t need) {
   if (ctx->team_wait == 0) return false;
   const bool fresh = ctx->team.ptr == nullptr;
-  if (fresh && ensure_buffer(ctx, ctx->team, kTeamSlotBytes + kTeamCtlBytes) != CQK_OK)
+  if (fresh && ensure_buffer(ctx, ctx->team, kTeamBytes) != CQK_OK)
     return false;
   if (!fresh && ctx->team_tag < 0x80000000u - need) return true;
   if (stream_capturing(ctx->stream)) return true;  // its tags come from device memory
   // waited for: the next call may come on another stream
-  if (hipMemsetAsync(ctx->team.ptr, 0, kTeamSlotBytes + (fresh ? kTeamCtlBytes : 0),
+  if (hipMemsetAsync(ctx->team.ptr, 0, fresh ? kTeamBytes : kTeamSlotBytes,
                      ctx->stream) != hipSuccess ||
       hipStreamSynchronize(ctx->stream) != hipSuccess) {
     (void)hipGetLastError();

@@ -36,6 +36,7 @@
 #include "cqk_alg1.h"
 #include "cqk_device.h"
 #include "cqk_internal.h"
+#include "cqk_team.h"
 
 namespace cqk {
 namespace {
@@ -74,20 +75,24 @@ struct BatArgs {
 };
 
 // The call's counters, in lines of 32 ints (128 bytes): line 0 holds the rows
-// of each class and the work items, the next kQueues lines one work queue
-// each, the next kQueues the queues of a second kernel (the general form's
-// wave rows), the last kQueues lines the call's outcome as summed by the
-// blocks of one queue (flags, survivors, rows whose lists overflowed).  Atomics on one
+// of each class, the work items, whether a team gave up and where each length
+// bucket of the workgroup rows starts in the list; then kQueues lines with
+// the call's outcome, each as summed by the blocks of one queue (flags,
+// survivors, rows whose lists overflowed), kQueues more for the rows solved
+// by teams (they count only when no team gave up), and two sets of work
+// queues, one line each (the second for the rows of teams of one).  Atomics on one
 // address take turns at about 13 ns each on this part, so one shared queue
 // and one shared survivor total, updated per row, bounded every call of many
 // rows (65 536 rows of 64-512 values: 1.70 ms for 147 456 atomics): blocks
 // now share a queue in groups of grid / kQueues and add their outcome once.
-constexpr int CTR_NLONG = 0, CTR_NSHORT = 1, CTR_NITEMS = 2;
+constexpr int CTR_NLONG = 0, CTR_NSHORT = 1, CTR_NITEMS = 2, CTR_GAVE_UP = 3, CTR_LBASE = 4;
 constexpr int CTR_FLAGS = 0, CTR_SURV = 1, CTR_OVER = 2;
 constexpr int kQueues = 32, kCtrLine = 32;
-constexpr int CTR_QUEUE0 = kCtrLine, CTR_QUEUE1 = (1 + kQueues) * kCtrLine,
-              CTR_STAT0 = (1 + 2 * kQueues) * kCtrLine,
-              CTR_TOTAL = (1 + 3 * kQueues) * kCtrLine;
+constexpr int CTR_STAT0 = kCtrLine, CTR_STAT1 = (1 + kQueues) * kCtrLine,
+              CTR_OUTCOME = (1 + 2 * kQueues) * kCtrLine,  // what the host reads
+              CTR_QUEUE0 = CTR_OUTCOME, CTR_QUEUE1 = CTR_QUEUE0 + kQueues * kCtrLine,
+              CTR_TOTAL = CTR_QUEUE1 + kQueues * kCtrLine;
+static_assert(CTR_LBASE + kNBW <= kCtrLine, "the bucket starts fit line 0");
 
 // A block's outcome, in LDS until the block ends.
 struct BatStat {
@@ -101,9 +106,9 @@ __device__ __forceinline__ void stat_init(BatStat& t) {
 // Adds the block's outcome to its group's line.  MAXOVER: `over` is a maximum
 // (the general form's iteration count), not a sum.
 template <bool MAXOVER>
-__device__ __forceinline__ void stat_flush(const BatStat& t, int32_t* counters) {
+__device__ __forceinline__ void stat_flush(const BatStat& t, int32_t* lines) {
   if (threadIdx.x == 0) {
-    int32_t* line = counters + CTR_STAT0 + (blockIdx.x % kQueues) * kCtrLine;
+    int32_t* line = lines + (blockIdx.x % kQueues) * kCtrLine;
     if (t.flags) atomicOr(&line[CTR_FLAGS], t.flags);
     if (t.surv) atomicAdd(&line[CTR_SURV], t.surv);
     if (t.over) {
@@ -153,6 +158,18 @@ __device__ __forceinline__ int bucket_of(int64_t L, int wave_max) {
   return (L <= wave_max) ? b : kNBW + b;
 }
 
+// Tags of the teams' exchanges, in device memory (replays must not repeat
+// them): every launch starts above the largest tag of the one before; near
+// the end of the range the slots are cleared and it starts over.
+struct BatTeamCtl {
+  uint32_t base, last;
+};
+constexpr uint32_t kTagRestart = 0xc0000000u, kTagEnd = 0xfffffff0u;
+
+// The planning's part in it, by one block.
+template <typename Args>
+__device__ __forceinline__ void start_teams(const Args&) {}
+
 // Planning: the rows are listed by length bucket (workgroup rows longest
 // bucket first, then the wave rows longest bucket first, so the four wave
 // rows of one work item have about the same length), in row order inside a
@@ -183,6 +200,12 @@ __device__ __forceinline__ int plan_bucket(const Args& A, int s) {
 }
 
 template <typename Args>
+__device__ __forceinline__ void clear_counters(const Args& A) {
+  for (int i = CTR_STAT0 + (int)threadIdx.x; i < CTR_TOTAL; i += kPBlock) A.counters[i] = 0;
+  start_teams(A);
+}
+
+template <typename Args>
 __global__ __launch_bounds__(kPBlock) void bat_count_kernel(Args A) {
   __shared__ int wh[kPW][kNB];
   const int s = blockIdx.x * kPBlock + (int)threadIdx.x;
@@ -198,8 +221,7 @@ __global__ __launch_bounds__(kPBlock) void bat_count_kernel(Args A) {
     for (int q = 0; q < kPW; ++q) c += wh[q][threadIdx.x];
     A.bhist[(size_t)blockIdx.x * kNB + threadIdx.x] = c;
   }
-  if (blockIdx.x == 0)
-    for (int i = CTR_QUEUE0 + (int)threadIdx.x; i < CTR_TOTAL; i += kPBlock) A.counters[i] = 0;
+  if (blockIdx.x == 0) clear_counters(A);
 }
 
 template <typename Args>
@@ -208,12 +230,16 @@ __global__ __launch_bounds__(kPBlock) void bat_place_kernel(Args A) {
   __shared__ int base[kNB], pre[kNB];
   __shared__ int wh[kPW][kNB];
   const int nblk = gridDim.x;
+  // one block (up to kPBlock rows) needs no counts of the others and no
+  // launch before it
+  const bool alone = nblk == 1;
+  if (alone) clear_counters(A);
   // bucket totals over all blocks and over the blocks before this one,
   // 32 threads per bucket
   for (int idx = threadIdx.x; idx < kNB * 32; idx += kPBlock) {
     const int k = idx / 32, sub = idx % 32;
     int t = 0, p = 0;
-    for (int q = sub; q < nblk; q += 32) {
+    for (int q = sub; q < nblk && !alone; q += 32) {
       const int v = A.bhist[(size_t)q * kNB + k];
       t += v;
       p += (q < (int)blockIdx.x) ? v : 0;
@@ -238,7 +264,6 @@ __global__ __launch_bounds__(kPBlock) void bat_place_kernel(Args A) {
       t += part[0][k][q];
       p += part[1][k][q];
     }
-    base[k] = t;  // totals for now
     pre[k] = p;
     // exclusive scan of the per-wave counts of this block
     int c = 0;
@@ -247,6 +272,7 @@ __global__ __launch_bounds__(kPBlock) void bat_place_kernel(Args A) {
       wh[q][k] = c;
       c += v;
     }
+    base[k] = alone ? c : t;  // totals for now
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -268,6 +294,8 @@ __global__ __launch_bounds__(kPBlock) void bat_place_kernel(Args A) {
       A.counters[CTR_NLONG] = nlong;
       A.counters[CTR_NSHORT] = nshort;
       A.counters[CTR_NITEMS] = nlong + (nshort + kWaves - 1) / kWaves;
+      A.counters[CTR_GAVE_UP] = 0;
+      for (int k = 0; k < kNBW; ++k) A.counters[CTR_LBASE + k] = base[kNBW + k];
     }
   }
   __syncthreads();
@@ -1034,7 +1062,7 @@ __global__ __launch_bounds__(kBlock, 3) void bat_solve_kernel(BatArgs A) {
     }
     __syncthreads();
   }
-  stat_flush<false>(L.stat, A.counters);
+  stat_flush<false>(L.stat, A.counters + CTR_STAT0);
 }
 
 // ---------------------------------------------------------------------------
@@ -1263,7 +1291,21 @@ struct BatCqkArgs {
   int64_t* lrow;
   int32_t* counters;
   int32_t* bhist;
+  uint64_t* tslots;     // teams: record slots, control words (BatTeamCtl), wait
+  BatTeamCtl* tctl;     // limit; tslots null: no teams
+  uint64_t tlimit;
 };
+
+template <>
+__device__ __forceinline__ void start_teams<BatCqkArgs>(const BatCqkArgs& A) {
+  if (A.tslots == nullptr) return;
+  const uint32_t last = A.tctl->last;
+  __syncthreads();
+  if (last >= kTagRestart)
+    for (size_t i = threadIdx.x; i < kBatTeamBytes / sizeof(uint64_t); i += kPBlock)
+      A.tslots[i] = 0;
+  if (threadIdx.x == 0) A.tctl->base = A.tctl->last = (last >= kTagRestart) ? 0u : last;
+}
 
 __device__ __forceinline__ GenState cqk_row_state(const BatCqkArgs& A, double r) {
   GenState st{};
@@ -1381,7 +1423,7 @@ __device__ void cqk_short_row(const BatCqkArgs& A, int s, int64_t base, int64_t 
       static_assert(P_P == 0 && P_A == 1 && P_QP == 2 && P_QM == 3, "the four sums");
       wave_sum4(acc.s, t);
       t[P_NIN] = (double)L;
-      update_after_eval(&st, t, nullptr);
+      update_after_eval<false>(&st, t, nullptr);
     } else {
       KeySum ks[2] = {KeySum{inf_d(), 0.0}, KeySum{inf_d(), 0.0}};
 #pragma unroll
@@ -1389,8 +1431,9 @@ __device__ void cqk_short_row(const BatCqkArgs& A, int s, int64_t base, int64_t 
         if (k < nk) bkpt_index(ks, c[k], sv[k], bl[k], bu[k], st.lam);
       ks[0] = wave_ks_min(ks[0]);
       ks[1] = wave_ks_min(ks[1]);
-      update_after_bkpt(&st, ks, nullptr);
+      update_after_bkpt<false>(&st, ks, nullptr);
     }
+    state_to_scalars(st);
   }
   const bool ok = cqk_has_lambda(st);
   const double lam = ok ? st.lam_final : __builtin_nan("");
@@ -1433,12 +1476,12 @@ struct CqkLds {
   double red[8 * kWaves];
   double tot[8];
   KeySum ks[2];
-  BatStat stat;
   int item;
 };
 
 template <typename TIn>
-__device__ void cqk_long_row(const BatCqkArgs& A, int s, int64_t base, int64_t L, CqkLds& S) {
+__device__ void cqk_long_row(const BatCqkArgs& A, int s, int64_t base, int64_t L, CqkLds& S,
+                             BatStat& stat) {
   const CqkArrays<TIn> V(A);
   const double r = A.r[s];
   GenState st = cqk_row_state(A, r);
@@ -1539,7 +1582,361 @@ __device__ void cqk_long_row(const BatCqkArgs& A, int s, int64_t base, int64_t L
     const double t = fma(vb, lam, va) / vd;
     x[i] = (TIn)(ok ? fmin(fmax(t, vl), vu) : __builtin_nan(""));
   });
-  if (threadIdx.x == 0) cqk_row_report(A, s, st, lam, S.stat);
+  if (threadIdx.x == 0) cqk_row_report(A, s, st, lam, stat);
+}
+
+// ---------------------------------------------------------------------------
+// Workgroup rows held on chip by teams of blocks.  A block of kRowBlock
+// threads holds E values per thread of the five arrays in registers (FP64: 8,
+// FP32: 16, 80 registers either way); a row of bit length b is shared evenly
+// by 2^(b - log2(kRowBlock E)) blocks, so it is read from memory once for all its
+// evaluations, the blocks exchanging their sums as the single solve's do
+// (cqk_team.h).  Four blocks per compute unit: some load while others wait
+// for their sums.  Bound by latency (a row's load 10 us, 2 us per evaluation,
+// 4-5 us with an exchange) against four rows in flight per compute unit.
+// 4e7 values from lambda_0 = 0, streamed / held, FP64: rows of 600 1557 /
+// 978 us, 2000 1022 / 541, 8000 1176 / 712, 60 000 1914 / 839, 500 000 4750 /
+// 1210; FP32: 1244 / 936, 716 / 480, 697 / 503, 1052 / 570, 4230 / 657.  VJP,
+// FP64: 757 / 497, 590 / 493, 775 / 459, 854 / 455, 2330 / 530 (4.9 TB/s).
+// ---------------------------------------------------------------------------
+constexpr int kRowBlock = 256;
+constexpr int kRowBlocksPerCu = 4;
+template <typename TIn>
+struct RowShape {
+  static constexpr int E = 64 / (int)sizeof(TIn);
+  static constexpr int kLog = sizeof(TIn) == 8 ? 11 : 12;  // bit length of one block's rows
+  static constexpr int kMaxLog = kLog + kBatTeamLogs - 1;  // longest team rows
+  static_assert(kRowBlock * E == 1 << kLog, "a row of bit length kLog fits one block");
+  static_assert(kMaxLog < kNBW - 1, "and every team row has a bucket of its own length");
+};
+static_assert((1 << (kBatTeamLogs - 1)) <= kTeamMax, "the largest team");
+
+// The rows of this block one after the other, each with its team.  Longest
+// classes first; a class with fewer rows than teams takes larger teams (never
+// larger than those of the class before: teams only split).  Rows of a class
+// go to its teams in turn, starting where the class before left off; the
+// rows of one block each come last, from the work queue.  Ids, extents and
+// right-hand sides are fetched for kWin rows at a time, one lane each.
+template <typename TIn>
+struct TeamRows {
+  static constexpr int kTeamLog = RowShape<TIn>::kLog, kTeamMaxLog = RowShape<TIn>::kMaxLog;
+  static constexpr int kWin = 4;
+  Team team;            // of the current row
+  int id;               // the row, its first element and length, its r
+  int64_t first, len;
+  double rhs;
+  int b, from, cnt, j, NT, off, cap, per, wi, wn;
+  int w_id;             // the window, a row per lane
+  int64_t w_first, w_len;
+  double w_rhs;
+  int bases;            // bucket starts, one per lane
+  int nlong;
+  ItemSource src;
+
+  __device__ __forceinline__ explicit TeamRows(const BatCqkArgs& A) {
+    const int lane = threadIdx.x & (kWave - 1);
+    bases = (lane < kNBW) ? A.counters[CTR_LBASE + lane] : 0;
+    nlong = scalar(A.counters[CTR_NLONG]);
+    team = Team{nullptr, A.tlimit, scalar(A.tctl->base), 1, 0, kBatTeamBlocks * kSlotWords};
+    b = kTeamMaxLog + 1;
+    from = cnt = j = off = wi = wn = 0;
+    NT = per = 1;
+    cap = kTeamMax;
+    while (cap > (int)gridDim.x) cap >>= 1;
+  }
+
+  __device__ __forceinline__ bool none() const { return nlong <= base_of(kTeamMaxLog); }
+
+  __device__ __forceinline__ int base_of(int k) const {
+    return __builtin_amdgcn_readlane(bases, k);
+  }
+
+  // rows at + k * step of the list, k < n, into the window
+  __device__ __forceinline__ void fetch(const BatCqkArgs& A, int at, int step, int n) {
+    const int lane = threadIdx.x & (kWave - 1);
+    w_id = 0;
+    w_first = w_len = 0;
+    w_rhs = 0.0;
+    if (lane < n) {
+      const size_t e = (size_t)at + (size_t)lane * step;
+      w_id = A.list[e];
+      w_first = A.lrow[2 * e];
+      w_len = A.lrow[2 * e + 1];
+      w_rhs = (A.r != nullptr) ? A.r[w_id] : 0.0;
+    }
+    wi = 0;
+    wn = n;
+  }
+
+  // The next row (called by the whole block; item: a word of LDS); false at
+  // the end.
+  __device__ __forceinline__ bool next(const BatCqkArgs& A, int* item) {
+    const int G = gridDim.x;
+    if (wi == wn && b > kTeamLog) {
+      while (j >= cnt) {
+        if (b <= kTeamMaxLog) off = (off + cnt % NT * team.T) % (NT * team.T);
+        if (--b == kTeamLog) break;
+        from = base_of(b);
+        cnt = base_of(b - 1) - from;
+        int lg = b - kTeamLog;
+        while (cnt > 0 && (2 << lg) <= cap && ((int64_t)cnt << (lg + 1)) <= G) ++lg;
+        const int T = 1 << lg, mine = (int)blockIdx.x / T;
+        if (cnt > 0) cap = T;
+        NT = G / T;
+        off -= off % T;
+        team.T = T;
+        team.me = (int)blockIdx.x % T;
+        team.slots = A.tslots +
+                     ((size_t)lg * 2 * kBatTeamBlocks + (size_t)mine * T) * kSlotWords;
+        // a block past the last whole team has no rows of this class
+        j = (mine < NT) ? (mine - off / T % NT + NT) % NT : cnt;
+      }
+      if (b > kTeamLog) {
+        const int n = min(kWin, (cnt - j + NT - 1) / NT);
+        fetch(A, from + j, NT, n);
+        j += n * NT;
+      } else {
+        from = base_of(kTeamLog);
+        cnt = nlong - from;
+        per = min(kWin, max(1, cnt / (G * 4)));
+        team.T = 1;
+        team.me = 0;
+      }
+    }
+    if (wi == wn) {
+      if (cnt <= 0) return false;
+      const int nitems = (cnt + per - 1) / per;
+      if (threadIdx.x < kWave) {
+        const int k = src.next(A.counters + CTR_QUEUE1, nitems);
+        if (threadIdx.x == 0) *item = k;
+      }
+      __syncthreads();
+      const int k = scalar(*item);
+      __syncthreads();
+      if (k >= nitems) return false;
+      fetch(A, from + k * per, 1, min(per, cnt - k * per));
+    }
+    id = __builtin_amdgcn_readlane(w_id, wi);
+    first = lane_value(w_first, wi);
+    len = lane_value(w_len, wi);
+    rhs = lane_value(w_rhs, wi);
+    ++wi;
+    return true;
+  }
+};
+
+// This block's share of a row of L values: [lo, hi), whole cache lines of
+// FP32 apart.
+__device__ __forceinline__ void team_share(const Team& team, int L, int& lo, int& hi) {
+  const int per = ((L + team.T - 1) / team.T + 31) / 32 * 32;
+  lo = min(L, per * team.me);
+  hi = min(L, lo + per);
+}
+
+// Vectors q = 0, 1, ... of an array for one thread: values lo + (q kRowBlock +
+// tid) V ... of a share [lo, hi) of a row of at least V values.  A vector that
+// would pass hi is moved back to end there, and the thread then owns only the
+// values no other thread holds; so every load is a whole vector with no test
+// before it, and all of a share's loads are in flight together.
+template <typename TIn>
+struct ShareVec {
+  static constexpr int V = VecWidth<TIn>::value;
+  typedef typename Raw16<TIn>::type Raw;
+  int lo, hi;   // a team row has fewer than 2^31 values
+  int tid;
+  __device__ __forceinline__ int want(int q) const { return lo + (q * kRowBlock + tid) * V; }
+  __device__ __forceinline__ int at(int q) const { return min(want(q), hi - V); }
+  __device__ __forceinline__ bool owns(int q, int k) const { return at(q) + k >= want(q); }
+  __device__ __forceinline__ int groups() const {
+    return (hi - lo + kRowBlock * V - 1) / (kRowBlock * V);
+  }
+  __device__ __forceinline__ Raw load(const TIn* p, int q) const {
+    return *reinterpret_cast<const Raw*>(p + (unsigned)at(q));
+  }
+  __device__ __forceinline__ void store(TIn* p, int q, Raw o) const {
+    const unsigned i = (unsigned)at(q);
+    if ((int)i == want(q)) {
+      st16(p + i, o);
+    } else {
+#pragma unroll
+      for (int k = 1; k < V; ++k)
+        if (owns(q, k)) p[i + k] = o[k];
+    }
+  }
+};
+
+// One row of a team.  The block keeps its share of the five arrays as loaded
+// and makes the per-index form again at every evaluation: holding the form
+// instead would mean reading the arrays a second time for x (eq. (xopt) from
+// the arrays' own values), which took twice as long as the load itself.
+template <typename TIn, int E>
+__device__ __forceinline__ bool cqk_team_row(const BatCqkArgs& A, TeamLds<kRowBlock>& S,
+                                             BatStat& stat, int& par, Team& team, int s,
+                                             int64_t base, int64_t L, double r) {
+  constexpr int V = VecWidth<TIn>::value;
+  constexpr int Q = E / V;
+  typedef typename Raw16<TIn>::type Raw;
+  const CqkArrays<TIn> P(A);
+  ShareVec<TIn> B;
+  B.tid = threadIdx.x;
+  asm volatile("" : "+v"(B.tid));  // nothing made from it is hoisted out of the loop over rows
+  team_share(team, (int)L, B.lo, B.hi);
+  const int nq = B.groups();
+  Raw rd[Q], ra[Q], rb[Q], rl[Q], ru[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    if (q < nq) {
+      rd[q] = B.load(P.d + base, q);
+      ra[q] = B.load(P.a + base, q);
+      rb[q] = B.load(P.b + base, q);
+      rl[q] = B.load(P.l + base, q);
+      ru[q] = B.load(P.u + base, q);
+    }
+  }
+  // The form is made anew for each use, one vector after the other: kept
+  // across the evaluations by the compiler, or made for all values at once,
+  // it would be spilled.
+  auto hold = [&]() {
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      asm volatile("" : "+v"(rd[q]), "+v"(ra[q]), "+v"(rb[q]), "+v"(rl[q]), "+v"(ru[q]));
+  };
+  auto each = [&](auto&& fn) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      if (q < nq) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+          double c, sv, bl, bu, b1 = 0.0;
+          to_form((double)rd[q][k], (double)ra[q][k], (double)rb[q][k], (double)rl[q][k],
+                  (double)ru[q][k], c, sv, bl, bu, b1);
+          fn(c, sv, bl, bu);
+        }
+      }
+    }
+  };
+  double bad = 0.0;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    if (q >= nq) break;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+      double c, sv, bl, bu, b1 = 0.0;
+      to_form((double)rd[q][k], (double)ra[q][k], (double)rb[q][k], (double)rl[q][k],
+              (double)ru[q][k], c, sv, bl, bu, b1);
+      const bool in = B.owns(q, k);
+      bad += in ? b1 : 0.0;
+      // a value another thread owns: b = 0, so it adds nothing to any sum
+      rd[q][k] = in ? rd[q][k] : (TIn)1;
+      ra[q][k] = in ? ra[q][k] : (TIn)0;
+      rb[q][k] = in ? rb[q][k] : (TIn)0;
+      rl[q][k] = in ? rl[q][k] : (TIn)0;
+      ru[q][k] = in ? ru[q][k] : (TIn)0;
+    }
+  }
+  hold();
+  GenState st = cqk_row_state(A, r);
+  if (!(fabs(r) < inf_d())) st.status = CQK_INVALID_ARG;
+  bool ok = true;
+  if (A.lambda0_mode == CQK_LAMBDA0_FORMULA && st.status == kRunning) {
+    double v[3] = {0.0, 0.0, bad}, tot[3];
+    each([&](double c, double sv, double, double) {
+      v[0] += c;
+      v[1] += sv;
+    });
+    ok = team_reduce<3, kRowBlock>(team, S, par, v, tot);
+    if (tot[2] > 0.0) st.status = CQK_INVALID_ARG;
+    else st.lam = st.lam0 = scalar((tot[1] > 0.0) ? (r - tot[0]) / tot[1] : 0.0);
+  }
+  while (ok && st.status == kRunning) {
+    hold();
+    const double lam = st.lam;
+    if (st.mode == kModeEval) {
+      Acc acc;
+      acc_init(acc);
+      each([&](double c, double sv, double bl, double bu) {
+        eval_index<false>(acc, c, sv, bl, bu, lam, 0.0, 0.0);
+      });
+      const double v[5] = {acc.s[P_P], acc.s[P_A], acc.s[P_QP], acc.s[P_QM], bad};
+      double tot[5], t[NSUM];
+      ok = team_reduce<5, kRowBlock>(team, S, par, v, tot);
+      t[P_P] = tot[0];
+      t[P_A] = tot[1];
+      t[P_QP] = tot[2];
+      t[P_QM] = tot[3];
+      t[P_BAD] = tot[4];
+      update_after_eval<false>(&st, t, nullptr);
+    } else {
+      KeySum ks[2] = {KeySum{inf_d(), 0.0}, KeySum{inf_d(), 0.0}};
+      each([&](double c, double sv, double bl, double bu) {
+        bkpt_index(ks, c, sv, bl, bu, lam);
+      });
+      ok = team_reduce_ks<kRowBlock>(team, S, par, ks);
+      update_after_bkpt<false>(&st, ks, nullptr);
+    }
+    state_to_scalars(st);
+  }
+  if (!ok) return false;
+  const bool has = cqk_has_lambda(st);
+  const double lam = has ? st.lam_final : __builtin_nan("");
+  hold();
+  asm volatile("" : "+v"(B.tid));  // the addresses again
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    if (q < nq) {
+      __builtin_amdgcn_sched_barrier(0);
+      Raw o;
+#pragma unroll
+      for (int k = 0; k < V; ++k) {
+        const double t = fma((double)rb[q][k], lam, (double)ra[q][k]) / (double)rd[q][k];
+        o[k] = (TIn)(has ? fmin(fmax(t, (double)rl[q][k]), (double)ru[q][k])
+                         : __builtin_nan(""));
+      }
+      B.store(P.x + base, q, o);
+    }
+  }
+  if (threadIdx.x == 0 && team.me == 0) cqk_row_report(A, s, st, lam, stat);
+  return true;
+}
+
+// What a team kernel does after its last row.
+__device__ __forceinline__ void team_end(const BatCqkArgs& A, const Team& team, uint32_t base_tag,
+                                         bool ok) {
+  if (threadIdx.x == 0) {
+    if (!ok) atomicOr(&A.counters[CTR_GAVE_UP], 1);
+    if (team.tag != base_tag) atomicMax(&A.tctl->last, team.tag);
+  }
+}
+
+template <typename TIn>
+__global__ __launch_bounds__(kRowBlock, kRowBlocksPerCu) void bat_cqk_team_kernel(BatCqkArgs A) {
+  __shared__ TeamLds<kRowBlock> S;
+  __shared__ BatStat stat;
+  __shared__ int item;
+  stat_init(stat);
+  if (threadIdx.x == 0) S.gave_up = 0;
+  __syncthreads();
+  TeamRows<TIn> rows(A);
+  if (rows.none()) return;
+  const uint32_t base_tag = rows.team.tag;
+  int par = 0;
+  bool ok = true;
+  while (ok && rows.next(A, &item))
+    ok = rows.team.tag < kTagEnd - 4096u &&
+         cqk_team_row<TIn, RowShape<TIn>::E>(A, S, stat, par, rows.team, rows.id, rows.first, rows.len, rows.rhs);
+  team_end(A, rows.team, base_tag, ok);
+  __syncthreads();
+  stat_flush<true>(stat, A.counters + CTR_STAT1);
+}
+
+// Workgroup rows that no team holds: those past the longest team rows, or all
+// of them when a team gave up or there are none.
+template <typename TIn>
+__device__ __forceinline__ int streamed_rows(const BatCqkArgs& A) {
+  if (A.tslots == nullptr || A.counters[CTR_GAVE_UP]) return A.counters[CTR_NLONG];
+  return A.counters[CTR_LBASE + RowShape<TIn>::kMaxLog];
 }
 
 // The wave rows, four to a block at a time; each wave takes kRowsPerWave rows
@@ -1548,36 +1945,37 @@ __device__ void cqk_long_row(const BatCqkArgs& A, int s, int64_t base, int64_t L
 // workgroup row's loads would cost its waves' occupancy.
 constexpr int kRowsPerWave = 4;
 
-// Lane j's value in every lane, as a scalar.
-template <typename T>
-__device__ __forceinline__ T lane_value(T v, int j) {
-  static_assert(sizeof(T) == 8, "two 32-bit halves");
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, j);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), j);
-  return __builtin_bit_cast(T, ((uint64_t)hi << 32) | lo);
-}
-
 template <int SP, typename TIn>
-__global__ __launch_bounds__(kBlock, 3) void bat_cqk_wave_kernel(BatCqkArgs A) {
+__global__ __launch_bounds__(kBlock, 3) void bat_cqk_solve_kernel(BatCqkArgs A) {
   __shared__ BatStat stat;
-  __shared__ int item_s;
+  __shared__ CqkLds S;
   const int nlong = A.counters[CTR_NLONG];
+  const int nstream = streamed_rows<TIn>(A);
   const int nshort = A.counters[CTR_NSHORT];
   const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int per = min(kRowsPerWave, max(1, nshort / ((int)gridDim.x * kWaves * kRowsPerWave)));
-  const int nitems = (nshort + kWaves * per - 1) / (kWaves * per);
+  const int ngroups = (nshort + kWaves * per - 1) / (kWaves * per);
+  const int nitems = nstream + ngroups;
   ItemSource src;
   stat_init(stat);
   for (;;) {
     if (threadIdx.x < kWave) {
-      const int next = src.next(A.counters + CTR_QUEUE1, nitems);
-      if (threadIdx.x == 0) item_s = next;
+      const int next = src.next(A.counters + CTR_QUEUE0, nitems);
+      if (threadIdx.x == 0) S.item = next;
     }
     __syncthreads();
-    const int item = item_s;
+    int item = scalar(S.item);
     __syncthreads();
     if (item >= nitems) break;
+    // workgroup rows that no team holds stream from memory at every evaluation
+    const int row = A.short_first ? item - ngroups : item;
+    if (row >= 0 && row < nstream) {
+      cqk_long_row<TIn>(A, A.list[row], A.lrow[2 * (size_t)row], A.lrow[2 * (size_t)row + 1], S,
+                        stat);
+      __syncthreads();
+      continue;
+    }
+    if (!A.short_first) item -= nstream;
     // the wave's rows of this item: ids, extents and right-hand sides in two
     // round trips for all of them, one lane each
     const int lane = threadIdx.x & (kWave - 1);
@@ -1597,29 +1995,7 @@ __global__ __launch_bounds__(kBlock, 3) void bat_cqk_wave_kernel(BatCqkArgs A) {
                              lane_value(len, j), lane_value(rhs, j), stat);
   }
   __syncthreads();
-  stat_flush<true>(stat, A.counters);
-}
-
-// The workgroup rows.
-template <typename TIn>
-__global__ __launch_bounds__(kBlock) void bat_cqk_solve_kernel(BatCqkArgs A) {
-  __shared__ CqkLds S;
-  const int nlong = A.counters[CTR_NLONG];
-  ItemSource src;
-  stat_init(S.stat);
-  for (;;) {
-    if (threadIdx.x < kWave) {
-      const int next = src.next(A.counters + CTR_QUEUE0, nlong);
-      if (threadIdx.x == 0) S.item = next;
-    }
-    __syncthreads();
-    const int idx = S.item;
-    __syncthreads();
-    if (idx >= nlong) break;
-    cqk_long_row<TIn>(A, A.list[idx], A.lrow[2 * (size_t)idx], A.lrow[2 * (size_t)idx + 1], S);
-    __syncthreads();
-  }
-  stat_flush<true>(S.stat, A.counters);
+  stat_flush<true>(stat, A.counters + CTR_STAT0);
 }
 
 // Backward of one wave row.
@@ -1737,13 +2113,106 @@ __device__ void cqk_vjp_long_row(const BatCqkArgs& A, int s, int64_t base, int64
   if (threadIdx.x == 0 && A.gr) A.gr[s] = mu;
 }
 
+// Backward of one team row: the share's g, d and b stay in registers from the
+// sums to the map, so the row is read once.
+template <typename TIn, int E>
+__device__ __forceinline__ bool cqk_team_vjp_row(const BatCqkArgs& A, TeamLds<kRowBlock>& S,
+                                                 int& par, Team& team, int s, int64_t base,
+                                                 int64_t L) {
+  constexpr int V = VecWidth<TIn>::value;
+  constexpr int Q = E / V;
+  typedef typename Raw16<TIn>::type Raw;
+  const CqkArrays<TIn> P(A);
+  ShareVec<TIn> B;
+  B.tid = threadIdx.x;
+  asm volatile("" : "+v"(B.tid));  // nothing made from it is hoisted out of the loop over rows
+  team_share(team, (int)L, B.lo, B.hi);
+  const int nq = B.groups();
+  Raw rg[Q], rd[Q], rb[Q];
+  uint32_t fr = 0;  // free and owned by this thread
+  {
+    Raw rx[Q], rl[Q], ru[Q];
+    // FP32: a vector past the share is not loaded (rows of 600 values 391 ->
+    // 344 us for 40e6); FP64 has half as many to save, and the branches cost
+    // it more registers than they save loads (rows of 60000 455 -> 480 us)
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      if (sizeof(TIn) == 8 || q < nq) {
+        rx[q] = B.load(P.x + base, q);
+        rl[q] = B.load(P.l + base, q);
+        ru[q] = B.load(P.u + base, q);
+        rg[q] = B.load(P.g + base, q);
+        rd[q] = B.load(P.d + base, q);
+        rb[q] = B.load(P.b + base, q);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+      for (int k = 0; k < V; ++k)
+        if ((sizeof(TIn) == 8 || q < nq) && B.owns(q, k) && rx[q][k] > rl[q][k] && rx[q][k] < ru[q][k]) fr |= 1u << (q * V + k);
+  }
+  double v[2] = {0.0, 0.0}, tot[2];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+      if ((fr >> (q * V + k)) & 1u) {
+        const double xb = (double)rb[q][k], xd = (double)rd[q][k];
+        v[0] += xb * xb / xd;
+        v[1] += (double)rg[q][k] * xb / xd;
+      }
+    }
+  }
+  if (!team_reduce<2, kRowBlock>(team, S, par, v, tot)) return false;
+  const double mu = (tot[0] > 0.0) ? tot[1] / tot[0] : 0.0;
+  asm volatile("" : "+v"(B.tid));  // the addresses again
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    if (q < nq) {
+      __builtin_amdgcn_sched_barrier(0);
+      Raw o;
+#pragma unroll
+      for (int k = 0; k < V; ++k)
+        o[k] = (TIn)(((fr >> (q * V + k)) & 1u)
+                         ? ((double)rg[q][k] - (double)rb[q][k] * mu) / (double)rd[q][k]
+                         : 0.0);
+      B.store(P.ga + base, q, o);
+    }
+  }
+  if (threadIdx.x == 0 && team.me == 0 && A.gr) A.gr[s] = mu;
+  return true;
+}
+
+template <typename TIn>
+__global__ __launch_bounds__(kRowBlock, kRowBlocksPerCu) void bat_cqk_team_vjp_kernel(
+    BatCqkArgs A) {
+  __shared__ TeamLds<kRowBlock> S;
+  __shared__ int item;
+  if (threadIdx.x == 0) S.gave_up = 0;
+  __syncthreads();
+  TeamRows<TIn> rows(A);
+  if (rows.none()) return;
+  const uint32_t base_tag = rows.team.tag;
+  int par = 0;
+  bool ok = true;
+  while (ok && rows.next(A, &item))
+    ok = rows.team.tag < kTagEnd - 4096u &&
+         cqk_team_vjp_row<TIn, RowShape<TIn>::E>(A, S, par, rows.team, rows.id, rows.first,
+                                                 rows.len);
+  team_end(A, rows.team, base_tag, ok);
+}
+
+// The wave rows and the workgroup rows that no team holds.
 template <int SP, typename TIn>
 __global__ __launch_bounds__(kBlock) void bat_cqk_vjp_kernel(BatCqkArgs A) {
   __shared__ CqkLds S;
   const int nlong = A.counters[CTR_NLONG];
   const int nshort = A.counters[CTR_NSHORT];
-  const int nitems = A.counters[CTR_NITEMS];
-  const int nsg = nitems - nlong;
+  const int nstream = streamed_rows<TIn>(A);
+  const int nsg = (nshort + kWaves - 1) / kWaves;
+  const int nitems = nstream + nsg;
   ItemSource src;
   for (;;) {
     if (threadIdx.x < kWave) {
@@ -1760,8 +2229,8 @@ __global__ __launch_bounds__(kBlock) void bat_cqk_vjp_kernel(BatCqkArgs A) {
       is_long = item >= nsg;
       idx = is_long ? item - nsg : item;
     } else {
-      is_long = item < nlong;
-      idx = is_long ? item : item - nlong;
+      is_long = item < nstream;
+      idx = is_long ? item : item - nstream;
     }
     if (is_long) {
       cqk_vjp_long_row<TIn>(A, A.list[idx], A.lrow[2 * (size_t)idx], A.lrow[2 * (size_t)idx + 1],
@@ -1781,7 +2250,8 @@ __global__ __launch_bounds__(kBlock) void bat_cqk_vjp_kernel(BatCqkArgs A) {
 // groups' lines combined.
 BatStat host_stat(const int32_t* hc, bool max_over) {
   BatStat t{0, 0, 0};
-  for (int q = 0; q < kQueues; ++q) {
+  const int lines = hc[CTR_GAVE_UP] ? kQueues : 2 * kQueues;
+  for (int q = 0; q < lines; ++q) {
     const int32_t* line = hc + CTR_STAT0 + q * kCtrLine;
     t.flags |= line[CTR_FLAGS];
     t.surv += line[CTR_SURV];
@@ -1845,7 +2315,7 @@ template <typename Args>
 void plan(cqk_ctx* ctx, const Args& A) {
   hipStream_t s = ctx->stream;
   const int gb = std::max(1, (A.nseg + kPBlock - 1) / kPBlock);
-  hipLaunchKernelGGL(bat_count_kernel<Args>, dim3(gb), dim3(kPBlock), 0, s, A);
+  if (gb > 1) hipLaunchKernelGGL(bat_count_kernel<Args>, dim3(gb), dim3(kPBlock), 0, s, A);
   hipLaunchKernelGGL(bat_place_kernel<Args>, dim3(gb), dim3(kPBlock), 0, s, A);
 }
 
@@ -1968,7 +2438,7 @@ cqk_status tune(cqk_ctx* ctx, const cqk_batch_schedule* cand, int ncand, int rep
 
 
 // Batched general CQK: the plan, then one persistent launch.
-BatCqkArgs cqk_args(int32_t nseg, const int64_t* offsets, const void* d, const void* a,
+BatCqkArgs cqk_args(cqk_ctx* ctx, int32_t nseg, const int64_t* offsets, const void* d, const void* a,
                     const void* b, const void* l, const void* u, const BatWs& w) {
   BatCqkArgs A{};
   A.nseg = nseg;
@@ -1982,6 +2452,12 @@ BatCqkArgs cqk_args(int32_t nseg, const int64_t* offsets, const void* d, const v
   A.counters = w.counters;
   A.bhist = w.bhist;
   A.lrow = w.lrow;
+  // every team size finds its blocks on the GPU at once
+  if (kRowBlocksPerCu * ctx->num_cus >= kTeamMax && team_ready(ctx, 0)) {
+    A.tctl = (BatTeamCtl*)((char*)ctx->team.ptr + kTeamBatCtl);
+    A.tslots = (uint64_t*)((char*)ctx->team.ptr + kTeamBatSlots);
+    A.tlimit = ctx->team_wait;
+  }
   return A;
 }
 
@@ -1994,24 +2470,25 @@ void cqk_apply_schedule(cqk_ctx* ctx, const cqk_batch_schedule& sc, BatCqkArgs* 
   *grid = dim3(std::max(1, std::min(ctx->num_cus * sc.blocks_per_cu, A->nseg)));
 }
 
+// The rows of teams; the rows it leaves (all of them when a team gave up) go
+// to the kernel queued behind it.
+template <typename Kern>
+void launch_teams(cqk_ctx* ctx, const BatCqkArgs& A, Kern kern) {
+  if (A.tslots == nullptr) return;
+  const dim3 grid(std::min(kBatTeamBlocks, kRowBlocksPerCu * ctx->num_cus));
+  hipLaunchKernelGGL(kern, grid, dim3(kRowBlock), 0, ctx->stream, A);
+}
+
 template <typename TIn>
 void launch_cqk_forward(cqk_ctx* ctx, const cqk_batch_schedule& sc, BatCqkArgs A) {
   dim3 grid;
   cqk_apply_schedule(ctx, sc, &A, &grid);
   plan(ctx, A);
-  auto wave_rows = [&]() {
-    if (sc.small_per == 4)
-      hipLaunchKernelGGL((bat_cqk_wave_kernel<4, TIn>), grid, dim3(kBlock), 0, ctx->stream, A);
-    else
-      hipLaunchKernelGGL((bat_cqk_wave_kernel<8, TIn>), grid, dim3(kBlock), 0, ctx->stream, A);
-  };
-  if (sc.short_first) wave_rows();
-  // at most two workgroup rows per compute unit: a row is read five times over,
-  // and with more of them in flight fewer of the re-reads are served by the
-  // 256 MB last-level cache
-  const dim3 lgrid(std::min<unsigned>(grid.x, 2u * (unsigned)ctx->num_cus));
-  hipLaunchKernelGGL((bat_cqk_solve_kernel<TIn>), lgrid, dim3(kBlock), 0, ctx->stream, A);
-  if (!sc.short_first) wave_rows();
+  launch_teams(ctx, A, bat_cqk_team_kernel<TIn>);
+  if (sc.small_per == 4)
+    hipLaunchKernelGGL((bat_cqk_solve_kernel<4, TIn>), grid, dim3(kBlock), 0, ctx->stream, A);
+  else
+    hipLaunchKernelGGL((bat_cqk_solve_kernel<8, TIn>), grid, dim3(kBlock), 0, ctx->stream, A);
 }
 
 template <typename TIn>
@@ -2019,6 +2496,7 @@ void launch_cqk_backward(cqk_ctx* ctx, const cqk_batch_schedule& sc, BatCqkArgs 
   dim3 grid;
   cqk_apply_schedule(ctx, sc, &A, &grid);
   plan(ctx, A);
+  launch_teams(ctx, A, bat_cqk_team_vjp_kernel<TIn>);
   if (sc.small_per == 4)
     hipLaunchKernelGGL((bat_cqk_vjp_kernel<4, TIn>), grid, dim3(kBlock), 0, ctx->stream, A);
   else
@@ -2036,7 +2514,7 @@ cqk_status run_batched_cqk(cqk_ctx* ctx, int32_t nseg, const int64_t* offsets, c
   BatWs w;
   cqk_status st = bat_workspace(ctx, nseg, &w);
   if (st != CQK_OK) return st;
-  BatCqkArgs A = cqk_args(nseg, offsets, d, a, b, l, u, w);
+  BatCqkArgs A = cqk_args(ctx, nseg, offsets, d, a, b, l, u, w);
   A.r = r;
   A.x = x;
   A.lam_out = lambda_out;
@@ -2076,14 +2554,14 @@ cqk_status run_batched_cqk(cqk_ctx* ctx, int32_t nseg, const int64_t* offsets, c
   };
   int32_t* dc = A.counters;
   ctx->last = [hc, dc, fill](cqk_info* inf) -> cqk_status {
-    if (hip_ok(hipMemcpy(hc, dc, CTR_TOTAL * sizeof(int32_t), hipMemcpyDeviceToHost)) != CQK_OK)
+    if (hip_ok(hipMemcpy(hc, dc, CTR_OUTCOME * sizeof(int32_t), hipMemcpyDeviceToHost)) != CQK_OK)
       return CQK_DEVICE_ERROR;
     fill(inf);
     return CQK_OK;
   };
   if (info) std::memset(info, 0, sizeof(*info));
   if (!o.sync) return CQK_OK;
-  if (hip_ok(hipMemcpyAsync(hc, A.counters, CTR_TOTAL * sizeof(int32_t), hipMemcpyDeviceToHost,
+  if (hip_ok(hipMemcpyAsync(hc, A.counters, CTR_OUTCOME * sizeof(int32_t), hipMemcpyDeviceToHost,
                             s)) != CQK_OK)
     return CQK_DEVICE_ERROR;
   if (hip_ok(hipStreamSynchronize(s)) != CQK_OK) return CQK_DEVICE_ERROR;
@@ -2099,7 +2577,7 @@ cqk_status run_batched_cqk_backward(cqk_ctx* ctx, int32_t nseg, const int64_t* o
   BatWs w;
   cqk_status st = bat_workspace(ctx, nseg, &w);
   if (st != CQK_OK) return st;
-  BatCqkArgs A = cqk_args(nseg, offsets, d, nullptr, b, l, u, w);
+  BatCqkArgs A = cqk_args(ctx, nseg, offsets, d, nullptr, b, l, u, w);
   A.x = const_cast<TIn*>(x);
   A.g = g;
   A.ga = grad_a;
@@ -2155,7 +2633,7 @@ cqk_status tune_batched_cqk(cqk_ctx* ctx, int32_t nseg, const int64_t* offsets, 
   BatWs w;
   cqk_status st = bat_workspace(ctx, nseg, &w);
   if (st != CQK_OK) return st;
-  BatCqkArgs A = cqk_args(nseg, offsets, d, a, b, l, u, w);
+  BatCqkArgs A = cqk_args(ctx, nseg, offsets, d, a, b, l, u, w);
   A.r = r;
   A.x = x;
   A.g = g;
@@ -2234,7 +2712,7 @@ void bat_fill_info(cqk_ctx* ctx, cqk_info* inf) {
 // counters (ctx->bat_counters) once the stream has finished it.
 cqk_status bat_read_last(cqk_ctx* ctx, cqk_info* inf) {
   int32_t* hc = (int32_t*)ctx->host_pinned;
-  if (hip_ok(hipMemcpy(hc, ctx->bat_counters, CTR_TOTAL * sizeof(int32_t),
+  if (hip_ok(hipMemcpy(hc, ctx->bat_counters, CTR_OUTCOME * sizeof(int32_t),
                        hipMemcpyDeviceToHost)) != CQK_OK)
     return CQK_DEVICE_ERROR;
   bat_fill_info(ctx, inf);
@@ -2263,7 +2741,7 @@ cqk_status run_batched_f32_on(cqk_ctx* ctx, int32_t nseg, const int64_t* offsets
   ctx->last = [ctx](cqk_info* inf) -> cqk_status { return bat_read_last(ctx, inf); };
   if (info) std::memset(info, 0, sizeof(*info));
   if (!o.sync) return CQK_OK;
-  if (hip_ok(hipMemcpyAsync(ctx->host_pinned, A.counters, CTR_TOTAL * sizeof(int32_t),
+  if (hip_ok(hipMemcpyAsync(ctx->host_pinned, A.counters, CTR_OUTCOME * sizeof(int32_t),
                             hipMemcpyDeviceToHost, s)) != CQK_OK)
     return CQK_DEVICE_ERROR;
   if (hip_ok(hipStreamSynchronize(s)) != CQK_OK) return CQK_DEVICE_ERROR;

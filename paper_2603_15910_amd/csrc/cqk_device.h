@@ -38,6 +38,7 @@ constexpr int kXor1 = 0xB1;        // quad_perm [1,0,3,2]
 constexpr int kXor2 = 0x4E;        // quad_perm [2,3,0,1]
 constexpr int kHalfMirror = 0x141;
 constexpr int kMirror = 0x140;
+constexpr int kRor8 = 0x128;       // row_ror:8, the other half of a row of 16
 constexpr int kBcast15 = 0x142;
 constexpr int kBcast31 = 0x143;
 }  // namespace dpp
@@ -104,6 +105,24 @@ __device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
   return v;
+}
+
+// Lane j's value in every lane, as a scalar.
+template <typename T>
+__device__ __forceinline__ T lane_value(T v, int j) {
+  static_assert(sizeof(T) == 8, "two 32-bit halves");
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, j);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), j);
+  return __builtin_bit_cast(T, ((uint64_t)hi << 32) | lo);
+}
+
+// A value that is the same in the whole wave, as a scalar: addresses and
+// bounds made from it stay out of the vector registers.
+template <typename T>
+__device__ __forceinline__ T scalar(T v) {
+  if constexpr (sizeof(T) == 8) return lane_value(v, 0);
+  else return (T)__builtin_amdgcn_readfirstlane((int)v);
 }
 
 // Number of set bits of a wave mask below this lane.

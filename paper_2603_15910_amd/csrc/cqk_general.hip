@@ -1606,7 +1606,6 @@ struct TeamResult {   // in the context's pinned host memory
 // and what such a launch leaves for the kernels queued behind it.
 struct TeamCtl {
   uint32_t base, next;   // tags of the current launch; first tag never used
-  GenState state;
   TeamResult res;
 };
 static_assert(sizeof(TeamCtl) <= kTeamCtlBytes, "the control block fits its reserve");
@@ -1619,9 +1618,11 @@ struct TeamArgs {
   int32_t formula;    // lam_0 from eq. (CQKlambda0)
   int32_t max_pass;
   GenState init;
-  Team team;
+  uint64_t* slots;
+  uint64_t limit;
+  uint32_t tag;       // the last tag used (a waiting call)
   TeamResult* res;
-  TeamCtl* ctl;       // queued or captured call: tags from here, state left here
+  const TeamCtl* ctl; // queued or captured call: tags from here
 };
 
 // Before a queued or captured one-launch solve: the run state of the kernels
@@ -1644,12 +1645,20 @@ __global__ __launch_bounds__(256) void gen_team_init_kernel(GenState* st, GenSta
   }
 }
 
-// After it: its state becomes the run state, so the passes queued behind
+// After it: its outcome becomes the run state's, so the passes queued behind
 // return at once, unless a block gave up; then those passes do the solve.
-__global__ void gen_team_commit_kernel(GenState* st, TeamCtl* ctl) {
-  if (ctl->res.gave_up) return;
-  *st = ctl->state;
-  st->team_done = (st->status != kRunning) ? 1 : 0;
+__global__ void gen_team_commit_kernel(GenState* st, const TeamCtl* ctl) {
+  const TeamResult& R = ctl->res;
+  if (R.gave_up || R.status == kRunning) return;
+  st->lam_final = R.lam_final;
+  st->lam0 = R.lam0;
+  st->bytes = R.bytes;
+  st->status = R.status;
+  st->iter = R.iter;
+  st->passes = R.passes;
+  st->stop_reason = R.stop_reason;
+  st->ntrace = R.ntrace;
+  st->team_done = 1;
 }
 
 template <typename TIn, int E>
@@ -1659,10 +1668,8 @@ __global__ __launch_bounds__(kTeamBlock) void gen_team_kernel(TeamArgs A) {
   // vectors of a load group (with E = 16 the form leaves registers for four
   // values of each array in flight)
   constexpr int Q = (E == 8 ? 8 : 4) / V;
-  __shared__ GenState st;
-  __shared__ double lds[8 * NW], mine[8], tot[8], all[8 * kTeamMax];
-  __shared__ KeySum ktot[2];
-  __shared__ int gave_up;
+  __shared__ TeamLds<kTeamBlock> S;
+  __shared__ double lds[3 * NW], tot3[3];
   const int tid = threadIdx.x;
   const int64_t n = A.n;
   const int64_t base = (int64_t)blockIdx.x * (kTeamBlock * E);
@@ -1735,35 +1742,45 @@ __global__ __launch_bounds__(kTeamBlock) void gen_team_kernel(TeamArgs A) {
       }
     }
   }
-  if (tid == 0) st = A.init;
-  if (A.ctl != nullptr) A.team.tag = A.ctl->base;
+  if (tid == 0) S.gave_up = 0;
+  __syncthreads();
+  Team team = grid_team(A.slots, A.ctl != nullptr ? A.ctl->base : A.tag, A.limit);
+  // the run state, the same in every lane of every block: in scalar registers
+  // between updates
+  GenState st{};
+  st.lam = A.init.lam;
+  st.lam0 = A.init.lam0;
+  st.lam_prev = st.lam_final = __builtin_nan("");
+  st.lo = -inf_d();
+  st.hi = inf_d();
+  st.phi_lo = st.phi_hi = __builtin_nan("");
+  st.r = A.init.r;
+  st.tol = A.init.tol;
+  st.status = kRunning;
+  st.max_iter = A.init.max_iter;
+  st.mode = kModeEval;
+  int par = 0;
   bool ok = true;
   if (start) {
     // lam_0 of the estimate, or of eq. (CQKlambda0) (gen_warm_update_kernel,
     // gen_lambda0_update_kernel)
+    double tot[WM_NSUM];
     w[WM_BAD] = bad;
-    block_reduce<WM_NSUM, 0, 0, kTeamBlock>(w, nullptr, nullptr, lds, mine);
-    ok = team_exchange<WM_NSUM>(A.team, mine, all, &gave_up);
-    team_sum<WM_NSUM>(all, tot);
-    if (tid == 0) {
-      st.passes += 1;
-      st.bytes += (pw != nullptr ? st.in_bytes * 6.0 / 5.0 : st.in_bytes) * (double)n;
-      if (tot[WM_BAD] > 0.0) {
-        st.status = CQK_INVALID_ARG;
-      } else {
-        double lam0;
-        if (pw != nullptr)
-          lam0 = (tot[WM_NJ] > 0.0) ? (st.r - tot[WM_FIX] - tot[WM_SJ]) / tot[WM_QJ]
-                                    : (st.r - tot[WM_SALL]) / tot[WM_QALL];
-        else
-          lam0 = (tot[WM_QALL] > 0.0) ? (st.r - tot[WM_SALL]) / tot[WM_QALL] : 0.0;
-        st.lam = st.lam0 = lam0;
-      }
-      st.ntrace += 1;
+    ok = team_reduce<WM_NSUM, kTeamBlock>(team, S, par, w, tot);
+    st.passes += 1;
+    st.ntrace += 1;
+    if (tot[WM_BAD] > 0.0) {
+      st.status = CQK_INVALID_ARG;
+    } else {
+      double lam0;
+      if (pw != nullptr)
+        lam0 = (tot[WM_NJ] > 0.0) ? (st.r - tot[WM_FIX] - tot[WM_SJ]) / tot[WM_QJ]
+                                  : (st.r - tot[WM_SALL]) / tot[WM_QALL];
+      else
+        lam0 = (tot[WM_QALL] > 0.0) ? (st.r - tot[WM_SALL]) / tot[WM_QALL] : 0.0;
+      st.lam = st.lam0 = scalar(lam0);
     }
   }
-  __syncthreads();
-  // every block takes the same branches: the state is the same in all
   for (int pass = 0; ok && pass < A.max_pass && st.status == kRunning; ++pass) {
     const double lam = st.lam;
     if (st.mode == kModeEval) {
@@ -1773,44 +1790,22 @@ __global__ __launch_bounds__(kTeamBlock) void gen_team_kernel(TeamArgs A) {
       for (int e = 0; e < E; ++e)
         eval_index<false>(acc, c[e], s[e], bl[e], bu[e], lam, 0.0, 0.0);
       const double v[5] = {acc.s[P_P], acc.s[P_A], acc.s[P_QP], acc.s[P_QM], bad};
-      block_reduce<5, 0, 0, kTeamBlock>(v, nullptr, nullptr, lds, mine);
-      ok = team_exchange<5>(A.team, mine, all, &gave_up);
-      team_sum<5>(all, tot);
-      if (tid == 0) {
-        double t[NSUM];
-#pragma unroll
-        for (int i = 0; i < NSUM; ++i) t[i] = 0.0;
-        t[P_P] = tot[0];
-        t[P_A] = tot[1];
-        t[P_QP] = tot[2];
-        t[P_QM] = tot[3];
-        t[P_BAD] = tot[4];
-        t[P_NIN] = (double)n;
-        // on the record in LDS: a copy in registers would cost every thread
-        // its size (256 VGPRs and spills)
-        update_after_eval(&st, t, nullptr);
-      }
+      double tot[5], t[NSUM];
+      ok = team_reduce<5, kTeamBlock>(team, S, par, v, tot);
+      t[P_P] = tot[0];
+      t[P_A] = tot[1];
+      t[P_QP] = tot[2];
+      t[P_QM] = tot[3];
+      t[P_BAD] = tot[4];
+      update_after_eval<false>(&st, t, nullptr);
     } else {
       KeySum ks[2] = {KeySum{inf_d(), 0.0}, KeySum{inf_d(), 0.0}};
 #pragma unroll
       for (int e = 0; e < E; ++e) bkpt_index(ks, c[e], s[e], bl[e], bu[e], lam);
-      block_ks_min<2, kTeamBlock>(ks, lds, ktot);
-      if (tid < 4) mine[tid] = (tid & 1) ? ktot[tid >> 1].w : ktot[tid >> 1].k;
-      __syncthreads();
-      ok = team_exchange<4>(A.team, mine, all, &gave_up);
-      if (tid < kWave) {
-        const int T = gridDim.x;
-        KeySum k2[2] = {KeySum{inf_d(), 0.0}, KeySum{inf_d(), 0.0}};
-        for (int g = tid; g < T; g += kWave) {
-          k2[0] = ks_min(k2[0], KeySum{all[g], all[T + g]});
-          k2[1] = ks_min(k2[1], KeySum{all[2 * T + g], all[3 * T + g]});
-        }
-        k2[0] = wave_ks_min(k2[0]);
-        k2[1] = wave_ks_min(k2[1]);
-        if (tid == 0) update_after_bkpt(&st, k2, nullptr);
-      }
+      ok = team_reduce_ks<kTeamBlock>(team, S, par, ks);
+      update_after_bkpt<false>(&st, ks, nullptr);
     }
-    __syncthreads();
+    state_to_scalars(st);
   }
   if (!ok) {
     if (tid == 0) A.res->gave_up = 1;
@@ -1856,20 +1851,20 @@ __global__ __launch_bounds__(kTeamBlock) void gen_team_kernel(TeamArgs A) {
       }
     }
   }
-  block_reduce<3, 0, 0, kTeamBlock>(sums, nullptr, nullptr, lds, tot);
-  if (tid < 3) A.res->part[3 * blockIdx.x + tid] = tot[tid];
+  block_reduce<3, 0, 0, kTeamBlock>(sums, nullptr, nullptr, lds, tot3);
+  if (tid < 3) A.res->part[3 * blockIdx.x + tid] = tot3[tid];
   if (blockIdx.x == 0 && tid == 0) {
     TeamResult& R = *A.res;
     R.lam_final = st.lam_final;
     R.lam0 = st.lam0;
-    R.bytes = st.bytes;
+    // the algorithmic bytes of the passes, as the multi-launch route's
+    R.bytes = A.init.in_bytes * (double)n * ((double)st.passes + (pw != nullptr ? 0.2 : 0.0));
     R.status = status;
     R.iter = st.iter;
     R.passes = st.passes;
     R.stop_reason = st.stop_reason;
-    R.tag = A.team.tag;
+    R.tag = team.tag;
     R.ntrace = st.ntrace;
-    if (A.ctl != nullptr) A.ctl->state = st;
   }
 }
 
@@ -2059,7 +2054,9 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     T.init = init;
     T.init.compaction = CQK_COMPACT_OFF;
     T.init.trace_cap = 0;
-    T.team = Team{(uint64_t*)ctx->team.ptr, ctx->team_tag, 0, ctx->team_wait};
+    T.slots = (uint64_t*)ctx->team.ptr;
+    T.limit = ctx->team_wait;
+    T.tag = ctx->team_tag;
     T.res = res;
     T.ctl = tc;
     auto go = [&](auto kern) {

@@ -27,89 +27,241 @@ namespace cqk {
 
 constexpr int kTeamBlock = 512;
 constexpr int kTeamMax = 256;     // blocks of a team
-constexpr int kSlotWords = 32;    // 8-byte words of one record slot (up to 16 doubles)
+constexpr int kSlotWords = 16;    // 8-byte words of one record slot (up to 8 doubles)
 constexpr size_t kTeamCtlBytes = 16384;  // behind the slots: a solver's control block
 constexpr size_t kTeamSlotBytes = (size_t)2 * kTeamMax * kSlotWords * sizeof(uint64_t);
 
+// The slots of teams that change size during a launch (the batched calls):
+// the smaller teams of a later class of rows are parts of the larger ones of
+// an earlier class, so their members agree on the tag, but a member of the
+// larger team may still be reading when another part moves on: every team
+// size has slots of its own.
+constexpr int kBatTeamBlocks = 1024;      // blocks of such a launch
+constexpr int kBatTeamLogs = 9;           // team sizes 1, 2, ... 256
+constexpr size_t kBatTeamBytes =
+    (size_t)kBatTeamLogs * 2 * kBatTeamBlocks * kSlotWords * sizeof(uint64_t);
+// The context's team buffer: slots and control block of the single solves,
+// then those of the batched calls.
+constexpr size_t kTeamBatCtl = kTeamSlotBytes + kTeamCtlBytes;
+constexpr size_t kTeamBatSlots = kTeamBatCtl + 256;
+constexpr size_t kTeamBytes = kTeamBatSlots + kBatTeamBytes;
+
 struct Team {
-  uint64_t* slots;
-  uint32_t tag;      // tag of the last exchange; the next one uses tag + 1
-  uint32_t pad_;
+  uint64_t* slots;   // the first member's slot of parity 0
   uint64_t limit;    // longest wait of one exchange, 100 MHz ticks
+  uint32_t tag;      // tag of the last exchange; the next one uses tag + 1
+  int T, me;         // blocks of the team, this block's place in it
+  int parity;        // words from one parity's slots to the other's
 };
 
-// One exchange: `mine` (LDS, NV doubles, written before a barrier by the
-// caller) goes out, all[v * T + g] (LDS) receives value v of block g.
-// Returns false when a wait ran into its limit (the same answer for the
-// whole block).  Ends with a barrier.
-template <int NV>
-__device__ __forceinline__ bool team_exchange(Team& team, const double* mine, double* all,
-                                              int* gave_up) {
+__device__ __forceinline__ Team grid_team(uint64_t* slots, uint32_t tag, uint64_t limit) {
+  return Team{slots, limit, tag, (int)gridDim.x, (int)blockIdx.x, kTeamMax * kSlotWords};
+}
+
+// LDS of the reductions below.
+template <int BLOCK>
+struct TeamLds {
+  double red[2][8 * (BLOCK / kWave)];  // the waves' sums, by the parity of the reduction
+  double part[2][8 * (BLOCK / kWave)];
+  int gave_up;                         // clear at the start of the kernel
+};
+
+// Posts a record: value v sits, the same in all of them, in the NW lanes from
+// v * NW on of the calling wave.
+template <int NV, int NW>
+__device__ __forceinline__ void team_post(const Team& team, uint64_t* slots, uint32_t tag,
+                                          double y, int lane) {
+  static_assert(NW >= 2 && NV * NW <= kWave, "two lanes of a wave per value");
+  if (lane < NV * NW && lane % NW < 2) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, y);
+    const uint64_t half = (lane % NW) ? (u >> 32) : (u & 0xffffffffull);
+    __hip_atomic_store(&slots[(size_t)team.me * kSlotWords + 2 * (lane / NW) + lane % NW],
+                       (half << 32) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// A wave reads the records from, from + 4, ... (steps of `step` groups of
+// four) below T: lane l takes word l % 16 of record l / 16 of a group, so one
+// load instruction covers four whole records, R of them in flight.  Each
+// record's value v is then in lanes 2v and 2v + 1 of its row of 16; the lane
+// adds it up, or (MIN) takes the (key, weight) minimum with the value two
+// lanes on as the weight.  (A lane per record instead, ten loads each of its
+// own line, took the exchange of 256 blocks from 3 to 7 us.)
+struct TeamRead {
+  double sum;
+  KeySum min;
+  bool late;   // a wait ran into its limit
+};
+
+template <int NV, bool MIN>
+__device__ __forceinline__ TeamRead team_read(const Team& team, const uint64_t* slots,
+                                              uint32_t tag, int from, int step, int lane) {
+  constexpr int R = 4;
+  TeamRead out{0.0, KeySum{inf_d(), 0.0}, false};
+  const bool mine = (lane & 15) < 2 * NV;
+  const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+  for (int g0 = from * 4; g0 < team.T && !out.late; g0 += R * step * 4) {
+    uint64_t w[R];
+    bool ok = false;
+    while (!ok && !out.late) {
+      ok = true;
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const int g = g0 + k * step * 4 + lane / 16;
+        w[k] = tag;
+        if (mine && g < team.T)
+          w[k] = __hip_atomic_load(&slots[(size_t)g * kSlotWords + (lane & 15)],
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+#pragma unroll
+      for (int k = 0; k < R; ++k) ok = ok && (uint32_t)w[k] == tag;
+      ok = __ballot(!ok) == 0;  // the wave goes round together
+      out.late = !ok && __builtin_amdgcn_s_memrealtime() - t0 > team.limit;
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const uint32_t half = (uint32_t)(w[k] >> 32);
+      const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)half, dpp::kXor1, 0xF,
+                                                                   0xF, false);
+      const uint32_t lo = (lane & 1) ? other : half, hi = (lane & 1) ? half : other;
+      const double v = __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+      const bool in = g0 + k * step * 4 + lane / 16 < team.T;
+      if constexpr (MIN) {
+        const double weight = dpp_move<dpp::kXor2, 0xF>(v, 0.0);
+        out.min = ks_min(out.min, in ? KeySum{v, weight} : KeySum{inf_d(), 0.0});
+      } else {
+        out.sum += in ? v : 0.0;
+      }
+    }
+  }
+  return out;
+}
+
+// Records are read by every wave of the block while a team is small (the
+// totals are then in every wave with no further trip through LDS), shared
+// among the waves in larger teams.
+constexpr int kTeamAllRead = 16;
+
+// Sums of NV values over the threads of a team's blocks; tot[] holds the
+// totals as scalars in every wave, the same bits in every block.  par: a
+// counter of the block's reductions (parity of the LDS buffers).  Returns
+// false, in the whole block, when a wait ran into its limit.  One barrier,
+// two with more than one block.
+template <int NV, int BLOCK>
+__device__ __forceinline__ bool team_reduce(Team& team, TeamLds<BLOCK>& S, int& par,
+                                            const double* v, double* tot) {
+  constexpr int NW = BLOCK / kWave;
+  constexpr int N = (NV <= 4) ? 4 : 8;
+  constexpr int SH = 6 - detail::ilog2(N);
+  static_assert(NV <= 8 && NV * NW <= kWave, "one lane per wave and value");
   static_assert(2 * NV <= kSlotWords, "a record fits its slot");
-  const int T = gridDim.x, me = blockIdx.x, tid = threadIdx.x;
-  if (T == 1) {
-    if (tid < NV) all[tid] = mine[tid];
-    __syncthreads();
+  static_assert(NW == 4 || NW == 8, "the sums over NW lanes below");
+  int tid = threadIdx.x;
+  // what is made from the thread index stays here: hoisted out of a loop of
+  // reductions the addresses would be spilled
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & (kWave - 1), wid = scalar(tid / kWave);
+  double x[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) x[i] = (i < NV) ? v[i] : 0.0;
+  wave_sum_many<N>(x);
+  par ^= 1;
+  double* red = S.red[par];
+  const int idx = lane >> SH;
+  if ((lane & ((1 << SH) - 1)) == 0 && idx < NV) red[idx * NW + wid] = x[0];
+  __syncthreads();
+  double y = (lane < NV * NW) ? red[lane] : 0.0;
+  y += dpp_move<dpp::kXor1, 0xF>(y, 0.0);
+  y += dpp_move<dpp::kXor2, 0xF>(y, 0.0);
+  if constexpr (NW == 8) y += dpp_move<dpp::kHalfMirror, 0xF>(y, 0.0);
+  if (team.T == 1) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) tot[i] = lane_value(y, i * NW);
     return true;
   }
   const uint32_t tag = ++team.tag;
-  uint64_t* slots = team.slots + (size_t)(tag & 1u) * kTeamMax * kSlotWords;
-  if (tid < 2 * NV) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, mine[tid >> 1]);
-    const uint64_t half = (tid & 1) ? (u >> 32) : (u & 0xffffffffull);
-    __hip_atomic_store(&slots[(size_t)me * kSlotWords + tid], (half << 32) | tag,
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  if (tid == 0) *gave_up = 0;
-  // word j of block g is item g * 2 NV + j; T <= kTeamMax = kTeamBlock / 2,
-  // so a thread has at most NV of them, all loaded before the first test
-  const int total = T * 2 * NV;
-  uint64_t w[NV];
-  bool ok = false, late = false;
-  const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-  while (!ok && !late) {
-    ok = true;
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      const int i = tid + k * kTeamBlock;
-      w[k] = tag;
-      if (i < total)
-        w[k] = __hip_atomic_load(&slots[(size_t)(i / (2 * NV)) * kSlotWords + i % (2 * NV)],
-                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-#pragma unroll
-    for (int k = 0; k < NV; ++k) ok = ok && (uint32_t)w[k] == tag;
-    late = !ok && __builtin_amdgcn_s_memrealtime() - t0 > team.limit;
-  }
-  __syncthreads();  // *gave_up is clear
-  if (late) *gave_up = 1;
-  uint32_t* out = reinterpret_cast<uint32_t*>(all);
-#pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    const int i = tid + k * kTeamBlock;
-    if (i < total) {
-      const int g = i / (2 * NV), j = i % (2 * NV);
-      out[2 * ((j >> 1) * T + g) + (j & 1)] = (uint32_t)(w[k] >> 32);
-    }
-  }
+  uint64_t* slots = team.slots + (size_t)(tag & 1u) * team.parity;
+  if (wid == 0) team_post<NV, NW>(team, slots, tag, y, lane);
+  const bool split = team.T > kTeamAllRead;
+  const TeamRead got =
+      team_read<NV, false>(team, slots, tag, split ? wid : 0, split ? NW : 1, lane);
+  if (got.late) S.gave_up = 1;
+  double z = got.sum;
+  // the four rows of 16 lanes
+  detail::halve<5, 1>(&z, lane);
+  detail::halve<4, 1>(&z, lane);
+  if (split && lane < 16 && (lane & 1) == 0) S.part[par][8 * wid + lane / 2] = z;
   __syncthreads();
-  return *gave_up == 0;
+  if (S.gave_up) return false;
+  if (!split) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) tot[i] = lane_value(z, 2 * i);
+    return true;
+  }
+  // value i of wave w at w * 8 + i: the waves' parts in lanes 8 apart
+  double p = (lane < 8 * NW) ? S.part[par][lane] : 0.0;
+  p += dpp_move<dpp::kRor8, 0xF>(p, 0.0);
+  detail::halve<5, 1>(&p, lane);
+  detail::halve<4, 1>(&p, lane);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) tot[i] = lane_value(p, i);
+  return true;
 }
 
-// Sums of the NV values over the T records, in record order per lane: wave v
-// takes value v, v + waves, ...; out[v] (LDS) is valid after the barrier it
-// ends with, the same bits in every block.
-template <int NV>
-__device__ __forceinline__ void team_sum(const double* all, double* out) {
-  const int T = gridDim.x;
-  const int lane = threadIdx.x & (kWave - 1);
-  for (int v = (int)(threadIdx.x / kWave); v < NV; v += kTeamBlock / kWave) {
-    double a = 0.0;
-    for (int g = lane; g < T; g += kWave) a += all[v * T + g];
-    a = wave_sum(a);
-    if (lane == 0) out[v] = a;
+// The two (key, weight) minima over the threads of a team's blocks, as
+// team_reduce.
+template <int BLOCK>
+__device__ __forceinline__ bool team_reduce_ks(Team& team, TeamLds<BLOCK>& S, int& par,
+                                               KeySum* ks) {
+  constexpr int NW = BLOCK / kWave;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & (kWave - 1), wid = scalar(tid / kWave);
+  par ^= 1;
+  double* red = S.red[par];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const KeySum k = wave_ks_min(ks[i]);
+    if (lane == 0) {
+      red[(2 * i) * NW + wid] = k.k;
+      red[(2 * i + 1) * NW + wid] = k.w;
+    }
   }
   __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    ks[i] = wave_ks_min(lane < NW ? KeySum{red[2 * i * NW + lane], red[(2 * i + 1) * NW + lane]}
+                                  : KeySum{inf_d(), 0.0});
+  if (team.T == 1) return true;
+  const uint32_t tag = ++team.tag;
+  uint64_t* slots = team.slots + (size_t)(tag & 1u) * team.parity;
+  const int q = lane / NW;
+  const KeySum k0 = ks[0], k1 = ks[1];  // read before the choice: both stay in registers
+  const double y = (q == 0) ? k0.k : (q == 1) ? k0.w : (q == 2) ? k1.k : k1.w;
+  if (wid == 0) team_post<4, NW>(team, slots, tag, y, lane);
+  // keys are in lanes 0, 1 and 4, 5 of a row of 16, their weights two lanes
+  // on; lane 0 (4) of each row takes both
+  const bool split = team.T > kTeamAllRead;
+  const TeamRead got = team_read<4, true>(team, slots, tag, split ? wid : 0, split ? NW : 1, lane);
+  if (got.late) S.gave_up = 1;
+  const KeySum k2 = got.min;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    ks[i] = wave_ks_min((lane & 15) == 4 * i ? k2 : KeySum{inf_d(), 0.0});
+  const KeySum m0 = ks[0], m1 = ks[1];
+  if (split && lane < 4)
+    S.part[par][8 * wid + lane] = (lane == 0) ? m0.k : (lane == 1) ? m0.w
+                                  : (lane == 2) ? m1.k : m1.w;
+  __syncthreads();
+  if (S.gave_up) return false;
+  if (!split) return true;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    ks[i] = KeySum{inf_d(), 0.0};
+    for (int k = 0; k < NW; ++k)
+      ks[i] = ks_min(ks[i], KeySum{S.part[par][8 * k + 2 * i], S.part[par][8 * k + 2 * i + 1]});
+  }
+  return true;
 }
 
 }  // namespace cqk
