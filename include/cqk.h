@@ -208,12 +208,14 @@ cqk_status cqk_set_stream(cqk_ctx* ctx, void* hip_stream);
 /* Grow the workspace for solves of up to max_n indices and batched calls of
  * up to max_seg rows. */
 cqk_status cqk_reserve(cqk_ctx* ctx, int64_t max_n, int32_t max_seg);
-/* Synchronous calls on small and middle-sized inputs run in one launch whose
- * blocks exchange their sums while they run, so they have to run side by
- * side; a block that waits longer than `ticks` of the GPU's 100 MHz clock for
- * the others (another stream holds the compute units) gives up, and the call
- * then takes its multi-launch route with the same results.  Default 2000000
- * (20 ms); 0: always the multi-launch route.  INVALID_ARG: ticks < 0. */
+/* Calls on inputs that fit the chip's registers (general CQK up to 2097152
+ * indices, projections up to 12582912 FP32 or 6291456 FP64 values, long rows
+ * of batched CQK) run in one launch whose blocks exchange their sums while
+ * they run, so they have to run side by side; a block that waits longer than
+ * `ticks` of the GPU's 100 MHz clock for the others (another stream holds the
+ * compute units) gives up, and the call then takes its multi-launch route
+ * with the same results.  Default 2000000 (20 ms); 0: always the multi-launch
+ * route.  INVALID_ARG: ticks < 0. */
 cqk_status cqk_set_team_wait(cqk_ctx* ctx, int64_t ticks);
 const char* cqk_status_string(int32_t status);
 void cqk_default_opts(cqk_opts* opts);

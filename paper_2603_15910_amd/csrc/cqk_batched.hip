@@ -1609,7 +1609,6 @@ struct RowShape {
   static_assert(kRowBlock * E == 1 << kLog, "a row of bit length kLog fits one block");
   static_assert(kMaxLog < kNBW - 1, "and every team row has a bucket of its own length");
 };
-static_assert((1 << (kBatTeamLogs - 1)) <= kTeamMax, "the largest team");
 
 // The rows of this block one after the other, each with its team.  Longest
 // classes first; a class with fewer rows than teams takes larger teams (never
@@ -1641,7 +1640,7 @@ struct TeamRows {
     b = kTeamMaxLog + 1;
     from = cnt = j = off = wi = wn = 0;
     NT = per = 1;
-    cap = kTeamMax;
+    cap = kBatTeamMax;
     while (cap > (int)gridDim.x) cap >>= 1;
   }
 
@@ -2453,7 +2452,7 @@ BatCqkArgs cqk_args(cqk_ctx* ctx, int32_t nseg, const int64_t* offsets, const vo
   A.bhist = w.bhist;
   A.lrow = w.lrow;
   // every team size finds its blocks on the GPU at once
-  if (kRowBlocksPerCu * ctx->num_cus >= kTeamMax && team_ready(ctx, 0)) {
+  if (kRowBlocksPerCu * ctx->num_cus >= kBatTeamMax && team_ready(ctx, 0)) {
     A.tctl = (BatTeamCtl*)((char*)ctx->team.ptr + kTeamBatCtl);
     A.tslots = (uint64_t*)((char*)ctx->team.ptr + kTeamBatSlots);
     A.tlimit = ctx->team_wait;

@@ -1600,16 +1600,12 @@ struct TeamResult {   // in the context's pinned host memory
   double part[3 * kTeamMax];  // per block: b^T x, sum |b x|, free indices
 };
 
-// Device memory behind the record slots: the control words of queued and
-// captured launches, whose tags come from device memory (a replay must not
-// repeat its tags; they have the top bit set, those of waiting calls clear),
-// and what such a launch leaves for the kernels queued behind it.
+// Behind the record slots, for queued and captured launches.
 struct TeamCtl {
-  uint32_t base, next;   // tags of the current launch; first tag never used
+  TeamTags tags;
   TeamResult res;
 };
 static_assert(sizeof(TeamCtl) <= kTeamCtlBytes, "the control block fits its reserve");
-constexpr uint32_t kTeamDeviceTags = 0x80000000u;
 
 struct TeamArgs {
   const void *d, *a, *b, *l, *u, *xw;
@@ -1625,27 +1621,7 @@ struct TeamArgs {
   const TeamCtl* ctl; // queued or captured call: tags from here
 };
 
-// Before a queued or captured one-launch solve: the run state of the kernels
-// queued behind it, a fresh range of tags (the slots are cleared when the
-// range starts over) and a clear result.
-__global__ __launch_bounds__(256) void gen_team_init_kernel(GenState* st, GenState init,
-                                                            TeamCtl* ctl, uint64_t* slots,
-                                                            uint32_t need) {
-  const uint32_t next = ctl->next;
-  const bool wrap = next == 0 || next > 0xffffffffu - need;
-  __syncthreads();
-  if (wrap)
-    for (size_t i = threadIdx.x; i < kTeamSlotBytes / sizeof(uint64_t); i += 256) slots[i] = 0;
-  if (threadIdx.x == 0) {
-    *st = init;
-    const uint32_t base = wrap ? kTeamDeviceTags : next;
-    ctl->base = base;
-    ctl->next = base + need;
-    ctl->res.gave_up = 0;
-  }
-}
-
-// After it: its outcome becomes the run state's, so the passes queued behind
+// After a queued one-launch solve: its outcome becomes the run state's, so the passes queued behind
 // return at once, unless a block gave up; then those passes do the solve.
 __global__ void gen_team_commit_kernel(GenState* st, const TeamCtl* ctl) {
   const TeamResult& R = ctl->res;
@@ -1744,7 +1720,7 @@ __global__ __launch_bounds__(kTeamBlock) void gen_team_kernel(TeamArgs A) {
   }
   if (tid == 0) S.gave_up = 0;
   __syncthreads();
-  Team team = grid_team(A.slots, A.ctl != nullptr ? A.ctl->base : A.tag, A.limit);
+  Team team = grid_team(A.slots, A.ctl != nullptr ? A.ctl->tags.base : A.tag, A.limit);
   // the run state, the same in every lane of every block: in scalar registers
   // between updates
   GenState st{};
@@ -2113,8 +2089,8 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     }
   }
   if (team && deferred) {
-    hipLaunchKernelGGL(gen_team_init_kernel, dim3(1), dim3(256), 0, s, A.st, init, ctl,
-                       (uint64_t*)ctx->team.ptr, need);
+    hipLaunchKernelGGL(team_init_kernel<GenState>, dim3(1), dim3(256), 0, s, A.st, init,
+                       &ctl->tags, &ctl->res.gave_up, (uint64_t*)ctx->team.ptr, need);
     launch_team(&ctl->res, ctl);
     hipLaunchKernelGGL(gen_team_commit_kernel, dim3(1), dim3(1), 0, s, A.st, ctl);
   } else {

@@ -89,7 +89,7 @@ struct SpxState {
   int32_t x_zeroed;               // 1: the start already wrote x = 0 everywhere
   int32_t warm;                   // 1: a warm start (the start pass also reads xbar)
   int32_t sp_over;                // sparse output: the support exceeded the capacity
-  int32_t pad_[1];
+  int32_t team_done;              // 1: a one-launch projection wrote x and this state
 };
 
 // Sparse output of a simplex / l1 projection: the support in ascending index

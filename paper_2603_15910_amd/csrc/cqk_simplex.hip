@@ -46,6 +46,9 @@
 //                           iteration inside its block.
 //   spx_tail_kernel         the same loop for an input that fits from the
 //                           start (read from y).
+//   spx_team_kernel         all of it in one launch, for inputs that fit the
+//                           compute units' registers; the kernels above are
+//                           its fallback and the route of longer inputs.
 //   spx_finalize_kernel     dense x = max(0, y + lam*) (or 0, or a copy of y);
 //   spx_scatter_kernel      x[idx] for the surviving indices when the rest of
 //                           x is known to be zero.
@@ -58,6 +61,7 @@
 
 #include "cqk_device.h"
 #include "cqk_internal.h"
+#include "cqk_team.h"
 
 namespace cqk {
 namespace {
@@ -324,9 +328,14 @@ constexpr int kSampleWaves = 1024;  // tiles in the sample, at most
 // The kernel also starts the solve: `init` is the solve's initial state,
 // which block 0 stores (no kernel of the call runs before this one).
 template <typename TIn, typename TA>
-__global__ __launch_bounds__(kBlock) void spx_condat_sample_kernel(SpxArgs A, SpxState init) {
+__global__ __launch_bounds__(kBlock) void spx_condat_sample_kernel(SpxArgs A, SpxState init,
+                                                                   int have_state) {
   SpxState* st = A.st;
-  if (blockIdx.x == 0 && threadIdx.x == 0) *st = init;
+  if (have_state) {
+    if (st->status != kRunning) return;
+  } else if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *st = init;
+  }
   if (init.status != kRunning) return;
   constexpr int V = VecWidth<TIn>::value;
   constexpr int K = kCondatK;
@@ -1349,7 +1358,7 @@ __device__ __forceinline__ int spx_fin_mode(const SpxState* st) {
 }
 
 __device__ __forceinline__ bool spx_done(const SpxState* st) {
-  return st->status == CQK_OK || st->status == CQK_NOT_CONVERGED;
+  return (st->status == CQK_OK || st->status == CQK_NOT_CONVERGED) && !st->team_done;
 }
 
 // Dense finalize over all n: x = max(0, y + lam) (l1: with the signs of y),
@@ -1712,6 +1721,478 @@ __global__ __launch_bounds__(kBlock) void spx_sp_write_kernel(SpxArgs A, int GS)
 
 __global__ void spx_init_kernel(SpxState* st, SpxState init) { *st = init; }
 
+// ---------------------------------------------------------------------------
+// The whole projection in one launch, for inputs that fit the compute units'
+// registers (kTeamBlock threads of E values, one block per compute unit:
+// 12 582 912 FP32 or 6 291 456 FP64 values on 256).  Every block reads its
+// values once and keeps them.  Start: each wave runs Algorithm 4 on the
+// largest value of every lane (any J gives lam_J >= lam*, eq. (lambdaJ)), the
+// block takes the smallest of its waves' bounds and lists the values above it
+// in LDS; one exchange between the blocks (cqk_team.h) gives the bound of the
+// union of the lists, a second the best of kTeamCand candidates below it.
+// Then Algorithm 4 on the lists, one exchange per iteration, and x from the
+// registers, or, for a sparse output, the support in ascending order at the
+// place the counts of the blocks before give (one more exchange).
+// Bound by latency: the load, about 3 us per exchange, the store.  Whole
+// waiting calls, against the multi-launch route (11 or 12 launches and the
+// gaps between them): FP32 1e3 values 72 -> 26 us, 65 536 70 -> 36, 1e6
+// 73 -> 36, 1e7 95 -> 56; sparse l1 of 1e7 142 -> 79; FP64 1e6 73 -> 43.
+// ---------------------------------------------------------------------------
+constexpr int kTeamCand = 4;
+constexpr int kTeamListBytes = 64 * 1024;  // a block's list; beyond it the registers are swept
+
+struct SpxTeamResult {   // in the context's pinned host memory, or behind the slots
+  double lam_final, lam0, sum_abs, n_init;
+  int32_t status, iter, passes, stop_reason, copy;
+  int32_t gave_up;       // 1: some block's wait ran out; nothing here counts
+  uint32_t tag;
+  int32_t pad_;
+  int64_t nnz;           // sparse output
+  double part[2 * kTeamMax];  // per block: sum |x|, values not zero
+};
+
+struct SpxTeamCtl {      // queued and captured calls
+  TeamTags tags;
+  SpxTeamResult res;
+};
+static_assert(sizeof(SpxTeamCtl) <= kTeamCtlBytes, "the control block fits its reserve");
+
+struct SpxTeamArgs {
+  const void *y, *xw;
+  void* x;               // null: sparse output
+  int64_t* sp_idx;
+  void* sp_val;
+  int64_t n, sp_cap;
+  double r, tol;
+  int32_t l1, max_iter;
+  uint64_t* slots;
+  uint64_t limit;
+  uint32_t tag;
+  SpxTeamResult* res;
+  const SpxTeamCtl* ctl;
+};
+
+// After the projection kernel: its outcome becomes the run state's, so the
+// kernels queued behind return at once, unless a block gave up.
+__global__ void spx_team_commit_kernel(SpxState* st, const SpxTeamCtl* ctl) {
+  const SpxTeamResult& R = ctl->res;
+  if (R.gave_up) return;
+  st->lam_final = R.lam_final;
+  st->lam0 = R.lam0;
+  st->sum_abs = R.sum_abs;
+  st->n_init = (int64_t)R.n_init;
+  st->status = R.status;
+  st->iter = R.iter;
+  st->passes = R.passes;
+  st->stop_reason = R.stop_reason;
+  if (R.copy) st->fin_mode = kFinCopy;
+  st->team_done = 1;
+}
+
+template <typename TIn, int E>
+__global__ __launch_bounds__(kTeamBlock) void spx_team_kernel(SpxTeamArgs A) {
+  constexpr int V = VecWidth<TIn>::value;
+  constexpr int Q = E / V;
+  constexpr int NW = kTeamBlock / kWave;
+  constexpr int CAP = kTeamListBytes / (int)sizeof(TIn) / NW;  // entries of a wave's list
+  constexpr int MW = (E + 31) / 32;
+  typedef typename Raw16<TIn>::type Raw;
+  __shared__ TeamLds<kTeamBlock> S;
+  __shared__ TIn lists[NW][CAP];
+  __shared__ int cnt[Q * NW + 1];
+  __shared__ double bounds[NW];
+  int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1), wid = scalar(tid / kWave);
+  const int64_t n = A.n;
+  const int64_t base = (int64_t)blockIdx.x * (kTeamBlock * E);
+  const bool whole = base + kTeamBlock * E <= n;
+  const double r = A.r;
+  const bool l1 = A.l1 != 0;
+  const TIn* y = (const TIn*)A.y;
+  const TIn* xw = (const TIn*)A.xw;
+  auto index = [&](int q) { return base + ((int64_t)q * kTeamBlock + tid) * V; };
+  // a value that is not there: above no bound, not the largest of anything
+  const TIn none = (TIn)__builtin_nan("");
+  Raw v[Q];
+  if (whole) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) v[q] = ld16(y + index(q));
+  } else {
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+      for (int k = 0; k < V; ++k) v[q][k] = (index(q) + k < n) ? y[index(q) + k] : none;
+  }
+  if (tid == 0) S.gave_up = 0;
+  // what is made from the values is made anew in each phase, a vector at a
+  // time: kept across them by the compiler it would be spilled
+  auto hold = [&]() {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) asm volatile("" : "+v"(v[q]));
+    asm volatile("" : "+v"(tid));
+  };
+  auto val = [&](int q, int k) { return l1 ? absval(v[q][k]) : v[q][k]; };
+  auto there = [&](int q, int k) { return whole || index(q) + k < n; };
+  // whether any value of vector q of the wave is above a: almost none is at
+  // the bounds used below, so most vectors cost this test and no more
+  auto any_above = [&](int q, TIn a) {
+    TIn mx = val(q, 0);
+#pragma unroll
+    for (int k = 1; k < V; ++k) mx = fmax(mx, val(q, k));
+    return __ballot(mx > a) != 0;
+  };
+  uint32_t in_i[MW];  // the estimate's support
+#pragma unroll
+  for (int m = 0; m < MW; ++m) in_i[m] = 0;
+  double abs_sum = 0.0, vmax_i = -inf_d();
+  TIn badacc = TIn(0), vmx = none;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+      if (there(q, k)) {
+        badacc += v[q][k] * TIn(0);
+        vmx = fmax(vmx, val(q, k));
+        if (l1) abs_sum += (double)absval(v[q][k]);
+      }
+    }
+  }
+  hold();
+  if (xw != nullptr) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      if (q % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < V; ++k) {
+        if (there(q, k)) {
+          const TIn w = xw[index(q) + k];
+          if (l1 ? (w != TIn(0)) : (w > TIn(0))) {
+            in_i[(q * V + k) / 32] |= 1u << ((q * V + k) % 32);
+            vmax_i = fmax(vmax_i, (double)val(q, k));
+          }
+        }
+      }
+    }
+  }
+  const double bad = (badacc == TIn(0)) ? 0.0 : 1.0;
+  // the wave's bound: Algorithm 4 on the lanes' largest values, from lam_J of
+  // the largest of them
+  const double lmax = (double)vmx, wmax = wave_max(lmax);
+  double lam = (wmax > -inf_d() && wmax < inf_d()) ? r - wmax : inf_d();
+  if (lam < inf_d()) {
+    double prev = 1.0;
+    for (int it = 0; it < kRefine; ++it) {
+      const bool on = lmax + lam > 0.0;
+      const double c = (double)__popcll(__ballot(on));
+      if (c == prev) break;
+      const double nl = (r - wave_sum(on ? lmax : 0.0)) / c;
+      if (!(nl < lam)) break;
+      lam = nl;
+      prev = c;
+    }
+  }
+  if (lane == 0) bounds[wid] = lam;
+  __syncthreads();
+  double lam_b = bounds[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) lam_b = fmin(lam_b, bounds[w]);
+  lam_b = scalar(lam_b);
+  // the values above the block's bound, in the wave's list; their count and
+  // sum, and those of the estimate's among them
+  TIn* list = lists[wid];
+  int nlist = 0;
+  const TIn thr = round_down_to<TIn>(-lam_b);
+  double c_keep = 0.0, s_keep = 0.0, c_i = 0.0, s_i = 0.0;
+  hold();
+  if (__ballot(vmx > thr) != 0) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (!any_above(q, thr)) continue;
+#pragma unroll
+      for (int k = 0; k < V; ++k) {
+        const TIn t = val(q, k);
+        const bool keep = t > thr;
+        const uint64_t m = __ballot(keep);
+        if (m == 0) continue;
+        const int at = nlist + lane_prefix(m);
+        nlist += __popcll(m);
+        if (keep) {
+          if (at < CAP) list[at] = t;
+          c_keep += 1.0;
+          s_keep += (double)t;
+          if ((in_i[(q * V + k) / 32] >> ((q * V + k) % 32)) & 1u) {
+            c_i += 1.0;
+            s_i += (double)t;
+          }
+        }
+      }
+    }
+  }
+  Team team = grid_team(A.slots, A.ctl != nullptr ? A.ctl->tags.base : A.tag, A.limit);
+  int par = 0;
+  const double v1[8] = {c_keep, s_keep, bad, abs_sum, c_i, s_i, -lmax, lam_b};
+  double tot[8];
+  bool ok = team_reduce<8, kTeamBlock, 2>(team, S, par, v1, tot);
+  double vmax = -tot[6], vmaxi = -inf_d();
+  if (ok && xw != nullptr) {
+    const double vi[1] = {-vmax_i};
+    double ti[1];
+    ok = team_reduce<1, kTeamBlock, 1>(team, S, par, vi, ti);
+    vmaxi = -ti[0];
+  }
+  const int m = scalar(nlist);
+  // the wave's values that can be above a bound lam <= lam_b, to fn
+  auto each = [&](auto&& fn) {
+    if (m <= CAP) {
+      for (int i = lane; i < m; i += kWave) fn((double)list[i]);
+    } else {
+      hold();
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < V; ++k)
+          if (val(q, k) > thr) fn((double)val(q, k));
+      }
+    }
+  };
+  int status = kRunning, iter = 0, reason = 0, passes = 1;
+  bool copy = false;
+  double lam_final = __builtin_nan(""), lam0 = __builtin_nan("");
+  double lo = -inf_d(), hi = inf_d();
+  if (tot[2] > 0.0) {
+    status = CQK_INVALID_ARG;
+  } else if (l1 && tot[3] <= r) {
+    copy = true;
+    status = CQK_OK;
+    lam_final = 0.0;
+    reason = 5;
+  } else {
+    // lam_J of the union of the lists, and the smallest block bound
+    lam = (tot[0] > 0.0) ? fmin((r - tot[1]) / tot[0], tot[7]) : tot[7];
+    bool bound = true;  // lam >= lam* is known
+    if (xw != nullptr) {
+      if (!(vmaxi > -inf_d())) {
+        // an empty support: the fallback max{r/n, -max v} of Section 3.1,
+        // Newton's first step decides its side
+        lam = fmax(r / (double)n, -vmax);
+        bound = false;
+      } else {
+        double lw = r - vmaxi;
+        if (tot[4] > 0.0) lw = fmin(lw, (r - tot[5]) / tot[4]);
+        lam = fmin(lam, lw);
+      }
+    }
+    lam = scalar(lam);
+    if (ok && bound && tot[0] > 1.0) {
+      // candidates between lam and -max v (a lower bound of lam*)
+      double vc[2 * kTeamCand], tc[2 * kTeamCand], cl[kTeamCand];
+#pragma unroll
+      for (int j = 0; j < kTeamCand; ++j) {
+        vc[j] = vc[kTeamCand + j] = 0.0;
+        cl[j] = scalar(-vmax + (lam + vmax) / (double)(2u << j));
+      }
+      each([&](double t) {
+#pragma unroll
+        for (int j = 0; j < kTeamCand; ++j) {
+          const bool on = t + cl[j] > 0.0;
+          vc[j] += on ? 1.0 : 0.0;
+          vc[kTeamCand + j] += on ? t : 0.0;
+        }
+      });
+      ok = team_reduce<2 * kTeamCand, kTeamBlock>(team, S, par, vc, tc);
+#pragma unroll
+      for (int j = 0; j < kTeamCand; ++j)
+        if (tc[j] > 0.0) lam = fmin(lam, (r - tc[kTeamCand + j]) / tc[j]);
+      lam = scalar(lam);
+      passes += 1;
+    }
+    lam0 = lam;
+    if (bound) hi = lam;
+  }
+  // Algorithm 4's update, as spx_update without sets and trace
+  double cm_prev = -1.0;
+  while (ok && status == kRunning) {
+    double ve[3] = {0.0, 0.0, 0.0}, te[3];
+    each([&](double t) {
+      const double z = t + lam;
+      ve[0] += z > 0.0 ? z : 0.0;
+      ve[1] += z > 0.0 ? 1.0 : 0.0;
+      ve[2] += z >= 0.0 ? 1.0 : 0.0;
+    });
+    ok = team_reduce<3, kTeamBlock>(team, S, par, ve, te);
+    const double phi = te[0], cm = te[1], cp = te[2];
+    const int k = iter;
+    iter += 1;
+    passes += 1;
+    const bool below = (k == 0 && phi < r);
+    lo = below ? lam : lo;
+    hi = (!below && phi > r) ? lam : hi;
+    const double step = (phi - r) / (below ? cp : cm), next = lam - step;
+    int why = 0;
+    double at = lam;
+    if (phi == r || (k > 0 && phi <= r)) {
+      why = 4;
+    } else if (fabs(step) < A.tol) {
+      why = 2;
+      at = next;
+    } else if (k > 0 && cm == cm_prev) {
+      why = 4;
+      at = next;
+    } else if (next == lam) {
+      why = 2;
+    } else if (hi - lo < A.tol * fmax(fabs(hi), fabs(lo))) {
+      why = 3;
+    }
+    if (why != 0) {
+      status = CQK_OK;
+      lam_final = at;
+      reason = why;
+    } else if (iter >= A.max_iter) {
+      status = CQK_NOT_CONVERGED;
+      lam_final = lam;
+    }
+    cm_prev = cm;
+    lam = scalar(next);
+    status = scalar(status);
+  }
+  if (!ok) {
+    if (tid == 0) A.res->gave_up = 1;
+    return;
+  }
+  double sums[2] = {0.0, 0.0};
+  int64_t nnz = 0;
+  if (status == CQK_OK || status == CQK_NOT_CONVERGED) {
+    const double lf = lam_final;
+    hold();
+    // v + lam > 0 exactly when v > end (y inside the l1 ball: every value)
+    const TIn end = copy ? (TIn)-1 : round_down_to<TIn>(-lf);
+    if (A.x != nullptr) {
+      TIn* x = (TIn*)A.x;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        __builtin_amdgcn_sched_barrier(0);
+        Raw o;
+#pragma unroll
+        for (int k = 0; k < V; ++k) o[k] = TIn(0);
+        if (any_above(q, end)) {
+#pragma unroll
+          for (int k = 0; k < V; ++k) {
+            o[k] = spx_x_of<TIn, double>(v[q][k], lf, l1, copy);
+            if (there(q, k)) {
+              sums[0] += fabs((double)o[k]);
+              sums[1] += (o[k] != TIn(0)) ? 1.0 : 0.0;
+            }
+          }
+        }
+        if (whole) {
+          st16(x + index(q), o);
+        } else {
+#pragma unroll
+          for (int k = 0; k < V; ++k)
+            if (there(q, k)) x[index(q) + k] = o[k];
+        }
+      }
+    } else {
+      // entries of each vector group and wave, then where they start
+      auto mask_of = [&](int q) {
+        uint32_t b = 0;
+#pragma unroll
+        for (int k = 0; k < V; ++k)
+          if (there(q, k) && spx_x_of<TIn, double>(v[q][k], lf, l1, copy) != TIn(0)) b |= 1u << k;
+        return b;
+      };
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        __builtin_amdgcn_sched_barrier(0);
+        int t = 0;
+        if (any_above(q, end)) {
+          const int c = __popc(mask_of(q));
+#pragma unroll
+          for (int b = 0; b < 3; ++b) t += __popcll(__ballot((c >> b) & 1)) << b;
+        }
+        if (lane == 0) cnt[q * NW + wid] = t;
+      }
+      __syncthreads();
+      if (wid == 0) {
+        int run = 0;
+        for (int i0 = 0; i0 < Q * NW; i0 += kWave) {
+          const int c = (i0 + lane < Q * NW) ? cnt[i0 + lane] : 0;
+          const int incl = wave_incl_scan(c);
+          if (i0 + lane < Q * NW) cnt[i0 + lane] = run + incl - c;
+          run += __builtin_amdgcn_readlane(incl, kWave - 1);
+        }
+        if (lane == 0) cnt[Q * NW] = run;
+      }
+      __syncthreads();
+      const double mine = (double)cnt[Q * NW];
+      // the entries of all blocks, and of those before this one
+      double total = mine, before = 0.0;
+      if (team.T > 1) ok = team_prefix(team, S, par, mine, &total, &before);
+      if (!ok) {
+        if (tid == 0) A.res->gave_up = 1;
+        return;
+      }
+      nnz = (int64_t)total;
+      const bool room = nnz <= A.sp_cap;
+      hold();
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (!any_above(q, end)) continue;
+        const uint32_t b = mask_of(q);
+        const int c = __popc(b);
+        int pre = 0;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) pre += lane_prefix(__ballot((c >> j) & 1)) << j;
+        int64_t at = (int64_t)before + cnt[q * NW + wid] + pre;
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+          if ((b >> k) & 1u) {
+            const TIn xo = spx_x_of<TIn, double>(v[q][k], lf, l1, copy);
+            if (room) {
+              A.sp_idx[at] = index(q) + k;
+              ((TIn*)A.sp_val)[at] = xo;
+            }
+            ++at;
+            sums[0] += fabs((double)xo);
+            sums[1] += 1.0;
+          }
+        }
+      }
+    }
+  }
+  // the block's share of sum |x| and of the count
+  __shared__ double lds[2 * NW], tot2[2];
+  block_reduce<2, 0, 0, kTeamBlock>(sums, nullptr, nullptr, lds, tot2);
+  if (tid < 2) A.res->part[2 * blockIdx.x + tid] = tot2[tid];
+  if (blockIdx.x == 0 && tid == 0) {
+    SpxTeamResult& R = *A.res;
+    R.lam_final = lam_final;
+    R.lam0 = lam0;
+    R.sum_abs = tot[3];
+    R.n_init = (status == CQK_INVALID_ARG || copy) ? 0.0 : tot[0];
+    R.status = status;
+    R.iter = iter;
+    R.passes = passes;
+    R.stop_reason = reason;
+    R.copy = copy ? 1 : 0;
+    R.tag = team.tag;
+    R.nnz = nnz;
+  }
+}
+
+// Values per thread of a one-launch projection: E0 in one block, the others in
+// up to one block per compute unit, the first that holds y.  12 582 912 FP32
+// values take 58 us (multi-launch 102), so the line is where the registers end:
+// 128 of them for values spill (1e7 values 110 us).
+template <typename TIn>
+struct SpxTeamLadder {
+  static constexpr int E0 = 32 / (int)sizeof(TIn), E1 = 4 * E0, E2 = 8 * E0, E3 = 12 * E0;
+};
+
 int grid0(int64_t n, int num_cus) {
   const int64_t want = (n + 2047) / 2048;
   return (int)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)num_cus * 8));
@@ -1863,8 +2344,107 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
     stt = ensure_events(ctx, nev);
     if (stt != CQK_OK) return stt;
   }
-  // the Algorithm 2 sample kernel stores the initial state itself
+  // One launch where y fits the registers, from the default and warm starts.
+  // Traced and timed calls report single passes and keep the multi-launch
+  // route, as does the FP32-accumulation variant.
+  typedef SpxTeamLadder<TIn> Ladder;
+  int tE = 0, tT = 0;
+  for (int E : {Ladder::E0, Ladder::E1, Ladder::E2, Ladder::E3}) {
+    const int64_t T = (n + (int64_t)kTeamBlock * E - 1) / ((int64_t)kTeamBlock * E);
+    if (tE == 0 && T <= (E == Ladder::E0 ? 1 : std::min(ctx->num_cus, kTeamMax))) {
+      tE = E;
+      tT = (int)T;
+    }
+  }
+  const uint32_t need = (uint32_t)std::min(o.max_iter, 1 << 20) + 8;
+  const bool team = tE != 0 && condat && r != 0.0 && sizeof(TA) == 8 && !o.trace && !o.timing &&
+                    o.max_iter <= (1 << 20) && team_ready(ctx, need);
+  SpxTeamCtl* const ctl = team ? (SpxTeamCtl*)((char*)ctx->team.ptr + kTeamSlotBytes) : nullptr;
+  auto launch_team = [&](SpxTeamResult* res, SpxTeamCtl* tc) {
+    SpxTeamArgs T{};
+    T.y = y;
+    T.xw = xw;
+    T.x = A.x;
+    T.sp_idx = A.sp_idx;
+    T.sp_val = A.sp_val;
+    T.n = n;
+    T.sp_cap = A.sp_cap;
+    T.r = r;
+    T.tol = init.tol;
+    T.l1 = init.l1;
+    T.max_iter = o.max_iter;
+    T.slots = (uint64_t*)ctx->team.ptr;
+    T.limit = ctx->team_wait;
+    T.tag = ctx->team_tag;
+    T.res = res;
+    T.ctl = tc;
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(tT), dim3(kTeamBlock), 0, s, T);
+    };
+    if (tE == Ladder::E0) go(spx_team_kernel<TIn, Ladder::E0>);
+    else if (tE == Ladder::E1) go(spx_team_kernel<TIn, Ladder::E1>);
+    else if (tE == Ladder::E2) go(spx_team_kernel<TIn, Ladder::E2>);
+    else go(spx_team_kernel<TIn, Ladder::E3>);
+  };
+  // what the x-writing kernels sum up, from the blocks' shares
+  auto team_sums = [r](const SpxTeamResult& R, int T, cqk_info* inf) {
+    double p = 0.0, nf = 0.0;
+    for (int g = 0; g < T; ++g) {
+      p += R.part[2 * g];
+      nf += R.part[2 * g + 1];
+    }
+    inf->residual = std::fabs(p - (R.copy ? R.sum_abs : r));
+    inf->abs_bx = p;
+    inf->n_free = (int64_t)nf;
+  };
+  if (team && !deferred) {
+    SpxTeamResult* res = (SpxTeamResult*)ctx->host_pinned;
+    res->gave_up = 0;
+    launch_team(res, nullptr);
+    if (hip_ok(hipGetLastError()) != CQK_OK) return CQK_DEVICE_ERROR;
+    ctx->team_tag += need;
+    if (hip_ok(hipStreamSynchronize(s)) != CQK_OK) return CQK_DEVICE_ERROR;
+    const SpxTeamResult& R = *res;
+    if (!R.gave_up) {
+      ctx->team_tag = R.tag;
+      ctx->last_trace.clear();
+      ctx->last_pass_ms.clear();
+      cqk_info out;
+      std::memset(&out, 0, sizeof(out));
+      out.status = R.status;
+      out.iterations = R.iter;
+      out.passes = R.passes;
+      out.stop_reason = R.stop_reason;
+      out.lambda = R.lam_final;
+      out.lambda0 = R.lam0;
+      team_sums(R, tT, &out);
+      out.n_after_init = (int64_t)R.n_init;
+      out.finalize_bytes = (double)n * sizeof(TIn) * (sparse ? 1.0 : 2.0);
+      out.pass_launches = 1;
+      if (sparse) {
+        ctx->bitmap_clean = true;  // not touched
+        sp->nnz = (out.status == CQK_OK || out.status == CQK_NOT_CONVERGED) ? R.nnz : 0;
+        if (sp->nnz > sp->cap) out.status = CQK_BUFFER_TOO_SMALL;
+      }
+      ctx->trivial = out;
+      ctx->last = [ctx](cqk_info* inf) -> cqk_status {
+        *inf = ctx->trivial;
+        return CQK_OK;
+      };
+      if (info) *info = out;
+      return CQK_OK;
+    }
+  }
+  // the Algorithm 2 sample kernel stores the initial state itself, unless a
+  // one-launch projection queued before it may have left its own
   const bool init_in_sample = condat && r != 0.0;
+  const bool team_queued = team && deferred;
+  if (team_queued) {
+    hipLaunchKernelGGL(team_init_kernel<SpxState>, dim3(1), dim3(256), 0, s, A.st, init,
+                       &ctl->tags, &ctl->res.gave_up, (uint64_t*)ctx->team.ptr, need);
+    launch_team(&ctl->res, ctl);
+    hipLaunchKernelGGL(spx_team_commit_kernel, dim3(1), dim3(1), 0, s, A.st, ctl);
+  }
   if (!init_in_sample) hipLaunchKernelGGL(spx_init_kernel, dim3(1), dim3(1), 0, s, A.st, init);
   int ev = 4;
   int npass = 0;  // grid passes queued
@@ -1927,7 +2507,7 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
         const bool rec = timing && ev + 2 <= (int)nev;
         launch_timed(spx_condat_sample_kernel<TIn, TA>, dim3(GSm), dim3(kBlock), s,
                      rec ? ctx->events[ev] : nullptr, rec ? ctx->events[ev + 1] : nullptr, A,
-                     init);
+                     init, team_queued ? 1 : 0);
         if (rec) ev += 2;
         ++npass;
       }
@@ -2056,10 +2636,17 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
       info->status = CQK_BUFFER_TOO_SMALL;
     return CQK_OK;
   };
-  ctx->last = [hs, A, report](cqk_info* inf) -> cqk_status {
+  ctx->last = [hs, A, report, ctl, team_sums, tT](cqk_info* inf) -> cqk_status {
     if (hip_ok(hipMemcpy(hs, A.st, sizeof(SpxState), hipMemcpyDeviceToHost)) != CQK_OK)
       return CQK_DEVICE_ERROR;
-    return report(inf);
+    const bool done = hs->team_done != 0;
+    const cqk_status st = report(inf);
+    if (st != CQK_OK || !done) return st;
+    SpxTeamResult* R = (SpxTeamResult*)hs;  // the state copy has been read
+    if (hip_ok(hipMemcpy(R, &ctl->res, sizeof(SpxTeamResult), hipMemcpyDeviceToHost)) != CQK_OK)
+      return CQK_DEVICE_ERROR;
+    team_sums(*R, tT, inf);
+    return CQK_OK;
   };
   if (deferred) {
     if (info) {

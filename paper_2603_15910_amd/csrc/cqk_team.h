@@ -14,7 +14,7 @@
 // exchange waits for every record of the one before.
 //
 // The blocks of a team have to run at the same time.  The grid never exceeds
-// one block per compute unit, but another stream's kernels may hold compute
+// what the GPU holds at once, but another stream's kernels may hold compute
 // units back, so every wait is bounded: a block that has waited `limit` ticks
 // of the 100 MHz clock gives up, says so in the launch's result and ends;
 // the others then run out of their own limit.  The host takes the
@@ -26,7 +26,7 @@
 namespace cqk {
 
 constexpr int kTeamBlock = 512;
-constexpr int kTeamMax = 256;     // blocks of a team
+constexpr int kTeamMax = 512;     // blocks of a team: up to two per compute unit
 constexpr int kSlotWords = 16;    // 8-byte words of one record slot (up to 8 doubles)
 constexpr size_t kTeamCtlBytes = 16384;  // behind the slots: a solver's control block
 constexpr size_t kTeamSlotBytes = (size_t)2 * kTeamMax * kSlotWords * sizeof(uint64_t);
@@ -37,7 +37,8 @@ constexpr size_t kTeamSlotBytes = (size_t)2 * kTeamMax * kSlotWords * sizeof(uin
 // larger team may still be reading when another part moves on: every team
 // size has slots of its own.
 constexpr int kBatTeamBlocks = 1024;      // blocks of such a launch
-constexpr int kBatTeamLogs = 9;           // team sizes 1, 2, ... 256
+constexpr int kBatTeamLogs = 9;           // team sizes 1, 2, ... kBatTeamMax
+constexpr int kBatTeamMax = 1 << (kBatTeamLogs - 1);
 constexpr size_t kBatTeamBytes =
     (size_t)kBatTeamLogs * 2 * kBatTeamBlocks * kSlotWords * sizeof(uint64_t);
 // The context's team buffer: slots and control block of the single solves,
@@ -84,8 +85,8 @@ __device__ __forceinline__ void team_post(const Team& team, uint64_t* slots, uin
 // four) below T: lane l takes word l % 16 of record l / 16 of a group, so one
 // load instruction covers four whole records, R of them in flight.  Each
 // record's value v is then in lanes 2v and 2v + 1 of its row of 16; the lane
-// adds it up, or (MIN) takes the (key, weight) minimum with the value two
-// lanes on as the weight.  (A lane per record instead, ten loads each of its
+// adds it up (lane_min: takes the minimum), or (MIN) takes the (key, weight)
+// minimum with the value two lanes on as the weight.  (A lane per record instead, ten loads each of its
 // own line, took the exchange of 256 blocks from 3 to 7 us.)
 struct TeamRead {
   double sum;
@@ -95,9 +96,10 @@ struct TeamRead {
 
 template <int NV, bool MIN>
 __device__ __forceinline__ TeamRead team_read(const Team& team, const uint64_t* slots,
-                                              uint32_t tag, int from, int step, int lane) {
+                                              uint32_t tag, int from, int step, int lane,
+                                              bool lane_min = false) {
   constexpr int R = 4;
-  TeamRead out{0.0, KeySum{inf_d(), 0.0}, false};
+  TeamRead out{lane_min ? inf_d() : 0.0, KeySum{inf_d(), 0.0}, false};
   const bool mine = (lane & 15) < 2 * NV;
   const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
   for (int g0 = from * 4; g0 < team.T && !out.late; g0 += R * step * 4) {
@@ -130,7 +132,7 @@ __device__ __forceinline__ TeamRead team_read(const Team& team, const uint64_t* 
         const double weight = dpp_move<dpp::kXor2, 0xF>(v, 0.0);
         out.min = ks_min(out.min, in ? KeySum{v, weight} : KeySum{inf_d(), 0.0});
       } else {
-        out.sum += in ? v : 0.0;
+        out.sum = lane_min ? fmin(out.sum, in ? v : inf_d()) : out.sum + (in ? v : 0.0);
       }
     }
   }
@@ -142,12 +144,13 @@ __device__ __forceinline__ TeamRead team_read(const Team& team, const uint64_t* 
 // among the waves in larger teams.
 constexpr int kTeamAllRead = 16;
 
-// Sums of NV values over the threads of a team's blocks; tot[] holds the
+// Sums of NV values over the threads of a team's blocks, the last NM of them
+// minima instead; tot[] holds the
 // totals as scalars in every wave, the same bits in every block.  par: a
 // counter of the block's reductions (parity of the LDS buffers).  Returns
 // false, in the whole block, when a wait ran into its limit.  One barrier,
 // two with more than one block.
-template <int NV, int BLOCK>
+template <int NV, int BLOCK, int NM = 0>
 __device__ __forceinline__ bool team_reduce(Team& team, TeamLds<BLOCK>& S, int& par,
                                             const double* v, double* tot) {
   constexpr int NW = BLOCK / kWave;
@@ -161,19 +164,28 @@ __device__ __forceinline__ bool team_reduce(Team& team, TeamLds<BLOCK>& S, int& 
   // reductions the addresses would be spilled
   asm volatile("" : "+v"(tid));
   const int lane = tid & (kWave - 1), wid = scalar(tid / kWave);
+  constexpr int NS = NV - NM;
   double x[N];
 #pragma unroll
-  for (int i = 0; i < N; ++i) x[i] = (i < NV) ? v[i] : 0.0;
+  for (int i = 0; i < N; ++i) x[i] = (i < NS) ? v[i] : 0.0;
   wave_sum_many<N>(x);
   par ^= 1;
   double* red = S.red[par];
   const int idx = lane >> SH;
-  if ((lane & ((1 << SH) - 1)) == 0 && idx < NV) red[idx * NW + wid] = x[0];
+  if ((lane & ((1 << SH) - 1)) == 0 && idx < NS) red[idx * NW + wid] = x[0];
+#pragma unroll
+  for (int i = NS; i < NV; ++i) {
+    const double m = wave_min(v[i]);
+    if (lane == 0) red[i * NW + wid] = m;
+  }
   __syncthreads();
+  // op: the sum, or the minimum in the lanes that hold one of the last NM
+  auto op = [](double a, double b, bool min) { return (NM > 0 && min) ? fmin(a, b) : a + b; };
   double y = (lane < NV * NW) ? red[lane] : 0.0;
-  y += dpp_move<dpp::kXor1, 0xF>(y, 0.0);
-  y += dpp_move<dpp::kXor2, 0xF>(y, 0.0);
-  if constexpr (NW == 8) y += dpp_move<dpp::kHalfMirror, 0xF>(y, 0.0);
+  const bool ym = lane >= NS * NW;
+  y = op(y, dpp_move<dpp::kXor1, 0xF>(y, 0.0), ym);
+  y = op(y, dpp_move<dpp::kXor2, 0xF>(y, 0.0), ym);
+  if constexpr (NW == 8) y = op(y, dpp_move<dpp::kHalfMirror, 0xF>(y, 0.0), ym);
   if (team.T == 1) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) tot[i] = lane_value(y, i * NW);
@@ -183,13 +195,14 @@ __device__ __forceinline__ bool team_reduce(Team& team, TeamLds<BLOCK>& S, int& 
   uint64_t* slots = team.slots + (size_t)(tag & 1u) * team.parity;
   if (wid == 0) team_post<NV, NW>(team, slots, tag, y, lane);
   const bool split = team.T > kTeamAllRead;
+  const bool zm = NM > 0 && (lane & 15) >= 2 * NS;
   const TeamRead got =
-      team_read<NV, false>(team, slots, tag, split ? wid : 0, split ? NW : 1, lane);
+      team_read<NV, false>(team, slots, tag, split ? wid : 0, split ? NW : 1, lane, zm);
   if (got.late) S.gave_up = 1;
   double z = got.sum;
   // the four rows of 16 lanes
-  detail::halve<5, 1>(&z, lane);
-  detail::halve<4, 1>(&z, lane);
+  z = op(z, __shfl_xor(z, 32, kWave), zm);
+  z = op(z, __shfl_xor(z, 16, kWave), zm);
   if (split && lane < 16 && (lane & 1) == 0) S.part[par][8 * wid + lane / 2] = z;
   __syncthreads();
   if (S.gave_up) return false;
@@ -199,10 +212,11 @@ __device__ __forceinline__ bool team_reduce(Team& team, TeamLds<BLOCK>& S, int& 
     return true;
   }
   // value i of wave w at w * 8 + i: the waves' parts in lanes 8 apart
-  double p = (lane < 8 * NW) ? S.part[par][lane] : 0.0;
-  p += dpp_move<dpp::kRor8, 0xF>(p, 0.0);
-  detail::halve<5, 1>(&p, lane);
-  detail::halve<4, 1>(&p, lane);
+  const bool pm = NM > 0 && (lane & 7) >= NS;
+  double p = (lane < 8 * NW) ? S.part[par][lane] : (pm ? inf_d() : 0.0);
+  p = op(p, dpp_move<dpp::kRor8, 0xF>(p, 0.0), pm);
+  p = op(p, __shfl_xor(p, 32, kWave), pm);
+  p = op(p, __shfl_xor(p, 16, kWave), pm);
 #pragma unroll
   for (int i = 0; i < NV; ++i) tot[i] = lane_value(p, i);
   return true;
@@ -262,6 +276,84 @@ __device__ __forceinline__ bool team_reduce_ks(Team& team, TeamLds<BLOCK>& S, in
       ks[i] = ks_min(ks[i], KeySum{S.part[par][8 * k + 2 * i], S.part[par][8 * k + 2 * i + 1]});
   }
   return true;
+}
+
+// The sum of one value per block over the team, and over the blocks before
+// this one, in every thread.  false as team_reduce.
+template <int BLOCK>
+__device__ __forceinline__ bool team_prefix(Team& team, TeamLds<BLOCK>& S, int& par, double mine,
+                                            double* total, double* before) {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & (kWave - 1), wid = scalar(tid / kWave);
+  const uint32_t tag = ++team.tag;
+  uint64_t* slots = team.slots + (size_t)(tag & 1u) * team.parity;
+  par ^= 1;
+  if (wid == 0) {
+    team_post<1, 2>(team, slots, tag, mine, lane);
+    double all = 0.0, low = 0.0;
+    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+    bool late = false;
+    for (int g = lane; g < team.T; g += kWave) {
+      uint64_t w0, w1;
+      bool ok = false;
+      while (!ok && !late) {
+        w0 = __hip_atomic_load(&slots[(size_t)g * kSlotWords], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        w1 = __hip_atomic_load(&slots[(size_t)g * kSlotWords + 1], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        ok = (uint32_t)w0 == tag && (uint32_t)w1 == tag;
+        late = !ok && __builtin_amdgcn_s_memrealtime() - t0 > team.limit;
+      }
+      if (ok) {
+        const double v =
+            __builtin_bit_cast(double, (w0 >> 32) | (w1 & 0xffffffff00000000ull));
+        all += v;
+        low += (g < team.me) ? v : 0.0;
+      }
+    }
+    if (late) S.gave_up = 1;
+    all = wave_sum(all);
+    low = wave_sum(low);
+    if (lane == 0) {
+      S.part[par][0] = all;
+      S.part[par][1] = low;
+    }
+  }
+  __syncthreads();
+  if (S.gave_up) return false;
+  *total = scalar(S.part[par][0]);
+  *before = scalar(S.part[par][1]);
+  return true;
+}
+
+// Tags of queued and captured launches, in device memory (a replay must not
+// repeat its tags): those of the current launch, and the first never used.
+// They have the top bit set, those of waiting calls clear.
+struct TeamTags {
+  uint32_t base, next;
+};
+constexpr uint32_t kTeamDeviceTags = 0x80000000u;
+
+// Before a queued or captured one-launch call: the run state of the kernels
+// queued behind it, a fresh range of tags (the slots are cleared when the
+// range starts over) and a clear result.
+template <typename State>
+__global__ __launch_bounds__(256) void team_init_kernel(State* st, State init, TeamTags* tags,
+                                                        int32_t* gave_up, uint64_t* slots,
+                                                        uint32_t need) {
+  const uint32_t next = tags->next;
+  const bool wrap = next == 0 || next > 0xffffffffu - need;
+  __syncthreads();
+  if (wrap)
+    for (size_t i = threadIdx.x; i < kTeamSlotBytes / sizeof(uint64_t); i += 256) slots[i] = 0;
+  if (threadIdx.x == 0) {
+    *st = init;
+    const uint32_t base = wrap ? kTeamDeviceTags : next;
+    tags->base = base;
+    tags->next = base + need;
+    *gave_up = 0;
+  }
 }
 
 }  // namespace cqk
