@@ -16,8 +16,8 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 F64, F32 = torch.float64, torch.float32
-# one block: 4096 FP32 / 2048 FP64 values; then blocks of 16384 / 8192, 256 of
-# them 4194304 / 2097152, and 2 and 3 times that
+# blocks of 4096 FP32 / 2048 FP64 values, up to 256 of them; then blocks of
+# 16384 / 8192, 256 of them 4194304 / 2097152, and 2 and 3 times that
 SIZES = {F32: [1, 2, 3, 5, 255, 4095, 4096, 4097, 16385, 4_194_303, 4_194_305, 8_388_609,
                12_582_911, 12_582_913],
          F64: [1, 2, 3, 5, 255, 2047, 2048, 2049, 8193, 2_097_151, 2_097_153, 4_194_305,
@@ -79,6 +79,19 @@ def test_sizes(ctx, dtype, which, l1):
     last = SIZES[dtype][-1]
     assert (info["pass_launches"] == 1) == (n < last)
     _check(x.cpu().numpy(), y, 1.0, l1, dtype)
+
+
+@pytest.mark.parametrize("past", [0, 1])
+@pytest.mark.parametrize("dtype", [F32, F64])
+def test_end_of_the_first_step(ctx, dtype, past):
+    """256 blocks of 4096 FP32 / 2048 FP64 values, and the next step."""
+    n = (1_048_576 if dtype == F32 else 524_288) + past
+    y = W.simplex_input(n, 21, "normal", _np(dtype))
+    t = torch.from_numpy(y).cuda()
+    for l1 in (False, True):
+        x, info = _both(ctx, t, 1.0, l1, dtype)
+        assert info["pass_launches"] == 1
+        _check(x.cpu().numpy(), y, 1.0, l1, dtype)
 
 
 @pytest.mark.parametrize("l1", [False, True])
