@@ -95,12 +95,16 @@ typedef enum cqk_compaction {
                                as soon as it would keep more than
                                compact_theta of the indices read; the next
                                pass reads the set of the side that happened.
-                               For n >= 2^22 a bracket estimated from two
-                               samples (4096 and 1048576 indices: the
-                               solution of the sampled equation +- 5
-                               estimated standard deviations, widened to
-                               the first iterate the sample predicts, or
-                               to the second when the first lies far out)
+                               For n >= 2^22 (2^21 where the remaining
+                               iterations run in one launch, from a known
+                               lam_0) a bracket estimated from two samples
+                               (4096 and 1048576 indices: the solution of
+                               the sampled equation +- 5 estimated standard
+                               deviations, widened to the first iterate the
+                               sample predicts, or to the second when the
+                               first lies far out; that first iterate, or
+                               the one after a later pass over all indices,
+                               then gets a second bracket of its own)
                                lets
                                the first pass, or the lam_0 pass of a warm
                                or formula start, compact too; a set is read

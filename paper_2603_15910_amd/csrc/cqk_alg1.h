@@ -129,19 +129,87 @@ __device__ __forceinline__ int eval_index(Acc& acc, double c, double s, double b
   return keep;
 }
 
-// One index of the first evaluation pass classified on a bracket [p, q]
-// estimated from a sample (not yet known to hold lam*): dropped into side 0's
-// sums when its bound is active on all of [p, q] or it is free on all of it
-// with g keeping one sign; returns 1 when kept.  The sums are exact for every
-// lam strictly inside (p, q), wherever lam* is.
-__device__ __forceinline__ int spec_index(Acc& acc, double c, double s, double bl, double bu,
-                                          double p, double q) {
+// How a bracket [p, q] resolves an index: its bound active on all of it, or
+// free on all of it with g keeping one sign.
+struct Resolved {
+  bool at_l, at_u, fr, pos;
+};
+__device__ __forceinline__ Resolved resolve(double c, double s, double bl, double bu, double p,
+                                            double q) {
   const double fp = fma(s, p, c);
   const double fq = fma(s, q, c);
-  const bool at_l = fq <= bl, at_u = fp >= bu;
-  const bool fr = !at_l && !at_u && (fp >= bl) && (fq <= bu) && (fp >= 0.0 || fq <= 0.0);
-  side_sums(acc, P_SIDE, at_l, at_u, fr, bl, bu, c, s, fp >= 0.0);
-  return (at_l || at_u || fr) ? 0 : 1;
+  Resolved R;
+  R.at_l = fq <= bl;
+  R.at_u = fp >= bu;
+  R.fr = !R.at_l && !R.at_u && (fp >= bl) && (fq <= bu) && (fp >= 0.0 || fq <= 0.0);
+  R.pos = fp >= 0.0;
+  return R;
+}
+
+// One index of an evaluation pass over the caller's arrays classified on a
+// bracket [p, q] estimated from a sample (not yet known to hold lam*) and, if
+// p2 < q2, on a second one around a predicted iterate: dropped when each
+// resolves it, into side 0's sums for the first bracket and side 1's for the
+// second; returns 1 when kept.  The sums are exact for every lam strictly
+// inside their bracket, wherever lam* is.
+__device__ __forceinline__ int spec_index(Acc& acc, double c, double s, double bl, double bu,
+                                          double p, double q, double p2, double q2) {
+  const Resolved R = resolve(c, s, bl, bu, p, q);
+  bool drop = R.at_l || R.at_u || R.fr;
+  if (p2 < q2) {
+    const Resolved T = resolve(c, s, bl, bu, p2, q2);
+    drop = drop && (T.at_l || T.at_u || T.fr);
+    side_sums(acc, P_SIDE + D_N, drop && T.at_l, drop && T.at_u, drop && T.fr, bl, bu, c, s,
+              T.pos);
+  }
+  side_sums(acc, P_SIDE, drop && R.at_l, drop && R.at_u, drop && R.fr, bl, bu, c, s, R.pos);
+  return drop ? 0 : 1;
+}
+
+// A pass at a lam_0 where the sample says that phi is flat, every index at
+// the bound on lam_0's side.  Algorithm 1 then takes breakpoint steps and can
+// jump past the last breakpoint, where phi is flat again: the pass also finds
+// what those steps need, so none of them reads the arrays.  For a solution to
+// the right: the closest breakpoint of the breakpoint search at lam_0 (near,
+// as ks[0] of bkpt_index), the last breakpoint of all with the slope that
+// opens there on its left (far: key -max ubar), and the sums of the upper
+// bounds.  To the left the same on the mirrored problem (lam, c, l, u all
+// negated, l and u exchanged; exact).  The divisions are made only for
+// indices that can change the wave's extremes (`slack` covers the rounding of
+// the test).
+struct FlatAcc {
+  KeySum near, far;
+  double nk, fk;   // the wave's smallest near key, largest far breakpoint
+  double b, ab;
+};
+
+__device__ __forceinline__ void flat_init(FlatAcc& F) {
+  F.near = F.far = KeySum{inf_d(), 0.0};
+  // finite: started from infinities, hipcc 7.2 (-O3) began the search at zero
+  F.nk = 1.7976931348623157e308;
+  F.fk = -1.7976931348623157e308;
+  F.b = F.ab = 0.0;
+}
+
+__device__ __forceinline__ void flat_index(FlatAcc& F, bool in, double c, double s, double bl,
+                                           double bu, double lam, bool left) {
+  const double cm = left ? -c : c, lm = left ? -bu : bl, um = left ? -bl : bu;
+  const double lamm = left ? -lam : lam;
+  F.b += in ? um : 0.0;
+  F.ab += in ? fabs(um) : 0.0;
+  const bool moves = in && lm < um;
+  const double dn = lm - cm, df = um - cm;
+  const double slack = 1e-12 * (fabs(lm) + fabs(um) + fabs(cm));
+  const bool near = moves && fma(s, lamm, cm) < lm && !(dn - slack > F.nk * s);
+  const bool far = moves && !(df + slack < F.fk * s);
+  if (__ballot(near) != 0) {
+    if (near) F.near = ks_min(F.near, KeySum{fmax(dn / s, lamm), s});
+    F.nk = wave_min(F.near.k);
+  }
+  if (__ballot(far) != 0) {
+    if (far) F.far = ks_min(F.far, KeySum{-(df / s), s});
+    F.fk = -wave_min(F.far.k);
+  }
 }
 
 // Closest breakpoints around lam (Algorithm 1, breakpoint steps), with the
@@ -205,25 +273,28 @@ __device__ __forceinline__ void check_source_eval(GenState* st, double next) {
 // Source of an evaluation at `next` once the sampled-bracket set exists: it
 // replaces the caller's arrays, or a larger set just adopted, when next lies
 // strictly inside its bracket.  It waits only while the passes read the
-// caller's arrays (passes over a compacted set may overwrite it).  Returns
-// whether it was taken.
+// caller's arrays (passes over a compacted set may overwrite it), or read the
+// set itself with the sums of its second bracket (they write no sides then,
+// plan_sides).  Returns whether it was taken.
 __device__ __forceinline__ bool take_spec_set(GenState* st, double next) {
   if (!st->spend) return false;
+  const bool free = st->src == 0 || st->src == kSpecSet;
   const bool inside = next > st->sp && next < st->sq;
-  const bool take = inside && (st->src == 0 || st->sn < st->n_src);
+  const bool second = !inside && next > st->p2 && next < st->q2;
+  const bool take = (inside && (free || st->sn < st->n_src)) || (second && st->src == 0);
   if (take) {
-    st->F = st->sF;
-    st->AF = st->sAF;
-    st->C0 = st->sC0;
-    st->C1 = st->sC1;
-    st->A0 = st->sA0;
-    st->A1 = st->sA1;
+    st->F = inside ? st->sF : st->s2F;
+    st->AF = inside ? st->sAF : st->s2AF;
+    st->C0 = inside ? st->sC0 : st->s2C0;
+    st->C1 = inside ? st->sC1 : st->s2C1;
+    st->A0 = inside ? st->sA0 : st->s2A0;
+    st->A1 = inside ? st->sA1 : st->s2A1;
     st->src = kSpecSet;
     st->n_src = st->sn;
-    st->vlo = st->sp;
-    st->vhi = st->sq;
+    st->vlo = inside ? st->sp : st->p2;
+    st->vhi = inside ? st->sq : st->q2;
   }
-  if (take || st->src != 0) st->spend = 0;
+  if ((take && inside) || !free) st->spend = 0;
   return take;
 }
 __device__ __forceinline__ void check_source_bkpt(GenState* st) {
@@ -249,6 +320,8 @@ __device__ __forceinline__ void plan_sides(GenState* st) {
     skip |= ((chi - lam) > cap) ? 1 : 0;
     skip |= ((lam - clo) > cap) ? 2 : 0;
   }
+  // read with its second bracket's sums, the sampled-bracket set goes on waiting
+  if (st->src == kSpecSet && st->spend) skip = 3;
   st->skip = skip;
 }
 
@@ -290,6 +363,13 @@ __device__ __forceinline__ void update_after_eval(GenState* st, const double* t,
     st->sA0 = t[P_SIDE + D_A0];
     st->sA1 = t[P_SIDE + D_A1];
     st->sn = (int64_t)t[P_SIDE + D_NOUT];
+    constexpr int o2 = P_SIDE + D_N;
+    st->s2F = t[o2 + D_F];
+    st->s2AF = t[o2 + D_AF];
+    st->s2C0 = t[o2 + D_C0];
+    st->s2C1 = t[o2 + D_C1];
+    st->s2A0 = t[o2 + D_A0];
+    st->s2A1 = t[o2 + D_A1];
     st->spend = 1;
   }
   double phi = t[P_P], A = t[P_A], Qp = t[P_QP], Qm = t[P_QM];
@@ -360,7 +440,7 @@ __device__ __forceinline__ void update_after_eval(GenState* st, const double* t,
     // sampled-bracket set is not used for it)
     st->mode = (res < 0.0) ? kModeBreakRight : kModeBreakLeft;
     if constexpr (SETS) {
-      if (st->src != 0) st->spend = 0;
+      if (st->src != 0 && st->src != kSpecSet) st->spend = 0;
       check_source_bkpt(st);
     }
     return;
@@ -428,7 +508,7 @@ __device__ __forceinline__ void update_after_bkpt(GenState* st, const KeySum* ks
   if (hi - lo < tol * fmax(fabs(hi), fabs(lo))) return finish(st, bp, 3);
   if (!(sw > 0.0)) {  // still flat past bp: search again from bp
     if constexpr (SETS) {
-      if (st->src != 0) st->spend = 0;
+      if (st->src != 0 && st->src != kSpecSet) st->spend = 0;
       check_source_bkpt(st);
     }
     return;
@@ -453,6 +533,43 @@ __device__ __forceinline__ void update_after_bkpt(GenState* st, const KeySum* ks
     st->ntrace += 1;
   }
   advance<SETS>(st, next);
+}
+
+// After a flat pass's update (flat_index): Algorithm 1's steps as long as
+// they need only the closest breakpoint, the last one (far = its position,
+// on the mirrored line for `left`) or phi beyond it.  The margin keeps the
+// predicates of an evaluation there clear of rounding.
+__device__ __forceinline__ void flat_steps(GenState* st, KeySum near, KeySum far, double b,
+                                           double ab, bool left, cqk_trace_rec* tr) {
+  const double lam0 = st->lam, bytes = st->bytes;
+  const double end = -far.k;
+  const int toward = left ? kModeBreakLeft : kModeBreakRight;
+  const int back = left ? kModeBreakRight : kModeBreakLeft;
+  bool searched = false;
+  for (int k = 0; k < 6 && st->status == kRunning && st->src == 0; ++k) {
+    const double lm = left ? -st->lam : st->lam;
+    const bool beyond = lm - end > 1e-6 * (fabs(lm) + fabs(end));
+    KeySum ks[2] = {KeySum{inf_d(), 0.0}, KeySum{inf_d(), 0.0}};
+    if (st->mode == toward && !searched && st->lam == lam0) {
+      ks[left ? 1 : 0] = near;
+      searched = true;
+      update_after_bkpt(st, ks, tr);
+    } else if (st->mode == back && beyond) {
+      ks[left ? 0 : 1] = far;
+      update_after_bkpt(st, ks, tr);
+    } else if (st->mode == kModeEval && beyond) {
+      double t[NSUM];
+      for (int i = 0; i < NSUM; ++i) t[i] = 0.0;
+      t[P_P] = left ? -b : b;
+      t[P_A] = ab;
+      t[P_NIN] = (double)st->n_all;
+      t[P_SIDE + D_DROP] = t[P_SIDE + D_N + D_DROP] = 1.0;
+      update_after_eval(st, t, tr);
+    } else {
+      break;
+    }
+  }
+  st->bytes = bytes;  // nothing was read for these
 }
 
 // The state a register copy needs between updates, the same in every lane of

@@ -21,7 +21,10 @@
 //   gen_finalize_kernel x(lam*) over all n indices (eq. (xopt)), b^T x;
 //   gen_sample_kernel, gen_sample2_kernel, gen_sample3_kernel (+ reduces),
 //   gen_spec_pass_kernel,
-//   gen_warm_spec_kernel: the sampled bracket (below).
+//   gen_warm_spec_kernel: the sampled bracket (below);
+//   gen_team_kernel     the whole solve in one launch, for small inputs;
+//   gen_rest_kernel     every iteration left once the passes read a compacted
+//                       set, in one launch.
 // The host queues passes in batches and reads the state once per batch;
 // a pass queued after the loop has stopped returns at once.
 //
@@ -55,7 +58,17 @@
 // carries the bracket its dropped sums hold on (GenState vlo, vhi) and is
 // read only at a multiplier strictly inside it, so Algorithm 1's iterates do
 // not depend on the estimate; the sampled set waits in set 3 until an
-// iterate falls inside (take_spec_set).
+// iterate falls inside (take_spec_set).  Where the sample puts Algorithm 1's
+// first iterate far from lam*, the set also holds the indices with a
+// breakpoint in a second bracket around that iterate, with dropped sums of
+// its own, and the pass there reads the set too; a later pass over the
+// caller's arrays writes the set anew for the iterate after it.  Where the
+// sample shows phi flat at lam_0, the first pass also finds the closest and
+// the last breakpoint and sums the bounds, and the breakpoint steps that
+// follow (and the evaluation past the last breakpoint) need no pass
+// (flat_index).  FP32, 3e7 indices: correlated data, whose first step
+// overshoots, 604 -> 417 us; the paper's weakly correlated class, flat at
+// lam_0 = 0, 1180 -> 700 us.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -110,6 +123,7 @@ struct GenArgs {
   int32_t* cnt[3];  // survivors of each wave in each set
   double* partials;
   float* smp;       // the sample, 4 floats per index (compaction only)
+  double* flat;     // a flat first pass's block records (the sample's memory, no longer needed then)
   GenState* st;
   cqk_trace_rec* trace;
 };
@@ -364,10 +378,12 @@ enum PassMode {
 // The LDS operations of one wave complete in issue order, so a lane reads
 // what another lane staged without a wait; the wave-scope fences only keep
 // the compiler from reordering those accesses.
-template <typename Src, int MODE>
-__device__ void eval_pass(const Src& src, int64_t count, int64_t first, int64_t stride, double lam,
+template <typename Src, int MODE, bool FLAT = false>
+__device__ __forceinline__ void eval_pass(const Src& src, int64_t count, int64_t first, int64_t stride, double lam,
                           double lo, double hi, double theta, double* const* out, Pieces op,
-                          int32_t* const* out_cnt, Acc& acc, double* stg, int skip = 0) {
+                          int32_t* const* out_cnt, Acc& acc, double* stg, int skip = 0,
+                          double lo2 = 0.0, double hi2 = 0.0, FlatAcc* flat = nullptr,
+                          bool left = false) {
   constexpr bool COMPACT = MODE != kEvalOnly;
   constexpr int NSIDE = (MODE == kSampled) ? 1 : 2;
   constexpr int STG = (MODE == kSampled) ? kStageSpec : kStage;  // ring length
@@ -428,8 +444,9 @@ __device__ void eval_pass(const Src& src, int64_t count, int64_t first, int64_t 
         if (MODE == kSampled) {
           if (in) {
             eval_index<false>(acc, c[e], s[e], bl[e], bu[e], lam, lo, hi);
-            keep = spec_index(acc, c[e], s[e], bl[e], bu[e], lo, hi);
+            keep = spec_index(acc, c[e], s[e], bl[e], bu[e], lo, hi, lo2, hi2);
           }
+          if constexpr (FLAT) flat_index(*flat, in, c[e], s[e], bl[e], bu[e], lam, left);
         } else {
           keep = in ? eval_index<COMPACT>(acc, c[e], s[e], bl[e], bu[e], lam, lo, hi) : 0;
         }
@@ -495,7 +512,7 @@ __device__ void eval_pass(const Src& src, int64_t count, int64_t first, int64_t 
 }
 
 template <typename Src>
-__device__ void bkpt_pass(const Src& src, int64_t count, int64_t first, int64_t stride, double lam,
+__device__ __forceinline__ void bkpt_pass(const Src& src, int64_t count, int64_t first, int64_t stride, double lam,
                           KeySum* ks) {
   constexpr int V = Src::V;
   constexpr int U = kTileE / V;  // 16-byte vectors per lane and array
@@ -535,7 +552,7 @@ __device__ void bkpt_pass(const Src& src, int64_t count, int64_t first, int64_t 
 template <typename TIn>
 __global__ __launch_bounds__(kBlock) void gen_pass_kernel(GenArgs A) {
   GenState* st = A.st;
-  if (st->status != kRunning) return;
+  if (st->status != kRunning || st->spec != 0) return;  // spec: gen_spec_pass_kernel's pass
   const int mode = st->mode;
   const int src = st->src;
   const bool compact = (mode == kModeEval) && (st->compaction != CQK_COMPACT_OFF);
@@ -690,14 +707,17 @@ __global__ __launch_bounds__(kBlock) void gen_first_pass_kernel(GenArgs A) {
 
 // The first Newton pass with a sampled bracket: the evaluation at lam_0 of
 // gen_first_pass_kernel, and the indices whose breakpoints fall in the
-// bracket [sp, sq] that gen_sample_kernel estimated written to compacted set
-// 3 (kSpecSet), with the others' contributions summed (spec_index).
+// bracket [sp, sq] that gen_sample_kernel estimated, or in the bracket [p2, q2]
+// around the first iterate it predicts, written to compacted set 3 (kSpecSet),
+// with the others' contributions on either bracket summed (spec_index).
 // Only one side's LDS ring.  When the sample gave no bracket, the plain
-// evaluation.
-template <typename TIn>
-__global__ __launch_bounds__(kBlock) void gen_spec_pass_kernel(GenArgs A) {
+// evaluation.  FLAT: the pass at a flat lam_0 (st->flat, flat_index), which
+// needs more registers than the others should pay for.  again: a later pass, only when it writes the set
+// anew (gen_sample3_reduce_kernel).
+template <typename TIn, bool FLAT>
+__global__ __launch_bounds__(kBlock) void gen_spec_pass_kernel(GenArgs A, bool again) {
   GenState* st = A.st;
-  if (st->status != kRunning) return;
+  if (st->status != kRunning || (st->flat != 0) != FLAT || (again && st->spec == 0)) return;
   const int rid = blockIdx.x * kWavesPerBlock + (int)(threadIdx.x / kWave);
   const int64_t nr = (int64_t)gridDim.x * kWavesPerBlock;
   const int64_t plane = nr * A.region;
@@ -708,24 +728,41 @@ __global__ __launch_bounds__(kBlock) void gen_spec_pass_kernel(GenArgs A) {
   double* stg = stage + (threadIdx.x / kWave) * 4 * kStageSpec;
   Acc acc;
   acc_init(acc);
+  FlatAcc flat;
+  if (FLAT) flat_init(flat);
   SrcOrig<TIn> s{(const TIn*)A.d, (const TIn*)A.a, (const TIn*)A.b, (const TIn*)A.l,
                  (const TIn*)A.u};
   constexpr int64_t T = (int64_t)kWave * kTileE;
   const int64_t first = (int64_t)rid * kPair * T, stride = nr * kPair * T;
   const double lam = st->lam;
-  if (st->spec != 0) {
+  if (FLAT || st->spec != 0) {
     double* out[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) out[j] = A.buf[kSpecSet - 1] + j * plane;
     int32_t* oc[1] = {A.cnt[kSpecSet - 1] + rid};
-    eval_pass<SrcOrig<TIn>, kSampled>(s, A.n, first, stride, lam, st->sp, st->sq, st->scap, out,
-                                      pc, oc, acc, stg);
+    eval_pass<SrcOrig<TIn>, kSampled, FLAT>(s, A.n, first, stride, lam, st->sp, st->sq, st->scap,
+                                            out, pc, oc, acc, stg, 0, st->p2, st->q2, &flat,
+                                            st->flat == 2);
   } else {
     eval_pass<SrcOrig<TIn>, kEvalOnly>(s, A.n, first, stride, lam, 0.0, 0.0, 0.0, nullptr, pc,
                                        nullptr, acc, stg);
   }
+  if (FLAT) {
+    // side 1's sums are free: there is no second bracket
+    acc.s[P_SIDE + D_N + D_F] = flat.b;
+    acc.s[P_SIDE + D_N + D_AF] = flat.ab;
+  }
   block_reduce<NSUM, 0, 0, kBlock>(acc.s, nullptr, nullptr, lds, tot);
   if (threadIdx.x == 0) write_partial(A.partials, tot, NPART);
+  if (FLAT) {
+    __shared__ KeySum ktot[2];
+    const KeySum ks[2] = {flat.near, flat.far};
+    block_ks_min<2, kBlock>(ks, lds, ktot);
+    if (threadIdx.x == 0) {
+      const double v[4] = {ktot[0].k, ktot[0].w, ktot[1].k, ktot[1].w};
+      write_partial(A.flat, v, 4);
+    }
+  }
 }
 
 // The lam_0 pass with the sampled bracket: the sums of eq. (CQKlambda0) --
@@ -871,10 +908,11 @@ constexpr int kS2Waves = kS2Threads / kWave;
 constexpr int kS2PerWave = 8;  // tiles per wave
 constexpr int kS2Blocks = 512;
 constexpr double kS2Lam1Width = 4.0;
+constexpr double kS2OwnWidth = 10.0;  // lam_1's own bracket: its error also has the slope's
 enum { S2_G = 0, S2_G2, S2_SF, S2_BAD, S2_G0, S2_QP0, S2_QM0, S2_C, S2_S, S2_N };
 constexpr int kS2Tiles = kS2Blocks * kS2Waves * kS2PerWave;
 constexpr int64_t kS2M = (int64_t)kS2Tiles * kWave;    // second sample's size
-constexpr int64_t kSmpMinN = (int64_t)1 << 22;
+constexpr int64_t kSmpMinN = (int64_t)1 << 21, kSmpMinLongN = (int64_t)1 << 22;
 static_assert(kSmpMinN >= (int64_t)kS2Tiles * kWave, "every sampled tile lies inside the arrays");
 
 template <typename TIn>
@@ -1130,6 +1168,7 @@ __global__ __launch_bounds__(kRBlock) void gen_sample2_reduce_kernel(GenArgs A) 
     const double rs = st->r * (m / (double)A.n);
     double lam = __builtin_nan(""), p = __builtin_nan(""), q = __builtin_nan("");
     double sdl = 0.0, share = 1.0, lam1_pred = __builtin_nan("");
+    double p2 = __builtin_nan(""), q2 = __builtin_nan("");
     bool use = false;
     if (ok1 && all[S2_BAD] == 0.0 && all[S2_SF] > 0.0) {
       lam = st->s1lam - (all[S2_G] - rs) / all[S2_SF];
@@ -1162,6 +1201,16 @@ __global__ __launch_bounds__(kRBlock) void gen_sample2_reduce_kernel(GenArgs A) 
           q = q1;
         }
         share = st->s1share * ((q - p) / (2.0 * st->s1half));
+        // further out, lam_1 gets a bracket of its own: the set then also
+        // holds the indices with a breakpoint there, and the pass at lam_1
+        // reads it (a pass over the caller's arrays less)
+        const double h2 = kS2OwnWidth * sdl, share2 = st->s1share * (h2 / st->s1half);
+        if (st->lam0_later == 0 && (lam1 + h2 < p || lam1 - h2 > q) &&
+            share + share2 < 0.5 * theta) {
+          p2 = lam1 - h2;
+          q2 = lam1 + h2;
+          share += share2;
+        }
       }
     }
     if (!(p < q) && ok1) {
@@ -1179,6 +1228,15 @@ __global__ __launch_bounds__(kRBlock) void gen_sample2_reduce_kernel(GenArgs A) 
     st->sq = use ? q : __builtin_nan("");
     st->scap = use ? fmin(theta, 1.5 * share + 1.0 / 32.0) : 0.0;
     st->spec = use ? 1 : 0;
+    // phi flat at a known lam_0 on the whole sample, lam* to its right (1) or
+    // left (2)
+    const double r0 = all[S2_G0] - rs;
+    st->flat = !(use && st->lam0_later == 0 && A.flat != nullptr) ? 0
+               : (r0 < 0.0 && all[S2_QP0] == 0.0)                 ? 1
+               : (r0 > 0.0 && all[S2_QM0] == 0.0)                 ? 2
+                                                                  : 0;
+    st->p2 = use ? p2 : __builtin_nan("");
+    st->q2 = use ? q2 : __builtin_nan("");
     // a predicted first iterate of a known lam_0 left outside: the third
     // estimate looks at the second
     st->s2lam1 = (use && st->lam0_later == 0 && __builtin_isfinite(lam1_pred) &&
@@ -1214,6 +1272,10 @@ __global__ __launch_bounds__(kRBlock) void gen_sample2_reduce_kernel(GenArgs A) 
 // bracket to the predicted lam_2 (+- kS3Width deviations) when that keeps
 // it within kS3MaxWiden times the width of the bracket around lam* and the
 // share allowed.  Both return at once when there is nothing to predict.
+// again: before a later pass over the caller's arrays at lam_k, the same for
+// the iterate after it; if that lies outside the sampled bracket it gets the
+// second bracket [p2, q2], and the pass at lam_k writes set 3 anew for both
+// (gen_spec_pass_kernel), so that the pass at lam_{k+1} reads the set.
 constexpr int kS3Blocks = 256;
 constexpr int kS3Threads = 256;
 constexpr int kS3Waves = kS3Threads / kWave;
@@ -1222,14 +1284,21 @@ constexpr int kS3Tiles = kS3Blocks * kS3Waves * kS3PerWave;
 constexpr int64_t kS3M = (int64_t)kS3Tiles * kWave;
 constexpr double kS3Width = 6.0;
 constexpr double kS3MaxWiden = 6.0;
+constexpr double kS3OwnWidth = 15.0;  // as kS2OwnWidth, from a quarter of the sample
 static_assert(kSmpMinN >= (int64_t)kS3Tiles * kWave, "every sampled tile lies inside the arrays");
 enum { S3_G = 0, S3_QP, S3_QM, S3_BAD, S3_N };
 
+__device__ __forceinline__ double sample3_at(const GenState* st, bool again) {
+  if (!again) return st->s2lam1;
+  const bool on = st->src == 0 && st->mode == kModeEval && st->sp < st->sq;
+  return on ? st->lam : __builtin_nan("");
+}
+
 template <typename TIn>
-__global__ __launch_bounds__(kS3Threads) void gen_sample3_kernel(GenArgs A) {
+__global__ __launch_bounds__(kS3Threads) void gen_sample3_kernel(GenArgs A, bool again) {
   GenState* st = A.st;
   if (st->status != kRunning) return;
-  const double mu = st->s2lam1;
+  const double mu = sample3_at(st, again);
   if (!__builtin_isfinite(mu)) return;
   const int lane = threadIdx.x & (kWave - 1);
   const int w = threadIdx.x / kWave;
@@ -1270,10 +1339,10 @@ __global__ __launch_bounds__(kS3Threads) void gen_sample3_kernel(GenArgs A) {
   if (threadIdx.x == 0) write_partial(A.partials, tot, S3_N);
 }
 
-__global__ __launch_bounds__(kRBlock) void gen_sample3_reduce_kernel(GenArgs A) {
+__global__ __launch_bounds__(kRBlock) void gen_sample3_reduce_kernel(GenArgs A, bool again) {
   GenState* st = A.st;
   if (st->status != kRunning) return;
-  const double mu = st->s2lam1;
+  const double mu = sample3_at(st, again);
   if (!__builtin_isfinite(mu)) return;
   __shared__ double rl[S3_N * (kRBlock / kWave)];
   __shared__ double all[S3_N];
@@ -1283,12 +1352,24 @@ __global__ __launch_bounds__(kRBlock) void gen_sample3_reduce_kernel(GenArgs A) 
     const double res = all[S3_G] - st->r * (m / (double)A.n);
     const double sl = (res < 0.0) ? all[S3_QP] : all[S3_QM];
     const double p = st->sp, q = st->sq, ssd = st->ssd;
-    if (all[S3_BAD] == 0.0 && sl > 0.0 && p < q) {
+    if (again && all[S3_BAD] == 0.0 && sl > 0.0) {
+      const double next = mu - res / sl, h2 = kS3OwnWidth * ssd;
+      const double share = st->s1share * ((q - p + 2.0 * h2) / (2.0 * st->s1half));
+      if ((next + h2 < p || next - h2 > q) && share < 0.5 * st->theta) {
+        st->p2 = next - h2;
+        st->q2 = next + h2;
+        st->scap = fmin(st->theta, 1.5 * share + 1.0 / 32.0);
+        st->spec = 1;
+        st->spend = 0;
+      }
+    } else if (!again && all[S3_BAD] == 0.0 && sl > 0.0 && p < q) {
       const double lam2 = mu - res / sl;
       const double p2 = fmin(p, lam2 - kS3Width * ssd);
       const double q2 = fmax(q, lam2 + kS3Width * ssd);
       const double base = 2.0 * kSmpWidth * ssd;
-      const double share = st->s1share * ((q2 - p2) / (2.0 * st->s1half));
+      const double share = st->s1share * ((q2 - p2) / (2.0 * st->s1half)) +
+                           ((st->p2 < st->q2) ? st->s1share * ((st->q2 - st->p2) /
+                                                               (2.0 * st->s1half)) : 0.0);
       if (q2 - p2 <= kS3MaxWiden * base && share < 0.5 * st->theta) {
         st->sp = p2;
         st->sq = q2;
@@ -1316,6 +1397,7 @@ __global__ __launch_bounds__(kRBlock) void gen_update_kernel(GenArgs A, int G) {
   __shared__ double tot[NPART];
   // the scalar update works on a register copy of the state record (one
   // round trip to memory instead of one per field access)
+  if (st->flat != 0) return;  // gen_flat_update_kernel's
   if (st->mode == kModeEval) {
     reduce_partials<NSUM, 0, 0, kRBlock>(A.partials, G, lds, tot);
     if (threadIdx.x == 0) {
@@ -1331,6 +1413,28 @@ __global__ __launch_bounds__(kRBlock) void gen_update_kernel(GenArgs A, int G) {
       update_after_bkpt(&s, ktot, A.trace);
       *st = s;
     }
+  }
+}
+
+// The update after a pass at a flat lam_0, and the steps that need no pass
+// (flat_steps; in a kernel of its own for its registers).
+__global__ __launch_bounds__(kRBlock) void gen_flat_update_kernel(GenArgs A, int G) {
+  GenState* st = A.st;
+  const int flat = st->flat;
+  if (st->status != kRunning || flat == 0) return;
+  __shared__ double lds[NPART * (kRBlock / kWave)];
+  __shared__ double tot[NPART];
+  __shared__ KeySum ktot[2];
+  reduce_partials<NSUM, 0, 0, kRBlock>(A.partials, G, lds, tot);
+  __syncthreads();
+  reduce_partials_ks<2, kRBlock>(A.flat, G, lds, ktot);
+  if (threadIdx.x == 0) {
+    GenState s = *st;
+    s.flat = 0;
+    update_after_eval(&s, tot, A.trace);
+    flat_steps(&s, ktot[0], ktot[1], tot[P_SIDE + D_N + D_F], tot[P_SIDE + D_N + D_AF],
+               flat == 2, A.trace);
+    *st = s;
   }
 }
 
@@ -1637,6 +1741,210 @@ __global__ void gen_team_commit_kernel(GenState* st, const TeamCtl* ctl) {
   st->team_done = 1;
 }
 
+// ---------------------------------------------------------------------------
+// The rest of a solve once its passes read a compacted set: every remaining
+// iteration in one launch.  The blocks (one per compute unit) share the set's
+// wave regions, hold kRestSlots pieces per wave in registers (what is left of
+// a long region is read again at each evaluation), exchange their sums
+// through memory (cqk_team.h) and run the scalar update on the same totals.
+// Nothing is compacted further: an evaluation on registers takes under a
+// microsecond, less than the writes it would save.  Block 0 writes the state
+// back when the loop stops, or when the next multiplier leaves the bracket
+// that the set's dropped-index sums hold on; a pass over the caller's arrays
+// goes on from there.  A block whose wait runs out ends without writing, and
+// the pass kernels queued behind go on from the unchanged state.
+// Bound by the load of the set (32 bytes per index), then by latency, about 3
+// us per iteration: 36 us for the 1.8e5 survivors of 1e7 FP64 indices, against
+// 105 us for the pass and update kernels and the gaps between them (whole
+// calls: 310 -> 266 us; 1e8 indices 1750 -> 1669).
+// ---------------------------------------------------------------------------
+constexpr int kRestSlots = 16;
+constexpr int kRestRegions = 4;   // a wave's regions (choose_grid: 8 blocks of 4 waves per unit)
+
+struct RestArgs {
+  const double* buf[3];
+  const int32_t* cnt[3];
+  int64_t region;
+  int64_t nr;          // wave regions of a set
+  int64_t max_src;     // larger sets stay with the pass kernels
+  int32_t max_pass;
+  GenState* st;
+  uint64_t* slots;
+  uint64_t limit;
+  uint32_t tag;        // the last tag used; with `tags`, relative to their base
+  const TeamTags* tags;
+};
+
+__global__ __launch_bounds__(kTeamBlock) void gen_rest_kernel(RestArgs A) {
+  constexpr int NW = kTeamBlock / kWave;
+  __shared__ TeamLds<kTeamBlock> S;
+  const GenState* in = A.st;
+  if (in->status != kRunning || in->src == 0 || in->n_src > A.max_src) return;
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1), wid = scalar(tid / kWave);
+  const int set = scalar(in->src) - 1;
+  const double* buf = (set == 0) ? A.buf[0] : (set == 1) ? A.buf[1] : A.buf[2];
+  const int32_t* cnt = (set == 0) ? A.cnt[0] : (set == 1) ? A.cnt[1] : A.cnt[2];
+  const int64_t nr = A.nr, plane = nr * A.region;
+  const int64_t tw = (int64_t)gridDim.x * NW, w0 = (int64_t)blockIdx.x * NW + wid;
+  // the wave's regions, w0 + i tw, and where their pieces start in its list
+  int count[kRestRegions], first[kRestRegions + 1];
+  first[0] = 0;
+#pragma unroll
+  for (int i = 0; i < kRestRegions; ++i) {
+    const int64_t rid = w0 + i * tw;
+    count[i] = (rid < nr) ? scalar(cnt[rid]) : 0;
+    first[i + 1] = first[i] + (count[i] + kPiece - 1) / kPiece;
+  }
+  const int pieces = first[kRestRegions];
+  // where piece j starts, and its values
+  auto piece = [&](int j, int64_t& at, int& m) {
+    int i = 0, f = 0, c = count[0];
+#pragma unroll
+    for (int k = 1; k < kRestRegions; ++k) {
+      const bool past = j >= first[k];
+      i = past ? k : i;
+      f = past ? first[k] : f;
+      c = past ? count[k] : c;
+    }
+    const int p = j - f;
+    at = ((int64_t)p * nr + w0 + i * tw) * kPiece;
+    m = (j < pieces) ? min(c - p * kPiece, kPiece) : 0;
+  };
+  double c[kRestSlots], s[kRestSlots], bl[kRestSlots], bu[kRestSlots];
+  int len[kRestSlots];
+#pragma unroll
+  for (int j = 0; j < kRestSlots; ++j) {
+    int64_t at;
+    piece(j, at, len[j]);
+    const int64_t q = (lane < len[j]) ? at + lane : 0;  // a place that is there
+    c[j] = buf[q];
+    s[j] = buf[plane + q];
+    bl[j] = buf[2 * plane + q];
+    bu[j] = buf[3 * plane + q];
+  }
+#pragma unroll
+  for (int j = 0; j < kRestSlots; ++j) {
+    const bool there = lane < len[j];
+    c[j] = there ? c[j] : 0.0;  // adds nothing: no slope, both bounds zero
+    s[j] = there ? s[j] : 0.0;
+    bl[j] = there ? bl[j] : 0.0;
+    bu[j] = there ? bu[j] : 0.0;
+  }
+  // the pieces beyond the registers
+  auto others = [&](auto&& fn) {
+    for (int j = kRestSlots; j < pieces; ++j) {
+      int64_t at;
+      int m;
+      piece(j, at, m);
+      if (lane < m) {
+        const int64_t q = at + lane;
+        fn(buf[q], buf[plane + q], buf[2 * plane + q], buf[3 * plane + q]);
+      }
+    }
+  };
+  if (tid == 0) S.gave_up = 0;
+  // the run state, the same in every lane of every block
+  GenState st{};
+  st.lam = in->lam;
+  st.lam_prev = in->lam_prev;
+  st.lam_final = in->lam_final;
+  st.lo = in->lo;
+  st.hi = in->hi;
+  st.phi_lo = in->phi_lo;
+  st.phi_hi = in->phi_hi;
+  st.r = in->r;
+  st.tol = in->tol;
+  st.status = kRunning;
+  st.iter = in->iter;
+  st.passes = in->passes;
+  st.max_iter = in->max_iter;
+  st.mode = in->mode;
+  st.ntrace = in->ntrace;
+  state_to_scalars(st);
+  // the dropped-index sums and the bracket they hold on, and those of the
+  // set's first bracket while the second's are in use (take_spec_set)
+  double F = scalar(in->F), AF = scalar(in->AF), C0 = scalar(in->C0);
+  double C1 = scalar(in->C1), A0 = scalar(in->A0), A1 = scalar(in->A1);
+  double vlo = scalar(in->vlo), vhi = scalar(in->vhi);
+  bool waits = set == kSpecSet - 1 && scalar(in->spend) != 0;
+  const double sF = scalar(in->sF), sAF = scalar(in->sAF), sC0 = scalar(in->sC0);
+  const double sC1 = scalar(in->sC1), sA0 = scalar(in->sA0), sA1 = scalar(in->sA1);
+  const double sp = scalar(in->sp), sq = scalar(in->sq);
+  const int passes0 = st.passes;
+  Team team = grid_team(A.slots, (A.tags != nullptr ? A.tags->base : 0u) + A.tag, A.limit);
+  __syncthreads();  // every read of the state comes before this block's first record
+  int par = 0;
+  bool ok = true, leave = false;
+  for (int pass = 0; ok && !leave && pass < A.max_pass && st.status == kRunning; ++pass) {
+    const double lam = st.lam;
+    if (st.mode == kModeEval) {
+      Acc acc;
+      acc_init(acc);
+#pragma unroll
+      for (int j = 0; j < kRestSlots; ++j)
+        eval_index<false>(acc, c[j], s[j], bl[j], bu[j], lam, 0.0, 0.0);
+      others([&](double oc, double os, double obl, double obu) {
+        eval_index<false>(acc, oc, os, obl, obu, lam, 0.0, 0.0);
+      });
+      const double v[4] = {acc.s[P_P], acc.s[P_A], acc.s[P_QP], acc.s[P_QM]};
+      double tot[4], t[NSUM];
+      ok = team_reduce<4, kTeamBlock>(team, S, par, v, tot);
+      t[P_P] = (F + C0) + (lam * C1 + tot[0]);
+      t[P_A] = (AF + A0) + (lam * A1 + tot[1]);
+      t[P_QP] = C1 + tot[2];
+      t[P_QM] = C1 + tot[3];
+      t[P_BAD] = 0.0;
+      update_after_eval<false>(&st, t, nullptr);
+    } else {
+      KeySum ks[2] = {KeySum{inf_d(), 0.0}, KeySum{inf_d(), 0.0}};
+#pragma unroll
+      for (int j = 0; j < kRestSlots; ++j) bkpt_index(ks, c[j], s[j], bl[j], bu[j], lam);
+      others([&](double oc, double os, double obl, double obu) {
+        bkpt_index(ks, oc, os, obl, obu, lam);
+      });
+      ok = team_reduce_ks<kTeamBlock>(team, S, par, ks);
+      update_after_bkpt<false>(&st, ks, nullptr);
+    }
+    state_to_scalars(st);
+    if (waits && st.mode == kModeEval && st.lam > sp && st.lam < sq) {
+      F = sF;
+      AF = sAF;
+      C0 = sC0;
+      C1 = sC1;
+      A0 = sA0;
+      A1 = sA1;
+      vlo = sp;
+      vhi = sq;
+      waits = false;
+    }
+    // check_source_eval, check_source_bkpt
+    leave = (st.mode == kModeEval) ? !(st.lam > vlo && st.lam < vhi)
+                                   : !(vlo <= st.lo && st.hi <= vhi);
+  }
+  if (!ok || blockIdx.x != 0 || tid != 0) return;
+  GenState* out = A.st;
+  out->bytes += 32.0 * (double)out->n_src * (double)(st.passes - passes0);
+  out->lam = st.lam;
+  out->lam_prev = st.lam_prev;
+  out->lam_final = st.lam_final;
+  out->lo = st.lo;
+  out->hi = st.hi;
+  out->phi_lo = st.phi_lo;
+  out->phi_hi = st.phi_hi;
+  out->iter = st.iter;
+  out->passes = st.passes;
+  out->mode = st.mode;
+  out->ntrace = st.ntrace;
+  out->stop_reason = st.stop_reason;
+  if (st.status == kRunning) {
+    out->spend = waits ? 1 : 0;
+    if (leave) to_caller_arrays(out);
+    plan_sides(out);
+  }
+  out->status = st.status;
+}
+
 template <typename TIn, int E>
 __global__ __launch_bounds__(kTeamBlock) void gen_team_kernel(TeamArgs A) {
   constexpr int V = VecWidth<TIn>::value;
@@ -1861,6 +2169,11 @@ TeamShape team_shape(int64_t n, int num_cus) {
   return {0, 0};
 }
 
+// waves of gen_rest_kernel
+int64_t rest_waves(int num_cus) {
+  return (int64_t)std::min(num_cus, kTeamMax) * (kTeamBlock / kWave);
+}
+
 int choose_grid(int64_t n, int num_cus) {
   const int64_t want = (n + 1023) / 1024;
   const int64_t cap = (int64_t)num_cus * 8;
@@ -1951,21 +2264,37 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     double* bb = (double*)(ws + part_bytes + cnt_bytes + Lg.smp_bytes);
     for (int k = 0; k < 3; ++k) A.buf[k] = bb + (size_t)k * 4 * NR * Lg.region;
   }
+  if ((size_t)G * 4 * sizeof(double) <= Lg.smp_bytes) A.flat = (double*)A.smp;
   A.st = (GenState*)ctx->state.ptr;
   A.trace = (cqk_trace_rec*)((char*)ctx->state.ptr + 1024);
 
   const bool is_f32 = sizeof(TIn) == 4;
   const double eps = (is_f32 && o.accum == CQK_ACCUM_F32) ? 1.1920928955078125e-07
                                                           : 2.220446049250313e-16;
+  const TeamShape shape = team_shape(n, ctx->num_cus);
+  const uint32_t need = 2 * (uint32_t)std::min(o.max_iter, 1 << 20) + 8;
+  // Longer inputs: the iterations on a compacted set in one launch
+  // (gen_rest_kernel), behind the passes that may leave one.
+  constexpr int kRests = 4;
+  const uint32_t rest_need = need;  // an exchange per pass at most
+  const bool rest = shape.E == 0 && compaction && !o.trace && !o.timing &&
+                    o.max_iter <= (1 << 20) && NR <= kRestRegions * rest_waves(ctx->num_cus) &&
+                    team_ready(ctx, kRests * rest_need);
   // With compaction on large inputs, a bracket estimated from a sample lets
-  // the first pass compact (gen_sample_kernel, gen_sample2_kernel); below
-  // kSmpMinN the sample costs more than it saves.  A warm or formula start
-  // then runs its lam_0 pass after the sample and writes the sampled set
+  // the first pass compact (gen_sample_kernel, gen_sample2_kernel), from
+  // kSmpMinN on where gen_rest_kernel then finishes the solve (2.2e6 FP32
+  // indices, uniform 136 us without the sample and 146 with it, correlated 205
+  // and 158, the paper's weakly correlated class 382 and 268), else from
+  // kSmpMinLongN on (below, the sample costs more than it saves: a warm start
+  // of 2.2e6 indices takes 116 us without and 146 with it).  A warm or formula
+  // start then runs its lam_0 pass after the sample and writes the sampled set
   // itself (gen_warm_spec_kernel), and the first Newton pass is a general
   // one.
   // (the second estimate's block records use the partials buffer)
-  const bool sampled = compaction && n >= kSmpMinN && (int64_t)G * NPART >= (int64_t)kS2Blocks * S2_N;
   const bool formula = xw == nullptr && o.lambda0_mode == CQK_LAMBDA0_FORMULA;
+  const bool sampled = compaction &&
+                       n >= ((rest && xw == nullptr && !formula) ? kSmpMinN : kSmpMinLongN) &&
+                       (int64_t)G * NPART >= (int64_t)kS2Blocks * S2_N;
   const bool warm_spec = sampled && (xw != nullptr || formula);
   GenState init{};
   init.lam = (o.lambda0_mode == CQK_LAMBDA0_USER && xw == nullptr) ? o.lambda0_user : 0.0;
@@ -1983,6 +2312,7 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
   init.vhi = __builtin_huge_val();
   init.sp = init.sq = __builtin_nan("");
   init.slam = init.ssd = init.s2lam1 = __builtin_nan("");
+  init.p2 = init.q2 = __builtin_nan("");
   init.warm = (xw != nullptr) ? 1 : 0;
   init.lam0_later = warm_spec ? 1 : 0;
   init.in_bytes = 5.0 * sizeof(TIn);
@@ -2010,8 +2340,6 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
   }
   // One launch where the problem fits the registers.  Traced and timed calls
   // report single passes and keep the multi-launch route.
-  const TeamShape shape = team_shape(n, ctx->num_cus);
-  const uint32_t need = 2 * (uint32_t)std::min(o.max_iter, 1 << 20) + 8;
   const bool team = shape.E != 0 && !o.trace && !o.timing && o.max_iter <= (1 << 20) &&
                     team_ready(ctx, need);
   TeamCtl* const ctl = team ? (TeamCtl*)((char*)ctx->team.ptr + kTeamSlotBytes) : nullptr;
@@ -2088,7 +2416,35 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
       return CQK_OK;
     }
   }
-  if (team && deferred) {
+  TeamCtl* const rctl = rest ? (TeamCtl*)((char*)ctx->team.ptr + kTeamSlotBytes) : nullptr;
+  int rests = 0;
+  auto launch_rest = [&]() {
+    if (!rest || rests == kRests) return;
+    RestArgs R{};
+    for (int k = 0; k < 3; ++k) {
+      R.buf[k] = A.buf[k];
+      R.cnt[k] = A.cnt[k];
+    }
+    R.region = A.region;
+    R.nr = NR;
+    const int blocks = std::min(ctx->num_cus, kTeamMax);
+    // twice what the registers hold
+    R.max_src = (int64_t)2 * blocks * kTeamBlock * kRestSlots;
+    R.max_pass = 2 * o.max_iter + 4;
+    R.st = A.st;
+    R.slots = (uint64_t*)ctx->team.ptr;
+    R.limit = ctx->team_wait;
+    R.tag = deferred ? (uint32_t)rests * rest_need : ctx->team_tag;
+    R.tags = deferred ? &rctl->tags : nullptr;
+    hipLaunchKernelGGL(gen_rest_kernel, dim3(blocks), dim3(kTeamBlock), 0, s, R);
+    if (!deferred) ctx->team_tag += rest_need;
+    ++rests;
+  };
+  if (rest && deferred) {
+    hipLaunchKernelGGL(team_init_kernel<GenState>, dim3(1), dim3(256), 0, s, A.st, init,
+                       &rctl->tags, &rctl->res.gave_up, (uint64_t*)ctx->team.ptr,
+                       kRests * rest_need);
+  } else if (team && deferred) {
     hipLaunchKernelGGL(team_init_kernel<GenState>, dim3(1), dim3(256), 0, s, A.st, init,
                        &ctl->tags, &ctl->res.gave_up, (uint64_t*)ctx->team.ptr, need);
     launch_team(&ctl->res, ctl);
@@ -2100,10 +2456,10 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
   int ev = 2;
   int npass = 0;  // grid passes queued
   // a grid pass (timed when asked) followed by its one-block reduction
-  auto launch = [&](auto kern, auto reduce, bool first_newton) {
+  auto launch = [&](auto kern, auto reduce, bool first_newton, auto... more) {
     const bool rec = (timing_all || (timing && first_newton)) && ev + 2 <= (int)nev;
     launch_timed(kern, dim3(G), dim3(kBlock), s, rec ? ctx->events[ev] : nullptr,
-                 rec ? ctx->events[ev + 1] : nullptr, A);
+                 rec ? ctx->events[ev + 1] : nullptr, A, more...);
     if (rec) ev += 2;
     ++npass;
     hipLaunchKernelGGL(reduce, dim3(1), dim3(kRBlock), 0, s, A, G);
@@ -2119,6 +2475,10 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     launch(gen_warm_kernel<TIn>, gen_warm_update_kernel, false);
   else if (formula && !warm_spec)
     launch(gen_lambda0_kernel<TIn>, gen_lambda0_update_kernel, false);
+  auto predict = [&](bool again) {
+    hipLaunchKernelGGL(gen_sample3_kernel<TIn>, dim3(kS3Blocks), dim3(kS3Threads), 0, s, A, again);
+    hipLaunchKernelGGL(gen_sample3_reduce_kernel, dim3(1), dim3(kRBlock), 0, s, A, again);
+  };
   if (sampled) {
     bool rec = timing_all && ev + 2 <= (int)nev;
     launch_timed(gen_sample_kernel<TIn>, dim3(kSmpBlocks), dim3(kSmpThreads), s,
@@ -2130,10 +2490,7 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     if (rec) ev += 2;
     hipLaunchKernelGGL(gen_sample2_reduce_kernel, dim3(1), dim3(kRBlock), 0, s, A);
     npass += 2;
-    if (!warm_spec) {
-      hipLaunchKernelGGL(gen_sample3_kernel<TIn>, dim3(kS3Blocks), dim3(kS3Threads), 0, s, A);
-      hipLaunchKernelGGL(gen_sample3_reduce_kernel, dim3(1), dim3(kRBlock), 0, s, A);
-    }
+    if (!warm_spec) predict(false);
   }
   if (warm_spec && xw != nullptr)
     launch(gen_warm_spec_kernel<TIn, true>, gen_warm_spec_update_kernel, false);
@@ -2145,23 +2502,50 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
   // the first Newton pass evaluates the caller's arrays: with the sampled
   // bracket it also compacts for it, else the lean kernel runs; every later
   // pass the general one
+  const bool ask_flat = rest && sampled && !deferred;
+  auto flat_pass = [&]() {
+    hipLaunchKernelGGL((gen_spec_pass_kernel<TIn, true>), dim3(G), dim3(kBlock), 0, s, A, false);
+    hipLaunchKernelGGL(gen_flat_update_kernel, dim3(1), dim3(kRBlock), 0, s, A, G);
+  };
   auto pass = [&]() {
     if (launched == 0 && warm_spec) launch(gen_pass_kernel<TIn>, gen_update_kernel, true);
-    else if (launched == 0 && sampled) launch(gen_spec_pass_kernel<TIn>, gen_update_kernel, true);
+    else if (launched == 0 && sampled) {
+      launch(gen_spec_pass_kernel<TIn, false>, gen_update_kernel, true, false);
+      // what gen_spec_pass_kernel and the update left to them; a waiting call
+      // whose first batch is one pass asks the state instead of queueing them
+      if (!ask_flat) flat_pass();
+    }
     else if (launched == 0) launch(gen_first_pass_kernel<TIn>, gen_update_kernel, true);
-    else launch(gen_pass_kernel<TIn>, gen_update_kernel, false);
+    else {
+      if (launched == 1 && sampled && !warm_spec) {
+        predict(true);
+        hipLaunchKernelGGL((gen_spec_pass_kernel<TIn, false>), dim3(G), dim3(kBlock), 0, s, A,
+                           true);
+      }
+      launch(gen_pass_kernel<TIn>, gen_update_kernel, false);
+    }
     ++launched;
   };
+  // a warm or formula start's lam_0 pass may already leave a compacted set
+  if (warm_spec) launch_rest();
   if (deferred) {
-    while (launched < max_launch) pass();
+    while (launched < max_launch) {
+      pass();
+      launch_rest();
+    }
     finalize();
     if (hip_ok(hipGetLastError()) != CQK_OK) return CQK_DEVICE_ERROR;
   } else {
-    // Algorithm 1 typically stops after five to seven evaluations here
-    int batch = 6;
+    // Algorithm 1 typically stops after five to seven evaluations here, all
+    // but the first one or two of them on a compacted set
+    int batch = !rest ? 6 : sampled ? 1 : 2;
     while (launched < max_launch) {
+      if (launched == 1 && ask_flat && hs->flat != 0) flat_pass();
       const int k = std::min(batch, max_launch - launched);
-      for (int i = 0; i < k; ++i) pass();
+      for (int i = 0; i < k; ++i) {
+        pass();
+        launch_rest();
+      }
       finalize();
       if (hip_ok(hipGetLastError()) != CQK_OK) return CQK_DEVICE_ERROR;
       if (hip_ok(hipMemcpyAsync(hs, A.st, sizeof(GenState), hipMemcpyDeviceToHost, s)) != CQK_OK)

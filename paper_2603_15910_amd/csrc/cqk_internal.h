@@ -50,6 +50,10 @@ struct GenState {
   double sp, sq, scap;
   double sF, sAF, sC0, sC1, sA0, sA1;
   int64_t sn;
+  // A second bracket [p2, q2] (NaN: none) around the first iterate that the
+  // sample predicts, with dropped-index sums of the same set for it
+  double p2, q2;
+  double s2F, s2AF, s2C0, s2C1, s2A0, s2A1;
   // the first estimate (solution, bracket half-width, share of the sample
   // inside), refined by the second
   double s1lam, s1half, s1share;
@@ -67,6 +71,7 @@ struct GenState {
   uint32_t ticket;
   int32_t spec;                   // 1: the next evaluation writes the sampled-bracket set
   int32_t spend;                  // 1: that set waits in set 3
+  int32_t flat;                   // the first pass is at a flat lam_0 (1: lam* right of it, 2: left)
   int32_t s1ok;                   // 1: the first estimate found a bracket
   int32_t skip;                   // sides the next evaluation does not write (bit k: side k)
   int32_t warm;                   // 1: lam_0 comes from a primal estimate
