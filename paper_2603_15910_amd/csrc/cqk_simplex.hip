@@ -47,8 +47,11 @@
 //   spx_tail_kernel         the same loop for an input that fits from the
 //                           start (read from y).
 //   spx_team_kernel         all of it in one launch, for inputs that fit the
-//                           compute units' registers; the kernels above are
-//                           its fallback and the route of longer inputs.
+//                           compute units' registers;
+//   spx_rest_kernel         for longer ones, all that follows the Algorithm 2
+//                           pass in one launch.  The kernels between are the
+//                           fallback of both and the route of traced calls,
+//                           other starts and FP32 accumulation.
 //   spx_finalize_kernel     dense x = max(0, y + lam*) (or 0, or a copy of y);
 //   spx_scatter_kernel      x[idx] for the surviving indices when the rest of
 //                           x is known to be zero.
@@ -1739,6 +1742,10 @@ __global__ void spx_init_kernel(SpxState* st, SpxState init) { *st = init; }
 // 73 -> 36, 1e7 95 -> 56; sparse l1 of 1e7 142 -> 79; FP64 1e6 73 -> 43.
 // ---------------------------------------------------------------------------
 constexpr int kTeamCand = 4;
+// survivors per compute unit that spx_rest_kernel takes: twice what its FP32
+// lists hold (beyond, it sweeps the regions at every iteration and would take
+// longer than the passes, which drop indices)
+constexpr int kRestMax = 2 * 16384;
 constexpr int kTeamListBytes = 64 * 1024;  // a block's list; beyond it the registers are swept
 
 struct SpxTeamResult {   // in the context's pinned host memory, or behind the slots
@@ -1787,6 +1794,134 @@ __global__ void spx_team_commit_kernel(SpxState* st, const SpxTeamCtl* ctl) {
   st->stop_reason = R.stop_reason;
   if (R.copy) st->fin_mode = kFinCopy;
   st->team_done = 1;
+}
+
+// What the start of a projection knows, and how its loop ended.
+struct SpxStart {
+  double cnt, sum;        // of the listed values (every value above lam_min is)
+  double bad, abs_sum;    // bad values; sum |y| (l1)
+  double cnt_i, sum_i;    // of the listed values in a warm start's support
+  double vmax, vmax_i;    // the largest value, of all and of the support
+  double lam_min;         // the smallest bound known
+};
+struct SpxOutcome {
+  double lam_final, lam0;
+  int status, iter, reason, passes;
+  bool copy;              // y lies inside the l1 ball
+};
+
+// Algorithm 4 on the listed values of a team's blocks, from the bounds of
+// the start: `each` runs a function over the calling wave's share of them.
+// false when a wait ran out.
+template <typename Args, typename Each>
+__device__ __forceinline__ bool spx_team_loop(Team& team, TeamLds<kTeamBlock>& S, int& par,
+                                              const Args& A, const SpxStart& B, Each&& each,
+                                              SpxOutcome& R) {
+  const double r = A.r;
+  const bool l1 = A.l1 != 0;
+  bool ok = true;
+  int status = kRunning, iter = 0, reason = 0, passes = 1;
+  bool copy = false;
+  double lam_final = __builtin_nan(""), lam0 = __builtin_nan("");
+  double lo = -inf_d(), hi = inf_d(), lam = inf_d();
+  if (B.bad > 0.0) {
+    status = CQK_INVALID_ARG;
+  } else if (l1 && B.abs_sum <= r) {
+    copy = true;
+    status = CQK_OK;
+    lam_final = 0.0;
+    reason = 5;
+  } else {
+    // lam_J of the union of the lists, and the smallest block bound
+    lam = (B.cnt > 0.0) ? fmin((r - B.sum) / B.cnt, B.lam_min) : B.lam_min;
+    bool bound = true;  // lam >= lam* is known
+    if (A.xw != nullptr) {
+      if (!(B.vmax_i > -inf_d())) {
+        // an empty support: the fallback max{r/n, -max v} of Section 3.1,
+        // Newton's first step decides its side
+        lam = fmax(r / (double)A.n, -B.vmax);
+        bound = false;
+      } else {
+        double lw = r - B.vmax_i;
+        if (B.cnt_i > 0.0) lw = fmin(lw, (r - B.sum_i) / B.cnt_i);
+        lam = fmin(lam, lw);
+      }
+    }
+    lam = scalar(lam);
+    if (bound && B.cnt > 1.0) {
+      // candidates between lam and -max v (a lower bound of lam*)
+      double vc[2 * kTeamCand], tc[2 * kTeamCand], cl[kTeamCand];
+#pragma unroll
+      for (int j = 0; j < kTeamCand; ++j) {
+        vc[j] = vc[kTeamCand + j] = 0.0;
+        cl[j] = scalar(-B.vmax + (lam + B.vmax) / (double)(2u << j));
+      }
+      each([&](double t) {
+#pragma unroll
+        for (int j = 0; j < kTeamCand; ++j) {
+          const bool on = t + cl[j] > 0.0;
+          vc[j] += on ? 1.0 : 0.0;
+          vc[kTeamCand + j] += on ? t : 0.0;
+        }
+      });
+      ok = team_reduce<2 * kTeamCand, kTeamBlock>(team, S, par, vc, tc);
+#pragma unroll
+      for (int j = 0; j < kTeamCand; ++j)
+        if (tc[j] > 0.0) lam = fmin(lam, (r - tc[kTeamCand + j]) / tc[j]);
+      lam = scalar(lam);
+      passes += 1;
+    }
+    lam0 = lam;
+    if (bound) hi = lam;
+  }
+  // Algorithm 4's update, as spx_update without sets and trace
+  double cm_prev = -1.0;
+  while (ok && status == kRunning) {
+    double ve[3] = {0.0, 0.0, 0.0}, te[3];
+    each([&](double t) {
+      const double z = t + lam;
+      ve[0] += z > 0.0 ? z : 0.0;
+      ve[1] += z > 0.0 ? 1.0 : 0.0;
+      ve[2] += z >= 0.0 ? 1.0 : 0.0;
+    });
+    ok = team_reduce<3, kTeamBlock>(team, S, par, ve, te);
+    const double phi = te[0], cm = te[1], cp = te[2];
+    const int k = iter;
+    iter += 1;
+    passes += 1;
+    const bool below = (k == 0 && phi < r);
+    lo = below ? lam : lo;
+    hi = (!below && phi > r) ? lam : hi;
+    const double step = (phi - r) / (below ? cp : cm), next = lam - step;
+    int why = 0;
+    double at = lam;
+    if (phi == r || (k > 0 && phi <= r)) {
+      why = 4;
+    } else if (fabs(step) < A.tol) {
+      why = 2;
+      at = next;
+    } else if (k > 0 && cm == cm_prev) {
+      why = 4;
+      at = next;
+    } else if (next == lam) {
+      why = 2;
+    } else if (hi - lo < A.tol * fmax(fabs(hi), fabs(lo))) {
+      why = 3;
+    }
+    if (why != 0) {
+      status = CQK_OK;
+      lam_final = at;
+      reason = why;
+    } else if (iter >= A.max_iter) {
+      status = CQK_NOT_CONVERGED;
+      lam_final = lam;
+    }
+    cm_prev = cm;
+    lam = scalar(next);
+    status = scalar(status);
+  }
+  R = SpxOutcome{lam_final, lam0, status, iter, reason, passes, copy};
+  return ok;
 }
 
 template <typename TIn, int E>
@@ -1958,106 +2093,14 @@ __global__ __launch_bounds__(kTeamBlock) void spx_team_kernel(SpxTeamArgs A) {
       }
     }
   };
-  int status = kRunning, iter = 0, reason = 0, passes = 1;
-  bool copy = false;
-  double lam_final = __builtin_nan(""), lam0 = __builtin_nan("");
-  double lo = -inf_d(), hi = inf_d();
-  if (tot[2] > 0.0) {
-    status = CQK_INVALID_ARG;
-  } else if (l1 && tot[3] <= r) {
-    copy = true;
-    status = CQK_OK;
-    lam_final = 0.0;
-    reason = 5;
-  } else {
-    // lam_J of the union of the lists, and the smallest block bound
-    lam = (tot[0] > 0.0) ? fmin((r - tot[1]) / tot[0], tot[7]) : tot[7];
-    bool bound = true;  // lam >= lam* is known
-    if (xw != nullptr) {
-      if (!(vmaxi > -inf_d())) {
-        // an empty support: the fallback max{r/n, -max v} of Section 3.1,
-        // Newton's first step decides its side
-        lam = fmax(r / (double)n, -vmax);
-        bound = false;
-      } else {
-        double lw = r - vmaxi;
-        if (tot[4] > 0.0) lw = fmin(lw, (r - tot[5]) / tot[4]);
-        lam = fmin(lam, lw);
-      }
-    }
-    lam = scalar(lam);
-    if (ok && bound && tot[0] > 1.0) {
-      // candidates between lam and -max v (a lower bound of lam*)
-      double vc[2 * kTeamCand], tc[2 * kTeamCand], cl[kTeamCand];
-#pragma unroll
-      for (int j = 0; j < kTeamCand; ++j) {
-        vc[j] = vc[kTeamCand + j] = 0.0;
-        cl[j] = scalar(-vmax + (lam + vmax) / (double)(2u << j));
-      }
-      each([&](double t) {
-#pragma unroll
-        for (int j = 0; j < kTeamCand; ++j) {
-          const bool on = t + cl[j] > 0.0;
-          vc[j] += on ? 1.0 : 0.0;
-          vc[kTeamCand + j] += on ? t : 0.0;
-        }
-      });
-      ok = team_reduce<2 * kTeamCand, kTeamBlock>(team, S, par, vc, tc);
-#pragma unroll
-      for (int j = 0; j < kTeamCand; ++j)
-        if (tc[j] > 0.0) lam = fmin(lam, (r - tc[kTeamCand + j]) / tc[j]);
-      lam = scalar(lam);
-      passes += 1;
-    }
-    lam0 = lam;
-    if (bound) hi = lam;
-  }
-  // Algorithm 4's update, as spx_update without sets and trace
-  double cm_prev = -1.0;
-  while (ok && status == kRunning) {
-    double ve[3] = {0.0, 0.0, 0.0}, te[3];
-    each([&](double t) {
-      const double z = t + lam;
-      ve[0] += z > 0.0 ? z : 0.0;
-      ve[1] += z > 0.0 ? 1.0 : 0.0;
-      ve[2] += z >= 0.0 ? 1.0 : 0.0;
-    });
-    ok = team_reduce<3, kTeamBlock>(team, S, par, ve, te);
-    const double phi = te[0], cm = te[1], cp = te[2];
-    const int k = iter;
-    iter += 1;
-    passes += 1;
-    const bool below = (k == 0 && phi < r);
-    lo = below ? lam : lo;
-    hi = (!below && phi > r) ? lam : hi;
-    const double step = (phi - r) / (below ? cp : cm), next = lam - step;
-    int why = 0;
-    double at = lam;
-    if (phi == r || (k > 0 && phi <= r)) {
-      why = 4;
-    } else if (fabs(step) < A.tol) {
-      why = 2;
-      at = next;
-    } else if (k > 0 && cm == cm_prev) {
-      why = 4;
-      at = next;
-    } else if (next == lam) {
-      why = 2;
-    } else if (hi - lo < A.tol * fmax(fabs(hi), fabs(lo))) {
-      why = 3;
-    }
-    if (why != 0) {
-      status = CQK_OK;
-      lam_final = at;
-      reason = why;
-    } else if (iter >= A.max_iter) {
-      status = CQK_NOT_CONVERGED;
-      lam_final = lam;
-    }
-    cm_prev = cm;
-    lam = scalar(next);
-    status = scalar(status);
-  }
+  SpxOutcome O{};
+  if (ok)
+    ok = spx_team_loop(
+        team, S, par, A,
+        SpxStart{tot[0], tot[1], tot[2], tot[3], tot[4], tot[5], vmax, vmaxi, tot[7]}, each, O);
+  const int status = O.status;
+  const bool copy = O.copy;
+  const double lam_final = O.lam_final;
   if (!ok) {
     if (tid == 0) A.res->gave_up = 1;
     return;
@@ -2171,16 +2214,171 @@ __global__ __launch_bounds__(kTeamBlock) void spx_team_kernel(SpxTeamArgs A) {
   if (blockIdx.x == 0 && tid == 0) {
     SpxTeamResult& R = *A.res;
     R.lam_final = lam_final;
-    R.lam0 = lam0;
+    R.lam0 = O.lam0;
     R.sum_abs = tot[3];
     R.n_init = (status == CQK_INVALID_ARG || copy) ? 0.0 : tot[0];
     R.status = status;
-    R.iter = iter;
-    R.passes = passes;
-    R.stop_reason = reason;
+    R.iter = O.iter;
+    R.passes = O.passes;
+    R.stop_reason = O.reason;
     R.copy = copy ? 1 : 0;
     R.tag = team.tag;
     R.nnz = nnz;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// What follows the Algorithm 2 pass over a long y (spx_condat_kernel), in one
+// launch: the merge of its block records, the candidates, Algorithm 4 on the
+// survivors and, for a dense output, x at the ones above -lam.  The blocks
+// (one per compute unit) share the wave regions; a wave lists its survivors
+// above the merged bound in LDS, or sweeps its regions when they do not fit.
+// Sets of more than max_n values, bad values and a y inside the l1 ball are
+// left to the kernels behind, as is everything when a wait runs out (values
+// already written to x are then written again).
+// Bound by latency: five to seven exchanges of about 3 us.  Whole calls,
+// against the eight kernels behind the pass: 1e8 FP32 values 240 -> 195 us
+// (the pass takes 144), sparse l1 of them 254 -> 206, 12 582 913 103 -> 70;
+// 6.4e6 FP64 values 95 -> 65.
+// ---------------------------------------------------------------------------
+struct SpxRestArgs {
+  const void* val;       // buffer 1 of the compacted sets
+  const uint32_t* idx;
+  const int32_t* cnt;
+  int64_t region, nr;
+  const double* partials;
+  int32_t G;             // block records in partials
+  const void* xw;        // a warm start (only whether)
+  void* x;               // null: sparse output, written by the kernels behind
+  int64_t n, max_n;
+  double r, tol;
+  int32_t l1, max_iter;
+  SpxState* st;
+  uint64_t* slots;
+  uint64_t limit;
+  uint32_t tag;
+  SpxTeamResult* res;    // gave_up is set until block 0 clears it
+  const TeamTags* tags;  // queued or captured call
+};
+
+template <typename TIn>
+__global__ __launch_bounds__(kTeamBlock) void spx_rest_kernel(SpxRestArgs A) {
+  constexpr int NW = kTeamBlock / kWave;
+  constexpr int CAP = kTeamListBytes / (int)sizeof(TIn) / NW;
+  __shared__ TeamLds<kTeamBlock> S;
+  __shared__ TIn lists[NW][CAP];
+  if (A.st->status != kRunning || A.st->team_done) return;
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1), wid = scalar(tid / kWave);
+  const bool l1 = A.l1 != 0;
+  const int64_t tw = (int64_t)gridDim.x * NW, w0 = (int64_t)blockIdx.x * NW + wid;
+  if (tid == 0) S.gave_up = 0;
+  // the block's share of the pass's records
+  double v1[7] = {0.0, 0.0, 0.0, 0.0, 0.0, inf_d(), inf_d()};
+  double vi = inf_d(), ci = 0.0, si = 0.0;
+  for (int g = blockIdx.x + tid * gridDim.x; g < A.G; g += kTeamBlock * gridDim.x) {
+    auto rec = [&](int i) { return A.partials[(size_t)i * A.G + g]; };
+    v1[0] += rec(C_CNT);
+    v1[1] += rec(C_SUM);
+    v1[2] += rec(C_BAD);
+    v1[3] += rec(C_ABS);
+    v1[5] = fmin(v1[5], -rec(C_NSUM + 1));
+    v1[6] = fmin(v1[6], rec(C_NSUM));
+    ci += rec(C_CNTI);
+    si += rec(C_SUMI);
+    vi = fmin(vi, -rec(C_NSUM + 2));
+  }
+  __syncthreads();  // the state is read before this block's first record
+  Team team = grid_team(A.slots, (A.tags != nullptr ? A.tags->base : 0u) + A.tag, A.limit);
+  int par = 0;
+  double tot[7], ti[3] = {0.0, 0.0, inf_d()};
+  bool ok = team_reduce<7, kTeamBlock, 2>(team, S, par, v1, tot);
+  if (ok && A.xw != nullptr) {
+    const double v2[3] = {ci, si, vi};
+    ok = team_reduce<3, kTeamBlock, 1>(team, S, par, v2, ti);
+  }
+  if (!ok || tot[2] > 0.0 || (l1 && tot[3] <= A.r) || !(tot[0] <= (double)A.max_n)) return;
+  const double bound = (tot[0] > 0.0) ? fmin((A.r - tot[1]) / tot[0], tot[6]) : tot[6];
+  const TIn thr = round_down_to<TIn>(-bound);
+  auto absl = [&](TIn t) { return l1 ? absval(t) : t; };
+  // fn(value, place) over the survivors above `above` in the wave's regions
+  auto sweep = [&](TIn above, auto&& fn) {
+    for (int64_t rid = w0; rid < A.nr; rid += tw) {
+      const int m = scalar(A.cnt[rid]);
+      const int64_t at = rid * A.region;
+      const TIn* val = (const TIn*)A.val + at;
+      for (int i0 = 0; i0 < m; i0 += kWave) {
+        const bool in = i0 + lane < m;
+        const TIn t = in ? val[i0 + lane] : TIn(0);
+        fn(t, at + i0 + lane, in && absl(t) > above);
+      }
+    }
+  };
+  TIn* list = lists[wid];
+  int m = 0;
+  sweep(thr, [&](TIn t, int64_t, bool keep) {
+    const uint64_t b = __ballot(keep);
+    const int at = m + lane_prefix(b);
+    if (keep && at < CAP) list[at] = absl(t);
+    m += __popcll(b);
+  });
+  m = scalar(m);
+  auto each = [&](auto&& fn) {
+    if (m <= CAP) {
+      for (int i = lane; i < m; i += kWave) fn((double)list[i]);
+    } else {
+      sweep(thr, [&](TIn t, int64_t, bool keep) {
+        if (keep) fn((double)absl(t));
+      });
+    }
+  };
+  SpxOutcome O{};
+  ok = spx_team_loop(team, S, par, A,
+                     SpxStart{tot[0], tot[1], tot[2], tot[3], ti[0], ti[1], -tot[5], -ti[2],
+                              tot[6]},
+                     each, O);
+  if (!ok) return;
+  const double lam = O.lam_final;
+  if (A.x != nullptr) {
+    double sums[2] = {0.0, 0.0};
+    TIn* x = (TIn*)A.x;
+    sweep(round_down_to<TIn>(-lam), [&](TIn t, int64_t at, bool keep) {
+      if (keep) {
+        const TIn xo = spx_x_of<TIn, double>(t, lam, l1, false);
+        x[A.idx[at]] = xo;
+        sums[0] += fabs((double)xo);
+        sums[1] += (xo != TIn(0)) ? 1.0 : 0.0;
+      }
+    });
+    __shared__ double lds[2 * NW], tot2[2];
+    block_reduce<2, 0, 0, kTeamBlock>(sums, nullptr, nullptr, lds, tot2);
+    if (tid < 2) A.res->part[2 * blockIdx.x + tid] = tot2[tid];
+  }
+  if (blockIdx.x == 0 && tid == 0) {
+    SpxTeamResult& R = *A.res;
+    R.lam_final = lam;
+    R.lam0 = O.lam0;
+    R.sum_abs = tot[3];
+    R.n_init = tot[0];
+    R.status = O.status;
+    R.iter = O.iter;
+    R.passes = O.passes + 1;
+    R.stop_reason = O.reason;
+    R.copy = 0;
+    R.gave_up = 0;
+    SpxState* st = A.st;
+    st->lam = st->lam_final = lam;
+    st->lam0 = O.lam0;
+    st->sum_abs = tot[3];
+    st->vmax = -tot[5];
+    st->n_init = st->n_src = (int64_t)tot[0];
+    st->src = 2;
+    st->x_zeroed = 1;
+    st->iter = O.iter;
+    st->passes += O.passes;
+    st->stop_reason = O.reason;
+    st->team_done = A.x != nullptr ? 1 : 0;
+    st->status = O.status;
   }
 }
 
@@ -2361,7 +2559,38 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
   const uint32_t need = (uint32_t)std::min(o.max_iter, 1 << 20) + 8;
   const bool team = tE != 0 && condat && r != 0.0 && sizeof(TA) == 8 && !o.trace && !o.timing &&
                     o.max_iter <= (1 << 20) && team_ready(ctx, need);
-  SpxTeamCtl* const ctl = team ? (SpxTeamCtl*)((char*)ctx->team.ptr + kTeamSlotBytes) : nullptr;
+  // Longer y: one launch behind the Algorithm 2 pass.
+  const bool rest = tE == 0 && condat && r != 0.0 && sizeof(TA) == 8 && !o.trace && !o.timing &&
+                    o.compaction != CQK_COMPACT_OFF && o.max_iter <= (1 << 20) &&
+                    team_ready(ctx, need);
+  if (rest) tT = std::min(ctx->num_cus, kTeamMax);
+  SpxTeamCtl* const ctl =
+      (team || rest) ? (SpxTeamCtl*)((char*)ctx->team.ptr + kTeamSlotBytes) : nullptr;
+  auto launch_rest = [&](SpxTeamResult* res, const TeamTags* tags) {
+    SpxRestArgs R{};
+    R.val = A.val[1];
+    R.idx = A.idx[1];
+    R.cnt = A.cnt[1];
+    R.region = chunk0 / kWaves;
+    R.nr = NR;
+    R.partials = A.partials;
+    R.G = G0;
+    R.xw = xw;
+    R.x = A.x;
+    R.n = n;
+    R.max_n = (int64_t)kRestMax * tT;
+    R.r = r;
+    R.tol = init.tol;
+    R.l1 = init.l1;
+    R.max_iter = o.max_iter;
+    R.st = A.st;
+    R.slots = (uint64_t*)ctx->team.ptr;
+    R.limit = ctx->team_wait;
+    R.tag = tags != nullptr ? 0u : ctx->team_tag;
+    R.res = res;
+    R.tags = tags;
+    hipLaunchKernelGGL(spx_rest_kernel<TIn>, dim3(tT), dim3(kTeamBlock), 0, s, R);
+  };
   auto launch_team = [&](SpxTeamResult* res, SpxTeamCtl* tc) {
     SpxTeamArgs T{};
     T.y = y;
@@ -2399,6 +2628,31 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
     inf->abs_bx = p;
     inf->n_free = (int64_t)nf;
   };
+  // a waiting call's outcome, read from its result
+  auto answer = [&](const SpxTeamResult& R, int launches, double fin_bytes) -> cqk_status {
+    ctx->last_trace.clear();
+    ctx->last_pass_ms.clear();
+    cqk_info out;
+    std::memset(&out, 0, sizeof(out));
+    out.status = R.status;
+    out.iterations = R.iter;
+    out.passes = R.passes;
+    out.stop_reason = R.stop_reason;
+    out.lambda = R.lam_final;
+    out.lambda0 = R.lam0;
+    team_sums(R, tT, &out);
+    out.n_after_init = (int64_t)R.n_init;
+    out.finalize_bytes = fin_bytes;
+    out.pass_launches = launches;
+    if (sparse && sp->nnz > sp->cap) out.status = CQK_BUFFER_TOO_SMALL;
+    ctx->trivial = out;
+    ctx->last = [ctx](cqk_info* inf) -> cqk_status {
+      *inf = ctx->trivial;
+      return CQK_OK;
+    };
+    if (info) *info = out;
+    return CQK_OK;
+  };
   if (team && !deferred) {
     SpxTeamResult* res = (SpxTeamResult*)ctx->host_pinned;
     res->gave_up = 0;
@@ -2406,42 +2660,23 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
     if (hip_ok(hipGetLastError()) != CQK_OK) return CQK_DEVICE_ERROR;
     ctx->team_tag += need;
     if (hip_ok(hipStreamSynchronize(s)) != CQK_OK) return CQK_DEVICE_ERROR;
-    const SpxTeamResult& R = *res;
-    if (!R.gave_up) {
-      ctx->team_tag = R.tag;
-      ctx->last_trace.clear();
-      ctx->last_pass_ms.clear();
-      cqk_info out;
-      std::memset(&out, 0, sizeof(out));
-      out.status = R.status;
-      out.iterations = R.iter;
-      out.passes = R.passes;
-      out.stop_reason = R.stop_reason;
-      out.lambda = R.lam_final;
-      out.lambda0 = R.lam0;
-      team_sums(R, tT, &out);
-      out.n_after_init = (int64_t)R.n_init;
-      out.finalize_bytes = (double)n * sizeof(TIn) * (sparse ? 1.0 : 2.0);
-      out.pass_launches = 1;
+    if (!res->gave_up) {
+      ctx->team_tag = res->tag;
       if (sparse) {
         ctx->bitmap_clean = true;  // not touched
-        sp->nnz = (out.status == CQK_OK || out.status == CQK_NOT_CONVERGED) ? R.nnz : 0;
-        if (sp->nnz > sp->cap) out.status = CQK_BUFFER_TOO_SMALL;
+        sp->nnz = (res->status == CQK_OK || res->status == CQK_NOT_CONVERGED) ? res->nnz : 0;
       }
-      ctx->trivial = out;
-      ctx->last = [ctx](cqk_info* inf) -> cqk_status {
-        *inf = ctx->trivial;
-        return CQK_OK;
-      };
-      if (info) *info = out;
-      return CQK_OK;
+      return answer(*res, 1, (double)n * sizeof(TIn) * (sparse ? 1.0 : 2.0));
     }
   }
   // the Algorithm 2 sample kernel stores the initial state itself, unless a
   // one-launch projection queued before it may have left its own
   const bool init_in_sample = condat && r != 0.0;
-  const bool team_queued = team && deferred;
-  if (team_queued) {
+  const bool team_queued = (team || rest) && deferred;
+  if (rest && deferred) {
+    hipLaunchKernelGGL(team_init_kernel<SpxState>, dim3(1), dim3(256), 0, s, A.st, init,
+                       &ctl->tags, &ctl->res.gave_up, (uint64_t*)ctx->team.ptr, need);
+  } else if (team_queued) {
     hipLaunchKernelGGL(team_init_kernel<SpxState>, dim3(1), dim3(256), 0, s, A.st, init,
                        &ctl->tags, &ctl->res.gave_up, (uint64_t*)ctx->team.ptr, need);
     launch_team(&ctl->res, ctl);
@@ -2500,6 +2735,7 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
       return CQK_DEVICE_ERROR;
     return hip_ok(hipStreamSynchronize(s));
   };
+  bool rest_done = false;  // spx_rest_kernel ran the loop of a waiting sparse call
   if (r == 0.0) {
     fin_chain();
     if (!deferred && wait_state() != CQK_OK) return CQK_DEVICE_ERROR;
@@ -2517,14 +2753,34 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
         launch(spx_condat_kernel<TIn, true>, G0);
       else
         launch(spx_condat_kernel<TIn, false>, G0);
-      reduce(spx_condat_merge_kernel<TIn, TA>, G0);
+      if (rest && deferred) {
+        launch_rest(&ctl->res, &ctl->tags);
+      } else if (rest) {
+        SpxTeamResult* res = (SpxTeamResult*)ctx->host_pinned;
+        res->gave_up = 1;
+        launch_rest(res, nullptr);
+        ctx->team_tag += need;
+        ++npass;
+        if (sparse) {
+          fin_chain();
+          if (wait_state() != CQK_OK) return CQK_DEVICE_ERROR;
+          rest_done = hs->status != kRunning;
+        } else {
+          if (hip_ok(hipGetLastError()) != CQK_OK ||
+              hip_ok(hipStreamSynchronize(s)) != CQK_OK)
+            return CQK_DEVICE_ERROR;
+          if (!res->gave_up)
+            return answer(*res, npass, (2.0 * sizeof(TIn) + 4.0) * res->n_init);
+        }
+      }
+      if (!rest_done) reduce(spx_condat_merge_kernel<TIn, TA>, G0);
     } else if (formula) {
       launch(spx_formula_kernel<TIn>, G0);
       reduce(spx_formula_update_kernel, G0);
     }
     // a small instance whose start reads y anyway runs in one block at once
     if (init.tail) tail();
-    if (condat) {
+    if (condat && !rest_done) {
       launch(spx_pass_kernel<TIn, TA, true>, G0);
       reduce(spx_start_update_kernel<TIn, TA>, G0);
     }
@@ -2534,7 +2790,7 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
     // leaves a set small enough for the one-block loop, which then takes a
     // pass (the pack) and an update (the loop)
     int batch = deferred ? max_launch : 2;
-    for (;;) {
+    while (!rest_done) {
       const int k = std::min(batch, max_launch - launched);
       for (int i = 0; i < k; ++i) {
         launch(spx_pass_kernel<TIn, TA, false>, G0);

@@ -213,3 +213,114 @@ def test_queued_and_replayed(ctx, n, l1):
         torch.cuda.synchronize()
         eager, _ = fn(t, 1.0)
         assert torch.equal(x, eager)
+
+
+# ---- past those sizes: one launch behind the pass over y ----
+
+LONG = {F32: 12_582_913, F64: 6_291_457}
+
+
+def _long_data(case, n, g):
+    if case == "few":
+        return g.standard_normal(n), 1.0
+    if case == "clustered":       # neighbours: a few waves hold every survivor
+        y = g.standard_normal(n)
+        y[1000:201_000] = 50.0 + 1e-3 * g.standard_normal(200_000)
+        return y, 10_000.0
+    if case == "spread":          # lists longer than LDS in every wave
+        y = g.uniform(0.0, 1.0, n)
+        return y, 0.45 * n * 0.45
+    if case == "all_free":        # more survivors than the launch takes
+        return 1.0 + 1e-3 * g.standard_normal(n), float(n)
+    if case == "ties":
+        return np.full(n, 0.25), 1.0
+    if case == "inside":
+        return 1e-9 * g.standard_normal(n), 1.0
+    if case == "zeros":
+        return np.zeros(n), 2.0
+    return np.concatenate([g.standard_normal(n - 1), [1e6]]), 1.0   # one_big
+
+
+@pytest.mark.parametrize("dtype", [F32, F64])
+@pytest.mark.parametrize("case", ["few", "clustered", "spread", "all_free", "ties", "inside",
+                                  "zeros", "one_big"])
+def test_long_inputs(ctx, dtype, case):
+    n = LONG[dtype]
+    y, r = _long_data(case, n, np.random.default_rng(17))
+    y = y.astype(_np(dtype))
+    t = torch.from_numpy(y).cuda()
+    for l1 in (False, True):
+        x, info = _both(ctx, t, r, l1, dtype)
+        _wait(ctx, 0)
+        x0, info0 = (ctx.project_l1 if l1 else ctx.project_simplex)(t, r)
+        _wait(ctx, 2_000_000)
+        if case in ("few", "clustered", "one_big"):
+            assert info["pass_launches"] == 3 < info0["pass_launches"]
+        assert abs(info["lambda"] - info0["lambda"]) <= 1e-13 * (1.0 + abs(info0["lambda"]))
+        _check(x.cpu().numpy(), y, r, l1, dtype)
+
+
+@pytest.mark.parametrize("dtype", [F32, F64])
+def test_long_warm_starts(ctx, dtype):
+    n = LONG[dtype]
+    y = W.simplex_input(n, 9, "normal", _np(dtype))
+    t = torch.from_numpy(y).cuda()
+    for l1 in (False, True):
+        fn = ctx.project_l1 if l1 else ctx.project_simplex
+        cold, _ = fn(t, 1.0)
+        for xbar in (cold, torch.zeros_like(cold), torch.ones_like(cold)):
+            x, info = _both(ctx, t, 1.0, l1, dtype, xbar=xbar)
+            assert info["pass_launches"] == 3
+            _check(x.cpu().numpy(), y, 1.0, l1, dtype)
+
+
+def test_long_bad_values_and_room(ctx):
+    n = LONG[F32]
+    y = W.simplex_input(n, 2, "uniform", np.float32)
+    t = torch.from_numpy(y).cuda()
+    i0, v0, _ = ctx.project_simplex_sparse(t, 1.0)
+    i, v, _ = ctx.project_simplex_sparse(t, 1.0, cap=5)
+    assert torch.equal(i, i0) and torch.equal(v, v0)
+    for bad in (np.nan, np.inf, -np.inf):
+        t[n - 3] = float(bad)
+        _, info = ctx.project_simplex(t, 1.0, check=False)
+        assert info["status"] == 2
+        _, _, info = ctx.project_l1_sparse(t, 1.0, check=False)
+        assert info["status"] == 2
+
+
+def test_long_give_up_queued_and_replayed(ctx):
+    n = LONG[F64]
+    ctx.reserve(n)
+    y = W.simplex_input(n, 5, "normal", np.float64)
+    t = torch.from_numpy(y).cuda()
+    first, info1 = ctx.project_simplex(t, 1.0)
+    for sync in (True, False):
+        for ticks in (1, 0, 2_000_000):
+            _wait(ctx, ticks)
+            x, info = ctx.project_simplex(t, 1.0, out=torch.full_like(t, 9.0), sync=sync,
+                                          max_iter=30)
+            if not sync:
+                st, info = ctx.ctx_last_info()
+                assert st == 0
+            _check(x.cpu().numpy(), y, 1.0, False, F64)
+            i, v, _ = ctx.project_simplex_sparse(t, 1.0)
+            assert torch.equal(i, torch.nonzero(first)[:, 0])
+            if ticks == 2_000_000:
+                assert torch.equal(x, first)
+                for k in ("lambda", "lambda0", "iterations", "stop_reason", "n_free", "residual"):
+                    assert info[k] == info1[k], k
+    x = torch.empty_like(t)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(s):
+        with torch.cuda.graph(graph, stream=s):
+            ctx.project_simplex(t, 1.0, out=x, max_iter=20)
+    for seed in (6, 7, 5):
+        t.copy_(torch.from_numpy(W.simplex_input(n, seed, "normal", np.float64)))
+        x.fill_(3.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        eager, _ = ctx.project_simplex(t, 1.0)
+        assert torch.equal(x, eager)
