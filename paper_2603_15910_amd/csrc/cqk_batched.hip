@@ -92,7 +92,11 @@ constexpr int CTR_STAT0 = kCtrLine, CTR_STAT1 = (1 + kQueues) * kCtrLine,
               CTR_OUTCOME = (1 + 2 * kQueues) * kCtrLine,  // what the host reads
               CTR_QUEUE0 = CTR_OUTCOME, CTR_QUEUE1 = CTR_QUEUE0 + kQueues * kCtrLine,
               CTR_TOTAL = CTR_QUEUE1 + kQueues * kCtrLine;
-static_assert(CTR_LBASE + kNBW <= kCtrLine, "the bucket starts fit line 0");
+// rows whose length has at most kGroupBucket bits (general form, four to a
+// wave): where they start in the list
+constexpr int kGroupBucket = 7;
+constexpr int CTR_GROUPS = CTR_LBASE + kNBW;
+static_assert(CTR_GROUPS < kCtrLine, "the bucket starts fit line 0");
 
 // A block's outcome, in LDS until the block ends.
 struct BatStat {
@@ -296,6 +300,7 @@ __global__ __launch_bounds__(kPBlock) void bat_place_kernel(Args A) {
       A.counters[CTR_NITEMS] = nlong + (nshort + kWaves - 1) / kWaves;
       A.counters[CTR_GAVE_UP] = 0;
       for (int k = 0; k < kNBW; ++k) A.counters[CTR_LBASE + k] = base[kNBW + k];
+      A.counters[CTR_GROUPS] = base[kGroupBucket];
     }
   }
   __syncthreads();
@@ -1274,6 +1279,7 @@ struct BatCqkArgs {
   int32_t nseg;
   int32_t small_max;    // longest wave row
   int32_t short_first;  // 1: wave rows are handed out first
+  int32_t grouped;      // 1: rows of up to kGroupBucket bits are the group kernel's
   int32_t lambda0_mode; // CQK_LAMBDA0_ZERO, _FORMULA or _USER
   int32_t max_iter;
   double tol;
@@ -1467,6 +1473,151 @@ __device__ void cqk_short_row(const BatCqkArgs& A, int s, int64_t base, int64_t 
     }
   }
   if (lane == 0) cqk_row_report(A, s, st, lam, stat);
+}
+
+// Rows of at most kGroupLanes * kGroupSlots values, kWave / kGroupLanes of
+// them side by side in a wave.
+constexpr int kGroupLanes = 16, kGroupSlots = 8;
+// Calls of at least this many rows take the group kernel: 16 384 FP32 rows of
+// 16 to 127 values 95 -> 75 us; a call without such rows pays for the empty
+// launch (128 to 512 values 111 -> 113 us), which at 8192 rows is as much as
+// it saves on a mixed call.
+constexpr int kGroupMinRows = 16384;
+static_assert(kGroupLanes * kGroupSlots >= (1 << kGroupBucket) - 1, "every row of the bucket fits");
+
+// Sum over a group's lanes (a DPP row), the same bits in each of them.
+__device__ __forceinline__ double group_sum(double v) {
+  v += dpp_move<dpp::kXor1, 0xF>(v, 0.0);
+  v += dpp_move<dpp::kXor2, 0xF>(v, 0.0);
+  v += dpp_move<dpp::kHalfMirror, 0xF>(v, 0.0);
+  v += dpp_move<dpp::kMirror, 0xF>(v, 0.0);
+  return v;
+}
+
+__device__ __forceinline__ KeySum group_ks_min(KeySum v) {
+#pragma unroll
+  for (int o = kGroupLanes / 2; o > 0; o >>= 1)
+    v = ks_min(v, KeySum{__shfl_xor(v.k, o, kWave), __shfl_xor(v.w, o, kWave)});
+  return v;
+}
+
+// Short rows side by side: the reductions and the scalar update, which cost a
+// wave the same however short its row is, run once for four of them.  A group
+// without a row has L < 0.
+template <typename TIn>
+__device__ __forceinline__ void cqk_group_rows(const BatCqkArgs& A, int s, int64_t base,
+                                               int64_t L, double r, BatStat& stat) {
+  constexpr int SP = kGroupSlots, GL = kGroupLanes;
+  const CqkArrays<TIn> V(A);
+  // what is made from the thread index stays here: hoisted out of the loop
+  // over the work items it would be spilled
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & (GL - 1);
+  double c[SP], sv[SP], bl[SP], bu[SP];
+  double bad = 0.0, sc = 0.0, ss = 0.0;
+#pragma unroll
+  for (int k = 0; k < SP; ++k) c[k] = sv[k] = bl[k] = bu[k] = 0.0;
+  // slots in use by any of the rows
+  int nk = 0;
+#pragma unroll
+  for (int g = 0; g < kWave; g += GL)
+    nk = max(nk, (__builtin_amdgcn_readlane((int)L, g) + GL - 1) / GL);
+  {
+    // every load issued before the first use (index clamped to the row; a
+    // group without values reads place 0 of the call's arrays)
+    TIn rd[SP], ra[SP], rb[SP], rl[SP], ru[SP];
+#pragma unroll
+    for (int k = 0; k < SP; ++k) {
+      if (k < nk) {
+        const int64_t i = lane + k * GL;
+        const int64_t e = (L > 0) ? base + (i < L ? i : L - 1) : 0;
+        rd[k] = V.d[e];
+        ra[k] = V.a[e];
+        rb[k] = V.b[e];
+        rl[k] = V.l[e];
+        ru[k] = V.u[e];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < SP; ++k) {
+      if (k < nk && lane + k * GL < L) {
+        to_form((double)rd[k], (double)ra[k], (double)rb[k], (double)rl[k], (double)ru[k], c[k],
+                sv[k], bl[k], bu[k], bad);
+        sc += c[k];
+        ss += sv[k];
+      }
+    }
+  }
+  GenState st = cqk_row_state(A, r);
+  bad = group_sum(bad);
+  if (A.lambda0_mode == CQK_LAMBDA0_FORMULA) {
+    const double tc = group_sum(sc), ts = group_sum(ss);
+    if (L > 0) st.lam = st.lam0 = (ts > 0.0) ? (r - tc) / ts : 0.0;
+  }
+  if (L < 0) {
+    st.status = CQK_OK;
+  } else if (bad > 0.0 || !(fabs(r) < inf_d())) {
+    st.status = CQK_INVALID_ARG;
+  } else if (L == 0) {
+    st.status = (r == 0.0) ? CQK_OK : CQK_INFEASIBLE;
+    st.lam_final = 0.0;
+  }
+  while (__ballot(st.status == kRunning) != 0) {
+    if (st.status == kRunning && st.mode == kModeEval) {
+      Acc acc;
+      acc_init(acc);
+#pragma unroll
+      for (int k = 0; k < SP; ++k)
+        if (k < nk) eval_index<false>(acc, c[k], sv[k], bl[k], bu[k], st.lam, 0.0, 0.0);
+      double t[NSUM];
+#pragma unroll
+      for (int i = 0; i < NSUM; ++i) t[i] = 0.0;
+      t[P_P] = group_sum(acc.s[P_P]);
+      t[P_A] = group_sum(acc.s[P_A]);
+      t[P_QP] = group_sum(acc.s[P_QP]);
+      t[P_QM] = group_sum(acc.s[P_QM]);
+      update_after_eval<false>(&st, t, nullptr);
+    } else if (st.status == kRunning) {
+      KeySum ks[2] = {KeySum{inf_d(), 0.0}, KeySum{inf_d(), 0.0}};
+#pragma unroll
+      for (int k = 0; k < SP; ++k)
+        if (k < nk) bkpt_index(ks, c[k], sv[k], bl[k], bu[k], st.lam);
+      ks[0] = group_ks_min(ks[0]);
+      ks[1] = group_ks_min(ks[1]);
+      update_after_bkpt<false>(&st, ks, nullptr);
+    }
+  }
+  const bool ok = cqk_has_lambda(st);
+  const double lam = ok ? st.lam_final : __builtin_nan("");
+  // the rows again (from cache): a slot's loads unguarded, issued together
+  constexpr int H = 4;
+#pragma unroll
+  for (int k0 = 0; k0 < SP; k0 += H) {
+    if (k0 < nk) {
+      TIn rd[H], ra[H], rb[H], rl[H], ru[H];
+#pragma unroll
+      for (int k = 0; k < H; ++k) {
+        const int64_t i = lane + (k0 + k) * GL;
+        const int64_t e = (L > 0) ? base + (i < L ? i : L - 1) : 0;
+        rd[k] = V.d[e];
+        ra[k] = V.a[e];
+        rb[k] = V.b[e];
+        rl[k] = V.l[e];
+        ru[k] = V.u[e];
+      }
+#pragma unroll
+      for (int k = 0; k < H; ++k) {
+        const int64_t i = lane + (k0 + k) * GL;
+        if (k0 + k < nk) {
+          const double xv = fmin(fmax(fma((double)rb[k], lam, (double)ra[k]) / (double)rd[k],
+                                      (double)rl[k]), (double)ru[k]);
+          if (i < L) V.x[base + i] = (TIn)(ok ? xv : __builtin_nan(""));
+        }
+      }
+    }
+  }
+  if (lane == 0 && L >= 0) cqk_row_report(A, s, st, lam, stat);
 }
 
 // ---------------------------------------------------------------------------
@@ -1950,7 +2101,8 @@ __global__ __launch_bounds__(kBlock, 3) void bat_cqk_solve_kernel(BatCqkArgs A) 
   __shared__ CqkLds S;
   const int nlong = A.counters[CTR_NLONG];
   const int nstream = streamed_rows<TIn>(A);
-  const int nshort = A.counters[CTR_NSHORT];
+  // the shortest may be the group kernel's
+  const int nshort = A.grouped ? A.counters[CTR_GROUPS] - nlong : A.counters[CTR_NSHORT];
   const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int per = min(kRowsPerWave, max(1, nshort / ((int)gridDim.x * kWaves * kRowsPerWave)));
   const int ngroups = (nshort + kWaves * per - 1) / (kWaves * per);
@@ -1992,6 +2144,39 @@ __global__ __launch_bounds__(kBlock, 3) void bat_cqk_solve_kernel(BatCqkArgs A) 
     for (int j = 0; j < per && k0 + j * kWaves < nshort; ++j)
       cqk_short_row<SP, TIn>(A, __builtin_amdgcn_readlane(id, j), lane_value(first, j),
                              lane_value(len, j), lane_value(rhs, j), stat);
+  }
+  __syncthreads();
+  stat_flush<true>(stat, A.counters + CTR_STAT0);
+}
+
+// The shortest rows (list entries from CTR_GROUPS on), four to a wave at a
+// time; all about as long, so they are handed out by number.  Bound by FP64
+// instructions, of which a row to a wave spends about half on reductions and
+// the scalar update.  65 536 rows, whole calls, a row to a wave against this:
+// 100 values FP32 212 -> 144 us, FP64 264 -> 153; 16 values FP32 202 -> 120,
+// FP64 220 -> 116.  (Two rows of up to 256 values to a wave gained nothing.)
+template <typename TIn>
+__global__ __launch_bounds__(kBlock, 3) void bat_cqk_group_kernel(BatCqkArgs A) {
+  __shared__ BatStat stat;
+  stat_init(stat);
+  __syncthreads();
+  const int lane = threadIdx.x & (kWave - 1);
+  constexpr int NG = kWave / kGroupLanes;
+  const int first = A.counters[CTR_GROUPS];
+  const int end = A.counters[CTR_NLONG] + A.counters[CTR_NSHORT];
+  const int wave = blockIdx.x * kWaves + scalar((int)(threadIdx.x / kWave));
+  for (int64_t k = first + (int64_t)wave * NG; k < end; k += (int64_t)gridDim.x * kWaves * NG) {
+    const int64_t e = k + lane / kGroupLanes;
+    int id = 0;
+    int64_t base = 0, len = -1;
+    double r = 0.0;
+    if (e < end) {
+      id = A.list[e];
+      base = A.lrow[2 * e];
+      len = A.lrow[2 * e + 1];
+      r = A.r[id];
+    }
+    cqk_group_rows<TIn>(A, id, base, len, r, stat);
   }
   __syncthreads();
   stat_flush<true>(stat, A.counters + CTR_STAT0);
@@ -2484,6 +2669,11 @@ void launch_cqk_forward(cqk_ctx* ctx, const cqk_batch_schedule& sc, BatCqkArgs A
   cqk_apply_schedule(ctx, sc, &A, &grid);
   plan(ctx, A);
   launch_teams(ctx, A, bat_cqk_team_kernel<TIn>);
+  // the shortest rows side by side, when there are enough of them to go round
+  A.grouped = A.nseg >= kGroupMinRows ? 1 : 0;
+  if (A.grouped)
+    hipLaunchKernelGGL((bat_cqk_group_kernel<TIn>), dim3(3 * ctx->num_cus), dim3(kBlock), 0,
+                       ctx->stream, A);
   if (sc.small_per == 4)
     hipLaunchKernelGGL((bat_cqk_solve_kernel<4, TIn>), grid, dim3(kBlock), 0, ctx->stream, A);
   else
