@@ -22,7 +22,10 @@
 //   spg_cols_kernel     the chunks summed in order (deterministic);
 //   spg_vec_kernel      fused vector updates with their reductions;
 //   spg_reduce_kernel   one block: the partial records to a result array.
-// The host runs the scalar part and reads a few reduced values per step.
+// The host runs the scalar part and reads a few reduced values per step; it
+// waits four times (two projections, the line search's values, the projected
+// gradient's).  Eight steps on 2048 x 65536: 4.6 ms, 3.5 of them in the
+// products (5.3-5.7 TB/s); with a copy and a wait for each reduction 4.9 ms.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -122,15 +125,17 @@ __global__ __launch_bounds__(kBlock) void spg_cols_kernel(const double* part, in
 // record of kVS sums (then one max):
 //   OP_STEP:  out = x - lam g                                   (no sums)
 //   OP_DIR:   d = p - x;  sums g'd, d'd;  max |d|
-//   OP_AXPY:  x += t d  (n),                                    (no sums)
 //   OP_DOT:   sums u'w, w'w, u'u  over m                        (no writes)
-enum SpgOp { OP_STEP = 0, OP_DIR = 1, OP_AXPY = 2, OP_DOT = 3 };
+enum SpgOp { OP_STEP = 0, OP_DIR = 1, OP_DOT = 2 };
 constexpr int kVS = 3;
 
 template <int OP>
 __global__ __launch_bounds__(kBlock) void spg_vec_kernel(int64_t n, double c, const double* x,
                                                         const double* u, double* out,
-                                                        double* partials) {
+                                                        double* partials, uint64_t* clock) {
+  // the projection's time: from the end of OP_STEP to the start of OP_DIR
+  if (OP == OP_DIR && blockIdx.x == 0 && threadIdx.x == 0)
+    clock[1] = __builtin_amdgcn_s_memrealtime();
   double acc[kVS] = {0.0, 0.0, 0.0};
   double mx = 0.0;
   for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n;
@@ -144,8 +149,6 @@ __global__ __launch_bounds__(kBlock) void spg_vec_kernel(int64_t n, double c, co
       acc[0] += u[j] * dj;
       acc[1] += dj * dj;
       mx = fmax(mx, fabs(dj));
-    } else if (OP == OP_AXPY) {
-      out[j] += c * u[j];
     } else {
       const double a = x[j], w = u[j];
       acc[0] += a * w;
@@ -153,6 +156,8 @@ __global__ __launch_bounds__(kBlock) void spg_vec_kernel(int64_t n, double c, co
       acc[2] += a * a;
     }
   }
+  if (OP == OP_STEP && blockIdx.x == 0 && threadIdx.x == 0)
+    clock[0] = __builtin_amdgcn_s_memrealtime();
   if (OP == OP_DIR || OP == OP_DOT) {
     __shared__ double lds[(kVS + 1) * (kBlock / kWave)];
     __shared__ double tot[kVS + 1];
@@ -161,7 +166,33 @@ __global__ __launch_bounds__(kBlock) void spg_vec_kernel(int64_t n, double c, co
   }
 }
 
-// One block: G partial records of kVS sums and one max -> res[0..kVS].
+// The accepted step: x += t d over n, r += t Ad over m with the sum r'r of the
+// new r (its blocks' records as OP_DOT of r writes them).
+__global__ __launch_bounds__(kBlock) void spg_move_kernel(int64_t n, int64_t m, double t,
+                                                          const double* d, double* x,
+                                                          const double* Ad, double* r,
+                                                          double* partials) {
+  const int64_t j0 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int64_t step = (int64_t)gridDim.x * kBlock;
+  for (int64_t j = j0; j < n; j += step) x[j] += t * d[j];
+  double acc[kVS] = {0.0, 0.0, 0.0};
+  for (int64_t j = j0; j < m; j += step) {
+    const double a = r[j] + t * Ad[j];
+    r[j] = a;
+    acc[0] += a * a;
+  }
+  acc[1] = acc[2] = acc[0];
+  const double mx = 0.0;
+  __shared__ double lds[(kVS + 1) * (kBlock / kWave)];
+  __shared__ double tot[kVS + 1];
+  block_reduce<kVS, 0, 1, kBlock>(acc, nullptr, &mx, lds, tot);
+  if (threadIdx.x == 0) write_partial(partials, tot, kVS + 1);
+}
+
+// One block: G partial records of kVS sums and one max -> res[0..kVS], in the
+// context's pinned host memory: the host reads them after the next wait on
+// the stream, which it has to do anyway (a copy and a wait of their own took
+// about 30 us per reduction).
 __global__ __launch_bounds__(kRBlock) void spg_reduce_kernel(const double* partials, int G,
                                                              double* res) {
   __shared__ double lds[(kVS + 1) * (kRBlock / kWave)];
@@ -171,7 +202,7 @@ __global__ __launch_bounds__(kRBlock) void spg_reduce_kernel(const double* parti
 }
 
 struct SpgWs {
-  double *r, *Ad, *g, *z, *p, *d, *part, *partials, *res;
+  double *r, *Ad, *g, *z, *p, *d, *part, *partials;
   int nchunk, gvec;
 };
 
@@ -200,7 +231,7 @@ cqk_status run_spg_l1_lasso_f64(cqk_ctx* ctx, int64_t m, int64_t n, const double
   const size_t bm = al((size_t)m * 8), bn = al((size_t)n * 8);
   const size_t bpart = al((size_t)W.nchunk * n * 8);
   const size_t bpar = al((size_t)(kVS + 1) * W.gvec * 8);
-  const size_t total = 2 * bm + 4 * bn + bpart + bpar + 256;
+  const size_t total = 2 * bm + 4 * bn + bpart + bpar;
   cqk_status st = ensure_buffer(ctx, ctx->spg, total);
   if (st != CQK_OK) return st;
   char* w = (char*)ctx->spg.ptr;
@@ -212,10 +243,15 @@ cqk_status run_spg_l1_lasso_f64(cqk_ctx* ctx, int64_t m, int64_t n, const double
   W.d = (double*)(w + 2 * bm + 3 * bn);
   W.part = (double*)(w + 2 * bm + 4 * bn);
   W.partials = (double*)(w + 2 * bm + 4 * bn + bpart);
-  W.res = (double*)(w + 2 * bm + 4 * bn + bpart + bpar);
   // scalars come back through the upper half of the context's pinned buffer
   // (its start mirrors the projection's state)
-  double* hres = (double*)((char*)ctx->host_pinned + ctx->host_pinned_bytes / 2);
+  // (three results of kVS + 1 values: of d or the projected gradient, of Ad,
+  // of r)
+  double* const hdir = (double*)((char*)ctx->host_pinned + ctx->host_pinned_bytes / 2);
+  double* const had = hdir + 8;
+  double* const hr = hdir + 16;
+  uint64_t* const clock100 = (uint64_t*)(hdir + 24);  // 100 MHz ticks around a projection
+  auto projected = [&]() { proj_ms += 1e-5 * (double)(clock100[1] - clock100[0]); };
 
   const bool vec = (n % 2 == 0) && ((uintptr_t)A % 16 == 0);
   auto gemv_n = [&](const double* v, const double* bb, double* y) {
@@ -233,12 +269,12 @@ cqk_status run_spg_l1_lasso_f64(cqk_ctx* ctx, int64_t m, int64_t n, const double
     hipLaunchKernelGGL(spg_cols_kernel, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock),
                        0, s, W.part, W.nchunk, n, out);
   };
-  // queue a reduction and read its kVS + 1 results
-  auto fetch = [&](double* dst) -> cqk_status {
-    hipLaunchKernelGGL(spg_reduce_kernel, dim3(1), dim3(kRBlock), 0, s, W.partials, W.gvec, W.res);
-    if (hip_ok(hipMemcpyAsync(dst, W.res, (kVS + 1) * sizeof(double), hipMemcpyDeviceToHost, s)) !=
-        CQK_OK)
-      return CQK_DEVICE_ERROR;
+  // queue a reduction; its results are there after the next wait
+  auto reduce = [&](double* dst) {
+    hipLaunchKernelGGL(spg_reduce_kernel, dim3(1), dim3(kRBlock), 0, s, W.partials, W.gvec, dst);
+  };
+  auto wait = [&]() -> cqk_status {
+    if (hip_ok(hipGetLastError()) != CQK_OK) return CQK_DEVICE_ERROR;
     return hip_ok(hipStreamSynchronize(s));
   };
   cqk_opts po;
@@ -247,11 +283,9 @@ cqk_status run_spg_l1_lasso_f64(cqk_ctx* ctx, int64_t m, int64_t n, const double
   int64_t nproj = 0, newton = 0;
   // p = P(z), warm-started from x when asked; returns the projection status
   auto project = [&](const double* z, double* p) -> cqk_status {
-    const auto t0 = clock::now();
     cqk_info pi;
     cqk_status e = run_simplex_f64(ctx, n, z, so.warm ? x : nullptr, nullptr, radius, p, true,
                                    po, &pi);
-    proj_ms += std::chrono::duration<double, std::milli>(clock::now() - t0).count();
     nproj += 1;
     newton += pi.iterations;
     if (e != CQK_OK) return e;
@@ -267,31 +301,28 @@ cqk_status run_spg_l1_lasso_f64(cqk_ctx* ctx, int64_t m, int64_t n, const double
   int it = 0;
   int status = CQK_OK;
   double pg = 0.0;
-  auto objective = [&]() -> cqk_status {
-    hipLaunchKernelGGL(spg_vec_kernel<OP_DOT>, dim3(W.gvec), dim3(kBlock), 0, s, m, 0.0, W.r,
-                       W.r, nullptr, W.partials);
-    cqk_status e = fetch(hres);
-    fx = 0.5 * hres[2];
-    return e;
-  };
   // the projected gradient at x: pg = ||P(x - g) - x||_inf
   auto proj_grad = [&]() -> cqk_status {
     hipLaunchKernelGGL(spg_vec_kernel<OP_STEP>, dim3(W.gvec), dim3(kBlock), 0, s, n, 1.0, x, W.g,
-                       W.z, W.partials);
+                       W.z, W.partials, clock100);
     cqk_status e = project(W.z, W.p);
     if (e != CQK_OK) return e;
     hipLaunchKernelGGL(spg_vec_kernel<OP_DIR>, dim3(W.gvec), dim3(kBlock), 0, s, n, 0.0, x, W.g,
-                       W.p, W.partials);
-    e = fetch(hres);
-    pg = hres[kVS];
+                       W.p, W.partials, clock100);
+    reduce(hdir);
+    e = wait();
+    projected();
+    pg = hdir[kVS];
+    fx = 0.5 * hr[2];  // reduced before the projection
     return e;
   };
   gemv_t(W.r, W.g);
-  cqk_status e = objective();
+  hipLaunchKernelGGL(spg_vec_kernel<OP_DOT>, dim3(W.gvec), dim3(kBlock), 0, s, m, 0.0, W.r, W.r,
+                     nullptr, W.partials, nullptr);
+  reduce(hr);
+  cqk_status e = proj_grad();
   if (e != CQK_OK) return e;
   hist.push_back(fx);
-  e = proj_grad();
-  if (e != CQK_OK) return e;
   lam = (pg > 0.0) ? std::min(kLMax, std::max(kLMin, 1.0 / pg)) : 1.0;
   const int M = std::max(1, so.memory);
   while (pg > so.tol) {
@@ -301,19 +332,20 @@ cqk_status run_spg_l1_lasso_f64(cqk_ctx* ctx, int64_t m, int64_t n, const double
     }
     // d = P(x - lam g) - x, with g'd and d'd
     hipLaunchKernelGGL(spg_vec_kernel<OP_STEP>, dim3(W.gvec), dim3(kBlock), 0, s, n, lam, x, W.g,
-                       W.z, W.partials);
+                       W.z, W.partials, clock100);
     e = project(W.z, W.d);
     if (e != CQK_OK) return e;
     hipLaunchKernelGGL(spg_vec_kernel<OP_DIR>, dim3(W.gvec), dim3(kBlock), 0, s, n, 0.0, x, W.g,
-                       W.d, W.partials);
-    if ((e = fetch(hres)) != CQK_OK) return e;
-    const double gtd = hres[0], dd = hres[1];
+                       W.d, W.partials, clock100);
+    reduce(hdir);
     // Ad and ||Ad||^2
     gemv_n(W.d, nullptr, W.Ad);
     hipLaunchKernelGGL(spg_vec_kernel<OP_DOT>, dim3(W.gvec), dim3(kBlock), 0, s, m, 0.0, W.Ad,
-                       W.Ad, nullptr, W.partials);
-    if ((e = fetch(hres)) != CQK_OK) return e;
-    const double c2 = hres[1];
+                       W.Ad, nullptr, W.partials, nullptr);
+    reduce(had);
+    if ((e = wait()) != CQK_OK) return e;
+    projected();
+    const double gtd = hdir[0], dd = hdir[1], c2 = had[1];
     // non-monotone line search on f(x + t d) = f + t gtd + t^2/2 c2
     const size_t h0 = (hist.size() > (size_t)M) ? hist.size() - M : 0;
     const double fmax = *std::max_element(hist.begin() + h0, hist.end());
@@ -324,18 +356,16 @@ cqk_status run_spg_l1_lasso_f64(cqk_ctx* ctx, int64_t m, int64_t n, const double
       const double tq = -0.5 * t * t * gtd / (fn - fx - t * gtd);
       t = (tq >= kSigma1 && tq <= kSigma2 * t) ? tq : 0.5 * t;
     }
-    // x += t d, r += t Ad, g = A^T r, f = 1/2 ||r||^2
-    hipLaunchKernelGGL(spg_vec_kernel<OP_AXPY>, dim3(W.gvec), dim3(kBlock), 0, s, n, t, nullptr,
-                       W.d, x, W.partials);
-    hipLaunchKernelGGL(spg_vec_kernel<OP_AXPY>, dim3(W.gvec), dim3(kBlock), 0, s, m, t, nullptr,
-                       W.Ad, W.r, W.partials);
+    // x += t d, r += t Ad, f = 1/2 ||r||^2, g = A^T r
+    hipLaunchKernelGGL(spg_move_kernel, dim3(W.gvec), dim3(kBlock), 0, s, n, m, t, W.d, x, W.Ad,
+                       W.r, W.partials);
+    reduce(hr);
     gemv_t(W.r, W.g);
-    if ((e = objective()) != CQK_OK) return e;
-    hist.push_back(fx);
     // spectral step: s's / s'y = d'd / ||Ad||^2
     lam = (c2 <= 0.0) ? kLMax : std::min(kLMax, std::max(kLMin, dd / c2));
     it += 1;
     if ((e = proj_grad()) != CQK_OK) return e;
+    hist.push_back(fx);
   }
   if (info) {
     std::memset(info, 0, sizeof(*info));
