@@ -397,7 +397,7 @@ typedef struct cqk_spg_info {
   double objective;         /* 1/2 ||A x - b||^2 at the returned x */
   double pg;                /* ||P(x - g) - x||_inf there */
   double total_ms;          /* host wall time of the call */
-  double proj_ms;           /* of which in the projections */
+  double proj_ms;           /* of which in the projections (by the GPU's clock) */
 } cqk_spg_info;
 
 void cqk_spg_default_opts(cqk_spg_opts* opts);

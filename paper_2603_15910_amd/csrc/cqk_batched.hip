@@ -1356,13 +1356,6 @@ struct CqkArrays {
         u((const TIn*)A.u), g((const TIn*)A.g), x((TIn*)A.x), ga((TIn*)A.ga) {}
 };
 
-// x_i of eq. (xopt) at the row's multiplier.
-template <typename TIn>
-__device__ __forceinline__ double cqk_x_at(const CqkArrays<TIn>& V, int64_t i, double lam) {
-  const double t = fma((double)V.b[i], lam, (double)V.a[i]) / (double)V.d[i];
-  return fmin(fmax(t, (double)V.l[i]), (double)V.u[i]);
-}
-
 __device__ __forceinline__ bool cqk_has_lambda(const GenState& st) {
   return st.status == CQK_OK || st.status == CQK_NOT_CONVERGED;
 }
