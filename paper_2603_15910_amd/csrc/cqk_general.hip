@@ -2274,10 +2274,12 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
   const TeamShape shape = team_shape(n, ctx->num_cus);
   const uint32_t need = 2 * (uint32_t)std::min(o.max_iter, 1 << 20) + 8;
   // Longer inputs: the iterations on a compacted set in one launch
-  // (gen_rest_kernel), behind the passes that may leave one.
+  // (gen_rest_kernel), behind the passes that may leave one.  Not for calls
+  // that trace or time every pass (timing 2 times only the first pass and the
+  // recovery, which stay kernels of their own).
   constexpr int kRests = 4;
   const uint32_t rest_need = need;  // an exchange per pass at most
-  const bool rest = shape.E == 0 && compaction && !o.trace && !o.timing &&
+  const bool rest = shape.E == 0 && compaction && !o.trace && (!o.timing || o.timing == 2) &&
                     o.max_iter <= (1 << 20) && NR <= kRestRegions * rest_waves(ctx->num_cus) &&
                     team_ready(ctx, kRests * rest_need);
   // With compaction on large inputs, a bracket estimated from a sample lets
