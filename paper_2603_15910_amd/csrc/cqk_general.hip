@@ -1759,7 +1759,7 @@ __global__ void gen_team_commit_kernel(GenState* st, const TeamCtl* ctl) {
 // calls: 310 -> 266 us; 1e8 indices 1750 -> 1669).
 // ---------------------------------------------------------------------------
 constexpr int kRestSlots = 16;
-constexpr int kRestRegions = 4;   // a wave's regions (choose_grid: 8 blocks of 4 waves per unit)
+constexpr int kRestRegions = 4;   // a wave's regions (choose_grid: 6 blocks of 4 waves per unit)
 
 struct RestArgs {
   const double* buf[3];
@@ -2174,9 +2174,16 @@ int64_t rest_waves(int num_cus) {
   return (int64_t)std::min(num_cus, kTeamMax) * (kTeamBlock / kWave);
 }
 
+// The passes' registers let a compute unit hold 3 blocks: 6 are two full
+// rounds of them, 8 end with a round of two thirds, in which the
+// instructions of the FP32 passes, and the loads in flight of the FP64 ones,
+// fall behind (1e8 FP64 indices 1701 against 1677 us, 3e7 571 against 554,
+// 3e7 correlated FP32 412 against 403; 3 blocks 1699, 562 and 405).
+constexpr int kPassBlocksPerCu = 6;
+
 int choose_grid(int64_t n, int num_cus) {
   const int64_t want = (n + 1023) / 1024;
-  const int64_t cap = (int64_t)num_cus * 8;
+  const int64_t cap = (int64_t)num_cus * kPassBlocksPerCu;
   return (int)std::max<int64_t>(1, std::min(want, cap));
 }
 
@@ -2207,7 +2214,7 @@ GenLayout gen_layout(int64_t n, int num_cus, int vec, bool compaction, double th
   L.region = std::min<int64_t>((L.chunk + kPiece - 1) / kPiece * kPiece,
                                (keep + kPiece - 1) / kPiece * kPiece);
   const int64_t ftile = (int64_t)kBlock * vec * 4;
-  L.GF = (int)std::max<int64_t>(1, std::min<int64_t>(4 * (int64_t)L.G, (n + ftile - 1) / ftile));
+  L.GF = (int)std::max<int64_t>(1, std::min<int64_t>(32 * (int64_t)num_cus, (n + ftile - 1) / ftile));
   L.part_bytes = ((size_t)L.G * NPART * sizeof(double) + 255) / 256 * 256;
   L.cnt_bytes = ((size_t)3 * L.NR * sizeof(int32_t) + 255) / 256 * 256;
   const size_t buf_bytes =
