@@ -221,6 +221,11 @@ cqk_status cqk_reserve(cqk_ctx* ctx, int64_t max_n, int32_t max_seg);
  * with the same results.  Default 2000000 (20 ms); 0: always the multi-launch
  * route.  INVALID_ARG: ticks < 0. */
 cqk_status cqk_set_team_wait(cqk_ctx* ctx, int64_t ticks);
+/* For tests of that: block `block` of every such launch gives up at its
+ * `exchange`-th exchange (1: the first), after it has posted its own record,
+ * as if its wait had run out there.  exchange = 0 (the default): none does.
+ * INVALID_ARG: block or exchange < 0. */
+cqk_status cqk_set_team_late(cqk_ctx* ctx, int32_t block, int32_t exchange);
 const char* cqk_status_string(int32_t status);
 void cqk_default_opts(cqk_opts* opts);
 /* Outcome of the last call on this context (Section 1: the problem's status,

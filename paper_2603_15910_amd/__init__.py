@@ -70,6 +70,10 @@ def cqk_set_team_wait(ctx: int, ticks: int) -> int:
     return lib().cqk_set_team_wait(C.c_void_p(ctx), ticks)
 
 
+def cqk_set_team_late(ctx: int, block: int, exchange: int) -> int:
+    return lib().cqk_set_team_late(C.c_void_p(ctx), block, exchange)
+
+
 def cqk_status_string(status: int) -> str:
     return lib().cqk_status_string(status).decode()
 

@@ -148,6 +148,7 @@ SIGNATURES = {
     "cqk_set_stream": (C.c_int, [_P, _P]),
     "cqk_reserve": (C.c_int, [_P, _I64, _I32]),
     "cqk_set_team_wait": (C.c_int, [_P, _I64]),
+    "cqk_set_team_late": (C.c_int, [_P, _I32, _I32]),
     "cqk_status_string": (C.c_char_p, [_I32]),
     "cqk_default_opts": (None, [_OPTS]),
     "cqk_last_trace": (C.c_int, [_P, C.POINTER(cqk_trace_rec), _I32, C.POINTER(_I32)]),

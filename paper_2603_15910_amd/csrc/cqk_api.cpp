@@ -352,6 +352,12 @@ cqk_status cqk_set_team_wait(cqk_ctx* ctx, int64_t ticks) {
   return CQK_OK;
 }
 
+cqk_status cqk_set_team_late(cqk_ctx* ctx, int32_t block, int32_t exchange) {
+  if (!ctx || block < 0 || exchange < 0) return CQK_INVALID_ARG;
+  ctx->team_late = TeamLate{block, exchange};
+  return CQK_OK;
+}
+
 const char* cqk_status_string(int32_t s) {
   switch (s) {
     case CQK_OK: return "CQK_OK";

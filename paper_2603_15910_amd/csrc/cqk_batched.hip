@@ -1300,6 +1300,7 @@ struct BatCqkArgs {
   uint64_t* tslots;     // teams: record slots, control words (BatTeamCtl), wait
   BatTeamCtl* tctl;     // limit; tslots null: no teams
   uint64_t tlimit;
+  TeamLate tlate;
 };
 
 template <>
@@ -1780,7 +1781,8 @@ struct TeamRows {
     const int lane = threadIdx.x & (kWave - 1);
     bases = (lane < kNBW) ? A.counters[CTR_LBASE + lane] : 0;
     nlong = scalar(A.counters[CTR_NLONG]);
-    team = Team{nullptr, A.tlimit, scalar(A.tctl->base), 1, 0, kBatTeamBlocks * kSlotWords};
+    const uint32_t tag = scalar(A.tctl->base);
+    team = Team{nullptr, A.tlimit, tag, 1, 0, kBatTeamBlocks * kSlotWords, late_tag(A.tlate, tag)};
     b = kTeamMaxLog + 1;
     from = cnt = j = off = wi = wn = 0;
     NT = per = 1;
@@ -2634,6 +2636,7 @@ BatCqkArgs cqk_args(cqk_ctx* ctx, int32_t nseg, const int64_t* offsets, const vo
     A.tctl = (BatTeamCtl*)((char*)ctx->team.ptr + kTeamBatCtl);
     A.tslots = (uint64_t*)((char*)ctx->team.ptr + kTeamBatSlots);
     A.tlimit = ctx->team_wait;
+    A.tlate = ctx->team_late;
   }
   return A;
 }

@@ -1698,9 +1698,9 @@ __global__ void gen_init_kernel(GenState* st, GenState init) { *st = init; }
 struct TeamResult {   // in the context's pinned host memory
   double lam_final, lam0, bytes;
   int32_t status, iter, passes, stop_reason;
-  int32_t gave_up;    // 1: some block's wait ran out; nothing here counts
+  TeamFlags flags;    // with gave_up set nothing here counts
   uint32_t tag;       // the last exchange's tag
-  int32_t ntrace, pad_;
+  int32_t ntrace;
   double part[3 * kTeamMax];  // per block: b^T x, sum |b x|, free indices
 };
 
@@ -1721,6 +1721,7 @@ struct TeamArgs {
   uint64_t* slots;
   uint64_t limit;
   uint32_t tag;       // the last tag used (a waiting call)
+  TeamLate late;
   TeamResult* res;
   const TeamCtl* ctl; // queued or captured call: tags from here
 };
@@ -1729,7 +1730,7 @@ struct TeamArgs {
 // return at once, unless a block gave up; then those passes do the solve.
 __global__ void gen_team_commit_kernel(GenState* st, const TeamCtl* ctl) {
   const TeamResult& R = ctl->res;
-  if (R.gave_up || R.status == kRunning) return;
+  if (R.flags.gave_up || !R.flags.done || R.status == kRunning) return;
   st->lam_final = R.lam_final;
   st->lam0 = R.lam0;
   st->bytes = R.bytes;
@@ -1772,6 +1773,7 @@ struct RestArgs {
   uint64_t* slots;
   uint64_t limit;
   uint32_t tag;        // the last tag used; with `tags`, relative to their base
+  TeamLate late;
   const TeamTags* tags;
 };
 
@@ -1872,7 +1874,8 @@ __global__ __launch_bounds__(kTeamBlock) void gen_rest_kernel(RestArgs A) {
   const double sC1 = scalar(in->sC1), sA0 = scalar(in->sA0), sA1 = scalar(in->sA1);
   const double sp = scalar(in->sp), sq = scalar(in->sq);
   const int passes0 = st.passes;
-  Team team = grid_team(A.slots, (A.tags != nullptr ? A.tags->base : 0u) + A.tag, A.limit);
+  Team team = grid_team(A.slots, (A.tags != nullptr ? A.tags->base : 0u) + A.tag, A.limit,
+                        A.late);
   __syncthreads();  // every read of the state comes before this block's first record
   int par = 0;
   bool ok = true, leave = false;
@@ -2028,7 +2031,7 @@ __global__ __launch_bounds__(kTeamBlock) void gen_team_kernel(TeamArgs A) {
   }
   if (tid == 0) S.gave_up = 0;
   __syncthreads();
-  Team team = grid_team(A.slots, A.ctl != nullptr ? A.ctl->tags.base : A.tag, A.limit);
+  Team team = grid_team(A.slots, A.ctl != nullptr ? A.ctl->tags.base : A.tag, A.limit, A.late);
   // the run state, the same in every lane of every block: in scalar registers
   // between updates
   GenState st{};
@@ -2092,7 +2095,7 @@ __global__ __launch_bounds__(kTeamBlock) void gen_team_kernel(TeamArgs A) {
     state_to_scalars(st);
   }
   if (!ok) {
-    if (tid == 0) A.res->gave_up = 1;
+    if (tid == 0) A.res->flags.gave_up = 1;
     return;
   }
   const int status = st.status;
@@ -2149,6 +2152,7 @@ __global__ __launch_bounds__(kTeamBlock) void gen_team_kernel(TeamArgs A) {
     R.stop_reason = st.stop_reason;
     R.tag = team.tag;
     R.ntrace = st.ntrace;
+    R.flags.done = 1;
   }
 }
 
@@ -2370,6 +2374,7 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     T.slots = (uint64_t*)ctx->team.ptr;
     T.limit = ctx->team_wait;
     T.tag = ctx->team_tag;
+    T.late = ctx->team_late;
     T.res = res;
     T.ctl = tc;
     auto go = [&](auto kern) {
@@ -2393,13 +2398,13 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
   };
   if (team && !deferred) {
     TeamResult* res = (TeamResult*)ctx->host_pinned;
-    res->gave_up = 0;
+    res->flags = TeamFlags{0, 0};
     launch_team(res, nullptr);
     if (hip_ok(hipGetLastError()) != CQK_OK) return CQK_DEVICE_ERROR;
     ctx->team_tag += need;
     if (hip_ok(hipStreamSynchronize(s)) != CQK_OK) return CQK_DEVICE_ERROR;
     const TeamResult& R = *res;
-    if (!R.gave_up) {
+    if (R.flags.done && !R.flags.gave_up) {
       ctx->team_tag = R.tag;
       ctx->last_trace.clear();
       ctx->last_trace_count = R.ntrace;
@@ -2443,6 +2448,7 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     R.st = A.st;
     R.slots = (uint64_t*)ctx->team.ptr;
     R.limit = ctx->team_wait;
+    R.late = ctx->team_late;
     R.tag = deferred ? (uint32_t)rests * rest_need : ctx->team_tag;
     R.tags = deferred ? &rctl->tags : nullptr;
     hipLaunchKernelGGL(gen_rest_kernel, dim3(blocks), dim3(kTeamBlock), 0, s, R);
@@ -2451,11 +2457,11 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
   };
   if (rest && deferred) {
     hipLaunchKernelGGL(team_init_kernel<GenState>, dim3(1), dim3(256), 0, s, A.st, init,
-                       &rctl->tags, &rctl->res.gave_up, (uint64_t*)ctx->team.ptr,
+                       &rctl->tags, &rctl->res.flags, (uint64_t*)ctx->team.ptr,
                        kRests * rest_need);
   } else if (team && deferred) {
     hipLaunchKernelGGL(team_init_kernel<GenState>, dim3(1), dim3(256), 0, s, A.st, init,
-                       &ctl->tags, &ctl->res.gave_up, (uint64_t*)ctx->team.ptr, need);
+                       &ctl->tags, &ctl->res.flags, (uint64_t*)ctx->team.ptr, need);
     launch_team(&ctl->res, ctl);
     hipLaunchKernelGGL(gen_team_commit_kernel, dim3(1), dim3(1), 0, s, A.st, ctl);
   } else {

@@ -113,6 +113,11 @@ enum RunStatus : int32_t { kRunning = -1 };
 
 enum GenMode : int32_t { kModeEval = 0, kModeBreakRight = 1, kModeBreakLeft = 2 };
 
+// Tests of the routes behind a block that gives up (cqk_set_team_late).
+struct TeamLate {
+  int32_t block, exchange;
+};
+
 struct DeviceBuf {
   void* ptr = nullptr;
   size_t bytes = 0;
@@ -154,6 +159,7 @@ struct cqk_ctx {
   cqk::DeviceBuf team;
   uint32_t team_tag = 0;
   uint64_t team_wait = 2000000;
+  cqk::TeamLate team_late{0, 0};    // exchange 0: none
   void* scratch = nullptr;  // this device's no-allocation planning buffers (noalloc_scratch)
 };
 

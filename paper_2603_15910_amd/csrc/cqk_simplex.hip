@@ -1751,9 +1751,8 @@ constexpr int kTeamListBytes = 64 * 1024;  // a block's list; beyond it the regi
 struct SpxTeamResult {   // in the context's pinned host memory, or behind the slots
   double lam_final, lam0, sum_abs, n_init;
   int32_t status, iter, passes, stop_reason, copy;
-  int32_t gave_up;       // 1: some block's wait ran out; nothing here counts
+  TeamFlags flags;       // with gave_up set nothing here counts
   uint32_t tag;
-  int32_t pad_;
   int64_t nnz;           // sparse output
   double part[2 * kTeamMax];  // per block: sum |x|, values not zero
 };
@@ -1775,15 +1774,17 @@ struct SpxTeamArgs {
   uint64_t* slots;
   uint64_t limit;
   uint32_t tag;
+  TeamLate late;
   SpxTeamResult* res;
   const SpxTeamCtl* ctl;
 };
 
-// After the projection kernel: its outcome becomes the run state's, so the
-// kernels queued behind return at once, unless a block gave up.
-__global__ void spx_team_commit_kernel(SpxState* st, const SpxTeamCtl* ctl) {
+// After the projection kernel, or (rest) spx_rest_kernel's dense form: its
+// outcome becomes the run state's, so the kernels queued behind return at
+// once, unless a block gave up or the kernel left the work to them.
+__global__ void spx_team_commit_kernel(SpxState* st, const SpxTeamCtl* ctl, bool rest) {
   const SpxTeamResult& R = ctl->res;
-  if (R.gave_up) return;
+  if (R.flags.gave_up || !R.flags.done) return;
   st->lam_final = R.lam_final;
   st->lam0 = R.lam0;
   st->sum_abs = R.sum_abs;
@@ -1793,6 +1794,11 @@ __global__ void spx_team_commit_kernel(SpxState* st, const SpxTeamCtl* ctl) {
   st->passes = R.passes;
   st->stop_reason = R.stop_reason;
   if (R.copy) st->fin_mode = kFinCopy;
+  if (rest) {  // the survivors' entries, over the zeros of the Algorithm 2 pass
+    st->src = 2;
+    st->n_src = (int64_t)R.n_init;
+    st->x_zeroed = 1;
+  }
   st->team_done = 1;
 }
 
@@ -2065,7 +2071,7 @@ __global__ __launch_bounds__(kTeamBlock) void spx_team_kernel(SpxTeamArgs A) {
       }
     }
   }
-  Team team = grid_team(A.slots, A.ctl != nullptr ? A.ctl->tags.base : A.tag, A.limit);
+  Team team = grid_team(A.slots, A.ctl != nullptr ? A.ctl->tags.base : A.tag, A.limit, A.late);
   int par = 0;
   const double v1[8] = {c_keep, s_keep, bad, abs_sum, c_i, s_i, -lmax, lam_b};
   double tot[8];
@@ -2102,7 +2108,7 @@ __global__ __launch_bounds__(kTeamBlock) void spx_team_kernel(SpxTeamArgs A) {
   const bool copy = O.copy;
   const double lam_final = O.lam_final;
   if (!ok) {
-    if (tid == 0) A.res->gave_up = 1;
+    if (tid == 0) A.res->flags.gave_up = 1;
     return;
   }
   double sums[2] = {0.0, 0.0};
@@ -2175,7 +2181,7 @@ __global__ __launch_bounds__(kTeamBlock) void spx_team_kernel(SpxTeamArgs A) {
       double total = mine, before = 0.0;
       if (team.T > 1) ok = team_prefix(team, S, par, mine, &total, &before);
       if (!ok) {
-        if (tid == 0) A.res->gave_up = 1;
+        if (tid == 0) A.res->flags.gave_up = 1;
         return;
       }
       nnz = (int64_t)total;
@@ -2224,6 +2230,7 @@ __global__ __launch_bounds__(kTeamBlock) void spx_team_kernel(SpxTeamArgs A) {
     R.copy = copy ? 1 : 0;
     R.tag = team.tag;
     R.nnz = nnz;
+    R.flags.done = 1;
   }
 }
 
@@ -2234,8 +2241,10 @@ __global__ __launch_bounds__(kTeamBlock) void spx_team_kernel(SpxTeamArgs A) {
 // (one per compute unit) share the wave regions; a wave lists its survivors
 // above the merged bound in LDS, or sweeps its regions when they do not fit.
 // Sets of more than max_n values, bad values and a y inside the l1 ball are
-// left to the kernels behind, as is everything when a wait runs out (values
-// already written to x are then written again).
+// left to the kernels behind.  A dense output is every block's work, so its
+// outcome goes to the result and counts only when no block gave up (the host,
+// or spx_team_commit_kernel, looks at the flags); a sparse one is written
+// later from the run state, which is block 0's alone.
 // Bound by latency: five to seven exchanges of about 3 us.  Whole calls,
 // against the eight kernels behind the pass: 1e8 FP32 values 240 -> 195 us
 // (the pass takes 144), sparse l1 of them 254 -> 206, 12 582 913 103 -> 70;
@@ -2257,7 +2266,8 @@ struct SpxRestArgs {
   uint64_t* slots;
   uint64_t limit;
   uint32_t tag;
-  SpxTeamResult* res;    // gave_up is set until block 0 clears it
+  TeamLate late;
+  SpxTeamResult* res;
   const TeamTags* tags;  // queued or captured call
 };
 
@@ -2289,7 +2299,8 @@ __global__ __launch_bounds__(kTeamBlock) void spx_rest_kernel(SpxRestArgs A) {
     vi = fmin(vi, -rec(C_NSUM + 2));
   }
   __syncthreads();  // the state is read before this block's first record
-  Team team = grid_team(A.slots, (A.tags != nullptr ? A.tags->base : 0u) + A.tag, A.limit);
+  Team team = grid_team(A.slots, (A.tags != nullptr ? A.tags->base : 0u) + A.tag, A.limit,
+                        A.late);
   int par = 0;
   double tot[7], ti[3] = {0.0, 0.0, inf_d()};
   bool ok = team_reduce<7, kTeamBlock, 2>(team, S, par, v1, tot);
@@ -2297,7 +2308,11 @@ __global__ __launch_bounds__(kTeamBlock) void spx_rest_kernel(SpxRestArgs A) {
     const double v2[3] = {ci, si, vi};
     ok = team_reduce<3, kTeamBlock, 1>(team, S, par, v2, ti);
   }
-  if (!ok || tot[2] > 0.0 || (l1 && tot[3] <= A.r) || !(tot[0] <= (double)A.max_n)) return;
+  if (!ok) {
+    if (tid == 0) A.res->flags.gave_up = 1;
+    return;
+  }
+  if (tot[2] > 0.0 || (l1 && tot[3] <= A.r) || !(tot[0] <= (double)A.max_n)) return;
   const double bound = (tot[0] > 0.0) ? fmin((A.r - tot[1]) / tot[0], tot[6]) : tot[6];
   const TIn thr = round_down_to<TIn>(-bound);
   auto absl = [&](TIn t) { return l1 ? absval(t) : t; };
@@ -2337,7 +2352,10 @@ __global__ __launch_bounds__(kTeamBlock) void spx_rest_kernel(SpxRestArgs A) {
                      SpxStart{tot[0], tot[1], tot[2], tot[3], ti[0], ti[1], -tot[5], -ti[2],
                               tot[6]},
                      each, O);
-  if (!ok) return;
+  if (!ok) {
+    if (tid == 0) A.res->flags.gave_up = 1;
+    return;
+  }
   const double lam = O.lam_final;
   if (A.x != nullptr) {
     double sums[2] = {0.0, 0.0};
@@ -2354,7 +2372,7 @@ __global__ __launch_bounds__(kTeamBlock) void spx_rest_kernel(SpxRestArgs A) {
     block_reduce<2, 0, 0, kTeamBlock>(sums, nullptr, nullptr, lds, tot2);
     if (tid < 2) A.res->part[2 * blockIdx.x + tid] = tot2[tid];
   }
-  if (blockIdx.x == 0 && tid == 0) {
+  if (blockIdx.x == 0 && tid == 0 && A.x != nullptr) {
     SpxTeamResult& R = *A.res;
     R.lam_final = lam;
     R.lam0 = O.lam0;
@@ -2365,7 +2383,8 @@ __global__ __launch_bounds__(kTeamBlock) void spx_rest_kernel(SpxRestArgs A) {
     R.passes = O.passes + 1;
     R.stop_reason = O.reason;
     R.copy = 0;
-    R.gave_up = 0;
+    R.flags.done = 1;
+  } else if (blockIdx.x == 0 && tid == 0) {
     SpxState* st = A.st;
     st->lam = st->lam_final = lam;
     st->lam0 = O.lam0;
@@ -2377,7 +2396,6 @@ __global__ __launch_bounds__(kTeamBlock) void spx_rest_kernel(SpxRestArgs A) {
     st->iter = O.iter;
     st->passes += O.passes;
     st->stop_reason = O.reason;
-    st->team_done = A.x != nullptr ? 1 : 0;
     st->status = O.status;
   }
 }
@@ -2587,6 +2605,7 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
     R.slots = (uint64_t*)ctx->team.ptr;
     R.limit = ctx->team_wait;
     R.tag = tags != nullptr ? 0u : ctx->team_tag;
+    R.late = ctx->team_late;
     R.res = res;
     R.tags = tags;
     hipLaunchKernelGGL(spx_rest_kernel<TIn>, dim3(tT), dim3(kTeamBlock), 0, s, R);
@@ -2607,6 +2626,7 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
     T.slots = (uint64_t*)ctx->team.ptr;
     T.limit = ctx->team_wait;
     T.tag = ctx->team_tag;
+    T.late = ctx->team_late;
     T.res = res;
     T.ctl = tc;
     auto go = [&](auto kern) {
@@ -2655,12 +2675,12 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
   };
   if (team && !deferred) {
     SpxTeamResult* res = (SpxTeamResult*)ctx->host_pinned;
-    res->gave_up = 0;
+    res->flags = TeamFlags{0, 0};
     launch_team(res, nullptr);
     if (hip_ok(hipGetLastError()) != CQK_OK) return CQK_DEVICE_ERROR;
     ctx->team_tag += need;
     if (hip_ok(hipStreamSynchronize(s)) != CQK_OK) return CQK_DEVICE_ERROR;
-    if (!res->gave_up) {
+    if (res->flags.done && !res->flags.gave_up) {
       ctx->team_tag = res->tag;
       if (sparse) {
         ctx->bitmap_clean = true;  // not touched
@@ -2675,12 +2695,12 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
   const bool team_queued = (team || rest) && deferred;
   if (rest && deferred) {
     hipLaunchKernelGGL(team_init_kernel<SpxState>, dim3(1), dim3(256), 0, s, A.st, init,
-                       &ctl->tags, &ctl->res.gave_up, (uint64_t*)ctx->team.ptr, need);
+                       &ctl->tags, &ctl->res.flags, (uint64_t*)ctx->team.ptr, need);
   } else if (team_queued) {
     hipLaunchKernelGGL(team_init_kernel<SpxState>, dim3(1), dim3(256), 0, s, A.st, init,
-                       &ctl->tags, &ctl->res.gave_up, (uint64_t*)ctx->team.ptr, need);
+                       &ctl->tags, &ctl->res.flags, (uint64_t*)ctx->team.ptr, need);
     launch_team(&ctl->res, ctl);
-    hipLaunchKernelGGL(spx_team_commit_kernel, dim3(1), dim3(1), 0, s, A.st, ctl);
+    hipLaunchKernelGGL(spx_team_commit_kernel, dim3(1), dim3(1), 0, s, A.st, ctl, false);
   }
   if (!init_in_sample) hipLaunchKernelGGL(spx_init_kernel, dim3(1), dim3(1), 0, s, A.st, init);
   int ev = 4;
@@ -2755,9 +2775,10 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
         launch(spx_condat_kernel<TIn, false>, G0);
       if (rest && deferred) {
         launch_rest(&ctl->res, &ctl->tags);
+        hipLaunchKernelGGL(spx_team_commit_kernel, dim3(1), dim3(1), 0, s, A.st, ctl, true);
       } else if (rest) {
         SpxTeamResult* res = (SpxTeamResult*)ctx->host_pinned;
-        res->gave_up = 1;
+        res->flags = TeamFlags{0, 0};
         launch_rest(res, nullptr);
         ctx->team_tag += need;
         ++npass;
@@ -2769,7 +2790,7 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
           if (hip_ok(hipGetLastError()) != CQK_OK ||
               hip_ok(hipStreamSynchronize(s)) != CQK_OK)
             return CQK_DEVICE_ERROR;
-          if (!res->gave_up)
+          if (res->flags.done && !res->flags.gave_up)
             return answer(*res, npass, (2.0 * sizeof(TIn) + 4.0) * res->n_init);
         }
       }

@@ -16,12 +16,17 @@
 // The blocks of a team have to run at the same time.  The grid never exceeds
 // what the GPU holds at once, but another stream's kernels may hold compute
 // units back, so every wait is bounded: a block that has waited `limit` ticks
-// of the 100 MHz clock gives up, says so in the launch's result and ends;
-// the others then run out of their own limit.  The host takes the
-// multi-launch route when any block gave up.
+// of the 100 MHz clock gives up, says so in the launch's result and ends.
+// The others then run out of their own limit, but for the last exchange: a
+// block posts its record before it waits, so there the rest of the team can
+// finish without it.  A result that any block besides block 0 has a part in
+// (x, the sums over it) therefore counts only when no block gave up, whatever
+// block 0 found; one that block 0 writes alone (a run state) stands on its
+// own.  Where it does not count, the multi-launch route answers.
 #pragma once
 
 #include "cqk_device.h"
+#include "cqk_internal.h"
 
 namespace cqk {
 
@@ -53,11 +58,26 @@ struct Team {
   uint32_t tag;      // tag of the last exchange; the next one uses tag + 1
   int T, me;         // blocks of the team, this block's place in it
   int parity;        // words from one parity's slots to the other's
+  uint32_t late;     // tag of the exchange this block gives up at (tests), 0: none
 };
 
-__device__ __forceinline__ Team grid_team(uint64_t* slots, uint32_t tag, uint64_t limit) {
-  return Team{slots, limit, tag, (int)gridDim.x, (int)blockIdx.x, kTeamMax * kSlotWords};
+// The tag of the exchange a test has this block give up at: 0 (no exchange
+// has it) unless the block is the chosen one.
+__device__ __forceinline__ uint32_t late_tag(TeamLate late, uint32_t tag) {
+  return (late.exchange > 0 && (int)blockIdx.x == late.block) ? tag + (uint32_t)late.exchange : 0u;
 }
+
+__device__ __forceinline__ Team grid_team(uint64_t* slots, uint32_t tag, uint64_t limit,
+                                          TeamLate late) {
+  return Team{slots, limit, tag, (int)gridDim.x, (int)blockIdx.x, kTeamMax * kSlotWords,
+              late_tag(late, tag)};
+}
+
+// How a launch ended: gave_up is set by any block whose wait ran out and
+// cleared only before the launch, done by block 0 when it got to the end.
+struct TeamFlags {
+  int32_t gave_up, done;
+};
 
 // LDS of the reductions below.
 template <int BLOCK>
@@ -99,7 +119,7 @@ __device__ __forceinline__ TeamRead team_read(const Team& team, const uint64_t* 
                                               uint32_t tag, int from, int step, int lane,
                                               bool lane_min = false) {
   constexpr int R = 4;
-  TeamRead out{lane_min ? inf_d() : 0.0, KeySum{inf_d(), 0.0}, false};
+  TeamRead out{lane_min ? inf_d() : 0.0, KeySum{inf_d(), 0.0}, tag == team.late};
   const bool mine = (lane & 15) < 2 * NV;
   const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
   for (int g0 = from * 4; g0 < team.T && !out.late; g0 += R * step * 4) {
@@ -293,7 +313,7 @@ __device__ __forceinline__ bool team_prefix(Team& team, TeamLds<BLOCK>& S, int& 
     team_post<1, 2>(team, slots, tag, mine, lane);
     double all = 0.0, low = 0.0;
     const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-    bool late = false;
+    bool late = tag == team.late;
     for (int g = lane; g < team.T; g += kWave) {
       uint64_t w0, w1;
       bool ok = false;
@@ -337,10 +357,10 @@ constexpr uint32_t kTeamDeviceTags = 0x80000000u;
 
 // Before a queued or captured one-launch call: the run state of the kernels
 // queued behind it, a fresh range of tags (the slots are cleared when the
-// range starts over) and a clear result.
+// range starts over) and clear flags.
 template <typename State>
 __global__ __launch_bounds__(256) void team_init_kernel(State* st, State init, TeamTags* tags,
-                                                        int32_t* gave_up, uint64_t* slots,
+                                                        TeamFlags* flags, uint64_t* slots,
                                                         uint32_t need) {
   const uint32_t next = tags->next;
   const bool wrap = next == 0 || next > 0xffffffffu - need;
@@ -352,7 +372,7 @@ __global__ __launch_bounds__(256) void team_init_kernel(State* st, State init, T
     const uint32_t base = wrap ? kTeamDeviceTags : next;
     tags->base = base;
     tags->next = base + need;
-    *gave_up = 0;
+    *flags = TeamFlags{0, 0};
   }
 }
 
