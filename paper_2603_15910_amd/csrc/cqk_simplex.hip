@@ -1802,6 +1802,28 @@ __global__ void spx_team_commit_kernel(SpxState* st, const SpxTeamCtl* ctl, bool
   st->team_done = 1;
 }
 
+// Behind a launch in which a block gave up (flags; null: known to the host):
+// zeros over the entries of x that its other blocks may have written.  The
+// kernels that follow take x as the Algorithm 2 pass left it and write only
+// the entries of their own final set.
+template <typename TIn>
+__global__ __launch_bounds__(kBlock) void spx_clear_kernel(TIn* x, int64_t n,
+                                                           const TeamFlags* flags) {
+  if (flags != nullptr && !flags->gave_up) return;
+  constexpr int V = VecWidth<TIn>::value;
+  typename Raw16<TIn>::type z;
+#pragma unroll
+  for (int k = 0; k < V; ++k) z[k] = TIn(0);
+  for (int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * V; i < n;
+       i += (int64_t)gridDim.x * kBlock * V) {
+    if (i + V <= n) {
+      st16(x + i, z);
+    } else {
+      for (int k = 0; i + k < n; ++k) x[i + k] = TIn(0);
+    }
+  }
+}
+
 // What the start of a projection knows, and how its loop ended.
 struct SpxStart {
   double cnt, sum;        // of the listed values (every value above lam_min is)
@@ -2243,7 +2265,8 @@ __global__ __launch_bounds__(kTeamBlock) void spx_team_kernel(SpxTeamArgs A) {
 // Sets of more than max_n values, bad values and a y inside the l1 ball are
 // left to the kernels behind.  A dense output is every block's work, so its
 // outcome goes to the result and counts only when no block gave up (the host,
-// or spx_team_commit_kernel, looks at the flags); a sparse one is written
+// or spx_team_commit_kernel, looks at the flags; spx_clear_kernel takes back
+// what was written of one that does not); a sparse one is written
 // later from the run state, which is block 0's alone.
 // Bound by latency: five to seven exchanges of about 3 us.  Whole calls,
 // against the eight kernels behind the pass: 1e8 FP32 values 240 -> 195 us
@@ -2776,6 +2799,8 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
       if (rest && deferred) {
         launch_rest(&ctl->res, &ctl->tags);
         hipLaunchKernelGGL(spx_team_commit_kernel, dim3(1), dim3(1), 0, s, A.st, ctl, true);
+        hipLaunchKernelGGL(spx_clear_kernel<TIn>, dim3(G0), dim3(kBlock), 0, s, x, n,
+                           (const TeamFlags*)&ctl->res.flags);
       } else if (rest) {
         SpxTeamResult* res = (SpxTeamResult*)ctx->host_pinned;
         res->flags = TeamFlags{0, 0};
@@ -2792,6 +2817,9 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
             return CQK_DEVICE_ERROR;
           if (res->flags.done && !res->flags.gave_up)
             return answer(*res, npass, (2.0 * sizeof(TIn) + 4.0) * res->n_init);
+          if (res->flags.gave_up)
+            hipLaunchKernelGGL(spx_clear_kernel<TIn>, dim3(G0), dim3(kBlock), 0, s, x, n,
+                               (const TeamFlags*)nullptr);
         }
       }
       if (!rest_done) reduce(spx_condat_merge_kernel<TIn, TA>, G0);

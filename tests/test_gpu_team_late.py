@@ -85,6 +85,37 @@ def test_long_projection(ctx, dtype, l1, block, sync):
 
 @pytest.mark.parametrize("sync", [True, False])
 @pytest.mark.parametrize("dtype", [F32, F64])
+def test_long_projection_stopped_early(ctx, dtype, sync):
+    """max_iter = 1: the two routes end at different multipliers, both above
+    lambda*.  Entries that the other blocks have written at the one launch's,
+    the larger here, do not stay behind in the other route's x."""
+    n = 12_600_001 if dtype == F32 else 6_300_001
+    # one value far above the rest: the candidates of either start end far
+    # from lambda*, the one launch's four further than the other's twelve
+    y = np.random.default_rng(6).random(n)
+    y[-1] = 3.0
+    t = torch.from_numpy(y).to("cuda", dtype)
+    kw = dict(max_iter=1, check=False)
+    _set(ctx, WAIT)
+    one = ctx.project_simplex(t, 100.0, **kw)
+    _set(ctx, 0)
+    want = ctx.project_simplex(t, 100.0, **kw)
+    assert one[1]["status"] == want[1]["status"] == 3
+    assert one[1]["n_free"] > want[1]["n_free"]
+    try:
+        for k in (1, 2, 3):   # the bound, the candidates, the evaluation
+            _set(ctx, WAIT, 1, k)
+            x, info = ctx.project_simplex(t, 100.0, out=torch.full_like(t, 9.0), sync=sync, **kw)
+            if not sync:
+                _, info = ctx.ctx_last_info()
+            assert info["n_free"] == want[1]["n_free"]
+            assert torch.equal(x, want[0])
+    finally:
+        _set(ctx, 2_000_000)
+
+
+@pytest.mark.parametrize("sync", [True, False])
+@pytest.mark.parametrize("dtype", [F32, F64])
 def test_projection(ctx, dtype, sync):
     n = 300_001
     y = W.simplex_input(n, 4, "normal", np.float32 if dtype == F32 else np.float64)
