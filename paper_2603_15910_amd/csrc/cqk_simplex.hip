@@ -1852,6 +1852,7 @@ __device__ __forceinline__ bool spx_team_loop(Team& team, TeamLds<kTeamBlock>& S
   bool copy = false;
   double lam_final = __builtin_nan(""), lam0 = __builtin_nan("");
   double lo = -inf_d(), hi = inf_d(), lam = inf_d();
+  double upper = inf_d();  // the lists' bound, where the first iterate is not one
   if (B.bad > 0.0) {
     status = CQK_INVALID_ARG;
   } else if (l1 && B.abs_sum <= r) {
@@ -1866,7 +1867,11 @@ __device__ __forceinline__ bool spx_team_loop(Team& team, TeamLds<kTeamBlock>& S
     if (A.xw != nullptr) {
       if (!(B.vmax_i > -inf_d())) {
         // an empty support: the fallback max{r/n, -max v} of Section 3.1,
-        // Newton's first step decides its side
+        // Newton's first step decides its side.  The lists hold what lies
+        // above their bound, so no later iterate goes past it: where the
+        // radius rounds away against max v they miss max v itself, and the
+        // step from a slope of zero would be infinite.
+        upper = lam;
         lam = fmax(r / (double)A.n, -B.vmax);
         bound = false;
       } else {
@@ -1920,7 +1925,8 @@ __device__ __forceinline__ bool spx_team_loop(Team& team, TeamLds<kTeamBlock>& S
     const bool below = (k == 0 && phi < r);
     lo = below ? lam : lo;
     hi = (!below && phi > r) ? lam : hi;
-    const double step = (phi - r) / (below ? cp : cm), next = lam - step;
+    const double step = (phi - r) / (below ? cp : cm);
+    const double next = (k == 0) ? fmin(lam - step, upper) : lam - step;
     int why = 0;
     double at = lam;
     if (phi == r || (k > 0 && phi <= r)) {
