@@ -62,11 +62,11 @@ cqk_status ensure_buffer(cqk_ctx* ctx, DeviceBuf& b, size_t bytes) {
 
 bool team_ready(cqk_ctx* ctx, uint32_t need) {
   if (ctx->team_wait == 0) return false;
-  const bool fresh = ctx->team.ptr == nullptr;
-  if (fresh && ensure_buffer(ctx, ctx->team, kTeamBytes) != CQK_OK)
-    return false;
+  if (ensure_buffer(ctx, ctx->team, kTeamBytes) != CQK_OK) return false;
+  const bool fresh = !ctx->team_zeroed;
   if (!fresh && ctx->team_tag < 0x80000000u - need) return true;
-  if (stream_capturing(ctx->stream)) return true;  // its tags come from device memory
+  // a captured call's tags come from device memory
+  if (stream_capturing(ctx->stream)) return !fresh;
   // waited for: the next call may come on another stream
   if (hipMemsetAsync(ctx->team.ptr, 0, fresh ? kTeamBytes : kTeamSlotBytes,
                      ctx->stream) != hipSuccess ||
@@ -74,6 +74,7 @@ bool team_ready(cqk_ctx* ctx, uint32_t need) {
     (void)hipGetLastError();
     return false;
   }
+  ctx->team_zeroed = true;
   ctx->team_tag = 0;
   return true;
 }

@@ -153,10 +153,12 @@ struct cqk_ctx {
   cqk_info trivial{};               // the last call answered on the host
   int32_t* bat_counters = nullptr;  // device counters of the last batched forward call
   bool bat_timing = false;          // that call recorded events[0..1]
-  // One-launch solves (cqk_team.h): the blocks' record slots (zeroed when
-  // allocated), the last tag used in them, the longest wait of an exchange in
-  // ticks of the 100 MHz clock (0: such solves are not used).
+  // One-launch solves (cqk_team.h): the blocks' record slots and control
+  // blocks (used only once they have been zeroed), the last tag used in them,
+  // the longest wait of an exchange in ticks of the 100 MHz clock (0: such
+  // solves are not used).
   cqk::DeviceBuf team;
+  bool team_zeroed = false;
   uint32_t team_tag = 0;
   uint64_t team_wait = 2000000;
   cqk::TeamLate team_late{0, 0};    // exchange 0: none
