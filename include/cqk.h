@@ -164,7 +164,9 @@ typedef struct cqk_info {
                                the row); 0 otherwise */
   int64_t pass_launches;    /* grid passes queued (pass_ms covers all of them;
                                those queued after the loop stopped return at
-                               once and move no bytes) */
+                               once and move no bytes; a pass queued in two
+                               forms counts twice here and, as the form that
+                               ran, once in pass_ms) */
 } cqk_info;
 
 /* One record per kernel pass (opts.trace = 1). */

@@ -1361,6 +1361,7 @@ __global__ __launch_bounds__(kRBlock) void gen_sample3_reduce_kernel(GenArgs A, 
         st->scap = fmin(st->theta, 1.5 * share + 1.0 / 32.0);
         st->spec = 1;
         st->spend = 0;
+        st->anew = 1;
       }
     } else if (!again && all[S3_BAD] == 0.0 && sl > 0.0 && p < q) {
       const double lam2 = mu - res / sl;
@@ -1431,6 +1432,7 @@ __global__ __launch_bounds__(kRBlock) void gen_flat_update_kernel(GenArgs A, int
   if (threadIdx.x == 0) {
     GenState s = *st;
     s.flat = 0;
+    s.was_flat = 1;
     update_after_eval(&s, tot, A.trace);
     flat_steps(&s, ktot[0], ktot[1], tot[P_SIDE + D_N + D_F], tot[P_SIDE + D_N + D_AF],
                flat == 2, A.trace);
@@ -2470,15 +2472,26 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
   if (hip_ok(hipGetLastError()) != CQK_OK) return CQK_DEVICE_ERROR;
   int ev = 2;
   int npass = 0;  // grid passes queued
-  // a grid pass (timed when asked) followed by its one-block reduction
-  auto launch = [&](auto kern, auto reduce, bool first_newton, auto... more) {
+  // a grid pass, timed when asked: the first of its events (0: not timed)
+  auto grid_pass = [&](auto kern, bool first_newton, auto... more) {
     const bool rec = (timing_all || (timing && first_newton)) && ev + 2 <= (int)nev;
     launch_timed(kern, dim3(G), dim3(kBlock), s, rec ? ctx->events[ev] : nullptr,
                  rec ? ctx->events[ev + 1] : nullptr, A, more...);
     if (rec) ev += 2;
     ++npass;
-    hipLaunchKernelGGL(reduce, dim3(1), dim3(kRBlock), 0, s, A, G);
+    return rec ? ev - 2 : 0;
   };
+  // one followed by its one-block reduction
+  auto launch = [&](auto kern, auto reduce, bool first_newton, auto... more) {
+    const int at = grid_pass(kern, first_newton, more...);
+    hipLaunchKernelGGL(reduce, dim3(1), dim3(kRBlock), 0, s, A, G);
+    return at;
+  };
+  // the first pass and the one after it are queued in two forms, of which the
+  // one that the state does not call for returns at once
+  struct {
+    int plain, flat, anew, second;   // their events
+  } forms{0, 0, 0, 0};
   // The primal recovery does nothing while the loop still runs, so it is
   // queued behind every batch and the host waits once per batch.
   auto finalize = [&]() {
@@ -2519,26 +2532,24 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
   // pass the general one
   const bool ask_flat = rest && sampled && !deferred;
   auto flat_pass = [&]() {
-    hipLaunchKernelGGL((gen_spec_pass_kernel<TIn, true>), dim3(G), dim3(kBlock), 0, s, A, false);
+    forms.flat = grid_pass(gen_spec_pass_kernel<TIn, true>, true, false);
     hipLaunchKernelGGL(gen_flat_update_kernel, dim3(1), dim3(kRBlock), 0, s, A, G);
   };
   auto pass = [&]() {
     if (launched == 0 && warm_spec) launch(gen_pass_kernel<TIn>, gen_update_kernel, true);
     else if (launched == 0 && sampled) {
-      launch(gen_spec_pass_kernel<TIn, false>, gen_update_kernel, true, false);
+      forms.plain = launch(gen_spec_pass_kernel<TIn, false>, gen_update_kernel, true, false);
       // what gen_spec_pass_kernel and the update left to them; a waiting call
       // whose first batch is one pass asks the state instead of queueing them
       if (!ask_flat) flat_pass();
     }
     else if (launched == 0) launch(gen_first_pass_kernel<TIn>, gen_update_kernel, true);
-    else {
-      if (launched == 1 && sampled && !warm_spec) {
-        predict(true);
-        hipLaunchKernelGGL((gen_spec_pass_kernel<TIn, false>), dim3(G), dim3(kBlock), 0, s, A,
-                           true);
-      }
-      launch(gen_pass_kernel<TIn>, gen_update_kernel, false);
+    else if (launched == 1 && sampled && !warm_spec) {
+      predict(true);
+      forms.anew = grid_pass(gen_spec_pass_kernel<TIn, false>, false, true);
+      forms.second = launch(gen_pass_kernel<TIn>, gen_update_kernel, false);
     }
+    else launch(gen_pass_kernel<TIn>, gen_update_kernel, false);
     ++launched;
   };
   // a warm or formula start's lam_0 pass may already leave a compacted set
@@ -2574,7 +2585,7 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
   const int trace_cap = init.trace_cap;
   // Fills an info record from the state copy in hs (the stream synchronised),
   // reading the trace ring too.
-  auto report = [ctx, hs, A, trace_cap, n, r, timing, pass_events, npass](cqk_info* inf) -> cqk_status {
+  auto report = [ctx, hs, A, trace_cap, n, r, timing, pass_events, npass, forms](cqk_info* inf) -> cqk_status {
     const int ntrace = std::min(hs->ntrace, trace_cap);
     ctx->last_trace.resize(ntrace);
     ctx->last_trace_count = hs->ntrace;
@@ -2598,8 +2609,11 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     inf->pass_launches = npass;
     ctx->last_pass_ms.clear();
     if (timing) {
-      // every grid pass queued; those after the loop stopped returned at once
+      // every grid pass queued but for the forms that were not called for;
+      // those after the loop stopped returned at once
       for (int i = 2; i + 1 < pass_events; i += 2) {
+        if (i == (hs->was_flat ? forms.plain : forms.flat)) continue;
+        if (i == (hs->anew ? forms.second : forms.anew)) continue;
         float ms = 0.f;
         hipEventElapsedTime(&ms, ctx->events[i], ctx->events[i + 1]);
         inf->pass_ms += ms;

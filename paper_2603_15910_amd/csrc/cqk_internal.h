@@ -72,6 +72,8 @@ struct GenState {
   int32_t spec;                   // 1: the next evaluation writes the sampled-bracket set
   int32_t spend;                  // 1: that set waits in set 3
   int32_t flat;                   // the first pass is at a flat lam_0 (1: lam* right of it, 2: left)
+  int32_t was_flat;               // 1: gen_spec_pass_kernel's flat form made the first pass
+  int32_t anew;                   // 1: a later pass wrote the sampled-bracket set anew
   int32_t s1ok;                   // 1: the first estimate found a bracket
   int32_t skip;                   // sides the next evaluation does not write (bit k: side k)
   int32_t warm;                   // 1: lam_0 comes from a primal estimate
