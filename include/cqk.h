@@ -220,8 +220,11 @@ cqk_status cqk_reserve(cqk_ctx* ctx, int64_t max_n, int32_t max_seg);
  * they run, so they have to run side by side; a block that waits longer than
  * `ticks` of the GPU's 100 MHz clock for the others (another stream holds the
  * compute units) gives up, and the call then takes its multi-launch route
- * with the same results.  Default 2000000 (20 ms); 0: always the multi-launch
- * route.  INVALID_ARG: ticks < 0. */
+ * with the same results, as do the context's next 16 calls (twice as many
+ * each time it happens again, up to 1024; 16 again after 64 calls without).
+ * Default 30000 (0.3 ms; an exchange takes 2-3 us, with the spread of the
+ * blocks' loads up to 30); 0: always the multi-launch route.  Setting it ends
+ * such a pause.  INVALID_ARG: ticks < 0. */
 cqk_status cqk_set_team_wait(cqk_ctx* ctx, int64_t ticks);
 /* For tests of that: block `block` of every such launch gives up at its
  * `exchange`-th exchange (1: the first), after it has posted its own record,

@@ -350,6 +350,8 @@ cqk_status cqk_reserve(cqk_ctx* ctx, int64_t max_n, int32_t max_seg) {
 cqk_status cqk_set_team_wait(cqk_ctx* ctx, int64_t ticks) {
   if (!ctx || ticks < 0) return CQK_INVALID_ARG;
   ctx->team_wait = (uint64_t)ticks;
+  ctx->team_pause = TeamPause{};
+  ctx->team_epoch += 1;
   return CQK_OK;
 }
 

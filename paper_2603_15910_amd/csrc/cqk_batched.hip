@@ -167,12 +167,20 @@ __device__ __forceinline__ int bucket_of(int64_t L, int wave_max) {
 // the end of the range the slots are cleared and it starts over.
 struct BatTeamCtl {
   uint32_t base, last;
+  TeamFlags flags;   // of the current launch (done: not used)
+  TeamPause pause;
+  uint32_t epoch;    // of the pause
 };
 constexpr uint32_t kTagRestart = 0xc0000000u, kTagEnd = 0xfffffff0u;
 
 // The planning's part in it, by one block.
 template <typename Args>
 __device__ __forceinline__ void start_teams(const Args&) {}
+// CTR_GAVE_UP at the start of a launch.
+template <typename Args>
+__device__ __forceinline__ int32_t teams_off(const Args&) {
+  return 0;
+}
 
 // Planning: the rows are listed by length bucket (workgroup rows longest
 // bucket first, then the wave rows longest bucket first, so the four wave
@@ -298,7 +306,7 @@ __global__ __launch_bounds__(kPBlock) void bat_place_kernel(Args A) {
       A.counters[CTR_NLONG] = nlong;
       A.counters[CTR_NSHORT] = nshort;
       A.counters[CTR_NITEMS] = nlong + (nshort + kWaves - 1) / kWaves;
-      A.counters[CTR_GAVE_UP] = 0;
+      A.counters[CTR_GAVE_UP] = teams_off(A);
       for (int k = 0; k < kNBW; ++k) A.counters[CTR_LBASE + k] = base[kNBW + k];
       A.counters[CTR_GROUPS] = base[kGroupBucket];
     }
@@ -1300,6 +1308,7 @@ struct BatCqkArgs {
   uint64_t* tslots;     // teams: record slots, control words (BatTeamCtl), wait
   BatTeamCtl* tctl;     // limit; tslots null: no teams
   uint64_t tlimit;
+  uint32_t tepoch;
   TeamLate tlate;
 };
 
@@ -1311,7 +1320,18 @@ __device__ __forceinline__ void start_teams<BatCqkArgs>(const BatCqkArgs& A) {
   if (last >= kTagRestart)
     for (size_t i = threadIdx.x; i < kBatTeamBytes / sizeof(uint64_t); i += kPBlock)
       A.tslots[i] = 0;
-  if (threadIdx.x == 0) A.tctl->base = A.tctl->last = (last >= kTagRestart) ? 0u : last;
+  if (threadIdx.x == 0) {
+    BatTeamCtl& T = *A.tctl;
+    T.base = T.last = (last >= kTagRestart) ? 0u : last;
+    TeamPause pause = T.pause;
+    T.flags = next_flags(T.flags, pause, T.epoch != A.tepoch);
+    T.pause = pause;
+    T.epoch = A.tepoch;
+  }
+}
+template <>
+__device__ __forceinline__ int32_t teams_off<BatCqkArgs>(const BatCqkArgs& A) {
+  return A.tslots != nullptr ? A.tctl->flags.gave_up : 0;
 }
 
 __device__ __forceinline__ GenState cqk_row_state(const BatCqkArgs& A, double r) {
@@ -2050,7 +2070,10 @@ __device__ __forceinline__ bool cqk_team_row(const BatCqkArgs& A, TeamLds<kRowBl
 __device__ __forceinline__ void team_end(const BatCqkArgs& A, const Team& team, uint32_t base_tag,
                                          bool ok) {
   if (threadIdx.x == 0) {
-    if (!ok) atomicOr(&A.counters[CTR_GAVE_UP], 1);
+    if (!ok) {
+      atomicOr(&A.counters[CTR_GAVE_UP], (int)kGaveUp);
+      A.tctl->flags.gave_up = kGaveUp;
+    }
     if (team.tag != base_tag) atomicMax(&A.tctl->last, team.tag);
   }
 }
@@ -2060,6 +2083,7 @@ __global__ __launch_bounds__(kRowBlock, kRowBlocksPerCu) void bat_cqk_team_kerne
   __shared__ TeamLds<kRowBlock> S;
   __shared__ BatStat stat;
   __shared__ int item;
+  if (team_is_off(&A.tctl->flags, &S.gave_up)) return;
   stat_init(stat);
   if (threadIdx.x == 0) S.gave_up = 0;
   __syncthreads();
@@ -2369,6 +2393,7 @@ __global__ __launch_bounds__(kRowBlock, kRowBlocksPerCu) void bat_cqk_team_vjp_k
     BatCqkArgs A) {
   __shared__ TeamLds<kRowBlock> S;
   __shared__ int item;
+  if (team_is_off(&A.tctl->flags, &S.gave_up)) return;
   if (threadIdx.x == 0) S.gave_up = 0;
   __syncthreads();
   TeamRows<TIn> rows(A);
@@ -2637,6 +2662,7 @@ BatCqkArgs cqk_args(cqk_ctx* ctx, int32_t nseg, const int64_t* offsets, const vo
     A.tslots = (uint64_t*)((char*)ctx->team.ptr + kTeamBatSlots);
     A.tlimit = ctx->team_wait;
     A.tlate = ctx->team_late;
+    A.tepoch = ctx->team_epoch;
   }
   return A;
 }

@@ -1700,7 +1700,7 @@ __global__ void gen_init_kernel(GenState* st, GenState init) { *st = init; }
 struct TeamResult {   // in the context's pinned host memory
   double lam_final, lam0, bytes;
   int32_t status, iter, passes, stop_reason;
-  TeamFlags flags;    // with gave_up set nothing here counts
+  TeamFlags flags;    // a waiting call's; with gave_up set nothing here counts
   uint32_t tag;       // the last exchange's tag
   int32_t ntrace;
   double part[3 * kTeamMax];  // per block: b^T x, sum |b x|, free indices
@@ -1724,6 +1724,7 @@ struct TeamArgs {
   uint64_t limit;
   uint32_t tag;       // the last tag used (a waiting call)
   TeamLate late;
+  TeamFlags* flags;
   TeamResult* res;
   const TeamCtl* ctl; // queued or captured call: tags from here
 };
@@ -1732,7 +1733,8 @@ struct TeamArgs {
 // return at once, unless a block gave up; then those passes do the solve.
 __global__ void gen_team_commit_kernel(GenState* st, const TeamCtl* ctl) {
   const TeamResult& R = ctl->res;
-  if (R.flags.gave_up || !R.flags.done || R.status == kRunning) return;
+  const TeamFlags& F = ctl->tags.flags;
+  if (F.gave_up || R.status == kRunning) return;
   st->lam_final = R.lam_final;
   st->lam0 = R.lam0;
   st->bytes = R.bytes;
@@ -1776,6 +1778,7 @@ struct RestArgs {
   uint64_t limit;
   uint32_t tag;        // the last tag used; with `tags`, relative to their base
   TeamLate late;
+  TeamFlags* flags;
   const TeamTags* tags;
 };
 
@@ -1784,6 +1787,7 @@ __global__ __launch_bounds__(kTeamBlock) void gen_rest_kernel(RestArgs A) {
   __shared__ TeamLds<kTeamBlock> S;
   const GenState* in = A.st;
   if (in->status != kRunning || in->src == 0 || in->n_src > A.max_src) return;
+  if (team_is_off(A.flags, &S.gave_up)) return;  // no second try in one call
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1), wid = scalar(tid / kWave);
   const int set = scalar(in->src) - 1;
@@ -1927,6 +1931,7 @@ __global__ __launch_bounds__(kTeamBlock) void gen_rest_kernel(RestArgs A) {
     leave = (st.mode == kModeEval) ? !(st.lam > vlo && st.lam < vhi)
                                    : !(vlo <= st.lo && st.hi <= vhi);
   }
+  if (!ok && tid == 0) A.flags->gave_up = kGaveUp;
   if (!ok || blockIdx.x != 0 || tid != 0) return;
   GenState* out = A.st;
   out->bytes += 32.0 * (double)out->n_src * (double)(st.passes - passes0);
@@ -1959,6 +1964,7 @@ __global__ __launch_bounds__(kTeamBlock) void gen_team_kernel(TeamArgs A) {
   constexpr int Q = (E == 8 ? 8 : 4) / V;
   __shared__ TeamLds<kTeamBlock> S;
   __shared__ double lds[3 * NW], tot3[3];
+  if (A.ctl != nullptr && team_is_off(A.flags, &S.gave_up)) return;
   const int tid = threadIdx.x;
   const int64_t n = A.n;
   const int64_t base = (int64_t)blockIdx.x * (kTeamBlock * E);
@@ -2097,7 +2103,7 @@ __global__ __launch_bounds__(kTeamBlock) void gen_team_kernel(TeamArgs A) {
     state_to_scalars(st);
   }
   if (!ok) {
-    if (tid == 0) A.res->flags.gave_up = 1;
+    if (tid == 0) A.flags->gave_up = kGaveUp;
     return;
   }
   const int status = st.status;
@@ -2154,7 +2160,6 @@ __global__ __launch_bounds__(kTeamBlock) void gen_team_kernel(TeamArgs A) {
     R.stop_reason = st.stop_reason;
     R.tag = team.tag;
     R.ntrace = st.ntrace;
-    R.flags.done = 1;
   }
 }
 
@@ -2284,6 +2289,11 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
   const bool is_f32 = sizeof(TIn) == 4;
   const double eps = (is_f32 && o.accum == CQK_ACCUM_F32) ? 1.1920928955078125e-07
                                                           : 2.220446049250313e-16;
+  hipStream_t s = ctx->stream;
+  // sync = 0 or graph capture: every pass the iteration cap allows is queued
+  // at once (those after the loop stops return at once) and nothing is read
+  // back; cqk_ctx_last_info reads the result later.  No per-pass timing then.
+  const bool deferred = !o.sync || stream_capturing(s);
   const TeamShape shape = team_shape(n, ctx->num_cus);
   const uint32_t need = 2 * (uint32_t)std::min(o.max_iter, 1 << 20) + 8;
   // Longer inputs: the iterations on a compacted set in one launch
@@ -2294,7 +2304,7 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
   const uint32_t rest_need = need;  // an exchange per pass at most
   const bool rest = shape.E == 0 && compaction && !o.trace && (!o.timing || o.timing == 2) &&
                     o.max_iter <= (1 << 20) && NR <= kRestRegions * rest_waves(ctx->num_cus) &&
-                    team_ready(ctx, kRests * rest_need);
+                    team_ready(ctx, kRests * rest_need) && (deferred || ctx->team_pause.turn());
   // With compaction on large inputs, a bracket estimated from a sample lets
   // the first pass compact (gen_sample_kernel, gen_sample2_kernel), from
   // kSmpMinN on where gen_rest_kernel then finishes the solve (2.2e6 FP32
@@ -2338,11 +2348,6 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
   init.nblocks = G;
   init.lam_final = __builtin_nan("");
 
-  hipStream_t s = ctx->stream;
-  // sync = 0 or graph capture: every pass the iteration cap allows is queued
-  // at once (those after the loop stops return at once) and nothing is read
-  // back; cqk_ctx_last_info reads the result later.  No per-pass timing then.
-  const bool deferred = !o.sync || stream_capturing(s);
   const bool timing = o.timing && !deferred;
   // timing 2: only the first Newton pass and the recovery carry events (the
   // runtime leaves a few microseconds around every timed dispatch)
@@ -2356,7 +2361,7 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
   // One launch where the problem fits the registers.  Traced and timed calls
   // report single passes and keep the multi-launch route.
   const bool team = shape.E != 0 && !o.trace && !o.timing && o.max_iter <= (1 << 20) &&
-                    team_ready(ctx, need);
+                    team_ready(ctx, need) && (deferred || ctx->team_pause.turn());
   TeamCtl* const ctl = team ? (TeamCtl*)((char*)ctx->team.ptr + kTeamSlotBytes) : nullptr;
   auto launch_team = [&](TeamResult* res, TeamCtl* tc) {
     TeamArgs T{};
@@ -2377,6 +2382,7 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     T.limit = ctx->team_wait;
     T.tag = ctx->team_tag;
     T.late = ctx->team_late;
+    T.flags = tc != nullptr ? &tc->tags.flags : &res->flags;
     T.res = res;
     T.ctl = tc;
     auto go = [&](auto kern) {
@@ -2406,7 +2412,8 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     ctx->team_tag += need;
     if (hip_ok(hipStreamSynchronize(s)) != CQK_OK) return CQK_DEVICE_ERROR;
     const TeamResult& R = *res;
-    if (R.flags.done && !R.flags.gave_up) {
+    ctx->team_pause.outcome(R.flags.gave_up != 0);
+    if (!R.flags.gave_up) {
       ctx->team_tag = R.tag;
       ctx->last_trace.clear();
       ctx->last_trace_count = R.ntrace;
@@ -2451,6 +2458,7 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     R.slots = (uint64_t*)ctx->team.ptr;
     R.limit = ctx->team_wait;
     R.late = ctx->team_late;
+    R.flags = deferred ? &rctl->tags.flags : &A.st->rest;
     R.tag = deferred ? (uint32_t)rests * rest_need : ctx->team_tag;
     R.tags = deferred ? &rctl->tags : nullptr;
     hipLaunchKernelGGL(gen_rest_kernel, dim3(blocks), dim3(kTeamBlock), 0, s, R);
@@ -2459,11 +2467,10 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
   };
   if (rest && deferred) {
     hipLaunchKernelGGL(team_init_kernel<GenState>, dim3(1), dim3(256), 0, s, A.st, init,
-                       &rctl->tags, &rctl->res.flags, (uint64_t*)ctx->team.ptr,
-                       kRests * rest_need);
+                       &rctl->tags, (uint64_t*)ctx->team.ptr, kRests * rest_need, ctx->team_epoch);
   } else if (team && deferred) {
     hipLaunchKernelGGL(team_init_kernel<GenState>, dim3(1), dim3(256), 0, s, A.st, init,
-                       &ctl->tags, &ctl->res.flags, (uint64_t*)ctx->team.ptr, need);
+                       &ctl->tags, (uint64_t*)ctx->team.ptr, need, ctx->team_epoch);
     launch_team(&ctl->res, ctl);
     hipLaunchKernelGGL(gen_team_commit_kernel, dim3(1), dim3(1), 0, s, A.st, ctl);
   } else {
@@ -2578,8 +2585,10 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
         return CQK_DEVICE_ERROR;
       if (hip_ok(hipStreamSynchronize(s)) != CQK_OK) return CQK_DEVICE_ERROR;
       if (hs->status != kRunning) break;
+      if (hs->rest.gave_up) rests = kRests;
       batch = 4;
     }
+    if (rest) ctx->team_pause.outcome(hs->rest.gave_up != 0);
   }
   const int pass_events = ev;
   const int trace_cap = init.trace_cap;

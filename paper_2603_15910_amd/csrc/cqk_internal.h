@@ -30,6 +30,41 @@ inline void launch_timed(F kern, dim3 grid, dim3 block, hipStream_t s, hipEvent_
   }
 }
 
+// After a block of a one-launch call gave up, the calls that pass that route
+// by before the next try: other streams hold the GPU, and every further try
+// would cost a whole wait.  Counted by the host for waiting calls, in device
+// memory for queued and captured ones.
+struct TeamPause {
+  static constexpr uint32_t kFirst = 16, kLongest = 1024;  // calls; doubled from one to the other
+  static constexpr uint32_t kForget = 64;                  // tries in a row that ended well
+  uint32_t left, length, good;
+  // whether this call tries
+  __host__ __device__ bool turn() {
+    if (left == 0) return true;
+    --left;
+    return false;
+  }
+  // how a try ended
+  __host__ __device__ void outcome(bool gave_up) {
+    if (gave_up) {
+      length = (length == 0) ? kFirst : (length < kLongest) ? 2 * length : kLongest;
+      left = length;
+      good = 0;
+    } else if (length != 0 && ++good >= kForget) {
+      length = good = 0;
+    }
+  }
+};
+
+// How a launch ended: gave_up is set by any block whose wait ran out (kGaveUp)
+// and cleared only before the launch, or set there for a launch that is not to
+// run (kNotRun).  done is set by block 0 of a launch that may leave its work to
+// the kernels behind, when it has done it.
+enum : int32_t { kGaveUp = 1, kNotRun = 2 };
+struct TeamFlags {
+  int32_t gave_up, done;
+};
+
 // Run state of the general (Algorithm 1) solver, one record in device memory.
 struct GenState {
   double lam, lam_prev, lo, hi, phi_lo, phi_hi;
@@ -79,6 +114,7 @@ struct GenState {
   int32_t warm;                   // 1: lam_0 comes from a primal estimate
   int32_t lam0_later;             // 1: lam_0 is computed after the sample (warm or formula start)
   int32_t team_done;              // 1: a one-launch solve wrote x and this state
+  TeamFlags rest;                 // a waiting call's gen_rest_kernel
 };
 
 // Run state of the simplex / l1 solver (Algorithm 4 on a compacted set).
@@ -162,7 +198,9 @@ struct cqk_ctx {
   cqk::DeviceBuf team;
   bool team_zeroed = false;
   uint32_t team_tag = 0;
-  uint64_t team_wait = 2000000;
+  uint64_t team_wait = 30000;
+  cqk::TeamPause team_pause{};
+  uint32_t team_epoch = 1;          // counts cqk_set_team_wait: ends the pauses in device memory
   cqk::TeamLate team_late{0, 0};    // exchange 0: none
   void* scratch = nullptr;  // this device's no-allocation planning buffers (noalloc_scratch)
 };

@@ -1751,7 +1751,7 @@ constexpr int kTeamListBytes = 64 * 1024;  // a block's list; beyond it the regi
 struct SpxTeamResult {   // in the context's pinned host memory, or behind the slots
   double lam_final, lam0, sum_abs, n_init;
   int32_t status, iter, passes, stop_reason, copy;
-  TeamFlags flags;       // with gave_up set nothing here counts
+  TeamFlags flags;       // a waiting call's; with gave_up set nothing here counts
   uint32_t tag;
   int64_t nnz;           // sparse output
   double part[2 * kTeamMax];  // per block: sum |x|, values not zero
@@ -1775,6 +1775,7 @@ struct SpxTeamArgs {
   uint64_t limit;
   uint32_t tag;
   TeamLate late;
+  TeamFlags* flags;
   SpxTeamResult* res;
   const SpxTeamCtl* ctl;
 };
@@ -1784,7 +1785,8 @@ struct SpxTeamArgs {
 // once, unless a block gave up or the kernel left the work to them.
 __global__ void spx_team_commit_kernel(SpxState* st, const SpxTeamCtl* ctl, bool rest) {
   const SpxTeamResult& R = ctl->res;
-  if (R.flags.gave_up || !R.flags.done) return;
+  const TeamFlags& F = ctl->tags.flags;
+  if (F.gave_up || (rest && !F.done)) return;
   st->lam_final = R.lam_final;
   st->lam0 = R.lam0;
   st->sum_abs = R.sum_abs;
@@ -1809,7 +1811,7 @@ __global__ void spx_team_commit_kernel(SpxState* st, const SpxTeamCtl* ctl, bool
 template <typename TIn>
 __global__ __launch_bounds__(kBlock) void spx_clear_kernel(TIn* x, int64_t n,
                                                            const TeamFlags* flags) {
-  if (flags != nullptr && !flags->gave_up) return;
+  if (flags != nullptr && flags->gave_up != kGaveUp) return;
   constexpr int V = VecWidth<TIn>::value;
   typename Raw16<TIn>::type z;
 #pragma unroll
@@ -1970,6 +1972,7 @@ __global__ __launch_bounds__(kTeamBlock) void spx_team_kernel(SpxTeamArgs A) {
   __shared__ TIn lists[NW][CAP];
   __shared__ int cnt[Q * NW + 1];
   __shared__ double bounds[NW];
+  if (A.ctl != nullptr && team_is_off(A.flags, &S.gave_up)) return;
   int tid = threadIdx.x;
   const int lane = tid & (kWave - 1), wid = scalar(tid / kWave);
   const int64_t n = A.n;
@@ -2136,7 +2139,7 @@ __global__ __launch_bounds__(kTeamBlock) void spx_team_kernel(SpxTeamArgs A) {
   const bool copy = O.copy;
   const double lam_final = O.lam_final;
   if (!ok) {
-    if (tid == 0) A.res->flags.gave_up = 1;
+    if (tid == 0) A.flags->gave_up = kGaveUp;
     return;
   }
   double sums[2] = {0.0, 0.0};
@@ -2209,7 +2212,7 @@ __global__ __launch_bounds__(kTeamBlock) void spx_team_kernel(SpxTeamArgs A) {
       double total = mine, before = 0.0;
       if (team.T > 1) ok = team_prefix(team, S, par, mine, &total, &before);
       if (!ok) {
-        if (tid == 0) A.res->flags.gave_up = 1;
+        if (tid == 0) A.flags->gave_up = kGaveUp;
         return;
       }
       nnz = (int64_t)total;
@@ -2258,7 +2261,6 @@ __global__ __launch_bounds__(kTeamBlock) void spx_team_kernel(SpxTeamArgs A) {
     R.copy = copy ? 1 : 0;
     R.tag = team.tag;
     R.nnz = nnz;
-    R.flags.done = 1;
   }
 }
 
@@ -2296,6 +2298,7 @@ struct SpxRestArgs {
   uint64_t limit;
   uint32_t tag;
   TeamLate late;
+  TeamFlags* flags;
   SpxTeamResult* res;
   const TeamTags* tags;  // queued or captured call
 };
@@ -2307,6 +2310,7 @@ __global__ __launch_bounds__(kTeamBlock) void spx_rest_kernel(SpxRestArgs A) {
   __shared__ TeamLds<kTeamBlock> S;
   __shared__ TIn lists[NW][CAP];
   if (A.st->status != kRunning || A.st->team_done) return;
+  if (A.tags != nullptr && team_is_off(A.flags, &S.gave_up)) return;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1), wid = scalar(tid / kWave);
   const bool l1 = A.l1 != 0;
@@ -2338,7 +2342,7 @@ __global__ __launch_bounds__(kTeamBlock) void spx_rest_kernel(SpxRestArgs A) {
     ok = team_reduce<3, kTeamBlock, 1>(team, S, par, v2, ti);
   }
   if (!ok) {
-    if (tid == 0) A.res->flags.gave_up = 1;
+    if (tid == 0) A.flags->gave_up = kGaveUp;
     return;
   }
   if (tot[2] > 0.0 || (l1 && tot[3] <= A.r) || !(tot[0] <= (double)A.max_n)) return;
@@ -2382,7 +2386,7 @@ __global__ __launch_bounds__(kTeamBlock) void spx_rest_kernel(SpxRestArgs A) {
                               tot[6]},
                      each, O);
   if (!ok) {
-    if (tid == 0) A.res->flags.gave_up = 1;
+    if (tid == 0) A.flags->gave_up = kGaveUp;
     return;
   }
   const double lam = O.lam_final;
@@ -2412,7 +2416,7 @@ __global__ __launch_bounds__(kTeamBlock) void spx_rest_kernel(SpxRestArgs A) {
     R.passes = O.passes + 1;
     R.stop_reason = O.reason;
     R.copy = 0;
-    R.flags.done = 1;
+    A.flags->done = 1;
   } else if (blockIdx.x == 0 && tid == 0) {
     SpxState* st = A.st;
     st->lam = st->lam_final = lam;
@@ -2605,11 +2609,12 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
   }
   const uint32_t need = (uint32_t)std::min(o.max_iter, 1 << 20) + 8;
   const bool team = tE != 0 && condat && r != 0.0 && sizeof(TA) == 8 && !o.trace && !o.timing &&
-                    o.max_iter <= (1 << 20) && team_ready(ctx, need);
+                    o.max_iter <= (1 << 20) && team_ready(ctx, need) &&
+                    (deferred || ctx->team_pause.turn());
   // Longer y: one launch behind the Algorithm 2 pass.
   const bool rest = tE == 0 && condat && r != 0.0 && sizeof(TA) == 8 && !o.trace && !o.timing &&
                     o.compaction != CQK_COMPACT_OFF && o.max_iter <= (1 << 20) &&
-                    team_ready(ctx, need);
+                    team_ready(ctx, need) && (deferred || ctx->team_pause.turn());
   if (rest) tT = std::min(ctx->num_cus, kTeamMax);
   SpxTeamCtl* const ctl =
       (team || rest) ? (SpxTeamCtl*)((char*)ctx->team.ptr + kTeamSlotBytes) : nullptr;
@@ -2635,6 +2640,7 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
     R.limit = ctx->team_wait;
     R.tag = tags != nullptr ? 0u : ctx->team_tag;
     R.late = ctx->team_late;
+    R.flags = tags != nullptr ? &ctl->tags.flags : &res->flags;
     R.res = res;
     R.tags = tags;
     hipLaunchKernelGGL(spx_rest_kernel<TIn>, dim3(tT), dim3(kTeamBlock), 0, s, R);
@@ -2656,6 +2662,7 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
     T.limit = ctx->team_wait;
     T.tag = ctx->team_tag;
     T.late = ctx->team_late;
+    T.flags = tc != nullptr ? &tc->tags.flags : &res->flags;
     T.res = res;
     T.ctl = tc;
     auto go = [&](auto kern) {
@@ -2709,7 +2716,8 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
     if (hip_ok(hipGetLastError()) != CQK_OK) return CQK_DEVICE_ERROR;
     ctx->team_tag += need;
     if (hip_ok(hipStreamSynchronize(s)) != CQK_OK) return CQK_DEVICE_ERROR;
-    if (res->flags.done && !res->flags.gave_up) {
+    ctx->team_pause.outcome(res->flags.gave_up != 0);
+    if (!res->flags.gave_up) {
       ctx->team_tag = res->tag;
       if (sparse) {
         ctx->bitmap_clean = true;  // not touched
@@ -2724,10 +2732,10 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
   const bool team_queued = (team || rest) && deferred;
   if (rest && deferred) {
     hipLaunchKernelGGL(team_init_kernel<SpxState>, dim3(1), dim3(256), 0, s, A.st, init,
-                       &ctl->tags, &ctl->res.flags, (uint64_t*)ctx->team.ptr, need);
+                       &ctl->tags, (uint64_t*)ctx->team.ptr, need, ctx->team_epoch);
   } else if (team_queued) {
     hipLaunchKernelGGL(team_init_kernel<SpxState>, dim3(1), dim3(256), 0, s, A.st, init,
-                       &ctl->tags, &ctl->res.flags, (uint64_t*)ctx->team.ptr, need);
+                       &ctl->tags, (uint64_t*)ctx->team.ptr, need, ctx->team_epoch);
     launch_team(&ctl->res, ctl);
     hipLaunchKernelGGL(spx_team_commit_kernel, dim3(1), dim3(1), 0, s, A.st, ctl, false);
   }
@@ -2806,9 +2814,12 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
         launch_rest(&ctl->res, &ctl->tags);
         hipLaunchKernelGGL(spx_team_commit_kernel, dim3(1), dim3(1), 0, s, A.st, ctl, true);
         hipLaunchKernelGGL(spx_clear_kernel<TIn>, dim3(G0), dim3(kBlock), 0, s, x, n,
-                           (const TeamFlags*)&ctl->res.flags);
+                           (const TeamFlags*)&ctl->tags.flags);
       } else if (rest) {
-        SpxTeamResult* res = (SpxTeamResult*)ctx->host_pinned;
+        // (a sparse call's state comes back to the buffer's start)
+        static_assert(sizeof(SpxState) <= 16384 && 16384 + sizeof(SpxTeamResult) <= 32768,
+                      "both fit the lower half of the pinned buffer");
+        SpxTeamResult* res = (SpxTeamResult*)((char*)ctx->host_pinned + 16384);
         res->flags = TeamFlags{0, 0};
         launch_rest(res, nullptr);
         ctx->team_tag += need;
@@ -2816,11 +2827,13 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
         if (sparse) {
           fin_chain();
           if (wait_state() != CQK_OK) return CQK_DEVICE_ERROR;
+          ctx->team_pause.outcome(res->flags.gave_up != 0);
           rest_done = hs->status != kRunning;
         } else {
           if (hip_ok(hipGetLastError()) != CQK_OK ||
               hip_ok(hipStreamSynchronize(s)) != CQK_OK)
             return CQK_DEVICE_ERROR;
+          ctx->team_pause.outcome(res->flags.gave_up != 0);
           if (res->flags.done && !res->flags.gave_up)
             return answer(*res, npass, (2.0 * sizeof(TIn) + 4.0) * res->n_init);
           if (res->flags.gave_up)

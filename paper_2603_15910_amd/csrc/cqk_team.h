@@ -73,12 +73,6 @@ __device__ __forceinline__ Team grid_team(uint64_t* slots, uint32_t tag, uint64_
               late_tag(late, tag)};
 }
 
-// How a launch ended: gave_up is set by any block whose wait ran out and
-// cleared only before the launch, done by block 0 when it got to the end.
-struct TeamFlags {
-  int32_t gave_up, done;
-};
-
 // LDS of the reductions below.
 template <int BLOCK>
 struct TeamLds {
@@ -352,16 +346,38 @@ __device__ __forceinline__ bool team_prefix(Team& team, TeamLds<BLOCK>& S, int& 
 // They have the top bit set, those of waiting calls clear.
 struct TeamTags {
   uint32_t base, next;
+  TeamFlags flags;   // of the current launch
+  TeamPause pause;
+  uint32_t epoch;    // of the pause
 };
 constexpr uint32_t kTeamDeviceTags = 0x80000000u;
 
+// What a launch's flags are at its start, from those of the one before.
+__device__ __forceinline__ TeamFlags next_flags(const TeamFlags& last, TeamPause& pause,
+                                                bool forget) {
+  if (forget) pause = TeamPause{0, 0, 0};
+  else if (last.gave_up != kNotRun) pause.outcome(last.gave_up != 0);
+  return TeamFlags{pause.turn() ? 0 : (int32_t)kNotRun, 0};
+}
+
+// Whether a queued launch's kernel is to return at once, the same in the
+// whole block: not to run, or a block gave up before this one started.
+__device__ __forceinline__ bool team_is_off(const TeamFlags* flags, int* lds) {
+  if (threadIdx.x == 0)
+    *lds = __hip_atomic_load(&flags->gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  const int off = *lds;
+  __syncthreads();
+  return off != 0;
+}
+
 // Before a queued or captured one-launch call: the run state of the kernels
 // queued behind it, a fresh range of tags (the slots are cleared when the
-// range starts over) and clear flags.
+// range starts over) and its flags.
 template <typename State>
 __global__ __launch_bounds__(256) void team_init_kernel(State* st, State init, TeamTags* tags,
-                                                        TeamFlags* flags, uint64_t* slots,
-                                                        uint32_t need) {
+                                                        uint64_t* slots, uint32_t need,
+                                                        uint32_t epoch) {
   const uint32_t next = tags->next;
   const bool wrap = next == 0 || next > 0xffffffffu - need;
   __syncthreads();
@@ -372,7 +388,10 @@ __global__ __launch_bounds__(256) void team_init_kernel(State* st, State init, T
     const uint32_t base = wrap ? kTeamDeviceTags : next;
     tags->base = base;
     tags->next = base + need;
-    *flags = TeamFlags{0, 0};
+    TeamPause pause = tags->pause;
+    tags->flags = next_flags(tags->flags, pause, tags->epoch != epoch);
+    tags->pause = pause;
+    tags->epoch = epoch;
   }
 }
 
