@@ -1773,15 +1773,46 @@ struct RowShape {
   static constexpr int kMaxLog = kLog + kBatTeamLogs - 1;  // longest team rows
   static_assert(kRowBlock * E == 1 << kLog, "a row of bit length kLog fits one block");
   static_assert(kMaxLog < kNBW - 1, "and every team row has a bucket of its own length");
+  static_assert(kBatTeamMax == 1 << (kMaxLog - kLog), "the longest rows take the largest teams");
 };
 
+// The shortest rows (their bit length) that teams hold in a call of nlong
+// workgroup rows; shorter ones are streamed beside the wave rows.  The team
+// kernel comes before those, so it adds its launch, a load and its exchanges
+// to the call's time, where a short row's evaluations find it in the cache.
+// kAlways: held in any call; each bit less wants so many workgroup rows.
+// Rows of one length, streamed / held, us.  FP64: 8 of 1000 values 47 / 52,
+// 3000 57 / 54 (but 58 / 73 among rows of 10 to 3000), 6000 81 / 55; 256 of
+// 3000 68 / 66 (300 of 600 to 4000 76 / 87), 512 of 3000 87 / 78, 1024 of 1200
+// 87 / 81, 2048 of 800 97 / 91.
+// FP32: 8 of 3000 53 / 55, 6000 74 / 60; 512 of 3000 70 / 70, 2048 of 2000 113
+// / 107, 8192 of 800 180 / 175.  Backward, FP64: 8 of 3000 37 / 42, 6000 44 /
+// 42; 512 of 3000 57 / 55, 1024 of 1200 57 / 58, 4096 of 800 81 / 79; FP32: 8
+// of 12 000 49 / 43 (but 47 / 58 among rows of 3000 to 9000), 256 of 8000 52 /
+// 51, 512 of 6000 56 / 57, 1024 of 3000 67 / 67, 4096 of 2000 99 / 87.
+template <typename TIn, bool BACKWARD>
+__device__ __forceinline__ int held_from(int nlong) {
+  constexpr bool k64 = sizeof(TIn) == 8;
+  constexpr int kAlways = (BACKWARD && !k64) ? 15 : 13;
+  // from one bit less down to 9, that of the shortest workgroup rows
+  constexpr int kLeast[6] = {BACKWARD ? (k64 ? 384 : 256) : 512,
+                             BACKWARD ? (k64 ? 1024 : 512) : (k64 ? 1024 : 2048),
+                             BACKWARD ? (k64 ? 3072 : 1024) : (k64 ? 2048 : 8192),
+                             BACKWARD ? (k64 ? 8192 : 3072) : (k64 ? 4096 : 16384),
+                             16384, 32768};
+  int b = kAlways;
+  while (b > 9 && nlong >= kLeast[kAlways - b]) --b;
+  return b;
+}
+
 // The rows of this block one after the other, each with its team.  Longest
-// classes first; a class with fewer rows than teams takes larger teams (never
-// larger than those of the class before: teams only split).  Rows of a class
-// go to its teams in turn, starting where the class before left off; the
-// rows of one block each come last, from the work queue.  Ids, extents and
-// right-hand sides are fetched for kWin rows at a time, one lane each.
-template <typename TIn>
+// classes first.  Rows of a class go to its teams in turn, starting where the
+// class before left off; the rows of one block each come last, from the work
+// queue.  Ids, extents and right-hand sides are fetched for kWin rows at a
+// time, one lane each.  (Larger teams for a class of few rows, an equal share
+// per block of a smaller piece, were slower throughout: 1 row of 12 000 FP64
+// values 67 against 56 us, 8 of 30 000 79 / 59, 32 of 100 000 121 / 118.)
+template <typename TIn, bool BACKWARD>
 struct TeamRows {
   static constexpr int kTeamLog = RowShape<TIn>::kLog, kTeamMaxLog = RowShape<TIn>::kMaxLog;
   static constexpr int kWin = 4;
@@ -1789,28 +1820,26 @@ struct TeamRows {
   int id;               // the row, its first element and length, its r
   int64_t first, len;
   double rhs;
-  int b, from, cnt, j, NT, off, cap, per, wi, wn;
+  int b, from, cnt, j, NT, off, per, wi, wn;
   int w_id;             // the window, a row per lane
   int64_t w_first, w_len;
   double w_rhs;
   int bases;            // bucket starts, one per lane
-  int nlong;
+  int end;              // of the held rows in the list
   ItemSource src;
 
   __device__ __forceinline__ explicit TeamRows(const BatCqkArgs& A) {
     const int lane = threadIdx.x & (kWave - 1);
     bases = (lane < kNBW) ? A.counters[CTR_LBASE + lane] : 0;
-    nlong = scalar(A.counters[CTR_NLONG]);
+    end = base_of(held_from<TIn, BACKWARD>(scalar(A.counters[CTR_NLONG])) - 1);
     const uint32_t tag = scalar(A.tctl->base);
     team = Team{nullptr, A.tlimit, tag, 1, 0, kBatTeamBlocks * kSlotWords, late_tag(A.tlate, tag)};
     b = kTeamMaxLog + 1;
     from = cnt = j = off = wi = wn = 0;
     NT = per = 1;
-    cap = kBatTeamMax;
-    while (cap > (int)gridDim.x) cap >>= 1;
   }
 
-  __device__ __forceinline__ bool none() const { return nlong <= base_of(kTeamMaxLog); }
+  __device__ __forceinline__ bool none() const { return end <= base_of(kTeamMaxLog); }
 
   __device__ __forceinline__ int base_of(int k) const {
     return __builtin_amdgcn_readlane(bases, k);
@@ -1842,11 +1871,8 @@ struct TeamRows {
         if (b <= kTeamMaxLog) off = (off + cnt % NT * team.T) % (NT * team.T);
         if (--b == kTeamLog) break;
         from = base_of(b);
-        cnt = base_of(b - 1) - from;
-        int lg = b - kTeamLog;
-        while (cnt > 0 && (2 << lg) <= cap && ((int64_t)cnt << (lg + 1)) <= G) ++lg;
-        const int T = 1 << lg, mine = (int)blockIdx.x / T;
-        if (cnt > 0) cap = T;
+        cnt = min(end, base_of(b - 1)) - from;
+        const int lg = b - kTeamLog, T = 1 << lg, mine = (int)blockIdx.x / T;
         NT = G / T;
         off -= off % T;
         team.T = T;
@@ -1862,7 +1888,7 @@ struct TeamRows {
         j += n * NT;
       } else {
         from = base_of(kTeamLog);
-        cnt = nlong - from;
+        cnt = end - from;
         per = min(kWin, max(1, cnt / (G * 4)));
         team.T = 1;
         team.me = 0;
@@ -2083,12 +2109,11 @@ __global__ __launch_bounds__(kRowBlock, kRowBlocksPerCu) void bat_cqk_team_kerne
   __shared__ TeamLds<kRowBlock> S;
   __shared__ BatStat stat;
   __shared__ int item;
-  if (team_is_off(&A.tctl->flags, &S.gave_up)) return;
+  TeamRows<TIn, false> rows(A);
+  if (rows.none() || team_is_off(&A.tctl->flags, &S.gave_up)) return;
   stat_init(stat);
   if (threadIdx.x == 0) S.gave_up = 0;
   __syncthreads();
-  TeamRows<TIn> rows(A);
-  if (rows.none()) return;
   const uint32_t base_tag = rows.team.tag;
   int par = 0;
   bool ok = true;
@@ -2100,12 +2125,21 @@ __global__ __launch_bounds__(kRowBlock, kRowBlocksPerCu) void bat_cqk_team_kerne
   stat_flush<true>(stat, A.counters + CTR_STAT1);
 }
 
-// Workgroup rows that no team holds: those past the longest team rows, or all
-// of them when a team gave up or there are none.
-template <typename TIn>
-__device__ __forceinline__ int streamed_rows(const BatCqkArgs& A) {
-  if (A.tslots == nullptr || A.counters[CTR_GAVE_UP]) return A.counters[CTR_NLONG];
-  return A.counters[CTR_LBASE + RowShape<TIn>::kMaxLog];
+// Workgroup rows that no team holds: those past the longest team rows and
+// those shorter than the held ones, or all of them when a team gave up or
+// there are none.
+struct Streamed {
+  int longer, held;   // entries before the held rows, and of these
+  int n;
+  __device__ __forceinline__ int entry(int k) const { return k < longer ? k : k + held; }
+};
+template <typename TIn, bool BACKWARD>
+__device__ __forceinline__ Streamed streamed_rows(const BatCqkArgs& A) {
+  const int nlong = A.counters[CTR_NLONG];
+  if (A.tslots == nullptr || A.counters[CTR_GAVE_UP]) return {nlong, 0, nlong};
+  const int longer = A.counters[CTR_LBASE + RowShape<TIn>::kMaxLog];
+  const int end = A.counters[CTR_LBASE + held_from<TIn, BACKWARD>(nlong) - 1];
+  return {longer, end - longer, nlong - (end - longer)};
 }
 
 // The wave rows, four to a block at a time; each wave takes kRowsPerWave rows
@@ -2119,7 +2153,8 @@ __global__ __launch_bounds__(kBlock, 3) void bat_cqk_solve_kernel(BatCqkArgs A) 
   __shared__ BatStat stat;
   __shared__ CqkLds S;
   const int nlong = A.counters[CTR_NLONG];
-  const int nstream = streamed_rows<TIn>(A);
+  const Streamed streamed = streamed_rows<TIn, false>(A);
+  const int nstream = streamed.n;
   // the shortest may be the group kernel's
   const int nshort = A.grouped ? A.counters[CTR_GROUPS] - nlong : A.counters[CTR_NSHORT];
   const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
@@ -2140,8 +2175,8 @@ __global__ __launch_bounds__(kBlock, 3) void bat_cqk_solve_kernel(BatCqkArgs A) 
     // workgroup rows that no team holds stream from memory at every evaluation
     const int row = A.short_first ? item - ngroups : item;
     if (row >= 0 && row < nstream) {
-      cqk_long_row<TIn>(A, A.list[row], A.lrow[2 * (size_t)row], A.lrow[2 * (size_t)row + 1], S,
-                        stat);
+      const size_t e = (size_t)streamed.entry(row);
+      cqk_long_row<TIn>(A, A.list[e], A.lrow[2 * e], A.lrow[2 * e + 1], S, stat);
       __syncthreads();
       continue;
     }
@@ -2393,11 +2428,10 @@ __global__ __launch_bounds__(kRowBlock, kRowBlocksPerCu) void bat_cqk_team_vjp_k
     BatCqkArgs A) {
   __shared__ TeamLds<kRowBlock> S;
   __shared__ int item;
-  if (team_is_off(&A.tctl->flags, &S.gave_up)) return;
+  TeamRows<TIn, true> rows(A);
+  if (rows.none() || team_is_off(&A.tctl->flags, &S.gave_up)) return;
   if (threadIdx.x == 0) S.gave_up = 0;
   __syncthreads();
-  TeamRows<TIn> rows(A);
-  if (rows.none()) return;
   const uint32_t base_tag = rows.team.tag;
   int par = 0;
   bool ok = true;
@@ -2414,7 +2448,8 @@ __global__ __launch_bounds__(kBlock) void bat_cqk_vjp_kernel(BatCqkArgs A) {
   __shared__ CqkLds S;
   const int nlong = A.counters[CTR_NLONG];
   const int nshort = A.counters[CTR_NSHORT];
-  const int nstream = streamed_rows<TIn>(A);
+  const Streamed streamed = streamed_rows<TIn, true>(A);
+  const int nstream = streamed.n;
   const int nsg = (nshort + kWaves - 1) / kWaves;
   const int nitems = nstream + nsg;
   ItemSource src;
@@ -2437,7 +2472,8 @@ __global__ __launch_bounds__(kBlock) void bat_cqk_vjp_kernel(BatCqkArgs A) {
       idx = is_long ? item : item - nstream;
     }
     if (is_long) {
-      cqk_vjp_long_row<TIn>(A, A.list[idx], A.lrow[2 * (size_t)idx], A.lrow[2 * (size_t)idx + 1],
+      const size_t e = (size_t)streamed.entry(idx);
+      cqk_vjp_long_row<TIn>(A, A.list[e], A.lrow[2 * e], A.lrow[2 * e + 1],
                             S);
     } else {
       const int k = idx * kWaves + (int)(threadIdx.x / kWave);
