@@ -2570,14 +2570,19 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     if (hip_ok(hipGetLastError()) != CQK_OK) return CQK_DEVICE_ERROR;
   } else {
     // Algorithm 1 typically stops after five to seven evaluations here, all
-    // but the first one or two of them on a compacted set
+    // but the first one or two of them on a compacted set.  Where the sampled
+    // bracket missed the first iterate the next pass or two leave one: two
+    // before the state is looked at again (four, the later ones with nothing
+    // to do, took 255 against 244 us for 2.2e6 uniform FP64 indices from
+    // lam_0 = 0.1; one, 563 against 522 where every pass reads the arrays).
     int batch = !rest ? 6 : sampled ? 1 : 2;
     while (launched < max_launch) {
       if (launched == 1 && ask_flat && hs->flat != 0) flat_pass();
       const int k = std::min(batch, max_launch - launched);
       for (int i = 0; i < k; ++i) {
         pass();
-        launch_rest();
+        // (the first pass without a sample leaves no set)
+        if (launched > 1 || sampled) launch_rest();
       }
       finalize();
       if (hip_ok(hipGetLastError()) != CQK_OK) return CQK_DEVICE_ERROR;
@@ -2586,7 +2591,7 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
       if (hip_ok(hipStreamSynchronize(s)) != CQK_OK) return CQK_DEVICE_ERROR;
       if (hs->status != kRunning) break;
       if (hs->rest.gave_up) rests = kRests;
-      batch = 4;
+      batch = (rest && sampled && launched == 1) ? 2 : 4;
     }
     if (rest) ctx->team_pause.outcome(hs->rest.gave_up != 0);
   }
