@@ -1852,7 +1852,7 @@ __device__ __forceinline__ bool spx_team_loop(Team& team, TeamLds<kTeamBlock>& S
   bool ok = true;
   int status = kRunning, iter = 0, reason = 0, passes = 1;
   bool copy = false;
-  double lam_final = __builtin_nan(""), lam0 = __builtin_nan("");
+  double lam_final = __builtin_nan(""), lam0 = 0.0;
   double lo = -inf_d(), hi = inf_d(), lam = inf_d();
   double upper = inf_d();  // the lists' bound, where the first iterate is not one
   if (B.bad > 0.0) {
