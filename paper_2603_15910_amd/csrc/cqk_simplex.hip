@@ -1796,7 +1796,7 @@ __global__ void spx_team_commit_kernel(SpxState* st, const SpxTeamCtl* ctl, bool
   st->passes = R.passes;
   st->stop_reason = R.stop_reason;
   if (R.copy) st->fin_mode = kFinCopy;
-  if (rest) {  // the survivors' entries, over the zeros of the Algorithm 2 pass
+  if (rest && !R.copy) {  // the survivors' entries, over the zeros of the Algorithm 2 pass
     st->src = 2;
     st->n_src = (int64_t)R.n_init;
     st->x_zeroed = 1;
@@ -2270,8 +2270,9 @@ __global__ __launch_bounds__(kTeamBlock) void spx_team_kernel(SpxTeamArgs A) {
 // survivors and, for a dense output, x at the ones above -lam.  The blocks
 // (one per compute unit) share the wave regions; a wave lists its survivors
 // above the merged bound in LDS, or sweeps its regions when they do not fit.
-// Sets of more than max_n values, bad values and a y inside the l1 ball are
-// left to the kernels behind.  A dense output is every block's work, so its
+// Sets of more than max_n values and bad values are left to the kernels
+// behind, and so is a sparse output of a y inside the l1 ball (a dense one is
+// copied here: another 20 us for the host to look and queue that copy).  A dense output is every block's work, so its
 // outcome goes to the result and counts only when no block gave up (the host,
 // or spx_team_commit_kernel, looks at the flags; spx_clear_kernel takes back
 // what was written of one that does not); a sparse one is written
@@ -2289,6 +2290,7 @@ struct SpxRestArgs {
   const double* partials;
   int32_t G;             // block records in partials
   const void* xw;        // a warm start (only whether)
+  const void* y;
   void* x;               // null: sparse output, written by the kernels behind
   int64_t n, max_n;
   double r, tol;
@@ -2302,6 +2304,63 @@ struct SpxRestArgs {
   SpxTeamResult* res;
   const TeamTags* tags;  // queued or captured call
 };
+
+// x = y, and the outcome of a y inside the ball, sum |y| = abs_sum.
+template <typename TIn>
+__device__ __forceinline__ void spx_rest_copy(const SpxRestArgs& A, double abs_sum) {
+  constexpr int V = VecWidth<TIn>::value, U = 4;   // U loads in flight
+  typedef typename Raw16<TIn>::type Raw;
+  const int tid = threadIdx.x;
+  const TIn* y = (const TIn*)A.y;
+  TIn* x = (TIn*)A.x;
+  double sums[2] = {0.0, 0.0};
+  auto add = [&](TIn t) {
+    sums[0] += fabs((double)t);
+    sums[1] += (t != TIn(0)) ? 1.0 : 0.0;
+  };
+  constexpr int64_t step = (int64_t)kTeamBlock * V;
+  for (int64_t b = (int64_t)blockIdx.x * U * step; b < A.n; b += (int64_t)gridDim.x * U * step) {
+    const int64_t i = b + (int64_t)tid * V;
+    if (b + U * step <= A.n) {
+      Raw t[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) t[u] = ld16(y + i + u * step);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        st16(x + i + u * step, t[u]);
+#pragma unroll
+        for (int k = 0; k < V; ++k) add(t[u][k]);
+      }
+    } else {
+      for (int u = 0; u < U; ++u) {
+        for (int k = 0; k < V; ++k) {
+          const int64_t j = i + u * step + k;
+          if (j < A.n) {
+            const TIn t = y[j];
+            x[j] = t;
+            add(t);
+          }
+        }
+      }
+    }
+  }
+  constexpr int NW = kTeamBlock / kWave;
+  __shared__ double lds[2 * NW], tot2[2];
+  block_reduce<2, 0, 0, kTeamBlock>(sums, nullptr, nullptr, lds, tot2);
+  if (tid < 2) A.res->part[2 * blockIdx.x + tid] = tot2[tid];
+  if (blockIdx.x == 0 && tid == 0) {
+    SpxTeamResult& R = *A.res;
+    R.lam_final = R.lam0 = 0.0;
+    R.sum_abs = abs_sum;
+    R.n_init = 0.0;
+    R.status = CQK_OK;
+    R.iter = 0;
+    R.passes = 1;
+    R.stop_reason = 5;
+    R.copy = 1;
+    A.flags->done = 1;
+  }
+}
 
 template <typename TIn>
 __global__ __launch_bounds__(kTeamBlock) void spx_rest_kernel(SpxRestArgs A) {
@@ -2345,7 +2404,12 @@ __global__ __launch_bounds__(kTeamBlock) void spx_rest_kernel(SpxRestArgs A) {
     if (tid == 0) A.flags->gave_up = kGaveUp;
     return;
   }
-  if (tot[2] > 0.0 || (l1 && tot[3] <= A.r) || !(tot[0] <= (double)A.max_n)) return;
+  const bool copy = l1 && tot[3] <= A.r;
+  if (tot[2] > 0.0 || (copy ? A.x == nullptr : !(tot[0] <= (double)A.max_n))) return;
+  if (copy) {
+    spx_rest_copy<TIn>(A, tot[3]);
+    return;
+  }
   const double bound = (tot[0] > 0.0) ? fmin((A.r - tot[1]) / tot[0], tot[6]) : tot[6];
   const TIn thr = round_down_to<TIn>(-bound);
   auto absl = [&](TIn t) { return l1 ? absval(t) : t; };
@@ -2628,6 +2692,7 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
     R.partials = A.partials;
     R.G = G0;
     R.xw = xw;
+    R.y = y;
     R.x = A.x;
     R.n = n;
     R.max_n = (int64_t)kRestMax * tT;
@@ -2835,7 +2900,8 @@ cqk_status run_simplex(cqk_ctx* ctx, int64_t n, const TIn* y, const TIn* xw, Spa
             return CQK_DEVICE_ERROR;
           ctx->team_pause.outcome(res->flags.gave_up != 0);
           if (res->flags.done && !res->flags.gave_up)
-            return answer(*res, npass, (2.0 * sizeof(TIn) + 4.0) * res->n_init);
+            return answer(*res, npass, res->copy ? 2.0 * sizeof(TIn) * (double)n
+                                                 : (2.0 * sizeof(TIn) + 4.0) * res->n_init);
           if (res->flags.gave_up)
             hipLaunchKernelGGL(spx_clear_kernel<TIn>, dim3(G0), dim3(kBlock), 0, s, x, n,
                                (const TeamFlags*)nullptr);

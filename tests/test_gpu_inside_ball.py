@@ -51,3 +51,19 @@ def test_inside(ctx, dtype, n):
             assert torch.equal(i, torch.nonzero(y)[:, 0]) and torch.equal(v, y[i])
             _says_inside(info, n, y)
     assert cqk.cqk_set_team_wait(ctx.handle, 30_000) == 0
+
+
+@pytest.mark.parametrize("n", [12_582_913, 12_599_999])
+@pytest.mark.parametrize("dtype", [F32, F64])
+def test_long_inside_in_three_launches(ctx, dtype, n):
+    """The sample, the pass over y and the launch behind it, which makes the
+    copy; the end of y that is no whole vector, and y and x at any element."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    for off in (0, 1, 3):
+        y = torch.randn(n + off, device="cuda", dtype=dtype, generator=g)[off:]
+        out = torch.full((n + 2 * off,), 9.0, device="cuda", dtype=dtype)
+        x, info = ctx.project_l1(y, 2.0 * n, out=out[off:off + n])
+        assert torch.equal(x, y) and info["pass_launches"] == 3
+        assert bool((out[:off] == 9.0).all()) and bool((out[off + n:] == 9.0).all())
+        _says_inside(info, n, y)
