@@ -26,6 +26,12 @@ COMMON = [
     f"--offload-arch={ARCH}",
     # keep the compiler from forming packed FP32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # assemble the device code from its text: an instruction's literal holds 32
+    # bits, and hipcc 7.2 (AMD clang 22) can write a 64-bit one for a scalar move
+    # (+inf as the start of a wave-uniform value under register pressure:
+    # s_mov_b64 s[88:89], 0x7ff0000000000000).  Straight to the object it encodes
+    # the low half alone, here zero, without a word; the assembler refuses it.
+    "-save-temps=obj",
     "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
     "-I", os.path.join(ROOT, "include"),
 ]
@@ -54,6 +60,11 @@ def _compile(src: str, verbose: bool) -> str:
         lines = [ln for ln in res.stderr.splitlines() if "packed-fp32-ops" not in ln]
         if lines:
             print("\n".join(lines), file=sys.stderr)
+    # the steps between
+    stem = os.path.splitext(os.path.basename(src))[0]
+    for f in os.listdir(BUILD_DIR):
+        if f.startswith((stem + "-hip-", stem + "-host-", os.path.basename(src) + "-hip-")):
+            os.remove(os.path.join(BUILD_DIR, f))
     return obj
 
 

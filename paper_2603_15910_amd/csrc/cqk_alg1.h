@@ -185,7 +185,9 @@ struct FlatAcc {
 
 __device__ __forceinline__ void flat_init(FlatAcc& F) {
   F.near = F.far = KeySum{inf_d(), 0.0};
-  // finite: started from infinities, hipcc 7.2 (-O3) began the search at zero
+  // finite: hipcc 7.2 moves an infinite start of these wave-uniform values
+  // into a scalar pair with a 64-bit literal, of which the instruction holds
+  // the low half, zero (the build refuses that now)
   F.nk = 1.7976931348623157e308;
   F.fk = -1.7976931348623157e308;
   F.b = F.ab = 0.0;
