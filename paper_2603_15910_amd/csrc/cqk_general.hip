@@ -1696,6 +1696,8 @@ __global__ void gen_init_kernel(GenState* st, GenState init) { *st = init; }
 // What bounds it is latency: launch, load, about 3 us per evaluation, store.
 // Whole calls, FP64, multi-launch route against this one: n = 1e3 92 / 35 us,
 // 1e5 93 / 41, 5e5 98 / 44, 1e6 117 / 57, 2e6 167 / 86.
+// E = 16 of FP64 takes all 256 VGPRs and spills 16 (68 B of scratch a lane,
+// 9 MB over the chip); the other instances spill none.
 // ---------------------------------------------------------------------------
 struct TeamResult {   // in the context's pinned host memory
   double lam_final, lam0, bytes;
