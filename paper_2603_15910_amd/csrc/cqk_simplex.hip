@@ -1767,6 +1767,7 @@ struct SpxTeamCtl {      // queued and captured calls
 static_assert(sizeof(SpxTeamCtl) <= kTeamCtlBytes, "the control block fits its reserve");
 
 struct SpxTeamArgs {
+  const SpxTeamCtl* ctl;  // queued or captured call: tags from here (in the line of y, n)
   const void *y, *xw;
   void* x;               // null: sparse output
   int64_t* sp_idx;
@@ -1780,7 +1781,6 @@ struct SpxTeamArgs {
   TeamLate late;
   TeamFlags* flags;
   SpxTeamResult* res;
-  const SpxTeamCtl* ctl;
 };
 
 // After the projection kernel, or (rest) spx_rest_kernel's dense form: its
