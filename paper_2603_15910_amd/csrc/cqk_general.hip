@@ -1786,12 +1786,17 @@ struct RestArgs {
   const TeamTags* tags;
 };
 
+// ASK: whether to look at the flags first, so that no call tries twice.  The
+// first launch of a waiting call has nothing to ask, and compiled with the
+// question the kernel loads the state and the counts behind it through the
+// vector cache (44.2 us for the headline's set, 42.1 without).
+template <bool ASK>
 __global__ __launch_bounds__(kTeamBlock) void gen_rest_kernel(RestArgs A) {
   constexpr int NW = kTeamBlock / kWave;
   __shared__ TeamLds<kTeamBlock> S;
   const GenState* in = A.st;
   if (in->status != kRunning || in->src == 0 || in->n_src > A.max_src) return;
-  if (team_is_off(A.flags, &S.gave_up)) return;  // no second try in one call
+  if (ASK && team_is_off(A.flags, &S.gave_up)) return;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1), wid = scalar(tid / kWave);
   const int set = scalar(in->src) - 1;
@@ -2465,7 +2470,10 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     R.flags = deferred ? &rctl->tags.flags : &A.st->rest;
     R.tag = deferred ? (uint32_t)rests * rest_need : ctx->team_tag;
     R.tags = deferred ? &rctl->tags : nullptr;
-    hipLaunchKernelGGL(gen_rest_kernel, dim3(blocks), dim3(kTeamBlock), 0, s, R);
+    if (deferred || rests != 0)
+      hipLaunchKernelGGL(gen_rest_kernel<true>, dim3(blocks), dim3(kTeamBlock), 0, s, R);
+    else
+      hipLaunchKernelGGL(gen_rest_kernel<false>, dim3(blocks), dim3(kTeamBlock), 0, s, R);
     if (!deferred) ctx->team_tag += rest_need;
     ++rests;
   };
