@@ -2587,6 +2587,8 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
     // before the state is looked at again (four, the later ones with nothing
     // to do, took 255 against 244 us for 2.2e6 uniform FP64 indices from
     // lam_0 = 0.1; one, 563 against 522 where every pass reads the arrays).
+    // Four where the passes read a set that the one launch left to them (1e8
+    // correlated FP64, 4.7e6 indices in the set: 1970 us with two, 1943).
     int batch = !rest ? 6 : sampled ? 1 : 2;
     while (launched < max_launch) {
       if (launched == 1 && ask_flat && hs->flat != 0) flat_pass();
@@ -2603,7 +2605,7 @@ cqk_status run_general(cqk_ctx* ctx, int64_t n, const TIn* d, const TIn* a, cons
       if (hip_ok(hipStreamSynchronize(s)) != CQK_OK) return CQK_DEVICE_ERROR;
       if (hs->status != kRunning) break;
       if (hs->rest.gave_up) rests = kRests;
-      batch = (rest && sampled && launched == 1) ? 2 : 4;
+      batch = (rest && sampled && launched == 1 && hs->src == 0) ? 2 : 4;
     }
     if (rest) ctx->team_pause.outcome(hs->rest.gave_up != 0);
   }
