@@ -1385,7 +1385,7 @@ __device__ __forceinline__ bool cqk_has_lambda(const GenState& st) {
 // One wave row (L <= 64 * SP), per-index form in registers.
 // ---------------------------------------------------------------------------
 template <int SP, typename TIn>
-__device__ void cqk_short_row(const BatCqkArgs& A, int s, int64_t base, int64_t L,
+__device__ __forceinline__ void cqk_short_row(const BatCqkArgs& A, int s, int64_t base, int64_t L,
                               double r, BatStat& stat) {
   const CqkArrays<TIn> V(A);
   const int lane = threadIdx.x & (kWave - 1);
@@ -1645,7 +1645,7 @@ struct CqkLds {
 };
 
 template <typename TIn>
-__device__ void cqk_long_row(const BatCqkArgs& A, int s, int64_t base, int64_t L, CqkLds& S,
+__device__ __forceinline__ void cqk_long_row(const BatCqkArgs& A, int s, int64_t base, int64_t L, CqkLds& S,
                              BatStat& stat) {
   const CqkArrays<TIn> V(A);
   const double r = A.r[s];
@@ -2127,21 +2127,20 @@ __global__ __launch_bounds__(kRowBlock, kRowBlocksPerCu) void bat_cqk_team_kerne
   stat_flush<true>(stat, A.counters + CTR_STAT1);
 }
 
-// Workgroup rows that no team holds: those past the longest team rows and
-// those shorter than the held ones, or all of them when a team gave up or
-// there are none.
-struct Streamed {
-  int longer, held;   // entries before the held rows, and of these
-  int n;
-  __device__ __forceinline__ int entry(int k) const { return k < longer ? k : k + held; }
-};
+// Workgroup rows that no team holds (their number, of nlong): those past the
+// longest team rows and, by the rule above, all shorter ones or none, or all
+// of them when a team gave up or there are none; and the list entry of one.
 template <typename TIn, bool BACKWARD>
-__device__ __forceinline__ Streamed streamed_rows(const BatCqkArgs& A) {
-  const int nlong = A.counters[CTR_NLONG];
-  if (A.tslots == nullptr || A.counters[CTR_GAVE_UP]) return {nlong, 0, nlong};
-  const int longer = A.counters[CTR_LBASE + RowShape<TIn>::kMaxLog];
-  const int end = A.counters[CTR_LBASE + held_from<TIn, BACKWARD>(nlong) - 1];
-  return {longer, end - longer, nlong - (end - longer)};
+__device__ __forceinline__ int streamed_rows(const BatCqkArgs& A, int nlong) {
+  if (A.tslots == nullptr || A.counters[CTR_GAVE_UP]) return nlong;
+  auto start = [&](int k) { return A.counters[CTR_LBASE + k]; };
+  return nlong - (start(held_from<TIn, BACKWARD>(nlong) - 1) - start(RowShape<TIn>::kMaxLog));
+}
+template <typename TIn>
+__device__ __forceinline__ size_t streamed_entry(const BatCqkArgs& A, int row, int nlong,
+                                                 int nstream) {
+  const int longer = scalar(A.counters[CTR_LBASE + RowShape<TIn>::kMaxLog]);
+  return (size_t)(row < longer ? row : row + (nlong - nstream));
 }
 
 // The wave rows, four to a block at a time; each wave takes kRowsPerWave rows
@@ -2150,13 +2149,24 @@ __device__ __forceinline__ Streamed streamed_rows(const BatCqkArgs& A) {
 // workgroup row's loads would cost its waves' occupancy.
 constexpr int kRowsPerWave = 4;
 
-template <int SP, typename TIn>
+//
+// Workgroup rows that no team holds come beside them.  HOLD: those of one block
+// are held, as a team of one would, with the same sums in the same order, so a
+// row's result does not depend on how many others the call has (6000 FP32 rows
+// of 513 to 999 values take 121 us, streamed 146, in teams 145; FP64 144, 177
+// and 145).  Not in calls of so many rows that the shortest have a kernel of
+// their own: there the wave rows bound the time, and the code for the others
+// costs them 4 of 256 us (65 536 FP32 rows of 64 to 512 values).  The other
+// workgroup rows stream from memory at every evaluation.
+template <int SP, typename TIn, bool HOLD>
 __global__ __launch_bounds__(kBlock, 3) void bat_cqk_solve_kernel(BatCqkArgs A) {
   __shared__ BatStat stat;
   __shared__ CqkLds S;
+  __shared__ TeamLds<kRowBlock> one;
+  Team alone = team_alone();
+  int par = 0;
   const int nlong = A.counters[CTR_NLONG];
-  const Streamed streamed = streamed_rows<TIn, false>(A);
-  const int nstream = streamed.n;
+  const int nstream = streamed_rows<TIn, false>(A, nlong);
   // the shortest may be the group kernel's
   const int nshort = A.grouped ? A.counters[CTR_GROUPS] - nlong : A.counters[CTR_NSHORT];
   const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
@@ -2174,11 +2184,15 @@ __global__ __launch_bounds__(kBlock, 3) void bat_cqk_solve_kernel(BatCqkArgs A) 
     int item = scalar(S.item);
     __syncthreads();
     if (item >= nitems) break;
-    // workgroup rows that no team holds stream from memory at every evaluation
     const int row = A.short_first ? item - ngroups : item;
     if (row >= 0 && row < nstream) {
-      const size_t e = (size_t)streamed.entry(row);
-      cqk_long_row<TIn>(A, A.list[e], A.lrow[2 * e], A.lrow[2 * e + 1], S, stat);
+      const size_t e = streamed_entry<TIn>(A, row, nlong, nstream);
+      const int id = A.list[e];
+      const int64_t first = A.lrow[2 * e], len = A.lrow[2 * e + 1];
+      if (HOLD && len < (1 << RowShape<TIn>::kLog))
+        cqk_team_row<TIn, RowShape<TIn>::E>(A, one, stat, par, alone, id, first, len, A.r[id]);
+      else
+        cqk_long_row<TIn>(A, id, first, len, S, stat);
       __syncthreads();
       continue;
     }
@@ -2450,8 +2464,7 @@ __global__ __launch_bounds__(kBlock) void bat_cqk_vjp_kernel(BatCqkArgs A) {
   __shared__ CqkLds S;
   const int nlong = A.counters[CTR_NLONG];
   const int nshort = A.counters[CTR_NSHORT];
-  const Streamed streamed = streamed_rows<TIn, true>(A);
-  const int nstream = streamed.n;
+  const int nstream = streamed_rows<TIn, true>(A, nlong);
   const int nsg = (nshort + kWaves - 1) / kWaves;
   const int nitems = nstream + nsg;
   ItemSource src;
@@ -2474,7 +2487,7 @@ __global__ __launch_bounds__(kBlock) void bat_cqk_vjp_kernel(BatCqkArgs A) {
       idx = is_long ? item : item - nstream;
     }
     if (is_long) {
-      const size_t e = (size_t)streamed.entry(idx);
+      const size_t e = streamed_entry<TIn>(A, idx, nlong, nstream);
       cqk_vjp_long_row<TIn>(A, A.list[e], A.lrow[2 * e], A.lrow[2 * e + 1],
                             S);
     } else {
@@ -2734,10 +2747,13 @@ void launch_cqk_forward(cqk_ctx* ctx, const cqk_batch_schedule& sc, BatCqkArgs A
   if (A.grouped)
     hipLaunchKernelGGL((bat_cqk_group_kernel<TIn>), dim3(3 * ctx->num_cus), dim3(kBlock), 0,
                        ctx->stream, A);
-  if (sc.small_per == 4)
-    hipLaunchKernelGGL((bat_cqk_solve_kernel<4, TIn>), grid, dim3(kBlock), 0, ctx->stream, A);
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(kBlock), 0, ctx->stream, A); };
+  if (A.grouped)
+    sc.small_per == 4 ? go(bat_cqk_solve_kernel<4, TIn, false>)
+                      : go(bat_cqk_solve_kernel<8, TIn, false>);
   else
-    hipLaunchKernelGGL((bat_cqk_solve_kernel<8, TIn>), grid, dim3(kBlock), 0, ctx->stream, A);
+    sc.small_per == 4 ? go(bat_cqk_solve_kernel<4, TIn, true>)
+                      : go(bat_cqk_solve_kernel<8, TIn, true>);
 }
 
 template <typename TIn>

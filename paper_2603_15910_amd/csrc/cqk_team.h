@@ -73,6 +73,9 @@ __device__ __forceinline__ Team grid_team(uint64_t* slots, uint32_t tag, uint64_
               late_tag(late, tag)};
 }
 
+// A block by itself: nothing is exchanged and nothing waited for.
+__device__ __forceinline__ Team team_alone() { return Team{nullptr, 0, 0, 1, 0, 0, 0}; }
+
 // LDS of the reductions below.
 template <int BLOCK>
 struct TeamLds {
