@@ -1776,11 +1776,17 @@ struct RowShape {
   static_assert(kBatTeamMax == 1 << (kMaxLog - kLog), "the longest rows take the largest teams");
 };
 
-// The shortest rows (their bit length) that teams hold in a call of nlong
-// workgroup rows; shorter ones are streamed beside the wave rows.  The team
-// kernel comes before those, so it adds its launch, a load and its exchanges
-// to the call's time, where a short row's evaluations find it in the cache.
-// kAlways: held in any call; each bit less wants so many workgroup rows.
+// Which workgroup rows teams hold in a call of nlong of them: all, where a
+// team has anything to hold; otherwise they stay beside the wave rows, where
+// the forward kernel may hold a row of one block and streams the others.
+// The team kernel comes before those, so it adds its launch, a load and its
+// exchanges to the call's time, where a short row's evaluations find it in the
+// cache; once it runs, a short row in it costs less than a second round in the
+// kernel behind (by each row's own length / all held, us: FP32 6000 rows of
+// 600 to 1500 167 / 159, backward 100 / 89, 100 of 5000 to 90 000 backward 97 /
+// 70; FP64 3000 of 513 to 1999 backward 98 / 85).
+// Rows of bit length kAlways are held in any call; each bit less wants so many
+// workgroup rows.
 // Rows of one length, streamed / held, us.  FP64: 8 of 1000 values 47 / 52,
 // 3000 57 / 54 (but 58 / 73 among rows of 10 to 3000), 6000 81 / 55; 256 of
 // 3000 68 / 66 (300 of 600 to 4000 76 / 87), 512 of 3000 87 / 78, 1024 of 1200
@@ -1803,6 +1809,14 @@ __device__ __forceinline__ int held_from(int nlong) {
   int b = kAlways;
   while (b > 9 && nlong >= kLeast[kAlways - b]) --b;
   return b;
+}
+
+// Where the held rows end in the list (they follow those too long); start: of
+// its length buckets, longest first.
+template <typename TIn, bool BACKWARD, typename F>
+__device__ __forceinline__ int held_end(int nlong, F&& start) {
+  const int longer = start(RowShape<TIn>::kMaxLog);
+  return start(held_from<TIn, BACKWARD>(nlong) - 1) > longer ? nlong : longer;
 }
 
 // The rows of this block one after the other, each with its team.  Longest
@@ -1831,7 +1845,8 @@ struct TeamRows {
   __device__ __forceinline__ explicit TeamRows(const BatCqkArgs& A) {
     const int lane = threadIdx.x & (kWave - 1);
     bases = (lane < kNBW) ? A.counters[CTR_LBASE + lane] : 0;
-    end = base_of(held_from<TIn, BACKWARD>(scalar(A.counters[CTR_NLONG])) - 1);
+    end = held_end<TIn, BACKWARD>(scalar(A.counters[CTR_NLONG]),
+                                  [&](int k) { return base_of(k); });
     const uint32_t tag = scalar(A.tctl->base);
     team = Team{nullptr, A.tlimit, tag, 1, 0, kBatTeamBlocks * kSlotWords, late_tag(A.tlate, tag)};
     b = kTeamMaxLog + 1;
@@ -2134,7 +2149,7 @@ template <typename TIn, bool BACKWARD>
 __device__ __forceinline__ int streamed_rows(const BatCqkArgs& A, int nlong) {
   if (A.tslots == nullptr || A.counters[CTR_GAVE_UP]) return nlong;
   auto start = [&](int k) { return A.counters[CTR_LBASE + k]; };
-  return nlong - (start(held_from<TIn, BACKWARD>(nlong) - 1) - start(RowShape<TIn>::kMaxLog));
+  return nlong - (held_end<TIn, BACKWARD>(nlong, start) - start(RowShape<TIn>::kMaxLog));
 }
 template <typename TIn>
 __device__ __forceinline__ size_t streamed_entry(const BatCqkArgs& A, int row, int nlong,
